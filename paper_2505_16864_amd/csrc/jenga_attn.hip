@@ -1,14 +1,17 @@
 // Block-sparse flash attention for gfx950 (appendix Alg. 4; Alg. 2 for the text rows; Eq. 1 inside
 // the visited blocks).
 //
-// One workgroup owns one query block of BLK rows of one (batch, head): BLK/32 wavefronts, each with
-// 32 query rows.  It walks the ascending list of selected key blocks.  Per key block:
-//     S^T = K Q^T         v_mfma_f32_32x32x16_bf16, K fragments from LDS, Q fragments in registers
-//     online softmax      float32, base-2 exponent, statistics per query row; the reference the
-//                         exponent is taken against moves lazily (128-token blocks: only when a row
-//                         sum leaves its range), row sums are float32 sums of P
-//     O^T += V^T P^T      v_mfma_f32_32x32x16_bf16, V^T fragments from LDS, P^T straight from the
-//                         S^T accumulators
+// One workgroup owns one query block of BLK rows of one (batch, head) and walks the ascending list of its
+// selected key blocks; a wavefront has 32 query rows.  Blocks of 64 and 128 tokens: BLK/32 wavefronts share the
+// key tiles through LDS (attn_h_kernel); blocks of 32: nothing to share, the list is split over the wavefronts
+// of the workgroup (attn_kernel).  Per key tile:
+//     S^T = K Q^T         v_mfma_f32_32x32x16_bf16, K fragments from LDS or global memory, Q fragments in
+//                         registers
+//     online softmax      float32, base-2 exponent, statistics per query row; the reference the exponent is
+//                         taken against moves only when a row sum leaves its range, row sums are float32 sums
+//                         of P
+//     O^T += V^T P^T      v_mfma_f32_32x32x16_bf16, V^T fragments likewise, P^T straight from the S^T
+//                         accumulators
 // Working on the transposed products keeps one query row in one lane (column) of every
 // accumulator, so the row maximum and row sum are lane-local (one cross-half exchange), and the
 // accumulator layout of S^T is already the B-operand layout PV needs: P never goes through LDS.
@@ -112,39 +115,7 @@ __device__ inline void dma_1kb_to_lds(const void* uniform_base, uint32_t lane_by
                         (uint32_t)(uintptr_t)(const __attribute__((address_space(3))) void*)lds_dst));
 }
 
-// Straight copy of one packed tile (global, fragment order) into LDS without passing through
-// registers.
-template <int NTHR, int CPT>
-__device__ inline void tile_to_lds(const u32x4* __restrict__ src_tile, u32x4* lds, int tid, int wave) {
-#pragma unroll
-  for (int c = 0; c < CPT; ++c)
-    dma_1kb_to_lds((const char*)src_tile + (size_t)c * NTHR * 16, (uint32_t)tid * 16u, lds + c * NTHR + wave * 64);
-}
-
 __device__ inline void wait_vmem() { __builtin_amdgcn_s_waitcnt(0x0F70); }   // vmcnt(0) only
-
-// Online-softmax bookkeeping with a lazily moved reference (Alg. 4 keeps a running maximum m and
-// rescales l and O whenever it grows).  Here the reference m_run only moves when some row's new
-// maximum exceeds it by more than LAZY_LOG2 (in base-2 logit units): until then the probabilities are
-// formed against the old reference and stay below 2^LAZY_LOG2, which the float32 sums and the bf16
-// products hold without loss (bf16 has float32's exponent range), and the final division by l
-// cancels the common factor exactly as it does for the running maximum.  The branch is uniform over
-// the wavefront; after the first few blocks it is almost never taken.
-constexpr float LAZY_LOG2 = 8.0f;
-template <int DT>
-__device__ __forceinline__ void rescale_if_grown(float cand, float& m_run, float& l_run, f32x16 (&O)[DT]) {
-  if (__ballot(cand > m_run + LAZY_LOG2)) {   // also taken by the first block with a valid key (m_run = -inf)
-    asm volatile("");                         // keep it a real branch
-    const float m_new = fmaxf(m_run, cand);
-    const float alpha = m_new == m_run ? 1.0f : __builtin_amdgcn_exp2f(m_run - m_new);
-    l_run *= alpha;
-    m_run = m_new;
-#pragma unroll
-    for (int dt = 0; dt < DT; ++dt)
-#pragma unroll
-      for (int r = 0; r < 16; ++r) O[dt][r] *= alpha;
-  }
-}
 
 // Work mapping shared by the attention kernels.  The text query blocks of every (batch, head) are
 // dense rows, several times longer than a vision row: they are dealt out first, ahead of all vision
@@ -166,157 +137,6 @@ __device__ inline bool map_work(int n, int n_bh, int M, int M_v, int chunk, int*
   *bh = s / chunk;
   *i = xcd * chunk + s % chunk;
   return *i < M_v;
-}
-
-template <int BLK, int D>
-struct AttnTraits {
-  static constexpr int NW = BLK / 32;          // wavefronts per workgroup
-  static constexpr int NTHR = NW * 64;
-  static constexpr int MT = BLK / 32;          // 32-key tiles per key block
-  static constexpr int KS = D / 16;            // k-steps of K Q^T
-  static constexpr int DT = D / 32;            // 32-channel tiles of the output
-  static constexpr int PS = BLK / 16;          // k-steps of V^T P^T
-  static constexpr int TILE_CHUNKS = BLK * D / 8;
-  static constexpr int CPT = TILE_CHUNKS / NTHR;   // 16-byte pieces per thread per tile
-  static constexpr int MIN_WAVES = (BLK == 128 && D == 128) ? 2 : 1;
-};
-
-template <int BLK, int D>
-__global__ __launch_bounds__((AttnTraits<BLK, D>::NTHR), (AttnTraits<BLK, D>::MIN_WAVES)) void attn_kernel(
-    const uint16_t* __restrict__ q, const u32x4* __restrict__ kp, const u32x4* __restrict__ vp,
-    const int32_t* __restrict__ sel_count, const int32_t* __restrict__ sel_index,
-    const int32_t* __restrict__ blk_valid, uint16_t* __restrict__ out, float* __restrict__ lse, int n_bh, int M,
-    int M_v, int n_pad, int chunk, float scale_log2e, float bias_log2e) {
-  using TR = AttnTraits<BLK, D>;
-  constexpr int NTHR = TR::NTHR, MT = TR::MT, KS = TR::KS, DT = TR::DT, PS = TR::PS;
-  constexpr int TILE_CHUNKS = TR::TILE_CHUNKS, CPT = TR::CPT;
-  __shared__ u32x4 Ks[TILE_CHUNKS];
-  __shared__ u32x4 Vs[TILE_CHUNKS];
-
-  int bh, i;
-  if (!map_work(blockIdx.x, n_bh, M, M_v, chunk, &bh, &i)) return;
-
-  const int tid = threadIdx.x, lane = tid & 63;
-  const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);   // wave-uniform, lets LDS bases live in SGPRs
-  const int hl = lane >> 5, ql = lane & 31;
-  const int qrow = i * BLK + 32 * wave + ql;
-
-  bf16x8 qf[KS];
-  {
-    const u32x4* qp = (const u32x4*)(q + ((size_t)bh * n_pad + qrow) * D);
-#pragma unroll
-    for (int ks = 0; ks < KS; ++ks) qf[ks] = __builtin_bit_cast(bf16x8, qp[2 * ks + hl]);
-  }
-
-  int cnt = sel_count[(size_t)bh * M + i];
-  cnt = min(max(cnt, 0), M);
-  const int32_t* idx = sel_index + ((size_t)bh * M + i) * M;
-  const u32x4* kbase = kp + (size_t)bh * M * TILE_CHUNKS;
-  const u32x4* vbase = vp + (size_t)bh * M * TILE_CHUNKS;
-
-  float m_run = -INFINITY, l_run = 0.f;
-  f32x16 O[DT];
-#pragma unroll
-  for (int dt = 0; dt < DT; ++dt)
-#pragma unroll
-    for (int r = 0; r < 16; ++r) O[dt][r] = 0.f;
-
-  if (cnt > 0) {
-    const int j0 = min(max(idx[0], 0), M - 1);
-    tile_to_lds<NTHR, CPT>(kbase + (size_t)j0 * TILE_CHUNKS, Ks, tid, wave);
-  }
-
-  for (int it = 0; it < cnt; ++it) {
-    const int j = min(max(idx[it], 0), M - 1);
-    wait_vmem();       // this wave's part of the K tile has landed
-    __syncthreads();   // K tile of this step is in LDS; every wave is past the previous PV
-    tile_to_lds<NTHR, CPT>(vbase + (size_t)j * TILE_CHUNKS, Vs, tid, wave);
-
-    f32x16 S[MT];
-#pragma unroll
-    for (int mt = 0; mt < MT; ++mt) {
-#pragma unroll
-      for (int r = 0; r < 16; ++r) S[mt][r] = 0.f;
-#pragma unroll
-      for (int ks = 0; ks < KS; ++ks) {
-        const bf16x8 a = __builtin_bit_cast(bf16x8, Ks[(mt * KS + ks) * 64 + lane]);
-        S[mt] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(a, qf[ks], S[mt], 0, 0, 0);
-      }
-    }
-
-    // ---- online softmax on S^T (lane = query row, registers = keys) ----
-    const int nv = blk_valid[j];
-    if (nv < BLK) {   // sequence-length mask: pad keys of a ragged block
-      asm volatile("");   // keep this a real (rarely taken) branch instead of 64 selects per tile
-#pragma unroll
-      for (int mt = 0; mt < MT; ++mt)
-#pragma unroll
-        for (int r = 0; r < 16; ++r) {
-          const int kv = 32 * mt + 8 * (r / 4) + 4 * hl + (r % 4);
-          if (kv >= nv) S[mt][r] = -INFINITY;
-        }
-    }
-    float mx = -INFINITY;
-#pragma unroll
-    for (int mt = 0; mt < MT; ++mt)
-#pragma unroll
-      for (int r = 0; r < 16; ++r) mx = fmaxf(mx, S[mt][r]);
-    mx = fmaxf(mx, __shfl_xor(mx, 32, 64));
-    const float bias = (i < M_v && j >= M_v) ? bias_log2e : 0.f;
-    rescale_if_grown(fmaf(mx, scale_log2e, bias), m_run, l_run, O);
-    const float off = m_run == -INFINITY ? 0.f : bias - m_run;   // every key so far was padding: keep it finite
-    float rs0 = 0.f, rs1 = 0.f;
-    bf16x8 pb[PS];
-#pragma unroll
-    for (int ps = 0; ps < PS; ++ps) {
-      uint32_t w[4];
-#pragma unroll
-      for (int e2 = 0; e2 < 4; ++e2) {
-        const float p0 = __builtin_amdgcn_exp2f(fmaf(S[ps >> 1][8 * (ps & 1) + 2 * e2], scale_log2e, off));
-        const float p1 = __builtin_amdgcn_exp2f(fmaf(S[ps >> 1][8 * (ps & 1) + 2 * e2 + 1], scale_log2e, off));
-        w[e2] = pack_bf16x2(p0, p1);
-        rs0 += p0;
-        rs1 += p1;
-      }
-      u32x4 pw = {w[0], w[1], w[2], w[3]};
-      pb[ps] = __builtin_bit_cast(bf16x8, pw);
-    }
-    l_run += rs0 + rs1;
-
-    wait_vmem();       // this wave's part of the V tile has landed
-    __syncthreads();   // V tile is in LDS; every wave is done reading the K tile
-    if (it + 1 < cnt) {
-      const int jn = min(max(idx[it + 1], 0), M - 1);
-      tile_to_lds<NTHR, CPT>(kbase + (size_t)jn * TILE_CHUNKS, Ks, tid, wave);
-    }
-
-#pragma unroll
-    for (int dt = 0; dt < DT; ++dt) {
-#pragma unroll
-      for (int ps = 0; ps < PS; ++ps) {
-        const bf16x8 a = __builtin_bit_cast(bf16x8, Vs[(dt * PS + ps) * 64 + lane]);
-        O[dt] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(a, pb[ps], O[dt], 0, 0, 0);
-      }
-    }
-  }
-
-  // ---- normalise and store: lane holds row qrow, channels 32*dt + 8*g + 4*hl + {0..3} ----
-  const float l_tot = l_run + __shfl_xor(l_run, 32, 64);
-  const bool row_ok = (32 * wave + ql) < blk_valid[i] && l_tot > 0.f;
-  const float inv = row_ok ? 1.0f / l_tot : 0.f;
-  // natural-log sum of exp(logit) over the visited keys: the running maximum is in base-2 units
-  if (lse != nullptr && hl == 0)
-    lse[(size_t)bh * n_pad + qrow] = row_ok ? (m_run + __builtin_amdgcn_logf(l_tot)) * 0.6931471805599453f : -INFINITY;
-  uint16_t* orow = out + ((size_t)bh * n_pad + qrow) * D;
-#pragma unroll
-  for (int dt = 0; dt < DT; ++dt)
-#pragma unroll
-    for (int g = 0; g < 4; ++g) {
-      uint2 w;
-      w.x = row_ok ? pack_bf16x2(O[dt][4 * g] * inv, O[dt][4 * g + 1] * inv) : 0u;
-      w.y = row_ok ? pack_bf16x2(O[dt][4 * g + 2] * inv, O[dt][4 * g + 3] * inv) : 0u;
-      *(uint2*)(orow + 32 * dt + 8 * g + 4 * hl) = w;
-    }
 }
 
 // compile-time loop: f(integral_constant<int, 0>) ... f(integral_constant<int, N-1>)
@@ -358,8 +178,8 @@ __device__ inline float max_with_other_half(float x) {
 #endif
 }
 
-// attn_h_kernel takes the lazy reference one step further and drops the row maximum from the common
-// path: the maximum over the 32 logits of a lane (16 v_max3, a cross-half exchange, a compare) is a
+// Alg. 4 keeps a running maximum m of every row and rescales l and O whenever it grows.  Here the row
+// maximum is not on the common path: the maximum over the 32 logits of a lane (16 v_max3, a cross-half exchange, a compare) is a
 // chain that has to finish after the last MFMA of S and before the first exponential can issue, in
 // every step of every wavefront.  Without it a step forms its probabilities against the reference as
 // it stands and only looks at the sum: while a lane's 32 probabilities add up to at most P_SUM_MAX they
@@ -371,13 +191,17 @@ __device__ inline float max_with_other_half(float x) {
 constexpr float P_SUM_MAX = 1073741824.0f;   // 2^30
 
 // ---------------------------------------------------------------------------------------------
-// attn_h_kernel: blocks of 128 tokens, walked in half blocks of 64 keys.
+// attn_h_kernel: blocks of 128 tokens, walked in half blocks of 64 keys, and blocks of 64 tokens.
 //
 // A wavefront does its softmax between its two runs of MFMAs, so it is the other wavefronts of the
 // SIMD that keep the MFMA pipe fed meanwhile: occupancy matters.  A step over 64 keys needs half
 // the S and P registers and half the LDS of a step over 128, which lets three workgroups (twelve
-// wavefronts) live on a CU instead of two; everything else is attn_kernel: 4 waves x 32 query
-// rows, transposed products, K and V^T fragments straight from the packed tiles, DMA to LDS.
+// wavefronts) live on a CU instead of two.
+//
+// Blocks of 64 tokens run the same loop with one step per block and two wavefronts: 32 KB of LDS at D = 128, five
+// workgroups on a CU.  12 heads x 14040 tokens, D = 128, k = 0.25 (0.41 TFLOP of tiles): 0.55 ms, 0.79 ms before
+// this loop replaced one that left every LDS read and the row maximum open.  At D = 64 the softmax, not the matrix
+// core, is the longer part of a step, and four wavefronts per SIMD (128 registers) fit.
 //
 // PACED (JENGA_FLAG_PACED_WALK): the selected blocks are not visited in list order.  A position G sweeps
 // over the key blocks once per lap, derived from the constant-frequency clock that every CU reads
@@ -388,15 +212,20 @@ constexpr float P_SUM_MAX = 1073741824.0f;   // 2^30
 // tile reads of the in-order walk, catches more than half of them (measured on the 720p workload).
 // The price: the order, and with it the last bits of the output, can differ from run to run.
 // ---------------------------------------------------------------------------------------------
-template <int D, bool PACED>
-__global__ __launch_bounds__(256, 3) void attn_h_kernel(
+template <int BLK, int D>
+constexpr int attn_h_min_waves() { return D == 128 ? 3 : 4; }   // wavefronts per SIMD the registers have to leave room for
+
+template <int BLK, int D, bool PACED>
+__global__ __launch_bounds__(2 * BLK, (attn_h_min_waves<BLK, D>())) void attn_h_kernel(
     const uint16_t* __restrict__ q, const u32x4* __restrict__ kp, const u32x4* __restrict__ vp,
     const int32_t* __restrict__ sel_count, const int32_t* __restrict__ sel_index,
     const int32_t* __restrict__ blk_valid, uint16_t* __restrict__ out, float* __restrict__ lse, int n_bh, int M,
     int M_v, int n_pad, int chunk, int pad_v, int pad_c, float scale_log2e, float bias_log2e,
     const uint32_t* __restrict__ pace_params) {
-  constexpr int BLK = 128, KS = D / 16, DT = D / 32, PS = BLK / 16, MH = 2, PH = 4;
-  constexpr int TILE_CHUNKS = BLK * D / 8, HALF_CHUNKS = TILE_CHUNKS / 2, CPT = HALF_CHUNKS / 256;
+  constexpr int KS = D / 16, DT = D / 32, PS = BLK / 16, MH = 2, PH = 4;
+  constexpr int NW = BLK / 32, NTHR = 64 * NW, HALVES = BLK / 64;   // wavefronts, threads, steps per key block
+  constexpr int TILE_CHUNKS = BLK * D / 8, HALF_CHUNKS = 64 * D / 8, CPT = HALF_CHUNKS / NTHR;
+  static_assert(HALVES >= 1 && (!PACED || HALVES == 2), "steps of 64 keys; the paced walk samples its clock in the first of two");
   __shared__ u32x4 Ks[HALF_CHUNKS];   // fragments (m2, ks) of the current 64 keys
   __shared__ u32x4 Vs[HALF_CHUNKS];   // fragments (dt, p2) of the current 64 keys
   __shared__ uint32_t rem_bits[PACED ? 64 : 1];   // PACED: bitmap of the blocks still to visit, 32 per word
@@ -426,7 +255,7 @@ __global__ __launch_bounds__(256, 3) void attn_h_kernel(
     pace_k = pace_params[0];
     if (tid < 64) rem_bits[tid] = 0;
     __syncthreads();
-    for (int t = tid; t < cnt; t += 256) {
+    for (int t = tid; t < cnt; t += NTHR) {
       const int jj = min(max(idx[t], 0), M - 1);
       atomicOr(&rem_bits[jj >> 5], 1u << (jj & 31));
     }
@@ -457,12 +286,12 @@ __global__ __launch_bounds__(256, 3) void attn_h_kernel(
     rem &= lane == src ? ~(1u << bit) : ~0u;
     return src * 32 + bit;
   };
-  const int steps = 2 * cnt;
+  const int steps = HALVES * cnt;
   const u32x4* kbase = kp + (size_t)bh * M * TILE_CHUNKS;
   const u32x4* vbase = vp + (size_t)bh * M * TILE_CHUNKS;
 
   // K half h of block j is one contiguous run of the packed tile; V half h is PH fragments out of
-  // every PS of each channel tile: wave w copies fragments f = c*4 + w, f = dt*PH + p2
+  // every PS of each channel tile: wave w copies fragments f = c*NW + w, f = dt*PH + p2
   const uint32_t ks_wave = __builtin_amdgcn_readfirstlane(
       (uint32_t)(uintptr_t)(const __attribute__((address_space(3))) void*)Ks + (uint32_t)wave * 1024u);
   const uint32_t vs_wave = __builtin_amdgcn_readfirstlane(
@@ -470,14 +299,15 @@ __global__ __launch_bounds__(256, 3) void attn_h_kernel(
   auto k_half_to_lds = [&](int j, int h) {
     const char* kt = (const char*)(kbase + (size_t)j * TILE_CHUNKS + h * HALF_CHUNKS);
 #pragma unroll
-    for (int c = 0; c < CPT; ++c) dma_1kb_to_lds_at(kt + (size_t)c * 4096, (uint32_t)tid * 16u, ks_wave + c * 4096u);
+    for (int c = 0; c < CPT; ++c) 
+      dma_1kb_to_lds_at(kt + (size_t)c * (NTHR * 16), (uint32_t)tid * 16u, ks_wave + c * (NTHR * 16u));
   };
   auto v_half_to_lds = [&](int j, int h) {
     const u32x4* vt = vbase + (size_t)j * TILE_CHUNKS + (PH * h) * 64;
 #pragma unroll
     for (int c = 0; c < CPT; ++c) {
-      const int f = c * 4 + wave, dt = f / PH, p2 = f % PH;
-      dma_1kb_to_lds_at(vt + (size_t)(dt * PS + p2) * 64, (uint32_t)lane * 16u, vs_wave + c * 4096u);
+      const int f = c * NW + wave, dt = f / PH, p2 = f % PH;
+      dma_1kb_to_lds_at(vt + (size_t)(dt * PS + p2) * 64, (uint32_t)lane * 16u, vs_wave + c * (NTHR * 16u));
     }
   };
 
@@ -504,7 +334,7 @@ __global__ __launch_bounds__(256, 3) void attn_h_kernel(
   if (cnt > 0) k_half_to_lds(j_next, 0);
 
   for (int st = 0; st < steps; ++st) {
-    const int h = st & 1;
+    const int h = HALVES == 2 ? st & 1 : 0;
     const int j = j_next;
     wait_vmem();       // this wave's part of the K half has landed
     __syncthreads();   // K half of this step is in LDS; every wave is past the previous PV
@@ -588,7 +418,7 @@ __global__ __launch_bounds__(256, 3) void attn_h_kernel(
           j_next = pick(pace_slot[((st >> 1) + 1) & 1]);                 // used after the next barrier
         }
       } else {
-        j_next = min(max(idx[min(st + 1, steps - 1) >> 1], 0), M - 1);   // used after the next barrier
+        j_next = min(max(idx[min(st + 1, steps - 1) / HALVES], 0), M - 1);   // used after the next barrier
       }
     };
     // Common path: probabilities against the reference as it stands, no row maximum (see P_SUM_MAX).  Exact
@@ -629,7 +459,7 @@ __global__ __launch_bounds__(256, 3) void attn_h_kernel(
 
     wait_vmem();       // this wave's part of the V half has landed
     __syncthreads();   // V half is in LDS; every wave is done reading the K half
-    if (st + 1 < steps) k_half_to_lds(j_next, (st + 1) & 1);
+    if (st + 1 < steps) k_half_to_lds(j_next, HALVES == 2 ? (st + 1) & 1 : 0);
 
     // O^T += V^T P^T, fragments (dt, p2) = (2 (g / 2) + (e & 1), 2 (g % 2) + e / 2), pipelined as above
     {
@@ -681,6 +511,195 @@ __global__ __launch_bounds__(256, 3) void attn_h_kernel(
       w.y = row_ok ? pack_bf16x2(O[dt][4 * g + 2] * inv, O[dt][4 * g + 3] * inv) : 0u;
       *(uint2*)(orow + 32 * dt + 8 * g + 4 * hl_e) = w;
     }
+}
+
+// ---------------------------------------------------------------------------------------------
+// attn_kernel: blocks of 32 tokens.
+//
+// A query block is one MFMA tile of rows, so no two wavefronts want the same key tile and staging it in LDS would
+// only add a copy, a barrier and its latency.  Every wavefront works alone: packed fragments go straight from
+// global memory to registers (coalesced 1 KB loads), K of the next block in flight under the softmax and the
+// second product, V under the logits and the softmax.  The NS wavefronts of a workgroup share one query block and
+// take every NS-th entry of its list, which keeps the chip busy on small grids and keeps the dense text rows
+// (every block of the sequence) from running on alone; their partial results meet in LDS at the end, in a fixed
+// order.  No barrier inside the loop.
+//
+// Measured on 2048 blocks x 2 heads, D = 64, k = 0.05 (lists of 305 of 2048 blocks): 0.77 ms, against 1.77 ms for one
+// wavefront per query block that staged its tiles in LDS.  What bounds it there is the path behind the L2: 32 rows
+// read 8 KB of K and V for 0.26 MFLOP, 10 GB in all, from a head (16 MB) that an XCD's 4 MB do not hold; 5.5 GB
+// miss, at 7.1 TB/s.  Eight wavefronts
+// per list at D = 64 (two workgroups fill a CU), four at D = 128 (the registers leave room for eight).
+// ---------------------------------------------------------------------------------------------
+template <int D, int NS>
+__global__ __launch_bounds__(64 * NS, (D == 128 ? 2 : 4)) void attn_kernel(
+    const uint16_t* __restrict__ q, const u32x4* __restrict__ kp, const u32x4* __restrict__ vp,
+    const int32_t* __restrict__ sel_count, const int32_t* __restrict__ sel_index, uint16_t* __restrict__ out,
+    float* __restrict__ lse, int n_bh, int M, int M_v, int n_pad, int chunk, int pad_v, int pad_c, float scale_log2e,
+    float bias_log2e) {
+  constexpr int BLK = 32, KS = D / 16, DT = D / 32, PS = BLK / 16, TILE_CHUNKS = BLK * D / 8;
+  __shared__ float part[NS][16][64];   // one channel tile of every wavefront's O, accumulator order
+  __shared__ float stat[NS][2][32];    // reference and sum of every row
+
+  int bh, i;
+  if (!map_work(blockIdx.x, n_bh, M, M_v, chunk, &bh, &i)) return;
+
+  const int lane = threadIdx.x & 63;
+  const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  const int hl = lane >> 5, ql = lane & 31;
+  const size_t qrow = (size_t)bh * n_pad + (size_t)i * BLK + ql;
+
+  bf16x8 qf[KS];
+  {
+    const u32x4* qp = (const u32x4*)(q + qrow * D);
+#pragma unroll
+    for (int ks = 0; ks < KS; ++ks) qf[ks] = __builtin_bit_cast(bf16x8, qp[2 * ks + hl]);
+  }
+
+  int cnt = sel_count[(size_t)bh * M + i];
+  cnt = min(max(cnt, 0), M);
+  const int32_t* idx = sel_index + ((size_t)bh * M + i) * M;
+  const u32x4* kbase = kp + (size_t)bh * M * TILE_CHUNKS + lane;
+  const u32x4* vbase = vp + (size_t)bh * M * TILE_CHUNKS + lane;
+  u32x4 kf[KS], vf[DT * PS];
+  auto load_k = [&](int j) {
+#pragma unroll
+    for (int f = 0; f < KS; ++f) kf[f] = kbase[(size_t)j * TILE_CHUNKS + f * 64];
+  };
+  auto load_v = [&](int j) {
+#pragma unroll
+    for (int f = 0; f < DT * PS; ++f) vf[f] = vbase[(size_t)j * TILE_CHUNKS + f * 64];
+  };
+  auto listed = [&](int t) { return min(max(idx[t], 0), M - 1); };
+
+  float m_run = -INFINITY, l_run = 0.f;
+  bool unset = true;   // no row has a reference yet (uniform: every row sees the same keys)
+  f32x16 O[DT];
+#pragma unroll
+  for (int dt = 0; dt < DT; ++dt)
+#pragma unroll
+    for (int r = 0; r < 16; ++r) O[dt][r] = 0.f;
+
+  int j = 0, j_next = 0;   // a list entry is fetched a block ahead of the loads that need it
+  if (wave < cnt) {
+    j = listed(wave);
+    load_k(j);
+    load_v(j);
+    j_next = listed(min(wave + NS, cnt - 1));
+  }
+  for (int t = wave; t < cnt; t += NS) {
+    const bool more = t + NS < cnt;
+    const int j_after = listed(min(t + 2 * NS, cnt - 1));
+    f32x16 S;
+#pragma unroll
+    for (int r = 0; r < 16; ++r) S[r] = 0.f;
+#pragma unroll
+    for (int ks = 0; ks < KS; ++ks)
+      S = __builtin_amdgcn_mfma_f32_32x32x16_bf16(__builtin_bit_cast(bf16x8, kf[ks]), qf[ks], S, 0, 0, 0);
+    if (more) load_k(j_next);
+
+    const int nv = BLK - (j == M_v - 1 ? pad_v : (j == M - 1 ? pad_c : 0));
+    if (nv < BLK) {   // sequence-length mask: pad keys of a ragged block
+      asm volatile("");   // a real, rarely taken branch
+#pragma unroll
+      for (int r = 0; r < 16; ++r)
+        if (8 * (r / 4) + 4 * hl + (r % 4) >= nv) S[r] = -INFINITY;
+    }
+    const float bias = (i < M_v && j >= M_v) ? bias_log2e : 0.f;
+    bf16x8 pb[PS];
+    auto probabilities = [&](float off) {
+      float rs0 = 0.f, rs1 = 0.f;
+#pragma unroll
+      for (int ps = 0; ps < PS; ++ps) {
+        uint32_t w[4];
+#pragma unroll
+        for (int e2 = 0; e2 < 4; ++e2) {
+          const float p0 = __builtin_amdgcn_exp2f(fmaf(S[8 * ps + 2 * e2], scale_log2e, off));
+          const float p1 = __builtin_amdgcn_exp2f(fmaf(S[8 * ps + 2 * e2 + 1], scale_log2e, off));
+          w[e2] = pack_bf16x2(p0, p1);
+          rs0 += p0;
+          rs1 += p1;
+        }
+        u32x4 pw = {w[0], w[1], w[2], w[3]};
+        pb[ps] = __builtin_bit_cast(bf16x8, pw);
+      }
+      return rs0 + rs1;
+    };
+    // as in attn_h_kernel: no row maximum while the sums stay in range (P_SUM_MAX); S is still there for the
+    // exact path
+    float rs = 0.f;
+    bool in_range = false;
+    if (!unset) {
+      rs = probabilities(bias - m_run);
+      in_range = __ballot(!(rs <= P_SUM_MAX)) == 0;
+    }
+    if (!in_range) {
+      asm volatile("");   // a real branch: the first block of a row, then almost never
+      float mx = -INFINITY;
+#pragma unroll
+      for (int r = 0; r < 16; ++r) mx = fmaxf(mx, S[r]);
+      mx = max_with_other_half(mx);
+      const float m_new = fmaxf(m_run, fmaf(mx, scale_log2e, bias));
+      const float alpha = m_new == m_run ? 1.0f : __builtin_amdgcn_exp2f(m_run - m_new);
+      l_run *= alpha;
+      m_run = m_new;
+#pragma unroll
+      for (int dt = 0; dt < DT; ++dt)
+#pragma unroll
+        for (int r = 0; r < 16; ++r) O[dt][r] *= alpha;
+      rs = probabilities(m_run == -INFINITY ? 0.f : bias - m_run);   // every key so far was padding: keep it finite
+      unset = __ballot(m_run == -INFINITY) != 0;
+    }
+    l_run += rs;
+
+#pragma unroll
+    for (int ps = 0; ps < PS; ++ps)
+#pragma unroll
+      for (int dt = 0; dt < DT; ++dt)
+        O[dt] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(__builtin_bit_cast(bf16x8, vf[dt * PS + ps]), pb[ps], O[dt],
+                                                        0, 0, 0);
+    if (more) load_v(j_next);
+    j = j_next;
+    j_next = j_after;
+  }
+
+  // ---- merge the NS partial rows, normalise, store ----
+  const float l_wave = l_run + __shfl_xor(l_run, 32, 64);
+  if (hl == 0) {
+    stat[wave][0][ql] = m_run;
+    stat[wave][1][ql] = l_wave;
+  }
+  __syncthreads();
+  float m_all = -INFINITY, l_all = 0.f;
+#pragma unroll
+  for (int s = 0; s < NS; ++s) m_all = fmaxf(m_all, stat[s][0][ql]);
+  const float ref = m_all == -INFINITY ? 0.f : m_all;
+#pragma unroll
+  for (int s = 0; s < NS; ++s) l_all += stat[s][1][ql] * __builtin_amdgcn_exp2f(stat[s][0][ql] - ref);
+  const int rows_valid = BLK - (i == M_v - 1 ? pad_v : (i == M - 1 ? pad_c : 0));
+  const bool row_ok = ql < rows_valid && l_all > 0.f;
+  if (lse != nullptr && threadIdx.x < 32)
+    lse[qrow] = row_ok ? (m_all + __builtin_amdgcn_logf(l_all)) * 0.6931471805599453f : -INFINITY;
+  const float mine = row_ok ? __builtin_amdgcn_exp2f(m_run - ref) / l_all : 0.f;   // weight of this wavefront's part
+  constexpr int RP = 16 / NS;   // accumulator registers of a channel tile that one wavefront adds up
+#pragma unroll
+  for (int dt = 0; dt < DT; ++dt) {
+    if (dt > 0) __syncthreads();   // the previous tile has been read
+#pragma unroll
+    for (int r = 0; r < 16; ++r) part[wave][r][lane] = O[dt][r] * mine;
+    __syncthreads();
+    float sum[RP];
+#pragma unroll
+    for (int u = 0; u < RP; ++u) {
+      sum[u] = 0.f;
+#pragma unroll
+      for (int s = 0; s < NS; ++s) sum[u] += part[s][wave * RP + u][lane];
+    }
+    // register r of a channel tile holds channel 8 * (r / 4) + 4 * hl + r % 4
+    const int r0 = wave * RP;
+    uint16_t* o = out + qrow * D + 32 * dt + 8 * (r0 / 4) + 4 * hl + r0 % 4;
+#pragma unroll
+    for (int u = 0; u < RP; u += 2) *(uint32_t*)(o + u) = row_ok ? pack_bf16x2(sum[u], sum[u + 1]) : 0u;
+  }
 }
 
 // Lap of the paced walk, common to all workgroups of a launch: a fixed fraction of the time a workgroup needs for
@@ -745,20 +764,23 @@ int run_attention(const jenga_plan* p, const void* q, void* ws, const int32_t* s
       // a workgroup spends about 6.3 us (D = 128; 3.6 us at D = 64) on a block of 128 keys when three share a CU
       uint32_t* params = (uint32_t*)((char*)ws + 2 * half);
       walk_pace_kernel<<<1, 1024, 0, st>>>(sel_count, bh * f.M, f.M, D == 128 ? 630.f : 360.f, params);
-      attn_h_kernel<D, true><<<dim3(n_wg), 256, 0, st>>>((const uint16_t*)q, kp, vp, sel_count, sel_index,
+      attn_h_kernel<BLK, D, true><<<dim3(n_wg), 2 * BLK, 0, st>>>((const uint16_t*)q, kp, vp, sel_count, sel_index,
                                                          p->d_blk_valid, (uint16_t*)out, lse, bh, f.M, f.M_v, f.N_pad,
                                                          chunk, f.pad_v, f.pad_c, scale, c.text_bias * log2e, params);
-    } else {
-      attn_h_kernel<D, false><<<dim3(n_wg), 256, 0, st>>>((const uint16_t*)q, kp, vp, sel_count, sel_index,
-                                                          p->d_blk_valid, (uint16_t*)out, lse, bh, f.M, f.M_v,
-                                                          f.N_pad, chunk, f.pad_v, f.pad_c, scale,
-                                                          c.text_bias * log2e, nullptr);
+      return hipGetLastError() == hipSuccess ? JENGA_OK : JENGA_EHIP;
     }
   }
-  else
-    attn_kernel<BLK, D><<<dim3(n_wg), AttnTraits<BLK, D>::NTHR, 0, st>>>(
-        (const uint16_t*)q, kp, vp, sel_count, sel_index, p->d_blk_valid, (uint16_t*)out, lse, bh, f.M, f.M_v,
-        f.N_pad, chunk, scale, c.text_bias * log2e);   // blocks of 32 or 64 tokens: in-order walk only
+  if constexpr (BLK == 32) {   // in-order walk only
+    constexpr int NS = D == 128 ? 4 : 8;
+    attn_kernel<D, NS><<<dim3(n_wg), 64 * NS, 0, st>>>((const uint16_t*)q, kp, vp, sel_count, sel_index, (uint16_t*)out,
+                                                       lse, bh, f.M, f.M_v, f.N_pad, chunk, f.pad_v, f.pad_c, scale,
+                                                       c.text_bias * log2e);
+  } else {
+    attn_h_kernel<BLK, D, false><<<dim3(n_wg), 2 * BLK, 0, st>>>((const uint16_t*)q, kp, vp, sel_count, sel_index,
+                                                                 p->d_blk_valid, (uint16_t*)out, lse, bh, f.M, f.M_v,
+                                                                 f.N_pad, chunk, f.pad_v, f.pad_c, scale,
+                                                                 c.text_bias * log2e, nullptr);
+  }
   return hipGetLastError() == hipSuccess ? JENGA_OK : JENGA_EHIP;
 }
 

@@ -1,0 +1,50 @@
+"""Attention with blocks of 32 and 64 tokens on lists of given lengths: shorter than the number of wavefronts that
+share a list, empty, one off a multiple of it, and full, with the ragged blocks anywhere in them."""
+import numpy as np
+import pytest
+import torch
+
+import jenga_inputs as ji
+from oracle import jenga_oracle as jo
+from paper_2505_16864_amd.layer import CarveLayer
+from gpu_util import oracle_layout, to_f64, check_output
+
+pytestmark = pytest.mark.gpu
+
+
+@pytest.mark.parametrize("head_dim,block", [(64, 32), (128, 32), (64, 64), (128, 64)])
+def test_list_lengths(head_dim, block):
+    w = dict(T=3, H=13, W=block // 2 + 3, n_text=2 * block + 5, batch=1, heads=2, head_dim=head_dim, block=block,
+             topk=0.3, p=0.3, text_bias=0.4)
+    print("list lengths", w, flush=True)
+    q, k, v = ji.make_qkv(w, 51)
+    layer = CarveLayer(w, "cuda:0", want_lse=True)
+    lay = oracle_layout(w)
+    rng = np.random.default_rng(7)
+    lengths = [0, 1, 2, 3, 4, 5, 7, 8, 9, 15, 16, 17, lay.M]
+    cnt = np.zeros((1, 2, lay.M), dtype=np.int32)
+    idx = np.full((1, 2, lay.M, lay.M), -1, dtype=np.int32)
+    mask = np.zeros((1, 2, lay.M, lay.M), dtype=bool)
+    for h in range(2):
+        for i in range(lay.M):
+            n = min(lengths[(i + 5 * h) % len(lengths)], lay.M)
+            chosen = rng.permutation(lay.M)[:n]
+            if n > 1 and i % 2:
+                chosen[0] = lay.M - 1       # the ragged text block first
+            chosen = list(dict.fromkeys(chosen.tolist()))
+            cnt[0, h, i] = len(chosen)
+            idx[0, h, i, :len(chosen)] = chosen
+            mask[0, h, i, chosen] = True
+    layer.permute_in(q.cuda(), k.cuda(), v.cuda())
+    layer.sel_count.copy_(torch.from_numpy(cnt))
+    layer.sel_index.copy_(torch.from_numpy(idx))
+    layer.o_c.view(torch.int16).fill_(0x7FC1)
+    layer.attend()
+    torch.cuda.synchronize()
+    qc, kc, vc = [jo.permute(to_f64(x), lay) for x in (q, k, v)]
+    want, want_lse = jo.block_sparse_attention(qc, kc, vc, mask, lay, beta=w["text_bias"], return_lse=True)
+    check_output(to_f64(layer.o_c), want, "list lengths %d/%d" % (head_dim, block))
+    got = layer.lse.cpu().numpy().astype(np.float64)
+    alive = np.isfinite(want_lse)
+    assert np.isneginf(got[~alive]).all()
+    assert np.abs(got[alive] - want_lse[alive]).max() <= 1e-3     # float32 sums and one float32 logarithm
