@@ -119,24 +119,73 @@ __device__ inline void wait_vmem() { __builtin_amdgcn_s_waitcnt(0x0F70); }   // 
 
 // Work mapping shared by the attention kernels.  The text query blocks of every (batch, head) are
 // dense rows, several times longer than a vision row: they are dealt out first, ahead of all vision
-// blocks, so that none of them starts late and runs on alone at the end.  The vision blocks follow
-// head by head; workgroups are dealt round-robin to the 8 XCDs, and each XCD gets a contiguous run
-// of query blocks of the head, so that the whole chip works on one head at a time (its K and V stay
-// in the last-level cache) and neighbouring query blocks, whose selections overlap, share an L2.
-// Returns false for the filler workgroups of the last run.
-__device__ inline bool map_work(int n, int n_bh, int M, int M_v, int chunk, int* bh, int* i) {
-  const int M_c = M - M_v;
-  const int n_text = n_bh * M_c;
-  if (n < n_text) {
-    *bh = n / M_c;
-    *i = M_v + n % M_c;
+// blocks, so that none of them starts late and runs on alone at the end.  The vision blocks follow.
+// Workgroups are dealt round-robin to the 8 XCDs; `share` of them (8, 4, 2 or 1) work on the same head
+// at a time and split its query blocks into contiguous runs of `chunk`, whose selections overlap; the
+// heads are divided evenly among the 8 / share groups.  plan_work() says how `share` is chosen.
+struct WorkMap {
+  int n_bh, M, M_v;
+  int share, chunk;   // XCDs per head, query blocks of a head per XCD
+  int units;          // n_bh * chunk: query blocks (with fillers) per member of a group, over all groups
+  int text_chunk;     // text blocks per XCD when share < 8
+  int text_wgs, n_wg; // workgroups of the text blocks, all workgroups
+};
+
+// Fewer XCDs on a head mean more of the workgroups that share an L2 read the same keys at about the same time: with
+// share = 8 and M_v = 234 an XCD's 128 resident workgroups belong to four heads, with share = 1 to one.  So the
+// largest share is taken that still gives an XCD enough query blocks of one head to fill it, but the heads that
+// are then in flight at once have to stay in the 256 MB last-level cache (720p: a head is 61 MB, and share = 1 costs
+// 8 %).  Attention time at share 8 / 4 / 2 / 1, the rule's choice marked:
+//   47 blocks x 16 heads, D = 64            138 / 137 / 132 / 111* us (each XCD also gets its own text rows)
+//   220 blocks of 64 x 12 heads, D = 128    511 / 476 / 469 / 472* us
+//   260 blocks x 24 heads, D = 128          4.40 / 4.35 / 4.33* / 4.33 ms
+//   2032 blocks of 32 x 2 heads, D = 64     0.75* / 0.88 / 0.90 / 0.88 ms
+//   929 blocks x 24 heads, D = 128          20.8* / 20.5 / 20.8 / 22.4 ms (k = 0.1)
+//
+// With few XCDs per head a head with long lists keeps its XCDs busy longer than the others.  Lists have about the same
+// length as long as K_top decides it; where the cumulative-probability rule does (p well above k) heads differ, and
+// a grid of several generations of workgroups stays at share = 8 (248 blocks x 12 heads, p = 0.9: share = 2 is up to
+// 2.3 % slower).
+WorkMap plan_work(int n_bh, int M, int M_v, int slots_per_xcd, size_t head_kv_bytes, double topk_ratio,
+                  double cum_prob) {
+  WorkMap w;
+  const bool even = cum_prob <= 2.0 * topk_ratio || (long long)n_bh * M <= 8ll * slots_per_xcd;
+  w.n_bh = n_bh;
+  w.M = M;
+  w.M_v = M_v;
+  int share = 8;
+  while (even && share > 1 && M_v / share < slots_per_xcd &&
+         (size_t)(16 / share) * head_kv_bytes <= (size_t)192 << 20)
+    share /= 2;
+  w.share = share;
+  w.chunk = (M_v + share - 1) / share;
+  w.units = n_bh * w.chunk;
+  const int n_text = n_bh * (M - M_v);
+  w.text_chunk = (n_text + 7) / 8;
+  w.text_wgs = share == 8 ? n_text : 8 * w.text_chunk;
+  const int groups = 8 / share;
+  w.n_wg = w.text_wgs + 8 * ((w.units + groups - 1) / groups);
+  return w;
+}
+
+// Returns false for the filler workgroups at the end of a run.
+__device__ inline bool map_work(int n, const WorkMap& w, int* bh, int* i) {
+  const int M_c = w.M - w.M_v;
+  if (n < w.text_wgs) {
+    const int t = w.share == 8 ? n : (n & 7) * w.text_chunk + (n >> 3);
+    if (t >= w.n_bh * M_c) return false;
+    *bh = t / M_c;
+    *i = w.M_v + t % M_c;
     return true;
   }
-  n -= n_text;
-  const int xcd = n & 7, s = n >> 3;
-  *bh = s / chunk;
-  *i = xcd * chunk + s % chunk;
-  return *i < M_v;
+  n -= w.text_wgs;
+  const int xcd = n & 7, groups = 8 / w.share, group = xcd / w.share, member = xcd % w.share;
+  const int first = (int)((long long)w.units * group / groups), end = (int)((long long)w.units * (group + 1) / groups);
+  const int u = first + (n >> 3);
+  if (u >= end) return false;
+  *bh = u / w.chunk;
+  *i = member * w.chunk + u % w.chunk;
+  return *i < w.M_v;
 }
 
 // compile-time loop: f(integral_constant<int, 0>) ... f(integral_constant<int, N-1>)
@@ -179,8 +228,8 @@ __device__ inline float max_with_other_half(float x) {
 }
 
 // Alg. 4 keeps a running maximum m of every row and rescales l and O whenever it grows.  Here the row
-// maximum is not on the common path: the maximum over the 32 logits of a lane (16 v_max3, a cross-half exchange, a compare) is a
-// chain that has to finish after the last MFMA of S and before the first exponential can issue, in
+// maximum is not on the common path: the maximum over the 32 logits of a lane (16 v_max3, a cross-half
+// exchange, a compare) is a chain that has to finish after the last MFMA of S and before the first exponential can issue, in
 // every step of every wavefront.  Without it a step forms its probabilities against the reference as
 // it stands and only looks at the sum: while a lane's 32 probabilities add up to at most P_SUM_MAX they
 // are all representable, and so are the float32 sums and products built from them (bf16 and float32
@@ -213,26 +262,26 @@ constexpr float P_SUM_MAX = 1073741824.0f;   // 2^30
 // The price: the order, and with it the last bits of the output, can differ from run to run.
 // ---------------------------------------------------------------------------------------------
 template <int BLK, int D>
-constexpr int attn_h_min_waves() { return D == 128 ? 3 : 4; }   // wavefronts per SIMD the registers have to leave room for
+constexpr int attn_h_min_waves() { return D == 128 ? 3 : 4; }   // wavefronts per SIMD that the registers have to allow
 
 template <int BLK, int D, bool PACED>
 __global__ __launch_bounds__(2 * BLK, (attn_h_min_waves<BLK, D>())) void attn_h_kernel(
     const uint16_t* __restrict__ q, const u32x4* __restrict__ kp, const u32x4* __restrict__ vp,
     const int32_t* __restrict__ sel_count, const int32_t* __restrict__ sel_index,
-    const int32_t* __restrict__ blk_valid, uint16_t* __restrict__ out, float* __restrict__ lse, int n_bh, int M,
-    int M_v, int n_pad, int chunk, int pad_v, int pad_c, float scale_log2e, float bias_log2e,
-    const uint32_t* __restrict__ pace_params) {
+    uint16_t* __restrict__ out, float* __restrict__ lse, WorkMap work, int n_pad, int pad_v, int pad_c,
+    float scale_log2e, float bias_log2e, const uint32_t* __restrict__ pace_params) {
   constexpr int KS = D / 16, DT = D / 32, PS = BLK / 16, MH = 2, PH = 4;
   constexpr int NW = BLK / 32, NTHR = 64 * NW, HALVES = BLK / 64;   // wavefronts, threads, steps per key block
   constexpr int TILE_CHUNKS = BLK * D / 8, HALF_CHUNKS = 64 * D / 8, CPT = HALF_CHUNKS / NTHR;
-  static_assert(HALVES >= 1 && (!PACED || HALVES == 2), "steps of 64 keys; the paced walk samples its clock in the first of two");
+  static_assert(HALVES >= 1 && (!PACED || HALVES == 2), "64 keys a step; the paced walk needs two steps a block");
   __shared__ u32x4 Ks[HALF_CHUNKS];   // fragments (m2, ks) of the current 64 keys
   __shared__ u32x4 Vs[HALF_CHUNKS];   // fragments (dt, p2) of the current 64 keys
   __shared__ uint32_t rem_bits[PACED ? 64 : 1];   // PACED: bitmap of the blocks still to visit, 32 per word
   __shared__ int pace_slot[2];                    // PACED: G for the next pick, published by thread 0
 
   int bh, i;
-  if (!map_work(blockIdx.x, n_bh, M, M_v, chunk, &bh, &i)) return;
+  if (!map_work(blockIdx.x, work, &bh, &i)) return;
+  const int M = work.M, M_v = work.M_v;
 
   const int tid = threadIdx.x, lane = tid & 63;
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
@@ -534,14 +583,14 @@ template <int D, int NS>
 __global__ __launch_bounds__(64 * NS, (D == 128 ? 2 : 4)) void attn_kernel(
     const uint16_t* __restrict__ q, const u32x4* __restrict__ kp, const u32x4* __restrict__ vp,
     const int32_t* __restrict__ sel_count, const int32_t* __restrict__ sel_index, uint16_t* __restrict__ out,
-    float* __restrict__ lse, int n_bh, int M, int M_v, int n_pad, int chunk, int pad_v, int pad_c, float scale_log2e,
-    float bias_log2e) {
+    float* __restrict__ lse, WorkMap work, int n_pad, int pad_v, int pad_c, float scale_log2e, float bias_log2e) {
   constexpr int BLK = 32, KS = D / 16, DT = D / 32, PS = BLK / 16, TILE_CHUNKS = BLK * D / 8;
   __shared__ float part[NS][16][64];   // one channel tile of every wavefront's O, accumulator order
   __shared__ float stat[NS][2][32];    // reference and sum of every row
 
   int bh, i;
-  if (!map_work(blockIdx.x, n_bh, M, M_v, chunk, &bh, &i)) return;
+  if (!map_work(blockIdx.x, work, &bh, &i)) return;
+  const int M = work.M, M_v = work.M_v;
 
   const int lane = threadIdx.x & 63;
   const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
@@ -755,31 +804,31 @@ int run_attention(const jenga_plan* p, const void* q, void* ws, const int32_t* s
   const size_t half = (((size_t)bh * f.N_pad * D * 2) + 255) & ~(size_t)255;
   const u32x4* kp = (const u32x4*)ws;
   const u32x4* vp = (const u32x4*)((const char*)ws + half);
-  const int chunk = (f.M_v + 7) / 8;                      // vision query blocks per XCD and head
-  const int n_wg = bh * f.M_c + bh * 8 * chunk;           // text blocks first, then the vision runs
+  // workgroups resident on the 32 CUs of an XCD: by registers and LDS 2, 3 to 4 or 5 to 8 per CU
+  constexpr int PER_CU = BLK == 32 ? 2 : BLK == 64 ? (D == 128 ? 5 : 8) : (D == 128 ? 3 : 4);
+  const WorkMap work = plan_work(bh, f.M, f.M_v, 32 * PER_CU, (size_t)f.N_pad * D * 4, c.topk_ratio, c.cum_prob);
   const float log2e = 1.4426950408889634f;
-  const float scale = log2e / sqrtf((float)D);
+  const float scale = log2e / sqrtf((float)D), bias = c.text_bias * log2e;
   if constexpr (BLK == 128) {
     if (c.flags & JENGA_FLAG_PACED_WALK) {
       // a workgroup spends about 6.3 us (D = 128; 3.6 us at D = 64) on a block of 128 keys when three share a CU
       uint32_t* params = (uint32_t*)((char*)ws + 2 * half);
       walk_pace_kernel<<<1, 1024, 0, st>>>(sel_count, bh * f.M, f.M, D == 128 ? 630.f : 360.f, params);
-      attn_h_kernel<BLK, D, true><<<dim3(n_wg), 2 * BLK, 0, st>>>((const uint16_t*)q, kp, vp, sel_count, sel_index,
-                                                         p->d_blk_valid, (uint16_t*)out, lse, bh, f.M, f.M_v, f.N_pad,
-                                                         chunk, f.pad_v, f.pad_c, scale, c.text_bias * log2e, params);
+      attn_h_kernel<BLK, D, true><<<dim3(work.n_wg), 2 * BLK, 0, st>>>((const uint16_t*)q, kp, vp, sel_count, sel_index,
+                                                                       (uint16_t*)out, lse, work, f.N_pad, f.pad_v,
+                                                                       f.pad_c, scale, bias, params);
       return hipGetLastError() == hipSuccess ? JENGA_OK : JENGA_EHIP;
     }
   }
   if constexpr (BLK == 32) {   // in-order walk only
     constexpr int NS = D == 128 ? 4 : 8;
-    attn_kernel<D, NS><<<dim3(n_wg), 64 * NS, 0, st>>>((const uint16_t*)q, kp, vp, sel_count, sel_index, (uint16_t*)out,
-                                                       lse, bh, f.M, f.M_v, f.N_pad, chunk, f.pad_v, f.pad_c, scale,
-                                                       c.text_bias * log2e);
+    attn_kernel<D, NS><<<dim3(work.n_wg), 64 * NS, 0, st>>>((const uint16_t*)q, kp, vp, sel_count, sel_index,
+                                                            (uint16_t*)out, lse, work, f.N_pad, f.pad_v, f.pad_c, scale,
+                                                            bias);
   } else {
-    attn_h_kernel<BLK, D, false><<<dim3(n_wg), 2 * BLK, 0, st>>>((const uint16_t*)q, kp, vp, sel_count, sel_index,
-                                                                 p->d_blk_valid, (uint16_t*)out, lse, bh, f.M, f.M_v,
-                                                                 f.N_pad, chunk, f.pad_v, f.pad_c, scale,
-                                                                 c.text_bias * log2e, nullptr);
+    attn_h_kernel<BLK, D, false><<<dim3(work.n_wg), 2 * BLK, 0, st>>>((const uint16_t*)q, kp, vp, sel_count, sel_index,
+                                                                      (uint16_t*)out, lse, work, f.N_pad, f.pad_v,
+                                                                      f.pad_c, scale, bias, nullptr);
   }
   return hipGetLastError() == hipSuccess ? JENGA_OK : JENGA_EHIP;
 }

@@ -48,3 +48,29 @@ def test_list_lengths(head_dim, block):
     alive = np.isfinite(want_lse)
     assert np.isneginf(got[~alive]).all()
     assert np.abs(got[alive] - want_lse[alive]).max() <= 1e-3     # float32 sums and one float32 logarithm
+
+
+# Query blocks per head around the sizes at which the heads are dealt to 8, 4, 2 or 1 of the XCDs each, head counts
+# that do not divide: every block has to be computed once, by somebody.
+@pytest.mark.parametrize("m_v,heads,n_text", [(1, 1, 0), (7, 3, 40), (127, 3, 0), (129, 5, 70), (257, 3, 33), (513, 2, 5)])
+def test_every_query_block_is_dealt_out(m_v, heads, n_text):
+    w = dict(T=1, H=1, W=32 * m_v - 3, n_text=n_text, batch=1, heads=heads, head_dim=64, block=32, topk=0.3, p=0.3)
+    print("dealt out", w, flush=True)
+    q, k, v = ji.make_qkv(w, 52)
+    layer = CarveLayer(w, "cuda:0")
+    lay = oracle_layout(w)
+    mask = np.zeros((1, heads, lay.M, lay.M), dtype=bool)
+    mask[:, :, np.arange(lay.M), np.arange(lay.M)] = True
+    mask[:, :, :, lay.M - 1] = True
+    cnt, idx = jo.mask_to_lists(mask)
+    layer.permute_in(q.cuda(), k.cuda(), v.cuda())
+    layer.sel_count.copy_(torch.from_numpy(cnt))
+    layer.sel_index.copy_(torch.from_numpy(idx))
+    layer.o_c.view(torch.int16).fill_(0x7FC1)
+    layer.attend()
+    torch.cuda.synchronize()
+    qc, kc, vc = [jo.permute(to_f64(x), lay) for x in (q, k, v)]
+    # A row has a few dozen keys here and |o| reaches max |v|, so the bound is per rounding, not the one for long rows:
+    # half a bf16 ulp (at most 2^-8 relative) on every probability and on the result, so 2^-8 (max |v| + |o|).
+    err = np.abs(to_f64(layer.o_c) - jo.block_sparse_attention(qc, kc, vc, mask, lay))
+    assert err.max() <= 2.0 ** -7 * np.abs(vc).max()
