@@ -1,16 +1,17 @@
-// Block selection (Sec. 3.1 Eq. 3; appendix Alg. 3 and Eq. 5) in three kernels:
+// Block selection (Sec. 3.1 Eq. 3; appendix Alg. 3 and Eq. 5) in two kernels:
 //   pool_kernel    BlockPool: per-block mean of Q (vision blocks) and K (all blocks)   HBM-bound
-//   scores_kernel  S = Q^ K^T / sqrt(d_k), a small float64 GEMM per (batch, head)       ALU-bound
-//   select_kernel  one wavefront per query block: softmax, N_k, top-N_k, union, compaction
+//   select_kernel  S = Q^ K^T / sqrt(d_k) on the float64 matrix cores into LDS, then one wavefront per query block:
+//                  softmax, N_k, top-N_k, union, compaction
 //
 // All arithmetic is float64: the outcome is a set of integers, and in float64 the sums of bf16
 // inputs are exact and the remaining rounding (1e-16 relative) is far below the spacing of the
 // block probabilities, so the sets do not depend on the order of summation.
 //
-// select_kernel keeps a row of R in registers (NT values per lane) and never sorts.  Positive
-// doubles order like their bit patterns, so the N-th largest value is found by building its bit
-// pattern from the top bit down, counting with wave ballots; the cumulative-probability rule uses
-// the same descent on the sum of the values at or above the candidate.
+// A row of R stays in registers (NT values per lane) and is never sorted.  Positive doubles order like their bit
+// patterns, so the N-th largest value is found by building its bit pattern from the top bit down, counting with wave
+// ballots; the cumulative-probability rule uses the same descent on the sum of the values at or above the candidate.
+// A descent starts below the bits that all values share, compares high words as long as the low ones are undecided,
+// and goes on with one value per lane as soon as 64 are left in question.
 #include <hip/hip_runtime.h>
 
 #include <cmath>
@@ -28,16 +29,13 @@ __device__ inline double bf16_bits_to_double(uint32_t bits16) {
   return (double)__uint_as_float(bits16 << 16);
 }
 
-__device__ inline double wave_sum(double v) {
-#pragma unroll
-  for (int o = 32; o >= 1; o >>= 1) v += __shfl_xor(v, o, 64);
-  return v;
-}
-
-__device__ inline double wave_max(double v) {
-#pragma unroll
-  for (int o = 32; o >= 1; o >>= 1) v = fmax(v, __shfl_xor(v, o, 64));
-  return v;
+// Where channel d of block j lies in its pooled row: pieces of 64 bytes, their order rotated by an exclusive or with the
+// block index.  select_kernel reads the same piece of 16 consecutive blocks at a time; without the rotation those lie
+// a row (1 KB at D = 128) apart and fall on a quarter of the L2's channels (the products of 929 x 931 blocks x 24 heads:
+// 175 us without it, 105 us with).
+template <int D>
+__device__ inline int pooled_pos(int j, int d) {
+  return ((((d >> 3) ^ j) & (D / 8 - 1)) << 3) | (d & 7);
 }
 
 // grid (M, batch*heads, 2): z = 0 pools Q (vision blocks only), z = 1 pools K (all blocks).
@@ -87,96 +85,94 @@ __global__ __launch_bounds__(256) void pool_kernel(const uint16_t* __restrict__ 
     double s = 0.0;
 #pragma unroll
     for (int gg = 0; gg < G; ++gg) s += red[gg][threadIdx.x];
-    out[((size_t)bh * n_blk + j) * D + threadIdx.x] = s / (double)nv;
+    out[((size_t)bh * n_blk + j) * D + pooled_pos<D>(j, threadIdx.x)] = s / (double)nv;
   }
 }
 
-// S[bh][i][j] = sum_d qh[bh][i][d] * kh[bh][j][d] / sqrt(D).  128 x 128 tile per workgroup, 8 x 8 per
-// thread with rows ty + 16 r and columns tx + 16 c: the 16 lanes that differ in tx read consecutive
-// doubles of a K^ row slice (no bank conflicts) and share one address of the Q^ slice (broadcast),
-// and 64 FMAs stand against 16 LDS reads.
-template <int D>
-__global__ __launch_bounds__(256) void scores_kernel(const double* __restrict__ qh, const double* __restrict__ kh,
-                                                     double* __restrict__ S, int M_v, int M) {
-  constexpr int DC = 8, T = 128;
-  __shared__ double As[DC][T];
-  __shared__ double Bs[DC][T];
-  const int bh = blockIdx.z;
-  const int i0 = blockIdx.y * T, j0 = blockIdx.x * T;
-  const int tx = threadIdx.x % 16, ty = threadIdx.x / 16;
-  const int lr = threadIdx.x / 2, ld = (threadIdx.x % 2) * 4;   // loader: row of the tile, first of 4 d's
-  const double* qa = qh + ((size_t)bh * M_v + min(i0 + lr, M_v - 1)) * D + ld;
-  const double* kb = kh + ((size_t)bh * M + min(j0 + lr, M - 1)) * D + ld;
-  double acc[8][8];
-#pragma unroll
-  for (int r = 0; r < 8; ++r)
-#pragma unroll
-    for (int c = 0; c < 8; ++c) acc[r][c] = 0.0;
-  for (int d0 = 0; d0 < D; d0 += DC) {
-#pragma unroll
-    for (int e = 0; e < 4; ++e) {
-      As[ld + e][lr] = qa[d0 + e];
-      Bs[ld + e][lr] = kb[d0 + e];
-    }
-    __syncthreads();
-#pragma unroll
-    for (int dd = 0; dd < DC; ++dd) {
-      double a[8], b[8];
-#pragma unroll
-      for (int r = 0; r < 8; ++r) a[r] = As[dd][ty + 16 * r];
-#pragma unroll
-      for (int c = 0; c < 8; ++c) b[c] = Bs[dd][tx + 16 * c];
-#pragma unroll
-      for (int r = 0; r < 8; ++r)
-#pragma unroll
-        for (int c = 0; c < 8; ++c) acc[r][c] = fma(a[r], b[c], acc[r][c]);
-    }
-    __syncthreads();
-  }
-  const double inv = 1.0 / sqrt((double)D);
-#pragma unroll
-  for (int r = 0; r < 8; ++r) {
-    const int i = i0 + ty + 16 * r;
-    if (i >= M_v) continue;
-#pragma unroll
-    for (int c = 0; c < 8; ++c) {
-      const int j = j0 + tx + 16 * c;
-      if (j < M) S[((size_t)bh * M_v + i) * M + j] = acc[r][c] * inv;
-    }
-  }
+// Wave-wide reductions in the vector ALU (DPP): six dependent steps of a few cycles each, where the same through
+// __shfl_xor is twelve LDS round trips.  The result is uniform.
+template <int CTRL, int ROW_MASK>
+__device__ inline double dpp_move(double old, double x) {
+  const uint64_t o = (uint64_t)__double_as_longlong(old), v = (uint64_t)__double_as_longlong(x);
+  const uint32_t lo = __builtin_amdgcn_update_dpp((uint32_t)o, (uint32_t)v, CTRL, ROW_MASK, 0xF, false);
+  const uint32_t hi = __builtin_amdgcn_update_dpp((uint32_t)(o >> 32), (uint32_t)(v >> 32), CTRL, ROW_MASK, 0xF, false);
+  return __longlong_as_double((long long)(((uint64_t)hi << 32) | lo));
+}
+__device__ inline uint64_t readlane64(uint64_t x, int lane) {
+  return ((uint64_t)(uint32_t)__builtin_amdgcn_readlane((uint32_t)(x >> 32), lane) << 32) |
+         (uint32_t)__builtin_amdgcn_readlane((uint32_t)x, lane);
+}
+__device__ inline double lane63(double x) {
+  return __longlong_as_double((long long)readlane64((uint64_t)__double_as_longlong(x), 63));
+}
+// row_shr 1, 2, 4, 8 sum each row of 16 lanes into its last lane; row_bcast 15 and 31 add the rows up
+__device__ inline double wave_sum(double v) {
+  v += dpp_move<0x111, 0xF>(0.0, v);
+  v += dpp_move<0x112, 0xF>(0.0, v);
+  v += dpp_move<0x114, 0xF>(0.0, v);
+  v += dpp_move<0x118, 0xF>(0.0, v);
+  v += dpp_move<0x142, 0xA>(0.0, v);
+  v += dpp_move<0x143, 0xC>(0.0, v);
+  return lane63(v);
+}
+__device__ inline double wave_max(double v) {
+  v = fmax(v, dpp_move<0x111, 0xF>(v, v));
+  v = fmax(v, dpp_move<0x112, 0xF>(v, v));
+  v = fmax(v, dpp_move<0x114, 0xF>(v, v));
+  v = fmax(v, dpp_move<0x118, 0xF>(v, v));
+  v = fmax(v, dpp_move<0x142, 0xA>(v, v));
+  v = fmax(v, dpp_move<0x143, 0xC>(v, v));
+  return lane63(v);
+}
+__device__ inline uint32_t wave_min_u32(uint32_t v) {
+  v = min(v, (uint32_t)__builtin_amdgcn_update_dpp(v, v, 0x111, 0xF, 0xF, false));
+  v = min(v, (uint32_t)__builtin_amdgcn_update_dpp(v, v, 0x112, 0xF, 0xF, false));
+  v = min(v, (uint32_t)__builtin_amdgcn_update_dpp(v, v, 0x114, 0xF, 0xF, false));
+  v = min(v, (uint32_t)__builtin_amdgcn_update_dpp(v, v, 0x118, 0xF, 0xF, false));
+  v = min(v, (uint32_t)__builtin_amdgcn_update_dpp(v, v, 0x142, 0xA, 0xF, false));
+  v = min(v, (uint32_t)__builtin_amdgcn_update_dpp(v, v, 0x143, 0xC, 0xF, false));
+  return __builtin_amdgcn_readlane(v, 63);
 }
 
-// One wavefront per (batch, head, query block).  NT = values per lane, M <= 64*NT.
+// Descent over the bit patterns of a row of R (one wavefront, NT values per lane), highest bit first.  The answer lies
+// in [lo, end); bits above `b` are decided.  n_lo and n_end count the values at or above lo and end.
+struct Interval {
+  uint64_t lo, end;
+  int b, n_lo, n_end;
+};
+
+// Compacts the at most 64 values inside the interval to one per lane, 0 in the lanes left over.
 template <int NT>
-__global__ __launch_bounds__(256) void select_kernel(const double* __restrict__ S,
-                                                     const uint64_t* __restrict__ fixed_bits,
-                                                     int32_t* __restrict__ sel_count, int32_t* __restrict__ sel_index,
-                                                     uint8_t* __restrict__ mask, int M_v, int M, int n_rows,
-                                                     int K_top, double p, int nt64) {
-  const int lane = threadIdx.x & 63;
-  const int row = blockIdx.x * 4 + (threadIdx.x >> 6);
-  if (row >= n_rows) return;
-  const int bh = row / M, i = row % M;
-  int32_t* idx_out = sel_index + (size_t)row * M;
-  uint8_t* mask_out = mask ? mask + (size_t)row * M : nullptr;
+__device__ __forceinline__ uint64_t values_inside(const double (&r)[NT], const Interval& v, int M, int lane, double* row) {
   const uint64_t lt_mask = (1ull << lane) - 1ull;
-
-  if (i >= M_v) {   // text query block: sees every block (Alg. 2)
-    for (int j = lane; j < M; j += 64) {
-      idx_out[j] = j;
-      if (mask_out) mask_out[j] = 1;
-    }
-    if (lane == 0) sel_count[row] = M;
-    return;
+  int base = 0;
+#pragma unroll
+  for (int t = 0; t < NT; ++t) {
+    const uint64_t key = (uint64_t)__double_as_longlong(r[t]);
+    const bool in = t * 64 + lane < M && key >= v.lo && key < v.end;
+    const uint64_t m = __ballot(in);
+    if (in) row[base + (int)__popcll(m & lt_mask)] = r[t];
+    base += (int)__popcll(m);
   }
+  __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");   // the other lanes' values, same wavefront
+  const uint64_t key = lane < base ? (uint64_t)__double_as_longlong(row[lane]) : 0;
+  __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+  return key;
+}
 
-  const double* srow = S + ((size_t)bh * M_v + i) * M;
+// One row of the selection by one wavefront: softmax of the scores in `row` (LDS, overwritten), N_k, the top N_k, the
+// union with `fixed_lane` (lane t holds word t of the row's fixed mask), compaction.  See the head of this file.
+template <int NT>
+__device__ __forceinline__ void select_row(double* row, uint64_t fixed_lane, int32_t* idx_out, uint8_t* mask_out, int* count,
+                                  int M, int K_top, double p) {
+  const int lane = threadIdx.x & 63;
+  const uint64_t lt_mask = (1ull << lane) - 1ull;
   double r[NT];
   double mx = -INFINITY;
 #pragma unroll
   for (int t = 0; t < NT; ++t) {
     const int j = t * 64 + lane;
-    r[t] = j < M ? srow[j] : -INFINITY;
+    r[t] = j < M ? row[j] : -INFINITY;
     mx = fmax(mx, r[t]);
   }
   mx = wave_max(mx);
@@ -188,33 +184,103 @@ __global__ __launch_bounds__(256) void select_kernel(const double* __restrict__ 
     z += r[t];
   }
   z = wave_sum(z);
-  uint64_t key[NT];
+  if (z != z) {   // an undefined or infinite score: no order to select by, every block is kept
+#pragma unroll
+    for (int t = 0; t < NT; ++t) {
+      const int j = t * 64 + lane;
+      if (j < M) {
+        idx_out[j] = j;
+        if (mask_out) mask_out[j] = 1;
+      }
+    }
+    if (lane == 0) *count = M;
+    return;
+  }
+  if constexpr (NT == 1) {
+    // One value per lane: its rank and C_n by comparing it with every other, no chain of dependent reductions.
+    // (8 heads of 17 blocks: 9.6 -> 5.4 us for the kernel; with two values per lane the descents are as fast.)
+    const double mine = r[0] = r[0] / z;
+    int rank = 0;
+    double sum_before = 0.0;
+#pragma unroll 4
+    for (int j = 0; j < M; ++j) {
+      const double rj = __longlong_as_double((long long)readlane64((uint64_t)__double_as_longlong(mine), j));
+      const bool before = rj > mine || (rj == mine && j < lane);
+      rank += before ? 1 : 0;
+      sum_before += before ? rj : 0.0;
+    }
+    const bool valid = lane < M;
+    const int n_star = (int)__popcll(__ballot(valid && sum_before + mine <= p)) + 1;
+    const uint64_t fixed = readlane64(fixed_lane, 0);
+    const bool sel = valid && (rank < max(n_star, K_top) || ((fixed >> lane) & 1ull));
+    const uint64_t sel_mask = __ballot(sel);
+    if (sel) idx_out[__popcll(sel_mask & lt_mask)] = lane;
+    if (mask_out && valid) mask_out[lane] = sel ? 1 : 0;
+    if (lane == 0) *count = (int)__popcll(sel_mask);
+    return;
+  }
+  uint32_t hi_min = 0xFFFFFFFFu;
 #pragma unroll
   for (int t = 0; t < NT; ++t) {
-    r[t] = r[t] / z;
-    key[t] = (uint64_t)__double_as_longlong(r[t]);   // R >= 0: bit order is value order
+    r[t] = r[t] / z;   // >= 0: bit order is value order
+    if (t * 64 + lane < M) hi_min = min(hi_min, (uint32_t)__double2hiint(r[t]));
   }
-
-  // value of the K_top-th largest: largest pattern with count(key >= pattern) >= K_top
-  // The descent stops as soon as exactly K_top values lie at or above the pattern built so far: that set is the
-  // answer whatever the remaining bits are (typically after 20-25 of the 63 bits).
-  uint64_t tau_k = 0;
-  for (int bit = 62; bit >= 0; --bit) {
-    const uint64_t cand = tau_k | (1ull << bit);
-    int cnt = 0;
+  hi_min = wave_min_u32(hi_min);
+  // The largest value is exp(0) / z.  The leading bits that it shares with the smallest are those of every value.
+  const uint32_t hi_max = __builtin_amdgcn_readfirstlane((uint32_t)__double2hiint(1.0 / z));
+  Interval all;
+  all.b = 31 + (hi_min == hi_max ? 0 : 32 - __builtin_clz(hi_min ^ hi_max));
+  all.lo = ((uint64_t)hi_max << 32) & ~((2ull << all.b) - 1ull);
+  all.end = all.lo + (2ull << all.b);
+  all.n_lo = M;
+  all.n_end = 0;
+  auto count_from = [&](uint64_t cand, int b) {   // values at or above cand, whose bits below b are zero
+    int n = 0;
+    if (b >= 32) {
 #pragma unroll
-    for (int t = 0; t < NT; ++t) cnt += __popcll(__ballot(key[t] >= cand));
-    if (cnt >= K_top) {
-      tau_k = cand;
-      if (cnt == K_top) break;
+      for (int t = 0; t < NT; ++t) n += (int)__popcll(__ballot((uint32_t)__double2hiint(r[t]) >= (uint32_t)(cand >> 32)));
+    } else {
+#pragma unroll
+      for (int t = 0; t < NT; ++t) n += (int)__popcll(__ballot((uint64_t)__double_as_longlong(r[t]) >= cand));
+    }
+    return n;
+  };
+
+  // value of the K_top-th largest: the largest pattern with at least K_top values at or above it.  Stops as soon as
+  // exactly K_top values lie there: that set is the answer whatever the remaining bits are.
+  Interval v = all;
+  while (v.b >= 0 && v.n_lo != K_top && v.n_lo - v.n_end > 64) {
+    const uint64_t cand = v.lo | (1ull << v.b);
+    const int n = count_from(cand, v.b);
+    if (n >= K_top) {
+      v.lo = cand;
+      v.n_lo = n;
+    } else {
+      v.end = cand;
+      v.n_end = n;
+    }
+    --v.b;
+  }
+  if (v.b >= 0 && v.n_lo != K_top) {   // at most 64 candidates are left
+    const uint64_t mine = values_inside<NT>(r, v, M, lane, row);
+    const int above = v.n_end;
+    for (; v.b >= 0 && v.n_lo != K_top; --v.b) {
+      const uint64_t cand = v.lo | (1ull << v.b);
+      const int n = above + (int)__popcll(__ballot(mine >= cand));
+      if (n >= K_top) {
+        v.lo = cand;
+        v.n_lo = n;
+      }
     }
   }
+  const uint64_t tau_k = v.lo;
+  const bool exact = v.n_lo == K_top;   // the K_top values are those at or above tau_k
   int cnt_gt = 0;
   double sum_gt = 0.0;
 #pragma unroll
   for (int t = 0; t < NT; ++t) {
-    const bool gt = key[t] > tau_k;
-    cnt_gt += __popcll(__ballot(gt));
+    const bool gt = (uint64_t)__double_as_longlong(r[t]) > tau_k;
+    cnt_gt += (int)__popcll(__ballot(gt));
     sum_gt += gt ? r[t] : 0.0;
   }
   sum_gt = wave_sum(sum_gt);
@@ -223,43 +289,76 @@ __global__ __launch_bounds__(256) void select_kernel(const double* __restrict__ 
   uint64_t tau = tau_k;
   int n_keep = K_top;
   if (!(topk_mass > p)) {
-    // cumulative-probability rule: largest pattern whose upper set still sums to more than p
-    // The answer is one of the row's values.  After bit b it lies in [tau_p, tau_p + 2^b); once that interval
-    // holds a single value, that value is the answer and the remaining bits are its bits.
-    uint64_t tau_p = 0;
-    for (int bit = 62; bit >= 0; --bit) {
-      const uint64_t cand = tau_p | (1ull << bit);
-      double f = 0.0;
+    // Cumulative-probability rule: the largest pattern whose upper set still sums to more than p.  It is one of the
+    // row's values below the K_top already summed; once the interval holds a single value, that is the answer.
+    v = all;
+    v.end = exact ? tau_k : tau_k + 1;
+    v.n_end = exact ? K_top : cnt_gt;
+    double f_end = exact ? topk_mass : sum_gt;   // sum of the values at or above end
+    while (v.b >= 0 && v.n_lo - v.n_end > 64) {
+      const uint64_t cand = v.lo | (1ull << v.b);
+      if (cand < v.end) {
+        int n = 0;
+        double f = 0.0;
+        if (v.b >= 32) {
 #pragma unroll
-      for (int t = 0; t < NT; ++t) f += key[t] >= cand ? r[t] : 0.0;
-      f = wave_sum(f);
-      if (f > p) tau_p = cand;
-      const uint64_t hi = tau_p + (1ull << bit);     // exclusive end of the interval that still holds the answer
-      int inside = 0;
-      uint64_t mine = 0;
+          for (int t = 0; t < NT; ++t) {
+            const bool ge = (uint32_t)__double2hiint(r[t]) >= (uint32_t)(cand >> 32);
+            n += (int)__popcll(__ballot(ge));
+            f += ge ? r[t] : 0.0;
+          }
+        } else {
 #pragma unroll
-      for (int t = 0; t < NT; ++t) {
-        const bool in = key[t] >= tau_p && key[t] < hi;
-        inside += __popcll(__ballot(in));
-        if (in) mine = key[t];
+          for (int t = 0; t < NT; ++t) {
+            const bool ge = (uint64_t)__double_as_longlong(r[t]) >= cand;
+            n += (int)__popcll(__ballot(ge));
+            f += ge ? r[t] : 0.0;
+          }
+        }
+        f = wave_sum(f);
+        if (f > p) {
+          v.lo = cand;
+          v.n_lo = n;
+        } else {
+          v.end = cand;
+          v.n_end = n;
+          f_end = f;
+        }
       }
-      if (inside == 1) {
-        const uint64_t who = __ballot(mine != 0);
-        const int src = __builtin_ctzll(who);
-        const uint32_t lo32 = __builtin_amdgcn_readlane((uint32_t)mine, src);
-        const uint32_t hi32 = __builtin_amdgcn_readlane((uint32_t)(mine >> 32), src);
-        tau_p = ((uint64_t)hi32 << 32) | lo32;
-        break;
+      --v.b;
+    }
+    if (v.b >= 0 && v.n_lo > v.n_end) {
+      const uint64_t mine = values_inside<NT>(r, v, M, lane, row);
+      const int above = v.n_end;
+      for (; v.b >= 0 && v.n_lo - v.n_end != 1; --v.b) {
+        const uint64_t cand = v.lo | (1ull << v.b);
+        if (cand >= v.end) continue;
+        const bool ge = mine >= cand;
+        const int n = above + (int)__popcll(__ballot(ge));
+        const double f = f_end + wave_sum(ge ? __longlong_as_double((long long)mine) : 0.0);
+        if (f > p) {
+          v.lo = cand;
+          v.n_lo = n;
+        } else {
+          v.end = cand;
+          v.n_end = n;
+        }
+      }
+      if (v.n_lo - v.n_end == 1) {
+        const uint64_t who = __ballot(mine >= v.lo && mine < v.end && mine != 0);
+        if (who != 0) v.lo = readlane64(mine, __builtin_ctzll(who));   // 0: the one value left is 0.0, and so is lo
       }
     }
+    const uint64_t tau_p = v.lo;
     int g_cnt = 0, e_cnt = 0;
     double g_sum = 0.0;
 #pragma unroll
     for (int t = 0; t < NT; ++t) {
       const bool valid = t * 64 + lane < M;
-      const bool gt = key[t] > tau_p;
-      g_cnt += __popcll(__ballot(gt));
-      e_cnt += __popcll(__ballot(valid && key[t] == tau_p));
+      const uint64_t key = (uint64_t)__double_as_longlong(r[t]);
+      const bool gt = key > tau_p;
+      g_cnt += (int)__popcll(__ballot(gt));
+      e_cnt += (int)__popcll(__ballot(valid && key == tau_p));
       g_sum += gt ? r[t] : 0.0;
     }
     g_sum = wave_sum(g_sum);
@@ -281,18 +380,101 @@ __global__ __launch_bounds__(256) void select_kernel(const double* __restrict__ 
   for (int t = 0; t < NT; ++t) {
     const int j = t * 64 + lane;
     const bool valid = j < M;
-    const bool eq = valid && key[t] == tau;
+    const uint64_t key = (uint64_t)__double_as_longlong(r[t]);
+    const bool eq = valid && key == tau;
     const uint64_t eq_mask = __ballot(eq);
-    bool sel = (valid && key[t] > tau) || (eq && taken + (int)__popcll(eq_mask & lt_mask) < need);
+    const uint64_t fixed = readlane64(fixed_lane, t);
+    bool sel = (valid && key > tau) || (eq && taken + (int)__popcll(eq_mask & lt_mask) < need);
     taken += (int)__popcll(eq_mask);
-    if (t < nt64) sel = sel || ((fixed_bits[(size_t)i * nt64 + t] >> lane) & 1ull);
-    sel = sel && valid;
+    sel = (sel || ((fixed >> lane) & 1ull)) && valid;
     const uint64_t sel_mask = __ballot(sel);
-    if (sel) idx_out[out_pos + __popcll(sel_mask & lt_mask)] = j;
-    out_pos += __popcll(sel_mask);
+    if (sel) idx_out[out_pos + (int)__popcll(sel_mask & lt_mask)] = j;
+    out_pos += (int)__popcll(sel_mask);
     if (mask_out && valid) mask_out[j] = sel ? 1 : 0;
   }
-  if (lane == 0) sel_count[row] = out_pos;
+  if (lane == 0) *count = out_pos;
+}
+
+// Scores and selection of ROWS query blocks of one (batch, head) against all M <= 64 * NT key blocks.  First the
+// wavefronts share the columns: S = Q^ K^T / sqrt(D) in 16 x 16 tiles of v_mfma_f64_16x16x4_f64, operands straight
+// from global memory (16 rows x 64 bytes a load, K^ of a head stays in the L2 of the XCD that works on it), results
+// to LDS.  Then every wavefront selects for one row.  S never leaves the CU.
+//
+// LDS holds 16 rows up to 1024 blocks and 8 rows of 2048: the 8-row kernel computes its tiles with the rows twice.
+// Row stride = 16 mod 32 doubles, so the four rows a tile is written to at a time fall on different banks.
+//
+// Time of the kernel, against a 128 x 128 tile of vector FMAs that wrote S to memory and a selection with one chain of
+// LDS exchanges per bit of the cumulative rule:
+//   17 blocks x 8 heads, D = 128     5.4 us (was 43.6 + 11.7: one workgroup per head, most of its tile padding)
+//   222 x 12, D = 128                  19 us (48 + 21)
+//   262 x 24, D = 128                  38 us (53 + 19)
+//   2048 x 2, D = 64                  109 us (38 + 141)
+//   931 x 24, D = 128, k = 0.1        226 us (164 + 145): matrix cores 105 us (75 us at their full rate, the rest is the
+//                                     last round of 5.5 and the first loads), softmax 40, top K 30, the rest of the
+//                                     rows' work 50; the two halves do not overlap, LDS leaves one workgroup on a CU
+typedef double f64x4 __attribute__((ext_vector_type(4)));
+typedef double f64x2 __attribute__((ext_vector_type(2)));
+
+template <int D, int NT, int ROWS>
+__global__ __launch_bounds__(64 * ROWS) void select_kernel(const double* __restrict__ qh, const double* __restrict__ kh,
+                                                           const uint64_t* __restrict__ fixed_bits,
+                                                           int32_t* __restrict__ sel_count,
+                                                           int32_t* __restrict__ sel_index, uint8_t* __restrict__ mask,
+                                                           int M_v, int M, int n_tiles, int n_units, int K_top, double p,
+                                                           int nt64) {
+  __shared__ double S[ROWS][64 * NT + 16];
+  // workgroup n runs on XCD n % 8: each XCD gets a contiguous run of (head, row tile) units
+  const int per_xcd = (n_units + 7) / 8;
+  const int unit = (blockIdx.x & 7) * per_xcd + (blockIdx.x >> 3);
+  if ((int)(blockIdx.x >> 3) >= per_xcd || unit >= n_units) return;
+  const int bh = unit / n_tiles, i0 = unit % n_tiles * ROWS;
+  const int lane = threadIdx.x & 63;
+  const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  const int i = i0 + wave;
+  uint64_t fixed_lane = 0;   // asked for here, needed at the end
+  if (i < M_v && lane < nt64) fixed_lane = fixed_bits[(size_t)i * nt64 + lane];
+
+  if (i0 < M_v) {
+    // lane l: row l % 16 of both operands, channels 8 s + 2 (l / 16) and the next in step s
+    const int g = lane >> 4, c = lane & 15;
+    const int ia = min(i0 + c % ROWS, M_v - 1);
+    const double* qa = qh + ((size_t)bh * M_v + ia) * D;
+    f64x2 a[D / 8];
+#pragma unroll
+    for (int s = 0; s < D / 8; ++s) a[s] = *(const f64x2*)(qa + pooled_pos<D>(ia, 8 * s + 2 * g));
+    const double inv = 1.0 / sqrt((double)D);
+    for (int j0 = 16 * wave; j0 < M; j0 += 16 * ROWS) {
+      const int jb = min(j0 + c, M - 1);
+      const double* kb = kh + ((size_t)bh * M + jb) * D;
+      f64x2 b[D / 8];
+#pragma unroll
+      for (int s = 0; s < D / 8; ++s) b[s] = *(const f64x2*)(kb + pooled_pos<D>(jb, 8 * s + 2 * g));
+      f64x4 acc = {0.0, 0.0, 0.0, 0.0};
+#pragma unroll
+      for (int s = 0; s < D / 8; ++s) {
+        acc = __builtin_amdgcn_mfma_f64_16x16x4f64(a[s].x, b[s].x, acc, 0, 0, 0);
+        acc = __builtin_amdgcn_mfma_f64_16x16x4f64(a[s].y, b[s].y, acc, 0, 0, 0);
+      }
+      // register e of lane l holds row 4 e + l / 16, column l % 16; columns past M are never read
+#pragma unroll
+      for (int e = 0; e < ROWS / 4; ++e) S[4 * e + g][j0 + c] = acc[e] * inv;
+    }
+  }
+  __syncthreads();
+
+  if (i >= M) return;
+  const size_t out_row = (size_t)bh * M + i;
+  int32_t* idx_out = sel_index + out_row * M;
+  uint8_t* mask_out = mask ? mask + out_row * M : nullptr;
+  if (i >= M_v) {   // text query block: sees every block (Alg. 2)
+    for (int j = lane; j < M; j += 64) {
+      idx_out[j] = j;
+      if (mask_out) mask_out[j] = 1;
+    }
+    if (lane == 0) sel_count[out_row] = M;
+    return;
+  }
+  select_row<NT>(S[wave], fixed_lane, idx_out, mask_out, sel_count + out_row, M, K_top, p);
 }
 
 template <int D>
@@ -307,23 +489,21 @@ int run_select(const jenga_plan* p, const void* q, const void* k, int32_t* sel_c
   w += align256((size_t)bh * f.M_v * D * 8);
   double* kh = (double*)w;
   w += align256((size_t)bh * f.M * D * 8);
-  double* S = (double*)w;
-  if (f.M_v > 0) {
+  if (f.M_v > 0)
     pool_kernel<D><<<dim3(f.M, bh, 2), 256, 0, st>>>((const uint16_t*)q, (const uint16_t*)k, qh, kh, p->d_blk_valid,
                                                     f.N_pad, c.block, f.M_v, f.M);
-    scores_kernel<D><<<dim3((f.M + 127) / 128, (f.M_v + 127) / 128, bh), 256, 0, st>>>(qh, kh, S, f.M_v, f.M);
-  }
-  const int n_rows = bh * f.M;
-  const dim3 grid((n_rows + 3) / 4);
-#define JENGA_SELECT(NTV)                                                                                      \
-  select_kernel<NTV><<<grid, 256, 0, st>>>(S, p->d_fixed_bits, sel_count, sel_index, mask, f.M_v, f.M, n_rows, \
-                                           f.K_top, c.cum_prob, p->nt64)
-  if (p->nt64 <= 1) JENGA_SELECT(1);
-  else if (p->nt64 <= 2) JENGA_SELECT(2);
-  else if (p->nt64 <= 4) JENGA_SELECT(4);
-  else if (p->nt64 <= 8) JENGA_SELECT(8);
-  else if (p->nt64 <= 16) JENGA_SELECT(16);
-  else JENGA_SELECT(32);
+#define JENGA_SELECT(NTV, ROWS)                                                                                      \
+  do {                                                                                                               \
+    const int tiles = (f.M + ROWS - 1) / ROWS, units = tiles * bh;                                                   \
+    select_kernel<D, NTV, ROWS><<<dim3((units + 7) / 8 * 8), 64 * ROWS, 0, st>>>(                                    \
+        qh, kh, p->d_fixed_bits, sel_count, sel_index, mask, f.M_v, f.M, tiles, units, f.K_top, c.cum_prob, p->nt64); \
+  } while (0)
+  if (p->nt64 <= 1) JENGA_SELECT(1, 16);
+  else if (p->nt64 <= 2) JENGA_SELECT(2, 16);
+  else if (p->nt64 <= 4) JENGA_SELECT(4, 16);
+  else if (p->nt64 <= 8) JENGA_SELECT(8, 16);
+  else if (p->nt64 <= 16) JENGA_SELECT(16, 16);
+  else JENGA_SELECT(32, 8);
 #undef JENGA_SELECT
   return hipGetLastError() == hipSuccess ? JENGA_OK : JENGA_EHIP;
 }
