@@ -186,8 +186,11 @@ int jenga_select_blocks_static(const jenga_plan* plan, const void* q_curve, cons
  *                caller needs to merge this result with attention over other keys.  Pad query rows
  *                and rows of an empty list get -inf.  Fully overwritten when given
  *   workspace  : at least attn_workspace_bytes, 256-byte aligned (K and V re-tiled for the
- *                matrix cores, and 256 bytes of launch parameters), contents undefined after
- * Equivalent to jenga_pack_kv followed by jenga_block_sparse_attn_packed on the same workspace.
+ *                matrix cores, 256 bytes of launch parameters, and on grids that leave the chip idle
+ *                the results of the parts that long lists are cut into), contents undefined after
+ * Equivalent to jenga_pack_kv followed by jenga_block_sparse_attn_packed on the same workspace (the latter
+ * never cuts lists, since calls on one packed workspace may overlap: where this call does, the two differ
+ * in the last bits).
  */
 int jenga_block_sparse_attn(const jenga_plan* plan, const void* q, const void* k, const void* v,
                             const int32_t* sel_count, const int32_t* sel_index, void* out_curve,
@@ -203,8 +206,8 @@ int jenga_pack_kv(const jenga_plan* plan, const void* k, const void* v, void* wo
 
 /*
  * Second half of jenga_block_sparse_attn: the block-sparse attention kernel itself, reading K and V
- * from a workspace filled by jenga_pack_kv for the same plan.  The packed tiles are only read; the last
- * 256 bytes of the workspace (launch parameters) may be written.  Other arguments as above.
+ * from a workspace filled by jenga_pack_kv for the same plan.  The packed tiles are only read; the 256
+ * bytes behind them (launch parameters) may be written.  Other arguments as above.
  */
 int jenga_block_sparse_attn_packed(const jenga_plan* plan, const void* q, void* packed_kv_workspace,
                                    size_t workspace_bytes, const int32_t* sel_count,

@@ -264,12 +264,23 @@ constexpr float P_SUM_MAX = 1073741824.0f;   // 2^30
 template <int BLK, int D>
 constexpr int attn_h_min_waves() { return D == 128 ? 3 : 4; }   // wavefronts per SIMD that the registers have to allow
 
-template <int BLK, int D, bool PACED>
+//
+// SPLIT: grids that leave the chip idle.  The list of a query block is cut into Split::of(cnt) parts of equal length, a
+// workgroup each; the parts' O, reference and sum go to the workspace and merge_kernel puts them together.
+struct Split {
+  int parts, chunk;   // most parts of a list, list entries from which on there is one more part
+  int stride;         // workgroups per part
+  float* o;           // [batch*heads*M][parts][BLK/32][D/32][4][64][4]: O in accumulator order
+  float* stat;        // [batch*heads*M][parts][2][BLK]: reference, sum
+  __device__ int of(int cnt) const { return max(1, min(parts, (cnt + chunk - 1) / chunk)); }
+};
+
+template <int BLK, int D, bool PACED, bool SPLIT>
 __global__ __launch_bounds__(2 * BLK, (attn_h_min_waves<BLK, D>())) void attn_h_kernel(
     const uint16_t* __restrict__ q, const u32x4* __restrict__ kp, const u32x4* __restrict__ vp,
     const int32_t* __restrict__ sel_count, const int32_t* __restrict__ sel_index,
     uint16_t* __restrict__ out, float* __restrict__ lse, WorkMap work, int n_pad, int pad_v, int pad_c,
-    float scale_log2e, float bias_log2e, const uint32_t* __restrict__ pace_params) {
+    float scale_log2e, float bias_log2e, const uint32_t* __restrict__ pace_params, Split split) {
   constexpr int KS = D / 16, DT = D / 32, PS = BLK / 16, MH = 2, PH = 4;
   constexpr int NW = BLK / 32, NTHR = 64 * NW, HALVES = BLK / 64;   // wavefronts, threads, steps per key block
   constexpr int TILE_CHUNKS = BLK * D / 8, HALF_CHUNKS = 64 * D / 8, CPT = HALF_CHUNKS / NTHR;
@@ -280,8 +291,14 @@ __global__ __launch_bounds__(2 * BLK, (attn_h_min_waves<BLK, D>())) void attn_h_
   __shared__ int pace_slot[2];                    // PACED: G for the next pick, published by thread 0
 
   int bh, i;
-  if (!map_work(blockIdx.x, work, &bh, &i)) return;
+  const int part = SPLIT ? blockIdx.x / split.stride : 0;
+  if (!map_work(SPLIT ? blockIdx.x - part * split.stride : blockIdx.x, work, &bh, &i)) return;
   const int M = work.M, M_v = work.M_v;
+  int n_parts = 1;
+  if constexpr (SPLIT) {
+    n_parts = split.of(min(max(sel_count[(size_t)bh * M + i], 0), M));
+    if (part >= n_parts) return;
+  }
 
   const int tid = threadIdx.x, lane = tid & 63;
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
@@ -298,10 +315,15 @@ __global__ __launch_bounds__(2 * BLK, (attn_h_min_waves<BLK, D>())) void attn_h_
   int cnt = sel_count[(size_t)bh * M + i];
   cnt = min(max(cnt, 0), M);
   const int32_t* idx = sel_index + ((size_t)bh * M + i) * M;
+  if constexpr (SPLIT && !PACED) {   // positions [cnt * part / n_parts, cnt * (part + 1) / n_parts) of the list
+    const int lo = cnt * part / n_parts;
+    cnt = cnt * (part + 1) / n_parts - lo;
+    idx += lo;
+  }
   uint32_t rem = 0, pace_k = 0;
   if constexpr (PACED) {
     // the list as a bitmap (a block listed twice is visited once); lane w of every wavefront holds word w
-    pace_k = pace_params[0];
+    if constexpr (!SPLIT) pace_k = pace_params[0];
     if (tid < 64) rem_bits[tid] = 0;
     __syncthreads();
     for (int t = tid; t < cnt; t += NTHR) {
@@ -314,9 +336,28 @@ __global__ __launch_bounds__(2 * BLK, (attn_h_min_waves<BLK, D>())) void attn_h_
 #pragma unroll
     for (int o = 32; o >= 1; o >>= 1) pc += __shfl_xor(pc, o, 64);
     cnt = __builtin_amdgcn_readfirstlane(pc);
+    if constexpr (SPLIT) {   // the same positions of the bitmap, in ascending order: less than a generation of workgroups
+      const int lo = cnt * part / n_parts, hi = cnt * (part + 1) / n_parts;   // has no use for a common pace
+      const int own = __popc(rem);
+      int before = own;
+#pragma unroll
+      for (int o = 1; o < 64; o <<= 1) {
+        const int x = __shfl_up(before, o, 64);
+        before += lane >= o ? x : 0;
+      }
+      before -= own;   // set bits in the words of the lanes below
+      uint32_t kept = 0;
+      for (int r = before; rem != 0; ++r) {
+        const uint32_t bit = rem & (0u - rem);
+        kept |= r >= lo && r < hi ? bit : 0u;
+        rem ^= bit;
+      }
+      rem = kept;
+      cnt = hi - lo;
+    }
   }
   // G: the low 32 bits of the clock times 2^32 / lap wrap once per lap; the high half of that times M is the block
-  auto pace_now = [&]() { return (int)__umulhi((uint32_t)__builtin_amdgcn_s_memrealtime() * pace_k, (uint32_t)M); };
+  auto pace_now = [&]() { return SPLIT ? 0 : (int)__umulhi((uint32_t)__builtin_amdgcn_s_memrealtime() * pace_k, (uint32_t)M); };
   // The first remaining block at or after G, else the first one after the wrap.  Every wavefront runs this on its
   // own copy of the bitmap with the same G, so the four agree without exchanging the result.  Needs rem != 0.
   // G is wave-uniform, so most of this is scalar arithmetic.
@@ -544,6 +585,22 @@ __global__ __launch_bounds__(2 * BLK, (attn_h_min_waves<BLK, D>())) void attn_h_
   const int row_e = 32 * wave + ql_e;
   const size_t qrow_e = (size_t)bh * n_pad + (size_t)i * BLK + row_e;
   const float l_tot = l_run + __shfl_xor(l_run, 32, 64);
+  if constexpr (SPLIT) {
+    if (n_parts > 1) {
+      const size_t slot = ((size_t)bh * M + i) * split.parts + part;
+      float4* o = (float4*)split.o + (slot * NW + wave) * (DT * 4 * 64) + (tid_e & 63);
+#pragma unroll
+      for (int dt = 0; dt < DT; ++dt)
+#pragma unroll
+        for (int g = 0; g < 4; ++g)
+          o[(dt * 4 + g) * 64] = make_float4(O[dt][4 * g], O[dt][4 * g + 1], O[dt][4 * g + 2], O[dt][4 * g + 3]);
+      if (hl_e == 0) {
+        split.stat[(slot * 2) * BLK + row_e] = m_run;
+        split.stat[(slot * 2 + 1) * BLK + row_e] = l_tot;
+      }
+      return;
+    }
+  }
   const int rows_valid = BLK - (i == M_v - 1 ? pad_v : (i == M - 1 ? pad_c : 0));   // = blk_valid[i], without the load
   const bool row_ok = row_e < rows_valid && l_tot > 0.f;
   const float inv = row_ok ? 1.0f / l_tot : 0.f;
@@ -560,6 +617,67 @@ __global__ __launch_bounds__(2 * BLK, (attn_h_min_waves<BLK, D>())) void attn_h_
       w.y = row_ok ? pack_bf16x2(O[dt][4 * g + 2] * inv, O[dt][4 * g + 3] * inv) : 0u;
       *(uint2*)(orow + 32 * dt + 8 * g + 4 * hl_e) = w;
     }
+}
+
+// merge_kernel: grid (BLK / 32, M, batch * heads), one wavefront per channel tile of 32 query rows.  Puts the parts of
+// the lists that attn_h_kernel<.., SPLIT> cut together, in the order of the parts; the other rows are done already.
+template <int BLK, int D>
+__global__ __launch_bounds__(2 * D) void merge_kernel(const int32_t* __restrict__ sel_count, uint16_t* __restrict__ out,
+                                                      float* __restrict__ lse, int M, int M_v, int n_pad, int pad_v,
+                                                      int pad_c, Split split) {
+  constexpr int DT = D / 32, NW = BLK / 32;
+  const int i = blockIdx.y, bh = blockIdx.z, wave = blockIdx.x;
+  const int n_parts = split.of(min(max(sel_count[(size_t)bh * M + i], 0), M));
+  if (n_parts == 1) return;
+  const int lane = threadIdx.x & 63, dt = threadIdx.x >> 6, hl = lane >> 5, row = 32 * wave + (lane & 31);
+  const size_t slot = ((size_t)bh * M + i) * split.parts;
+  const float4* o = (const float4*)split.o + (slot * NW + wave) * (DT * 4 * 64) + dt * 4 * 64 + lane;
+  const float* stat = split.stat + slot * 2 * BLK + row;
+
+  float m = -INFINITY, l = 0.f, sum[16];
+#pragma unroll
+  for (int r = 0; r < 16; ++r) sum[r] = 0.f;
+  for (int s = 0; s < n_parts; ++s) m = fmaxf(m, stat[s * 2 * BLK]);
+  const float ref = m == -INFINITY ? 0.f : m;
+  for (int s0 = 0; s0 < n_parts; s0 += 4) {   // the loads of four parts in flight at a time
+    float4 v[4][4];
+    float w[4], ls[4];
+#pragma unroll
+    for (int u = 0; u < 4; ++u) {
+      const int s = min(s0 + u, n_parts - 1);
+#pragma unroll
+      for (int g = 0; g < 4; ++g) v[u][g] = o[(size_t)s * NW * (DT * 4 * 64) + g * 64];
+      w[u] = stat[s * 2 * BLK];
+      ls[u] = stat[(s * 2 + 1) * BLK];
+    }
+#pragma unroll
+    for (int u = 0; u < 4; ++u) {
+      if (s0 + u >= n_parts) break;
+      const float weight = __builtin_amdgcn_exp2f(w[u] - ref);
+      l += weight * ls[u];
+#pragma unroll
+      for (int g = 0; g < 4; ++g) {
+        sum[4 * g] += weight * v[u][g].x;
+        sum[4 * g + 1] += weight * v[u][g].y;
+        sum[4 * g + 2] += weight * v[u][g].z;
+        sum[4 * g + 3] += weight * v[u][g].w;
+      }
+    }
+  }
+  const int rows_valid = BLK - (i == M_v - 1 ? pad_v : (i == M - 1 ? pad_c : 0));
+  const bool row_ok = row < rows_valid && l > 0.f;
+  const float inv = row_ok ? 1.0f / l : 0.f;
+  const size_t qrow = (size_t)bh * n_pad + (size_t)i * BLK + row;
+  if (lse != nullptr && threadIdx.x < 32)
+    lse[qrow] = row_ok ? (m + __builtin_amdgcn_logf(l)) * 0.6931471805599453f : -INFINITY;
+  uint16_t* orow = out + qrow * D + 32 * dt + 4 * hl;
+#pragma unroll
+  for (int g = 0; g < 4; ++g) {
+    uint2 w;
+    w.x = row_ok ? pack_bf16x2(sum[4 * g] * inv, sum[4 * g + 1] * inv) : 0u;
+    w.y = row_ok ? pack_bf16x2(sum[4 * g + 2] * inv, sum[4 * g + 3] * inv) : 0u;
+    *(uint2*)(orow + 8 * g) = w;
+  }
 }
 
 // ---------------------------------------------------------------------------------------------
@@ -796,7 +914,7 @@ int run_pack(const jenga_plan* p, const void* k, const void* v, void* ws, hipStr
 }
 
 template <int BLK, int D>
-int run_attention(const jenga_plan* p, const void* q, void* ws, const int32_t* sel_count,
+int run_attention(const jenga_plan* p, const void* q, void* ws, bool may_split, const int32_t* sel_count,
                   const int32_t* sel_index, void* out, float* lse, hipStream_t st) {
   const jenga_config& c = p->cfg;
   const jenga_plan_info_t& f = p->info;
@@ -804,31 +922,47 @@ int run_attention(const jenga_plan* p, const void* q, void* ws, const int32_t* s
   const size_t half = (((size_t)bh * f.N_pad * D * 2) + 255) & ~(size_t)255;
   const u32x4* kp = (const u32x4*)ws;
   const u32x4* vp = (const u32x4*)((const char*)ws + half);
+  uint32_t* params = (uint32_t*)((char*)ws + 2 * half);
   // workgroups resident on the 32 CUs of an XCD: by registers and LDS 2, 3 to 4 or 5 to 8 per CU
-  constexpr int PER_CU = BLK == 32 ? 2 : BLK == 64 ? (D == 128 ? 5 : 8) : (D == 128 ? 3 : 4);
+  constexpr int PER_CU = BLK == 32 ? 2 : jenga::attn_h_per_cu(BLK, D);
   const WorkMap work = plan_work(bh, f.M, f.M_v, 32 * PER_CU, (size_t)f.N_pad * D * 4, c.topk_ratio, c.cum_prob);
   const float log2e = 1.4426950408889634f;
   const float scale = log2e / sqrtf((float)D), bias = c.text_bias * log2e;
-  if constexpr (BLK == 128) {
-    if (c.flags & JENGA_FLAG_PACED_WALK) {
-      // a workgroup spends about 6.3 us (D = 128; 3.6 us at D = 64) on a block of 128 keys when three share a CU
-      uint32_t* params = (uint32_t*)((char*)ws + 2 * half);
-      walk_pace_kernel<<<1, 1024, 0, st>>>(sel_count, bh * f.M, f.M, D == 128 ? 630.f : 360.f, params);
-      attn_h_kernel<BLK, D, true><<<dim3(work.n_wg), 2 * BLK, 0, st>>>((const uint16_t*)q, kp, vp, sel_count, sel_index,
-                                                                       (uint16_t*)out, lse, work, f.N_pad, f.pad_v,
-                                                                       f.pad_c, scale, bias, params);
-      return hipGetLastError() == hipSuccess ? JENGA_OK : JENGA_EHIP;
-    }
-  }
+  const uint16_t* qb = (const uint16_t*)q;
+  uint16_t* ob = (uint16_t*)out;
   if constexpr (BLK == 32) {   // in-order walk only
     constexpr int NS = D == 128 ? 4 : 8;
-    attn_kernel<D, NS><<<dim3(work.n_wg), 64 * NS, 0, st>>>((const uint16_t*)q, kp, vp, sel_count, sel_index,
-                                                            (uint16_t*)out, lse, work, f.N_pad, f.pad_v, f.pad_c, scale,
-                                                            bias);
+    attn_kernel<D, NS><<<dim3(work.n_wg), 64 * NS, 0, st>>>(qb, kp, vp, sel_count, sel_index, ob, lse, work, f.N_pad,
+                                                            f.pad_v, f.pad_c, scale, bias);
   } else {
-    attn_h_kernel<BLK, D, false><<<dim3(work.n_wg), 2 * BLK, 0, st>>>((const uint16_t*)q, kp, vp, sel_count, sel_index,
-                                                                      (uint16_t*)out, lse, work, f.N_pad, f.pad_v,
-                                                                      f.pad_c, scale, bias, nullptr);
+    const bool paced = BLK == 128 && (c.flags & JENGA_FLAG_PACED_WALK);
+    Split split = {};
+#define JENGA_ATTN(PACED, SPLIT, WGS)                                                                                 \
+  attn_h_kernel<BLK, D, PACED, SPLIT><<<dim3(WGS), 2 * BLK, 0, st>>>(qb, kp, vp, sel_count, sel_index, ob, lse, work, \
+                                                                     f.N_pad, f.pad_v, f.pad_c, scale, bias, params, split)
+    if (may_split && p->attn_parts > 1) {
+      split.parts = p->attn_parts;
+      split.chunk = p->attn_chunk;
+      split.stride = (work.n_wg + 7) & ~7;   // a multiple of the XCDs, which a query block's parts then share
+      split.o = (float*)((char*)ws + 2 * half + 256);
+      split.stat = split.o + (size_t)bh * f.M * split.parts * BLK * D;
+      if constexpr (BLK == 128) {
+        if (paced) JENGA_ATTN(true, true, split.parts * split.stride);
+      }
+      if (!paced) JENGA_ATTN(false, true, split.parts * split.stride);
+      merge_kernel<BLK, D><<<dim3(BLK / 32, f.M, bh), 2 * D, 0, st>>>(sel_count, ob, lse, f.M, f.M_v, f.N_pad, f.pad_v,
+                                                                      f.pad_c, split);
+      return hipGetLastError() == hipSuccess ? JENGA_OK : JENGA_EHIP;
+    }
+    if constexpr (BLK == 128) {
+      if (paced) {
+        // a workgroup spends about 6.3 us (D = 128; 3.6 us at D = 64) on a block of 128 keys when three share a CU
+        walk_pace_kernel<<<1, 1024, 0, st>>>(sel_count, bh * f.M, f.M, D == 128 ? 630.f : 360.f, params);
+        JENGA_ATTN(true, false, work.n_wg);
+      }
+    }
+    if (!paced) JENGA_ATTN(false, false, work.n_wg);
+#undef JENGA_ATTN
   }
   return hipGetLastError() == hipSuccess ? JENGA_OK : JENGA_EHIP;
 }
@@ -849,12 +983,12 @@ int launch_pack(const jenga_plan* p, const void* k, const void* v, void* ws, voi
   return JENGA_EUNSUPPORTED;
 }
 
-int launch_attention(const jenga_plan* p, const void* q, void* ws, const int32_t* sel_count,
+int launch_attention(const jenga_plan* p, const void* q, void* ws, bool may_split, const int32_t* sel_count,
                      const int32_t* sel_index, void* out, float* lse, void* stream) {
   hipStream_t st = (hipStream_t)stream;
   const int blk = p->cfg.block, d = p->cfg.head_dim;
 #define X(B, DD) \
-  if (blk == B && d == DD) return run_attention<B, DD>(p, q, ws, sel_count, sel_index, out, lse, st);
+  if (blk == B && d == DD) return run_attention<B, DD>(p, q, ws, may_split, sel_count, sel_index, out, lse, st);
   JENGA_FOR_SHAPES(X)
 #undef X
   return JENGA_EUNSUPPORTED;

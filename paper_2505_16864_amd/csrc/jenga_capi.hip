@@ -109,7 +109,7 @@ int jenga_block_sparse_attn(const jenga_plan* p, const void* q, const void* k, c
   if (workspace_bytes < p->info.attn_workspace_bytes) return JENGA_EWORKSPACE;
   const int rc = jenga::launch_pack(p, k, v, workspace, stream);
   if (rc != JENGA_OK) return rc;
-  return jenga::launch_attention(p, q, workspace, sel_count, sel_index, out_curve, lse_or_null, stream);
+  return jenga::launch_attention(p, q, workspace, true, sel_count, sel_index, out_curve, lse_or_null, stream);
 }
 
 int jenga_pack_kv(const jenga_plan* p, const void* k, const void* v, void* workspace, size_t workspace_bytes,
@@ -128,7 +128,7 @@ int jenga_block_sparse_attn_packed(const jenga_plan* p, const void* q, void* pac
   if (!on_plan_device(p)) return JENGA_EINVAL;
   if (((uintptr_t)packed_kv_workspace & 255u) != 0) return JENGA_EINVAL;
   if (workspace_bytes < p->info.attn_workspace_bytes) return JENGA_EWORKSPACE;
-  return jenga::launch_attention(p, q, packed_kv_workspace, sel_count, sel_index, out_curve, lse_or_null, stream);
+  return jenga::launch_attention(p, q, packed_kv_workspace, false, sel_count, sel_index, out_curve, lse_or_null, stream);
 }
 
 }  // extern "C"

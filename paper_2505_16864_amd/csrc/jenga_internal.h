@@ -10,6 +10,8 @@ struct jenga_plan {
   jenga_plan_info_t info;
   int device;
   int nt64;  // 64-bit words per row of the fixed-mask table: ceil(M / 64)
+  // attention: a list longer than attn_chunk entries is cut into up to attn_parts parts (1: lists stay whole)
+  int attn_parts, attn_chunk;
   // host tables
   std::vector<int32_t> perm, inv_perm;
   std::vector<int32_t> src_of_pos;  // [N_pad] index into the thw-side sequence, -1 for a pad
@@ -32,6 +34,11 @@ void curve_order(int T, int H, int W, bool use_curve, std::vector<int32_t>& perm
 // Host tables of a plan (no device work).  Returns a jenga_status.
 int build_host_tables(jenga_plan* plan);
 
+// Workgroups of the attention kernel for blocks of 64 and 128 tokens that are resident on a CU, by registers and LDS.
+constexpr int attn_h_per_cu(int block, int head_dim) {
+  return block == 64 ? (head_dim == 128 ? 5 : 8) : (head_dim == 128 ? 3 : 4);
+}
+
 // Kernel launchers (defined in the .hip files).  All return a jenga_status.
 int launch_permute(const jenga_plan* p, const void* src, void* dst, bool forward, void* stream);
 int launch_permute_rows(const jenga_plan* p, const void* src, void* dst, int row_bytes, void* stream);
@@ -40,7 +47,8 @@ int launch_select(const jenga_plan* p, const void* q, const void* k, int32_t* se
 // Looks up the address of the static selection scratch on `device` (the current device) once.
 int select_scratch_init(int device);
 int launch_pack(const jenga_plan* p, const void* k, const void* v, void* ws, void* stream);
-int launch_attention(const jenga_plan* p, const void* q, void* packed_ws, const int32_t* sel_count,
+// may_split: the call has the workspace to itself and may write behind the packed tiles.
+int launch_attention(const jenga_plan* p, const void* q, void* packed_ws, bool may_split, const int32_t* sel_count,
                      const int32_t* sel_index, void* out, float* lse, void* stream);
 
 }  // namespace jenga

@@ -130,6 +130,37 @@ void curve_order(int T, int H, int W, bool use_curve, std::vector<int32_t>& perm
   w.box({{0, 0, 0}}, v[0], v[1], v[2]);
 }
 
+// Whether the attention kernel cuts the lists of this plan, and where.
+//
+// With fewer query blocks than resident workgroups the longest lists (the text rows see every block) decide the time:
+// a step takes 1.2 us with one workgroup on a CU and 2.3 us with three.  Cut, a list costs about 6 us a part (index
+// and Q loads, first tiles, the part's way through memory) and the launch that puts the parts together.  So a part
+// gets the length that makes about 0.6 workgroups per place on the chip, six steps of 64 keys at least while there is
+// a CU for every query block and 24 from there on; at three quarters of the places lists stay whole.  Attention with
+// packing, lists whole -> cut:
+//   D = 128, blocks of 128:  18 query blocks 31 -> 23 us, 136 52 -> 44, 368 137 -> 116, 552 171 -> 158; 736 183 -> 191
+//   D = 64, blocks of 128:   192 96 -> 54, 384 101 -> 82; 768 131 -> 139
+//   D = 128, blocks of 64:   168 35 -> 32, 608 120 -> 97; 1824 202 -> 210
+// Lists of about a dozen steps lose what they gain (408 query blocks of 11.6 entries: 75 us whole, 80 us in parts of 8).
+static void split_lists(jenga_plan* plan) {
+  const jenga_config& c = plan->cfg;
+  const jenga_plan_info_t& f = plan->info;
+  plan->attn_parts = 1;
+  plan->attn_chunk = f.M;
+  if (c.block == 32) return;   // its wavefronts share the list already
+  const long long places = 256ll * attn_h_per_cu(c.block, c.head_dim);
+  const long long rows = (long long)c.batch * c.heads * f.M;
+  if (4 * rows >= 3 * places) return;
+  // expected list length: K_top and the blocks that are always on
+  long long fixed = 0;
+  for (uint64_t w : plan->fixed_bits) fixed += __builtin_popcountll(w);
+  const long long len = std::min<long long>(f.M, f.K_top + (fixed + f.M_v - 1) / f.M_v);
+  const long long shortest = (rows <= 256 ? 6 : 24) * 64 / c.block;
+  const long long chunk = std::max(shortest, (5 * rows * len + 3 * places - 1) / (3 * places));
+  plan->attn_parts = (int)std::min(std::min(8ll, 2 * places / rows), (f.M + chunk - 1) / chunk);
+  plan->attn_chunk = (int)chunk;
+}
+
 int build_host_tables(jenga_plan* plan) {
   const jenga_config& c = plan->cfg;
   jenga_plan_info_t& f = plan->info;
@@ -195,6 +226,10 @@ int build_host_tables(jenga_plan* plan) {
                              align256(bh * (uint64_t)f.M_v * f.M * 8);
   // attention: K and V re-tiled, bf16, one tile per (batch, head, block)
   f.attn_workspace_bytes = 2 * align256(bh * (uint64_t)f.N_pad * c.head_dim * 2) + 256;   // packed K, packed V, launch parameters
+  split_lists(plan);
+  // and, where lists are cut, O and two statistics per row and part, float32
+  if (plan->attn_parts > 1)
+    f.attn_workspace_bytes += align256(bh * f.M * plan->attn_parts * (uint64_t)m * (c.head_dim + 2) * 4);
   return JENGA_OK;
 }
 

@@ -74,3 +74,48 @@ def test_every_query_block_is_dealt_out(m_v, heads, n_text):
     # half a bf16 ulp (at most 2^-8 relative) on every probability and on the result, so 2^-8 (max |v| + |o|).
     err = np.abs(to_f64(layer.o_c) - jo.block_sparse_attention(qc, kc, vc, mask, lay))
     assert err.max() <= 2.0 ** -7 * np.abs(vc).max()
+
+
+# Grids small enough that lists are cut into parts: lists shorter than one part, one off a multiple of it, empty and
+# full, a block listed twice, with and without the paced walk (which visits it once), log-sum-exp included.
+@pytest.mark.parametrize("head_dim,block", [(64, 64), (128, 64), (64, 128), (128, 128)])
+@pytest.mark.parametrize("heads,paced", [(1, False), (2, True), (9, False)])
+def test_lists_cut_into_parts(head_dim, block, heads, paced):
+    if paced and block != 128:
+        pytest.skip("the paced walk exists for blocks of 128 tokens")
+    w = dict(T=1, H=1, W=block * 37 - 9, n_text=block + 5, batch=1, heads=heads, head_dim=head_dim, block=block,
+             topk=0.3, p=0.3, text_bias=0.4, flags=15 if paced else 7)
+    print("cut", w, flush=True)
+    q, k, v = ji.make_qkv(w, 61)
+    layer = CarveLayer(w, "cuda:0", want_lse=True)
+    lay = oracle_layout(w)
+    whole = 2 * (heads * layer.info.N_pad * head_dim * 2) + 256
+    assert layer.info.attn_workspace_bytes > whole          # there is room for parts
+    rng = np.random.default_rng(8)
+    lengths = [0, 1, 2, 3, 4, 6, 7, 8, 9, 12, 13, 17, 24, 25, lay.M - 1, lay.M]
+    cnt = np.zeros((1, heads, lay.M), dtype=np.int32)
+    idx = np.full((1, heads, lay.M, lay.M), -1, dtype=np.int32)
+    mask = np.zeros((1, heads, lay.M, lay.M), dtype=bool)
+    for h in range(heads):
+        for i in range(lay.M):
+            chosen = rng.permutation(lay.M)[:lengths[(i + 5 * h) % len(lengths)]].tolist()
+            mask[0, h, i, chosen] = True
+            if paced and 0 < len(chosen) < lay.M:
+                chosen.append(chosen[0])                     # listed twice, far apart
+            cnt[0, h, i] = len(chosen)
+            idx[0, h, i, :len(chosen)] = chosen
+    layer.permute_in(q.cuda(), k.cuda(), v.cuda())
+    layer.sel_count.copy_(torch.from_numpy(cnt))
+    layer.sel_index.copy_(torch.from_numpy(idx))
+    qc, kc, vc = [jo.permute(to_f64(x), lay) for x in (q, k, v)]
+    want, want_lse = jo.block_sparse_attention(qc, kc, vc, mask, lay, beta=w["text_bias"], return_lse=True)
+    alive = np.isfinite(want_lse)
+    for attend in (layer.attend, layer.attend_packed):       # in parts, whole
+        layer.o_c.view(torch.int16).fill_(0x7FC1)
+        layer.lse.fill_(7.0)
+        attend()
+        torch.cuda.synchronize()
+        check_output(to_f64(layer.o_c), want, "%s %d/%d" % (attend.__name__, head_dim, block))
+        got = layer.lse.cpu().numpy().astype(np.float64)
+        assert np.isneginf(got[~alive]).all()
+        assert np.abs(got[alive] - want_lse[alive]).max() <= 1e-3     # float32 sums and one float32 logarithm
