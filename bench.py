@@ -2,7 +2,7 @@
 """Benchmark of the attention-carving hot path on one MI355X.
 
 One "step" is one pass of the whole path over one synthetic layer input:
-    3 x jenga_curve_permute (Q, K, V)  ->  jenga_select_blocks  ->  jenga_block_sparse_attn
+    jenga_curve_permute_qkv  ->  jenga_select_blocks  ->  jenga_block_sparse_attn
     ->  jenga_unpermute
 with Q/K/V already resident in HBM.  The headline value is the time of what recurs per layer
 (select + attention); the permutes, which the paper pays once per DiT forward, are reported beside

@@ -121,6 +121,12 @@ int jenga_plan_tables(const jenga_config* cfg, jenga_plan_info_t* info, int32_t*
 int jenga_curve_permute(const jenga_plan* plan, const void* src_thw, void* dst_curve, void* stream);
 
 /*
+ * jenga_curve_permute of Q, K and V in one launch: the same results as three calls.
+ */
+int jenga_curve_permute_qkv(const jenga_plan* plan, const void* q_thw, const void* k_thw, const void* v_thw,
+                            void* q_curve, void* k_curve, void* v_curve, void* stream);
+
+/*
  * Eq. 2 applied to a per-token table that has to follow the tokens into curve order, such as the
  * rotary position-embedding frequencies (appendix, implementation details, "Frequency re-ordering":
  * f_blk = G(f); Alg. 1, the step that remaps the positional frequencies once per stage):

@@ -15,7 +15,8 @@ JENGA_FLAG_CURVE = 4
 JENGA_FLAG_PACED_WALK = 8
 
 EXPORTS = ["jenga_plan_create", "jenga_plan_destroy", "jenga_plan_info", "jenga_plan_export", "jenga_plan_tables",
-           "jenga_curve_permute", "jenga_curve_permute_rows", "jenga_select_blocks", "jenga_select_blocks_static",
+           "jenga_curve_permute", "jenga_curve_permute_qkv", "jenga_curve_permute_rows", "jenga_select_blocks",
+           "jenga_select_blocks_static",
            "jenga_block_sparse_attn", "jenga_pack_kv",
            "jenga_block_sparse_attn_packed", "jenga_unpermute", "jenga_stage_switch", "jenga_strerror"]
 
@@ -51,6 +52,7 @@ def _load():
     lib.jenga_plan_export.argtypes = [vp, vp, vp, vp]
     lib.jenga_plan_tables.argtypes = [ctypes.POINTER(jenga_config), ctypes.POINTER(jenga_plan_info_t), vp, vp, vp]
     lib.jenga_curve_permute.argtypes = [vp, vp, vp, vp]
+    lib.jenga_curve_permute_qkv.argtypes = [vp] * 8
     lib.jenga_unpermute.argtypes = [vp, vp, vp, vp]
     lib.jenga_curve_permute_rows.argtypes = [vp, vp, vp, ctypes.c_int32, vp]
     lib.jenga_select_blocks.argtypes = [vp, vp, vp, vp, vp, vp, vp, ctypes.c_size_t, vp]
@@ -121,6 +123,11 @@ def jenga_plan_tables(cfg, perm=None, inv_perm=None, adja=None):
 
 def jenga_curve_permute(plan, src_thw, dst_curve, stream=None):
     _check(_lib.jenga_curve_permute(plan, _ptr(src_thw), _ptr(dst_curve), stream), "jenga_curve_permute")
+
+
+def jenga_curve_permute_qkv(plan, q_thw, k_thw, v_thw, q_curve, k_curve, v_curve, stream=None):
+    _check(_lib.jenga_curve_permute_qkv(plan, _ptr(q_thw), _ptr(k_thw), _ptr(v_thw), _ptr(q_curve), _ptr(k_curve),
+                                        _ptr(v_curve), stream), "jenga_curve_permute_qkv")
 
 
 def jenga_curve_permute_rows(plan, src_rows, dst_rows, row_bytes, stream=None):

@@ -73,7 +73,16 @@ int jenga_plan_destroy(jenga_plan* p) {
 int jenga_curve_permute(const jenga_plan* p, const void* src_thw, void* dst_curve, void* stream) {
   if (!p || !src_thw || !dst_curve) return JENGA_EINVAL;
   if (!on_plan_device(p)) return JENGA_EINVAL;
-  return jenga::launch_permute(p, src_thw, dst_curve, true, stream);
+  return jenga::launch_permute(p, &src_thw, &dst_curve, 1, true, stream);
+}
+
+int jenga_curve_permute_qkv(const jenga_plan* p, const void* q_thw, const void* k_thw, const void* v_thw, void* q_curve,
+                            void* k_curve, void* v_curve, void* stream) {
+  if (!p || !q_thw || !k_thw || !v_thw || !q_curve || !k_curve || !v_curve) return JENGA_EINVAL;
+  if (!on_plan_device(p)) return JENGA_EINVAL;
+  const void* src[3] = {q_thw, k_thw, v_thw};
+  void* dst[3] = {q_curve, k_curve, v_curve};
+  return jenga::launch_permute(p, src, dst, 3, true, stream);
 }
 
 int jenga_curve_permute_rows(const jenga_plan* p, const void* src_rows, void* dst_rows, int32_t row_bytes,
@@ -87,7 +96,7 @@ int jenga_curve_permute_rows(const jenga_plan* p, const void* src_rows, void* ds
 int jenga_unpermute(const jenga_plan* p, const void* src_curve, void* dst_thw, void* stream) {
   if (!p || !src_curve || !dst_thw) return JENGA_EINVAL;
   if (!on_plan_device(p)) return JENGA_EINVAL;
-  return jenga::launch_permute(p, src_curve, dst_thw, false, stream);
+  return jenga::launch_permute(p, &src_curve, &dst_thw, 1, false, stream);
 }
 
 int jenga_select_blocks(const jenga_plan* p, const void* q_curve, const void* k_curve, int32_t* sel_count,

@@ -40,7 +40,9 @@ constexpr int attn_h_per_cu(int block, int head_dim) {
 }
 
 // Kernel launchers (defined in the .hip files).  All return a jenga_status.
-int launch_permute(const jenga_plan* p, const void* src, void* dst, bool forward, void* stream);
+// 1 to 3 tensors of the plan's shape
+int launch_permute(const jenga_plan* p, const void* const* src, void* const* dst, int tensors, bool forward,
+                   void* stream);
 int launch_permute_rows(const jenga_plan* p, const void* src, void* dst, int row_bytes, void* stream);
 int launch_select(const jenga_plan* p, const void* q, const void* k, int32_t* sel_count,
                   int32_t* sel_index, uint8_t* mask, void* ws, void* stream);

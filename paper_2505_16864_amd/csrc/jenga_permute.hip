@@ -11,16 +11,24 @@
 
 namespace {
 
+// Up to three tensors a launch (grid z = batch x tensors): Q, K and V of a small grid are 2.5 us of kernel and as much
+// of launching each.
+struct Tensors {
+  const uint4* src[3];
+  uint4* dst[3];
+};
+
 template <bool FORWARD>
-__global__ __launch_bounds__(256) void permute_kernel(const uint4* __restrict__ src, uint4* __restrict__ dst,
-                                                      const int32_t* __restrict__ src_of_pos, int n_src,
-                                                      int n_pad, int heads, int chunks, int heads_per_wg) {
+__global__ __launch_bounds__(256) void permute_kernel(Tensors tensors, const int32_t* __restrict__ src_of_pos, int n_src,
+                                                      int n_pad, int heads, int chunks, int heads_per_wg, int batch) {
   const int groups = 256 / chunks;
   const int c = threadIdx.x % chunks;
   const int g = threadIdx.x / chunks;
   const int i = blockIdx.x * groups + g;
   if (i >= n_pad) return;
-  const int b = blockIdx.z;
+  const int tensor = blockIdx.z / batch, b = blockIdx.z - tensor * batch;
+  const uint4* __restrict__ src = tensors.src[tensor];
+  uint4* __restrict__ dst = tensors.dst[tensor];
   const int h0 = blockIdx.y * heads_per_wg;
   const int h1 = min(h0 + heads_per_wg, heads);
   const int s = src_of_pos[i];
@@ -70,20 +78,33 @@ __global__ __launch_bounds__(256) void permute_kernel(const uint4* __restrict__ 
 
 namespace jenga {
 
-int launch_permute(const jenga_plan* p, const void* src, void* dst, bool forward, void* stream) {
+int launch_permute(const jenga_plan* p, const void* const* src, void* const* dst, int tensors, bool forward,
+                   void* stream) {
   const jenga_config& c = p->cfg;
   const int chunks = c.head_dim * 2 / 16;
   const int groups = 256 / chunks;
   const int heads_per_wg = 8;
-  dim3 grid((p->info.N_pad + groups - 1) / groups, (c.heads + heads_per_wg - 1) / heads_per_wg, c.batch);
+  if ((long long)c.batch * tensors > 65535) {   // more than a grid has in z
+    for (int t = 0; t < tensors; ++t) {
+      const int rc = launch_permute(p, src + t, dst + t, 1, forward, stream);
+      if (rc != JENGA_OK) return rc;
+    }
+    return JENGA_OK;
+  }
+  dim3 grid((p->info.N_pad + groups - 1) / groups, (c.heads + heads_per_wg - 1) / heads_per_wg, c.batch * tensors);
   const int n_src = p->info.N_v + c.n_text;
   hipStream_t st = (hipStream_t)stream;
+  Tensors all = {};
+  for (int t = 0; t < tensors; ++t) {
+    all.src[t] = (const uint4*)src[t];
+    all.dst[t] = (uint4*)dst[t];
+  }
   if (forward)
-    permute_kernel<true><<<grid, 256, 0, st>>>((const uint4*)src, (uint4*)dst, p->d_src_of_pos, n_src,
-                                               p->info.N_pad, c.heads, chunks, heads_per_wg);
+    permute_kernel<true><<<grid, 256, 0, st>>>(all, p->d_src_of_pos, n_src, p->info.N_pad, c.heads, chunks, heads_per_wg,
+                                               c.batch);
   else
-    permute_kernel<false><<<grid, 256, 0, st>>>((const uint4*)src, (uint4*)dst, p->d_src_of_pos, n_src,
-                                                p->info.N_pad, c.heads, chunks, heads_per_wg);
+    permute_kernel<false><<<grid, 256, 0, st>>>(all, p->d_src_of_pos, n_src, p->info.N_pad, c.heads, chunks, heads_per_wg,
+                                                c.batch);
   return hipGetLastError() == hipSuccess ? JENGA_OK : JENGA_EHIP;
 }
 
@@ -92,8 +113,9 @@ int launch_permute_rows(const jenga_plan* p, const void* src, void* dst, int row
   const int chunks = row_bytes / 16;
   const int groups = 256 / chunks;
   dim3 grid((p->info.N_pad + groups - 1) / groups, 1, 1);
-  permute_kernel<true><<<grid, 256, 0, (hipStream_t)stream>>>((const uint4*)src, (uint4*)dst, p->d_src_of_pos,
-                                                              p->info.N_v + p->cfg.n_text, p->info.N_pad, 1, chunks, 1);
+  const Tensors all = {{(const uint4*)src}, {(uint4*)dst}};
+  permute_kernel<true><<<grid, 256, 0, (hipStream_t)stream>>>(all, p->d_src_of_pos, p->info.N_v + p->cfg.n_text,
+                                                              p->info.N_pad, 1, chunks, 1, 1);
   return hipGetLastError() == hipSuccess ? JENGA_OK : JENGA_EHIP;
 }
 

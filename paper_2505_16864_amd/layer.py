@@ -34,13 +34,12 @@ class CarveLayer:
                                    dtype=torch.bfloat16, device=dev)
 
     def _stream(self):
-        return torch.cuda.current_stream(self.device).cuda_stream
+        # the raw handle, without building a Stream object (2 us) for every call
+        index = self.device.index
+        return torch._C._cuda_getCurrentRawStream(torch.cuda.current_device() if index is None else index)
 
     def permute_in(self, q, k, v):
-        s = self._stream()
-        B.jenga_curve_permute(self.plan, q, self.q_c, s)
-        B.jenga_curve_permute(self.plan, k, self.k_c, s)
-        B.jenga_curve_permute(self.plan, v, self.v_c, s)
+        B.jenga_curve_permute_qkv(self.plan, q, k, v, self.q_c, self.k_c, self.v_c, self._stream())
 
     def select(self):
         B.jenga_select_blocks(self.plan, self.q_c, self.k_c, self.sel_count, self.sel_index, self.mask,

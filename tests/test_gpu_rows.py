@@ -47,3 +47,24 @@ def test_row_width_must_be_a_power_of_two():
             assert err.value.status == -2
     finally:
         jb.jenga_plan_destroy(plan)
+
+
+@pytest.mark.parametrize("name", ["tiny", "small"])
+def test_three_tensors_in_one_launch(name):
+    from paper_2505_16864_amd import binding as jb
+    w = dict(ji.WORKLOADS[name], batch=2, heads=3)
+    q, k, v = [x.cuda() for x in ji.make_qkv(w, 90)]
+    plan = jb.jenga_plan_create(jb.make_config(w["T"], w["H"], w["W"], w["n_text"], w["batch"], w["heads"],
+                                               w["head_dim"], w["block"], w["topk"], w["p"]))
+    try:
+        shape = (w["batch"], w["heads"], jb.jenga_plan_info(plan).N_pad, w["head_dim"])
+        one = [torch.full(shape, 7.0, dtype=torch.bfloat16, device="cuda:0") for _ in range(3)]
+        all3 = [torch.full(shape, 8.0, dtype=torch.bfloat16, device="cuda:0") for _ in range(3)]
+        for src, dst in zip((q, k, v), one):
+            jb.jenga_curve_permute(plan, src, dst)
+        jb.jenga_curve_permute_qkv(plan, q, k, v, *all3)
+        torch.cuda.synchronize()
+    finally:
+        jb.jenga_plan_destroy(plan)
+    for a, b in zip(one, all3):
+        assert np.array_equal(ji.bits(a), ji.bits(b))
