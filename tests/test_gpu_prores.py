@@ -65,3 +65,26 @@ def test_invalid_arguments_launch_nothing():
         jb.jenga_stage_switch(x, e, n, out, w["channels"], (0, 5, 7), w["out"], 0.5)
     torch.cuda.synchronize()
     assert float(out.abs().max()) == 0.0
+
+
+# Rows that do not start on a 16-byte boundary, tiles that end with the tensor, windows of one and two cells per axis,
+# shrinking axes; against the kernel for unaligned inputs as well (one float further in a buffer): the same bits.
+@pytest.mark.parametrize("shape_in,shape_out", [((5, 21, 30), (5, 32, 45)), ((2, 7, 33), (3, 9, 34)), ((1, 1, 1), (2, 3, 5)),
+                                                ((3, 20, 41), (3, 20, 82)), ((3, 9, 131), (2, 11, 131)),
+                                                ((1, 5, 1031), (1, 6, 1033)), ((4, 33, 67), (2, 10, 30))])
+def test_rows_off_the_16_byte_grid(shape_in, shape_out):
+    from paper_2505_16864_amd import binding as jb
+    w = {"channels": 3, "in": shape_in, "out": shape_out, "sigma": 0.45}
+    got, want = run(w, 7050)
+    assert np.abs(got - want).max() <= ATOL
+    x, e, n = ji.make_latents(w, 7050, device="cuda:0")
+    shifted = []
+    for t in (x, e):
+        buf = torch.empty(t.numel() + 1, device="cuda:0")
+        buf[1:] = t.reshape(-1)
+        shifted.append(buf[1:])
+    out = torch.full((3,) + shape_out, float("nan"), device="cuda:0")
+    jb.jenga_stage_switch(shifted[0], shifted[1], n, out, 3, shape_in, shape_out, w["sigma"],
+                          torch.cuda.current_stream().cuda_stream)
+    torch.cuda.synchronize()
+    assert np.array_equal(out.cpu().numpy().astype(np.float64), got)
