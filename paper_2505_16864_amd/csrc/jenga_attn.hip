@@ -268,11 +268,11 @@ constexpr int attn_h_min_waves() { return D == 128 ? 3 : 4; }   // wavefronts pe
 // SPLIT: grids that leave the chip idle.  The list of a query block is cut into Split::of(cnt) parts of equal length, a
 // workgroup each; the parts' O, reference and sum go to the workspace and merge_kernel puts them together.
 struct Split {
-  int parts, chunk;   // most parts of a list, list entries from which on there is one more part
+  int parts, chunk;   // most parts of a list, list entries from which on there is one more part (0: always all parts)
   int stride;         // workgroups per part
   float* o;           // [batch*heads*M][parts][BLK/32][D/32][4][64][4]: O in accumulator order
   float* stat;        // [batch*heads*M][parts][2][BLK]: reference, sum
-  __device__ int of(int cnt) const { return max(1, min(parts, (cnt + chunk - 1) / chunk)); }
+  __device__ int of(int cnt) const { return chunk == 0 ? parts : max(1, min(parts, (cnt + chunk - 1) / chunk)); }
 };
 
 template <int BLK, int D, bool PACED, bool SPLIT>
@@ -694,20 +694,30 @@ __global__ __launch_bounds__(2 * D) void merge_kernel(const int32_t* __restrict_
 // Measured on 2048 blocks x 2 heads, D = 64, k = 0.05 (lists of 305 of 2048 blocks): 0.77 ms, against 1.77 ms for one
 // wavefront per query block that staged its tiles in LDS.  What bounds it there is the path behind the L2: 32 rows
 // read 8 KB of K and V for 0.26 MFLOP, 10 GB in all, from a head (16 MB) that an XCD's 4 MB do not hold; 5.5 GB
-// miss, at 7.1 TB/s.  Eight wavefronts
+// miss, at 7.1 TB/s.  In three passes over ranges of key blocks (RANGE) it takes 0.57 ms with the merge; 0.42 ms are
+// left when every load hits the L1.  Eight wavefronts
 // per list at D = 64 (two workgroups fill a CU), four at D = 128 (the registers leave room for eight).
 // ---------------------------------------------------------------------------------------------
-template <int D, int NS>
+//
+// RANGE: K and V of a head do not fit an XCD's L2.  A pass over all query blocks takes the entries of one of
+// `split.parts` ranges of key blocks, which then stays in the L2, and the next pass the next range; O, reference and sum
+// of the passes go to the workspace and merge_kernel puts them together.
+template <int D, int NS, bool RANGE>
 __global__ __launch_bounds__(64 * NS, (D == 128 ? 2 : 4)) void attn_kernel(
     const uint16_t* __restrict__ q, const u32x4* __restrict__ kp, const u32x4* __restrict__ vp,
     const int32_t* __restrict__ sel_count, const int32_t* __restrict__ sel_index, uint16_t* __restrict__ out,
-    float* __restrict__ lse, WorkMap work, int n_pad, int pad_v, int pad_c, float scale_log2e, float bias_log2e) {
+    float* __restrict__ lse, WorkMap work, int n_pad, int pad_v, int pad_c, float scale_log2e, float bias_log2e,
+    Split split) {
   constexpr int BLK = 32, KS = D / 16, DT = D / 32, PS = BLK / 16, TILE_CHUNKS = BLK * D / 8;
   __shared__ float part[NS][16][64];   // one channel tile of every wavefront's O, accumulator order
   __shared__ float stat[NS][2][32];    // reference and sum of every row
 
+  __shared__ uint16_t in_range[RANGE ? 2048 : 1];   // the list's entries in this pass's range, in list order
+  __shared__ int wave_entries[RANGE ? NS : 1];
+
   int bh, i;
-  if (!map_work(blockIdx.x, work, &bh, &i)) return;
+  const int range = RANGE ? blockIdx.x / split.stride : 0;
+  if (!map_work(RANGE ? blockIdx.x - range * split.stride : blockIdx.x, work, &bh, &i)) return;
   const int M = work.M, M_v = work.M_v;
 
   const int lane = threadIdx.x & 63;
@@ -725,6 +735,27 @@ __global__ __launch_bounds__(64 * NS, (D == 128 ? 2 : 4)) void attn_kernel(
   int cnt = sel_count[(size_t)bh * M + i];
   cnt = min(max(cnt, 0), M);
   const int32_t* idx = sel_index + ((size_t)bh * M + i) * M;
+  if constexpr (RANGE) {
+    const int lo = M * range / split.parts, hi = M * (range + 1) / split.parts;
+    int kept = 0;
+    for (int t0 = 0; t0 < cnt; t0 += 64 * NS) {
+      const int t = t0 + threadIdx.x;
+      const int jj = t < cnt ? min(max(idx[t], 0), M - 1) : -1;
+      const bool in = jj >= lo && jj < hi;
+      const uint64_t in_wave = __ballot(in);
+      if (lane == 0) wave_entries[wave] = (int)__popcll(in_wave);
+      __syncthreads();
+      int pos = kept + (int)__popcll(in_wave & ((1ull << lane) - 1ull));
+#pragma unroll
+      for (int s = 0; s < NS; ++s) {
+        pos += s < wave ? wave_entries[s] : 0;
+        kept += wave_entries[s];
+      }
+      if (in) in_range[pos] = (uint16_t)jj;
+      __syncthreads();
+    }
+    cnt = __builtin_amdgcn_readfirstlane(kept);
+  }
   const u32x4* kbase = kp + (size_t)bh * M * TILE_CHUNKS + lane;
   const u32x4* vbase = vp + (size_t)bh * M * TILE_CHUNKS + lane;
   u32x4 kf[KS], vf[DT * PS];
@@ -736,7 +767,9 @@ __global__ __launch_bounds__(64 * NS, (D == 128 ? 2 : 4)) void attn_kernel(
 #pragma unroll
     for (int f = 0; f < DT * PS; ++f) vf[f] = vbase[(size_t)j * TILE_CHUNKS + f * 64];
   };
-  auto listed = [&](int t) { return min(max(idx[t], 0), M - 1); };
+  auto listed = [&](int t) {
+    return RANGE ? __builtin_amdgcn_readfirstlane((int)in_range[t]) : min(max(idx[t], 0), M - 1);
+  };
 
   float m_run = -INFINITY, l_run = 0.f;
   bool unset = true;   // no row has a reference yet (uniform: every row sees the same keys)
@@ -844,9 +877,15 @@ __global__ __launch_bounds__(64 * NS, (D == 128 ? 2 : 4)) void attn_kernel(
   for (int s = 0; s < NS; ++s) l_all += stat[s][1][ql] * __builtin_amdgcn_exp2f(stat[s][0][ql] - ref);
   const int rows_valid = BLK - (i == M_v - 1 ? pad_v : (i == M - 1 ? pad_c : 0));
   const bool row_ok = ql < rows_valid && l_all > 0.f;
-  if (lse != nullptr && threadIdx.x < 32)
+  const size_t slot = ((size_t)bh * M + i) * split.parts + range;
+  if (RANGE && threadIdx.x < 32) {
+    split.stat[(slot * 2) * BLK + ql] = m_all;
+    split.stat[(slot * 2 + 1) * BLK + ql] = l_all;
+  }
+  if (!RANGE && lse != nullptr && threadIdx.x < 32)
     lse[qrow] = row_ok ? (m_all + __builtin_amdgcn_logf(l_all)) * 0.6931471805599453f : -INFINITY;
-  const float mine = row_ok ? __builtin_amdgcn_exp2f(m_run - ref) / l_all : 0.f;   // weight of this wavefront's part
+  // weight of this wavefront's part
+  const float mine = RANGE ? __builtin_amdgcn_exp2f(m_run - ref) : row_ok ? __builtin_amdgcn_exp2f(m_run - ref) / l_all : 0.f;
   constexpr int RP = 16 / NS;   // accumulator registers of a channel tile that one wavefront adds up
 #pragma unroll
   for (int dt = 0; dt < DT; ++dt) {
@@ -863,6 +902,12 @@ __global__ __launch_bounds__(64 * NS, (D == 128 ? 2 : 4)) void attn_kernel(
     }
     // register r of a channel tile holds channel 8 * (r / 4) + 4 * hl + r % 4
     const int r0 = wave * RP;
+    if constexpr (RANGE) {
+      float* o = split.o + (((slot * DT + dt) * 4 + r0 / 4) * 64 + lane) * 4 + r0 % 4;
+#pragma unroll
+      for (int u = 0; u < RP; u += 2) *(float2*)(o + u) = make_float2(sum[u], sum[u + 1]);
+      continue;
+    }
     uint16_t* o = out + qrow * D + 32 * dt + 8 * (r0 / 4) + 4 * hl + r0 % 4;
 #pragma unroll
     for (int u = 0; u < RP; u += 2) *(uint32_t*)(o + u) = row_ok ? pack_bf16x2(sum[u], sum[u + 1]) : 0u;
@@ -932,8 +977,20 @@ int run_attention(const jenga_plan* p, const void* q, void* ws, bool may_split, 
   uint16_t* ob = (uint16_t*)out;
   if constexpr (BLK == 32) {   // in-order walk only
     constexpr int NS = D == 128 ? 4 : 8;
-    attn_kernel<D, NS><<<dim3(work.n_wg), 64 * NS, 0, st>>>(qb, kp, vp, sel_count, sel_index, ob, lse, work, f.N_pad,
-                                                            f.pad_v, f.pad_c, scale, bias);
+    Split split = {};
+    if (may_split && p->attn_parts > 1) {
+      split.parts = p->attn_parts;
+      split.stride = (work.n_wg + 7) & ~7;
+      split.o = (float*)((char*)ws + 2 * half + 256);
+      split.stat = split.o + (size_t)bh * f.M * split.parts * BLK * D;
+      attn_kernel<D, NS, true><<<dim3(split.parts * split.stride), 64 * NS, 0, st>>>(
+          qb, kp, vp, sel_count, sel_index, ob, lse, work, f.N_pad, f.pad_v, f.pad_c, scale, bias, split);
+      merge_kernel<BLK, D><<<dim3(1, f.M, bh), 2 * D, 0, st>>>(sel_count, ob, lse, f.M, f.M_v, f.N_pad, f.pad_v, f.pad_c,
+                                                               split);
+    } else {
+      attn_kernel<D, NS, false><<<dim3(work.n_wg), 64 * NS, 0, st>>>(qb, kp, vp, sel_count, sel_index, ob, lse, work,
+                                                                     f.N_pad, f.pad_v, f.pad_c, scale, bias, split);
+    }
   } else {
     const bool paced = BLK == 128 && (c.flags & JENGA_FLAG_PACED_WALK);
     Split split = {};

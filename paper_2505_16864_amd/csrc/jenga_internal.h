@@ -10,7 +10,8 @@ struct jenga_plan {
   jenga_plan_info_t info;
   int device;
   int nt64;  // 64-bit words per row of the fixed-mask table: ceil(M / 64)
-  // attention: a list longer than attn_chunk entries is cut into up to attn_parts parts (1: lists stay whole)
+  // attention: a list longer than attn_chunk entries is cut into up to attn_parts parts (1: lists stay whole);
+  // attn_chunk = 0: every list into attn_parts ranges of key blocks
   int attn_parts, attn_chunk;
   // host tables
   std::vector<int32_t> perm, inv_perm;

@@ -142,19 +142,35 @@ void curve_order(int T, int H, int W, bool use_curve, std::vector<int32_t>& perm
 //   D = 64, blocks of 128:   192 96 -> 54, 384 101 -> 82; 768 131 -> 139
 //   D = 128, blocks of 64:   168 35 -> 32, 608 120 -> 97; 1824 202 -> 210
 // Lists of about a dozen steps lose what they gain (408 query blocks of 11.6 entries: 75 us whole, 80 us in parts of 8).
+//
+// Blocks of 32 tokens share their list among the wavefronts of a workgroup already; they are read 32 rows at a time, and
+// what bounds them is K and V of a head that is larger than an XCD's 4 MB L2.  There the parts are ranges of key blocks,
+// one pass each, and every list has them all.  Time in 1 / 2 / 3 / 4 parts, the rule's choice marked:
+//   16.8 MB a head (2048 blocks, D = 64, lists of 305)   777 / 598 / 587* / 602 us
+//   11.1 MB (678 blocks, D = 128, lists of 138)          319 / 285* / 299 / 309 us
+//   6.5 MB (398 blocks, D = 128, lists of 137)           650 / 611* / 633 / 680 us
+//   5.0 MB (303 blocks, D = 128, lists of 77)            206* / 221 / 238 / 261 us
 static void split_lists(jenga_plan* plan) {
   const jenga_config& c = plan->cfg;
   const jenga_plan_info_t& f = plan->info;
   plan->attn_parts = 1;
   plan->attn_chunk = f.M;
-  if (c.block == 32) return;   // its wavefronts share the list already
-  const long long places = 256ll * attn_h_per_cu(c.block, c.head_dim);
   const long long rows = (long long)c.batch * c.heads * f.M;
-  if (4 * rows >= 3 * places) return;
   // expected list length: K_top and the blocks that are always on
   long long fixed = 0;
   for (uint64_t w : plan->fixed_bits) fixed += __builtin_popcountll(w);
   const long long len = std::min<long long>(f.M, f.K_top + (fixed + f.M_v - 1) / f.M_v);
+  if (c.block == 32) {
+    const long long bytes = 4ll * f.N_pad * c.head_dim;   // K and V of a head
+    const int parts = bytes >= 12 << 20 ? 3 : bytes >= 6 << 20 ? 2 : 1;
+    if (rows >= 512 && len >= 32 * parts) {
+      plan->attn_parts = parts;
+      plan->attn_chunk = 0;
+    }
+    return;
+  }
+  const long long places = 256ll * attn_h_per_cu(c.block, c.head_dim);
+  if (4 * rows >= 3 * places) return;
   const long long shortest = (rows <= 256 ? 6 : 24) * 64 / c.block;
   const long long chunk = std::max(shortest, (5 * rows * len + 3 * places - 1) / (3 * places));
   plan->attn_parts = (int)std::min(std::min(8ll, 2 * places / rows), (f.M + chunk - 1) / chunk);

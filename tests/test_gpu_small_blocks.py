@@ -119,3 +119,50 @@ def test_lists_cut_into_parts(head_dim, block, heads, paced):
         got = layer.lse.cpu().numpy().astype(np.float64)
         assert np.isneginf(got[~alive]).all()
         assert np.abs(got[alive] - want_lse[alive]).max() <= 1e-3     # float32 sums and one float32 logarithm
+
+
+# Heads larger than an L2: blocks of 32 tokens are visited in passes over ranges of key blocks.  Lists in any order,
+# empty, of one block, inside one range, longer than the workgroup, full.
+@pytest.mark.parametrize("head_dim,m_v", [(128, 385), (64, 1538)])
+def test_passes_over_key_ranges(head_dim, m_v):
+    w = dict(T=1, H=1, W=32 * m_v - 3, n_text=37, batch=1, heads=2, head_dim=head_dim, block=32, topk=0.5, p=0.3,
+             text_bias=0.4)
+    print("ranges", w, flush=True)
+    q, k, v = ji.make_qkv(w, 62)
+    # Most rows here see one block, where a row can come close to a single V row: the error is up to 2^-9 |o| (bf16
+    # output) + 2^-9 |v| (bf16 probabilities) <= 2^-8 max|v|.  With V as drawn (max|v| above 5) that is beyond
+    # check_output's 2e-2, which is meant for |o| of about 3; a quarter of it is below.
+    v = v * 0.25
+    assert float(v.abs().max()) < 2.0 ** 8 * 2e-2
+    layer = CarveLayer(w, "cuda:0", want_lse=True)
+    lay = oracle_layout(w)
+    M = lay.M
+    assert layer.info.attn_workspace_bytes > 2 * (2 * layer.info.N_pad * head_dim * 2) + 256
+    rng = np.random.default_rng(9)
+    cnt = np.ones((1, 2, M), dtype=np.int32)
+    idx = np.zeros((1, 2, M, M), dtype=np.int32)
+    idx[0, :, :, 0] = np.arange(M)
+    mask = np.zeros((1, 2, M, M), dtype=bool)
+    mask[0, :] = np.eye(M, dtype=bool)
+    for h, i, chosen in [(0, 0, []), (0, 1, [M - 1]), (0, 2, rng.permutation(M)), (1, 3, rng.permutation(M)[:300]),
+                         (1, 4, rng.permutation(M // 4)), (0, M - 1, np.arange(M)), (1, M - 2, rng.permutation(M)[:7]),
+                         (0, 7, M - 1 - np.arange(65))]:
+        cnt[0, h, i] = len(chosen)
+        idx[0, h, i, :len(chosen)] = chosen
+        mask[0, h, i] = False
+        mask[0, h, i, list(chosen)] = True
+    layer.permute_in(q.cuda(), k.cuda(), v.cuda())
+    layer.sel_count.copy_(torch.from_numpy(cnt))
+    layer.sel_index.copy_(torch.from_numpy(idx))
+    qc, kc, vc = [jo.permute(to_f64(x), lay) for x in (q, k, v)]
+    want, want_lse = jo.block_sparse_attention(qc, kc, vc, mask, lay, beta=w["text_bias"], return_lse=True)
+    alive = np.isfinite(want_lse)
+    for attend in (layer.attend, layer.attend_packed):       # in passes, whole
+        layer.o_c.view(torch.int16).fill_(0x7FC1)
+        layer.lse.fill_(7.0)
+        attend()
+        torch.cuda.synchronize()
+        check_output(to_f64(layer.o_c), want, "%s %d" % (attend.__name__, head_dim))
+        got = layer.lse.cpu().numpy().astype(np.float64)
+        assert np.isneginf(got[~alive]).all()
+        assert np.abs(got[alive] - want_lse[alive]).max() <= 1e-3     # float32 sums and one float32 logarithm
