@@ -191,7 +191,7 @@ int jenga_select_blocks_static(const jenga_plan* plan, const void* q_curve, cons
  *                biased as above): Alg. 4's running maximum and running sum combined, the value a
  *                caller needs to merge this result with attention over other keys.  Pad query rows
  *                and rows of an empty list get -inf.  Fully overwritten when given
- *   workspace  : at least attn_workspace_bytes, 256-byte aligned (K and V re-tiled for the
+ *   workspace  : at least attn_workspace_bytes, 256-byte aligned (V and where needed K re-tiled for the
  *                matrix cores, 256 bytes of launch parameters, and on grids that leave the chip idle
  *                the results of the parts that long lists are cut into), contents undefined after
  * Equivalent to jenga_pack_kv followed by jenga_block_sparse_attn_packed on the same workspace (the latter

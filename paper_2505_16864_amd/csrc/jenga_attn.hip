@@ -16,9 +16,10 @@
 // accumulator, so the row maximum and row sum are lane-local (one cross-half exchange), and the
 // accumulator layout of S^T is already the B-operand layout PV needs: P never goes through LDS.
 //
-// K and V are first re-tiled once per call (pack_kernel) into "fragment order": for every block a
-// 16-byte piece per (fragment, lane) in exactly the order the LDS reads want them, so that a tile
-// moves global -> LDS as a straight copy and every LDS read is a conflict-free 1 KB wave read.
+// V, and for some kernels K, are first re-tiled once per call (pack_kernel) into "fragment order": for every
+// block a 16-byte piece per (fragment, lane) in exactly the order the LDS reads want them, so that a tile
+// moves global -> LDS as a straight copy and every LDS read is a conflict-free 1 KB wave read.  The in-order
+// kernels for blocks of 64 and 128 tokens take K as it is (K_ROWS).
 // The V tile is stored transposed, with its key index permuted to match the accumulator layout:
 //     accumulator register r of kv-tile mt, lane l  <->  key 32*mt + 8*(r/4) + 4*(l/32) + r%4,
 //     query (l%32).
@@ -46,13 +47,13 @@ __device__ inline uint32_t pack_bf16x2(float lo, float hi) {
   return __builtin_bit_cast(uint32_t, __builtin_convertvector(v, bf16x2));
 }
 
-// grid (M, batch*heads, 2).  z = 0: K tile -> fragment order; z = 1: V tile -> transposed fragment order, pad rows zeroed.
+// grid (M, batch*heads, 2).  z = 0: K tile -> fragment order, or copied (k_rows); z = 1: V tile -> transposed fragment order, pad rows zeroed.
 // A workgroup each, so that the two chains of loads and stores run side by side: 931 blocks x 24 heads (2.9 GB) 531 ->
 // 511 us = 5.7 TB/s, 262 x 24 156 -> 145 us; HBM-bound from there on.
 template <int BLK, int D>
 __global__ __launch_bounds__(256) void pack_kernel(const uint16_t* __restrict__ k, const uint16_t* __restrict__ v,
                                                    uint4* __restrict__ kp, uint4* __restrict__ vp,
-                                                   const int32_t* __restrict__ blk_valid, int M, int n_pad) {
+                                                   const int32_t* __restrict__ blk_valid, int M, int n_pad, int first, bool k_rows) {
   constexpr int KS = D / 16, PS = BLK / 16, CH = D / 8;
   constexpr int TILE_CHUNKS = BLK * D / 8;
   constexpr int LDV = D + 8;   // padded row length (elements) of the staged V tile
@@ -65,13 +66,13 @@ __global__ __launch_bounds__(256) void pack_kernel(const uint16_t* __restrict__ 
   uint4* kdst = kp + ((size_t)bh * M + j) * TILE_CHUNKS;
   uint4* vdst = vp + ((size_t)bh * M + j) * TILE_CHUNKS;
 
-  if (blockIdx.z == 0) {
+  if (blockIdx.z + first == 0) {
 #pragma unroll
     for (int o = threadIdx.x; o < TILE_CHUNKS; o += 256) {
       const int lane = o & 63, f = o >> 6;
       const int ks = f % KS, mt = f / KS;
       const int row = 32 * mt + (lane & 31);
-      kdst[o] = ksrc[row * CH + 2 * ks + (lane >> 5)];
+      kdst[o] = ksrc[k_rows ? o : row * CH + 2 * ks + (lane >> 5)];
     }
     return;
   }
@@ -294,7 +295,13 @@ __global__ __launch_bounds__(2 * BLK, (attn_h_min_waves<BLK, D>())) void attn_h_
   constexpr int NW = BLK / 32, NTHR = 64 * NW, HALVES = BLK / 64;   // wavefronts, threads, steps per key block
   constexpr int TILE_CHUNKS = BLK * D / 8, HALF_CHUNKS = 64 * D / 8, CPT = HALF_CHUNKS / NTHR;
   static_assert(HALVES >= 1 && (!PACED || HALVES == 2), "64 keys a step; the paced walk needs two steps a block");
-  __shared__ u32x4 Ks[HALF_CHUNKS];   // fragments (m2, ks) of the current 64 keys
+  // The current 64 keys: fragments (m2, ks) from packed tiles, or (K_ROWS) rows of D channels as they lie in K, with the
+  // 16-byte pieces of a row rotated by an exclusive or with k_swizzle(row), so that the 16 rows that are read at a time
+  // fall on different banks.  K_ROWS needs no packed K (lowres layer of 262 blocks x 24 heads: 4505 -> 4448 us with
+  // packing, 931 blocks at k = 0.1 21.01 -> 20.74 ms, 222 blocks of 64 580 -> 570 us) but eight address instructions
+  // a step; the paced walk, which is closest to what the matrix cores can do, loses 0.6 % to them and keeps the tiles.
+  constexpr bool K_ROWS = !PACED;
+  __shared__ __align__(256) u32x4 Ks[HALF_CHUNKS];
   __shared__ u32x4 Vs[HALF_CHUNKS];   // fragments (dt, p2) of the current 64 keys
   __shared__ uint32_t rem_bits[PACED ? 64 : 1];   // PACED: bitmap of the blocks still to visit, 32 per word
   __shared__ int pace_slot[2];                    // PACED: G for the next pick, published by thread 0
@@ -395,11 +402,16 @@ __global__ __launch_bounds__(2 * BLK, (attn_h_min_waves<BLK, D>())) void attn_h_
       (uint32_t)(uintptr_t)(const __attribute__((address_space(3))) void*)Ks + (uint32_t)wave * 1024u);
   const uint32_t vs_wave = __builtin_amdgcn_readfirstlane(
       (uint32_t)(uintptr_t)(const __attribute__((address_space(3))) void*)Vs + (uint32_t)wave * 1024u);
+  constexpr int CH = D / 8, ROWS_PER_COPY = NTHR / CH;
+  auto k_swizzle = [](int row) { return D == 128 ? row & 15 : (row >> 1) & 7; };
+  const uint32_t k_off = (uint32_t)(K_ROWS ? tid / CH * CH + (tid % CH ^ k_swizzle(tid / CH)) : tid) * 16u;
   auto k_half_to_lds = [&](int j, int h) {
     const char* kt = (const char*)(kbase + (size_t)j * TILE_CHUNKS + h * HALF_CHUNKS);
 #pragma unroll
     for (int c = 0; c < CPT; ++c) 
-      dma_1kb_to_lds_at(kt + (size_t)c * (NTHR * 16), (uint32_t)tid * 16u, ks_wave + c * (NTHR * 16u));
+      dma_1kb_to_lds_at(kt + (size_t)c * (NTHR * 16),
+                        K_ROWS ? k_off ^ (uint32_t)k_swizzle(c * ROWS_PER_COPY) * 16u : k_off,
+                        ks_wave + c * (NTHR * 16u));
   };
   auto v_half_to_lds = [&](int j, int h) {
     const u32x4* vt = vbase + (size_t)j * TILE_CHUNKS + (PH * h) * 64;
@@ -417,7 +429,15 @@ __global__ __launch_bounds__(2 * BLK, (attn_h_min_waves<BLK, D>())) void attn_h_
   for (int dt = 0; dt < DT; ++dt)
 #pragma unroll
     for (int r = 0; r < 16; ++r) O[dt][r] = 0.f;
-  const uint32_t ks_lane = (uint32_t)(uintptr_t)(const __attribute__((address_space(3))) void*)Ks + lane * 16;
+  const uint32_t ks_lane = (uint32_t)(uintptr_t)(const __attribute__((address_space(3))) void*)Ks +
+                           (K_ROWS ? ql * (2 * D) + (hl ^ k_swizzle(ql)) * 16 : lane * 16);
+  auto k_frag = [&](u32x4& dst, auto M2, auto KSTEP) {   // fragment (m2, ks); K_ROWS: piece 2 ks + hl of row 32 m2 + ql
+    constexpr int m2 = decltype(M2)::value, ks = decltype(KSTEP)::value;
+    if constexpr (K_ROWS)
+      lds_frag<m2 * 64 * D>(dst, ks_lane ^ ks * 32);
+    else
+      lds_frag<(m2 * KS + ks) * 1024>(dst, ks_lane);
+  };
   const uint32_t vs_lane = (uint32_t)(uintptr_t)(const __attribute__((address_space(3))) void*)Vs + lane * 16;
 
   // The block index of the next step is fetched a step ahead, and the valid-token count of a
@@ -454,7 +474,7 @@ __global__ __launch_bounds__(2 * BLK, (attn_h_min_waves<BLK, D>())) void attn_h_
         u32x4 A[2][4];
         static_for<4>([&](auto E) {
           constexpr int e = decltype(E)::value;
-          lds_frag<((e & 1) * KS + e / 2) * 1024>(A[0][e], ks_lane);
+          k_frag(A[0][e], std::integral_constant<int, e & 1>{}, std::integral_constant<int, e / 2>{});
         });
         static_for<NG>([&](auto G) {
           constexpr int g = decltype(G)::value;
@@ -462,7 +482,8 @@ __global__ __launch_bounds__(2 * BLK, (attn_h_min_waves<BLK, D>())) void attn_h_
           if constexpr (g + 1 < NG)
             static_for<4>([&](auto E) {
               constexpr int e = decltype(E)::value;
-              lds_frag<((e & 1) * KS + 2 * (g + 1) + e / 2) * 1024>(A[(g + 1) & 1][e], ks_lane);
+              k_frag(A[(g + 1) & 1][e], std::integral_constant<int, e & 1>{},
+                     std::integral_constant<int, 2 * (g + 1) + e / 2>{});
             });
           static_for<4>([&](auto E) {
             constexpr int e = decltype(E)::value, m2 = e & 1, ks = 2 * g + e / 2;
@@ -954,27 +975,35 @@ __global__ __launch_bounds__(1024) void walk_pace_kernel(const int32_t* __restri
   }
 }
 
+// Whether the attention kernel of a plan reads K as rows (see K_ROWS) or as packed tiles.
+template <int BLK>
+bool reads_k_rows(const jenga_plan* p) {
+  return BLK == 64 || (BLK == 128 && !(p->cfg.flags & JENGA_FLAG_PACED_WALK));
+}
+
 template <int BLK, int D>
-int run_pack(const jenga_plan* p, const void* k, const void* v, void* ws, hipStream_t st) {
+int run_pack(const jenga_plan* p, const void* k, const void* v, void* ws, bool with_k, hipStream_t st) {
   const jenga_config& c = p->cfg;
   const jenga_plan_info_t& f = p->info;
   const int bh = c.batch * c.heads;
   const size_t half = (((size_t)bh * f.N_pad * D * 2) + 255) & ~(size_t)255;
   uint4* kp = (uint4*)ws;
   uint4* vp = (uint4*)((char*)ws + half);
-  pack_kernel<BLK, D><<<dim3(f.M, bh, 2), 256, 0, st>>>((const uint16_t*)k, (const uint16_t*)v, kp, vp,
-                                                     p->d_blk_valid, f.M, f.N_pad);
+  const bool k_rows = reads_k_rows<BLK>(p);
+  const int first = with_k || !k_rows ? 0 : 1;
+  pack_kernel<BLK, D><<<dim3(f.M, bh, 2 - first), 256, 0, st>>>((const uint16_t*)k, (const uint16_t*)v, kp, vp,
+                                                             p->d_blk_valid, f.M, f.N_pad, first, k_rows);
   return hipGetLastError() == hipSuccess ? JENGA_OK : JENGA_EHIP;
 }
 
 template <int BLK, int D>
-int run_attention(const jenga_plan* p, const void* q, void* ws, bool may_split, const int32_t* sel_count,
+int run_attention(const jenga_plan* p, const void* q, const void* k, void* ws, bool may_split, const int32_t* sel_count,
                   const int32_t* sel_index, void* out, float* lse, hipStream_t st) {
   const jenga_config& c = p->cfg;
   const jenga_plan_info_t& f = p->info;
   const int bh = c.batch * c.heads;
   const size_t half = (((size_t)bh * f.N_pad * D * 2) + 255) & ~(size_t)255;
-  const u32x4* kp = (const u32x4*)ws;
+  const u32x4* kp = reads_k_rows<BLK>(p) && k != nullptr ? (const u32x4*)k : (const u32x4*)ws;
   const u32x4* vp = (const u32x4*)((const char*)ws + half);
   uint32_t* params = (uint32_t*)((char*)ws + 2 * half);
   // workgroups resident on the 32 CUs of an XCD: by registers and LDS 2, 3 to 4 or 5 to 8 per CU
@@ -1039,22 +1068,22 @@ namespace jenga {
 
 #define JENGA_FOR_SHAPES(X) X(128, 128) X(64, 128) X(32, 128) X(128, 64) X(64, 64) X(32, 64)
 
-int launch_pack(const jenga_plan* p, const void* k, const void* v, void* ws, void* stream) {
+int launch_pack(const jenga_plan* p, const void* k, const void* v, void* ws, bool with_k, void* stream) {
   hipStream_t st = (hipStream_t)stream;
   const int blk = p->cfg.block, d = p->cfg.head_dim;
 #define X(B, DD) \
-  if (blk == B && d == DD) return run_pack<B, DD>(p, k, v, ws, st);
+  if (blk == B && d == DD) return run_pack<B, DD>(p, k, v, ws, with_k, st);
   JENGA_FOR_SHAPES(X)
 #undef X
   return JENGA_EUNSUPPORTED;
 }
 
-int launch_attention(const jenga_plan* p, const void* q, void* ws, bool may_split, const int32_t* sel_count,
+int launch_attention(const jenga_plan* p, const void* q, const void* k, void* ws, bool may_split, const int32_t* sel_count,
                      const int32_t* sel_index, void* out, float* lse, void* stream) {
   hipStream_t st = (hipStream_t)stream;
   const int blk = p->cfg.block, d = p->cfg.head_dim;
 #define X(B, DD) \
-  if (blk == B && d == DD) return run_attention<B, DD>(p, q, ws, may_split, sel_count, sel_index, out, lse, st);
+  if (blk == B && d == DD) return run_attention<B, DD>(p, q, k, ws, may_split, sel_count, sel_index, out, lse, st);
   JENGA_FOR_SHAPES(X)
 #undef X
   return JENGA_EUNSUPPORTED;

@@ -16,6 +16,10 @@ bool on_plan_device(const jenga_plan* p) {
   return hipGetDevice(&dev) == hipSuccess && dev == p->device;
 }
 
+bool overlap(const void* a, size_t a_bytes, const void* b, size_t b_bytes) {
+  return (uintptr_t)a < (uintptr_t)b + b_bytes && (uintptr_t)b < (uintptr_t)a + a_bytes;
+}
+
 template <typename T>
 int to_device(const std::vector<T>& h, T** d) {
   *d = nullptr;
@@ -116,9 +120,13 @@ int jenga_block_sparse_attn(const jenga_plan* p, const void* q, const void* k, c
   if (!on_plan_device(p)) return JENGA_EINVAL;
   if (((uintptr_t)workspace & 255u) != 0) return JENGA_EINVAL;
   if (workspace_bytes < p->info.attn_workspace_bytes) return JENGA_EWORKSPACE;
-  const int rc = jenga::launch_pack(p, k, v, workspace, stream);
+  // K is read in place unless an output lies over it
+  const size_t rows = (size_t)p->cfg.batch * p->cfg.heads * p->info.N_pad, bytes = rows * p->cfg.head_dim * 2;
+  const bool copy_k = overlap(k, bytes, out_curve, bytes) || (lse_or_null && overlap(k, bytes, lse_or_null, rows * 4));
+  const int rc = jenga::launch_pack(p, k, v, workspace, copy_k, stream);
   if (rc != JENGA_OK) return rc;
-  return jenga::launch_attention(p, q, workspace, true, sel_count, sel_index, out_curve, lse_or_null, stream);
+  return jenga::launch_attention(p, q, copy_k ? nullptr : k, workspace, true, sel_count, sel_index, out_curve,
+                                 lse_or_null, stream);
 }
 
 int jenga_pack_kv(const jenga_plan* p, const void* k, const void* v, void* workspace, size_t workspace_bytes,
@@ -127,7 +135,7 @@ int jenga_pack_kv(const jenga_plan* p, const void* k, const void* v, void* works
   if (!on_plan_device(p)) return JENGA_EINVAL;
   if (((uintptr_t)workspace & 255u) != 0) return JENGA_EINVAL;
   if (workspace_bytes < p->info.attn_workspace_bytes) return JENGA_EWORKSPACE;
-  return jenga::launch_pack(p, k, v, workspace, stream);
+  return jenga::launch_pack(p, k, v, workspace, true, stream);
 }
 
 int jenga_block_sparse_attn_packed(const jenga_plan* p, const void* q, void* packed_kv_workspace,
@@ -137,7 +145,7 @@ int jenga_block_sparse_attn_packed(const jenga_plan* p, const void* q, void* pac
   if (!on_plan_device(p)) return JENGA_EINVAL;
   if (((uintptr_t)packed_kv_workspace & 255u) != 0) return JENGA_EINVAL;
   if (workspace_bytes < p->info.attn_workspace_bytes) return JENGA_EWORKSPACE;
-  return jenga::launch_attention(p, q, packed_kv_workspace, false, sel_count, sel_index, out_curve, lse_or_null, stream);
+  return jenga::launch_attention(p, q, nullptr, packed_kv_workspace, false, sel_count, sel_index, out_curve, lse_or_null, stream);
 }
 
 }  // extern "C"
