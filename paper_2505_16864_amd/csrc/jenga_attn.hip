@@ -104,8 +104,7 @@ __global__ __launch_bounds__(256) void pack_kernel(const uint16_t* __restrict__ 
 // Written as asm so that the compiler does not track these copies: it would otherwise order every
 // later LDS read of the same array behind them with a full vmcnt(0) wait.  Completion is tracked by
 // vmcnt and waited for explicitly (wait_vmem) before the barrier that publishes a tile.
-// dma_1kb_to_lds_at takes the LDS byte address as a number the caller keeps in an SGPR;
-// dma_1kb_to_lds derives it from a pointer (a few more instructions per copy).
+// The LDS byte address is a number that the caller keeps in an SGPR.
 __device__ inline void dma_1kb_to_lds_at(const void* uniform_base, uint32_t lane_byte_off, uint32_t lds_addr) {
   const uint64_t b = (uint64_t)uniform_base;
   const uint32_t lo = __builtin_amdgcn_readfirstlane((uint32_t)b);
@@ -115,11 +114,6 @@ __device__ inline void dma_1kb_to_lds_at(const void* uniform_base, uint32_t lane
                :
                : "s"(lds_addr), "v"(lane_byte_off), "s"(base)
                : "memory", "m0");
-}
-__device__ inline void dma_1kb_to_lds(const void* uniform_base, uint32_t lane_byte_off, const void* lds_dst) {
-  dma_1kb_to_lds_at(uniform_base, lane_byte_off,
-                    __builtin_amdgcn_readfirstlane(
-                        (uint32_t)(uintptr_t)(const __attribute__((address_space(3))) void*)lds_dst));
 }
 
 __device__ inline void wait_vmem() { __builtin_amdgcn_s_waitcnt(0x0F70); }   // vmcnt(0) only
@@ -274,7 +268,6 @@ constexpr float P_SUM_MAX = 1073741824.0f;   // 2^30
 template <int BLK, int D>
 constexpr int attn_h_min_waves() { return D == 128 ? 3 : 4; }   // wavefronts per SIMD that the registers have to allow
 
-//
 // SPLIT: grids that leave the chip idle.  The list of a query block is cut into Split::of(cnt) parts of equal length, a
 // workgroup each; the parts' O, reference and sum go to the workspace and merge_kernel puts them together.
 struct Split {
