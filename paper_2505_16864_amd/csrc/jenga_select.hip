@@ -198,7 +198,8 @@ __device__ __forceinline__ void select_row(double* row, uint64_t fixed_lane, int
   }
   if constexpr (NT == 1) {
     // One value per lane: its rank and C_n by comparing it with every other, no chain of dependent reductions.
-    // (8 heads of 17 blocks: 9.6 -> 5.4 us for the kernel; with two values per lane the descents are as fast.)
+    // (The kernel on 17 blocks x 8 heads: 9.8 -> 9.0 us.  It grows with M: on 48 blocks x 16 heads the two are about
+    // equal, and above 64 the descents are taken.)
     const double mine = r[0] = r[0] / z;
     int rank = 0;
     double sum_before = 0.0;
@@ -405,8 +406,8 @@ __device__ __forceinline__ void select_row(double* row, uint64_t fixed_lane, int
 //
 // Time of the kernel, against a 128 x 128 tile of vector FMAs that wrote S to memory and a selection with one chain of
 // LDS exchanges per bit of the cumulative rule:
-//   17 blocks x 8 heads, D = 128     5.4 us (was 43.6 + 11.7: one workgroup per head, most of its tile padding)
-//   222 x 12, D = 128                  19 us (48 + 21)
+//   17 blocks x 8 heads, D = 128     9.0 us (was 43.6 + 11.7: one workgroup per head, most of its tile padding)
+//   222 x 12, D = 128                  20 us (48 + 21)
 //   262 x 24, D = 128                  38 us (53 + 19)
 //   2048 x 2, D = 64                  109 us (38 + 141)
 //   931 x 24, D = 128, k = 0.1        226 us (164 + 145): matrix cores 105 us (75 us at their full rate, the rest is the
