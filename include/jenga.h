@@ -205,15 +205,18 @@ int jenga_block_sparse_attn(const jenga_plan* plan, const void* q, const void* k
 /*
  * First half of jenga_block_sparse_attn: re-tiles K and V of every block (Alg. 4's "load key-value
  * block") into the matrix-core fragment order inside `workspace`; pad rows of V are zeroed.
- * A caller that attends several times to the same K and V (a sweep of k or p) packs once.
+ * A caller that attends several times to the same K and V (a sweep of k or p) packs once: what is packed
+ * depends on T, H, W, n_text, batch, heads, head_dim and block alone.
  */
 int jenga_pack_kv(const jenga_plan* plan, const void* k, const void* v, void* workspace,
                   size_t workspace_bytes, void* stream);
 
 /*
  * Second half of jenga_block_sparse_attn: the block-sparse attention kernel itself, reading K and V
- * from a workspace filled by jenga_pack_kv for the same plan.  The packed tiles are only read; the 256
- * bytes behind them (launch parameters) may be written.  Other arguments as above.
+ * from a workspace filled by jenga_pack_kv for this plan or for one that differs in topk_ratio, cum_prob,
+ * text_bias or flags only (jenga_block_sparse_attn leaves nothing in its workspace that could be read
+ * here).  The packed tiles are only read; the 256 bytes behind them (launch parameters) may be written.
+ * Other arguments as above.
  */
 int jenga_block_sparse_attn_packed(const jenga_plan* plan, const void* q, void* packed_kv_workspace,
                                    size_t workspace_bytes, const int32_t* sel_count,

@@ -18,8 +18,9 @@
 //
 // V, and for some kernels K, are first re-tiled once per call (pack_kernel) into "fragment order": for every
 // block a 16-byte piece per (fragment, lane) in exactly the order the LDS reads want them, so that a tile
-// moves global -> LDS as a straight copy and every LDS read is a conflict-free 1 KB wave read.  The in-order
-// kernels for blocks of 64 and 128 tokens take K as it is (K_ROWS).
+// moves global -> LDS as a straight copy and every LDS read is a conflict-free 1 KB wave read.  A call that is
+// given K itself takes it as it is in the in-order kernels for blocks of 64 and 128 tokens (K_ROWS).  A packed
+// workspace always holds both in fragment order, whatever the walk: plans of one grid may share it.
 // The V tile is stored transposed, with its key index permuted to match the accumulator layout:
 //     accumulator register r of kv-tile mt, lane l  <->  key 32*mt + 8*(r/4) + 4*(l/32) + r%4,
 //     query (l%32).
@@ -47,13 +48,14 @@ __device__ inline uint32_t pack_bf16x2(float lo, float hi) {
   return __builtin_bit_cast(uint32_t, __builtin_convertvector(v, bf16x2));
 }
 
-// grid (M, batch*heads, 2).  z = 0: K tile -> fragment order, or copied (k_rows); z = 1: V tile -> transposed fragment order, pad rows zeroed.
+// grid (M, batch*heads, 2).  z = 0: K tile -> fragment order; z = 1: V tile -> transposed fragment order, pad rows zeroed.
+// grid (M, batch*heads, 1) with first = 1: V only.
 // A workgroup each, so that the two chains of loads and stores run side by side: 931 blocks x 24 heads (2.9 GB) 531 ->
 // 511 us = 5.7 TB/s, 262 x 24 156 -> 145 us; HBM-bound from there on.
 template <int BLK, int D>
 __global__ __launch_bounds__(256) void pack_kernel(const uint16_t* __restrict__ k, const uint16_t* __restrict__ v,
                                                    uint4* __restrict__ kp, uint4* __restrict__ vp,
-                                                   const int32_t* __restrict__ blk_valid, int M, int n_pad, int first, bool k_rows) {
+                                                   const int32_t* __restrict__ blk_valid, int M, int n_pad, int first) {
   constexpr int KS = D / 16, PS = BLK / 16, CH = D / 8;
   constexpr int TILE_CHUNKS = BLK * D / 8;
   constexpr int LDV = D + 8;   // padded row length (elements) of the staged V tile
@@ -72,7 +74,7 @@ __global__ __launch_bounds__(256) void pack_kernel(const uint16_t* __restrict__ 
       const int lane = o & 63, f = o >> 6;
       const int ks = f % KS, mt = f / KS;
       const int row = 32 * mt + (lane & 31);
-      kdst[o] = ksrc[k_rows ? o : row * CH + 2 * ks + (lane >> 5)];
+      kdst[o] = ksrc[row * CH + 2 * ks + (lane >> 5)];
     }
     return;
   }
@@ -278,7 +280,7 @@ struct Split {
   __device__ int of(int cnt) const { return chunk == 0 ? parts : max(1, min(parts, (cnt + chunk - 1) / chunk)); }
 };
 
-template <int BLK, int D, bool PACED, bool SPLIT>
+template <int BLK, int D, bool PACED, bool SPLIT, bool K_ROWS>
 __global__ __launch_bounds__(2 * BLK, (attn_h_min_waves<BLK, D>())) void attn_h_kernel(
     const uint16_t* __restrict__ q, const u32x4* __restrict__ kp, const u32x4* __restrict__ vp,
     const int32_t* __restrict__ sel_count, const int32_t* __restrict__ sel_index,
@@ -292,8 +294,9 @@ __global__ __launch_bounds__(2 * BLK, (attn_h_min_waves<BLK, D>())) void attn_h_
   // 16-byte pieces of a row rotated by an exclusive or with k_swizzle(row), so that the 16 rows that are read at a time
   // fall on different banks.  K_ROWS needs no packed K (lowres layer of 262 blocks x 24 heads: 4505 -> 4448 us with
   // packing, 931 blocks at k = 0.1 21.01 -> 20.74 ms, 222 blocks of 64 580 -> 570 us) but eight address instructions
-  // a step; the paced walk, which is closest to what the matrix cores can do, loses 0.6 % to them and keeps the tiles.
-  constexpr bool K_ROWS = !PACED;
+  // a step; the paced walk, which is closest to what the matrix cores can do, loses 0.6 % to them and keeps the tiles,
+  // and so does whoever has packed K already.
+  static_assert(!(PACED && K_ROWS), "the paced walk reads packed tiles");
   __shared__ __align__(256) u32x4 Ks[HALF_CHUNKS];
   __shared__ u32x4 Vs[HALF_CHUNKS];   // fragments (dt, p2) of the current 64 keys
   __shared__ uint32_t rem_bits[PACED ? 64 : 1];   // PACED: bitmap of the blocks still to visit, 32 per word
@@ -968,7 +971,7 @@ __global__ __launch_bounds__(1024) void walk_pace_kernel(const int32_t* __restri
   }
 }
 
-// Whether the attention kernel of a plan reads K as rows (see K_ROWS) or as packed tiles.
+// Whether the attention kernel of a plan reads K in place (see K_ROWS) if it is given it.
 template <int BLK>
 bool reads_k_rows(const jenga_plan* p) {
   return BLK == 64 || (BLK == 128 && !(p->cfg.flags & JENGA_FLAG_PACED_WALK));
@@ -982,10 +985,9 @@ int run_pack(const jenga_plan* p, const void* k, const void* v, void* ws, bool w
   const size_t half = (((size_t)bh * f.N_pad * D * 2) + 255) & ~(size_t)255;
   uint4* kp = (uint4*)ws;
   uint4* vp = (uint4*)((char*)ws + half);
-  const bool k_rows = reads_k_rows<BLK>(p);
-  const int first = with_k || !k_rows ? 0 : 1;
+  const int first = with_k || !reads_k_rows<BLK>(p) ? 0 : 1;
   pack_kernel<BLK, D><<<dim3(f.M, bh, 2 - first), 256, 0, st>>>((const uint16_t*)k, (const uint16_t*)v, kp, vp,
-                                                             p->d_blk_valid, f.M, f.N_pad, first, k_rows);
+                                                             p->d_blk_valid, f.M, f.N_pad, first);
   return hipGetLastError() == hipSuccess ? JENGA_OK : JENGA_EHIP;
 }
 
@@ -996,7 +998,8 @@ int run_attention(const jenga_plan* p, const void* q, const void* k, void* ws, b
   const jenga_plan_info_t& f = p->info;
   const int bh = c.batch * c.heads;
   const size_t half = (((size_t)bh * f.N_pad * D * 2) + 255) & ~(size_t)255;
-  const u32x4* kp = reads_k_rows<BLK>(p) && k != nullptr ? (const u32x4*)k : (const u32x4*)ws;
+  const bool k_rows = reads_k_rows<BLK>(p) && k != nullptr;
+  const u32x4* kp = k_rows ? (const u32x4*)k : (const u32x4*)ws;
   const u32x4* vp = (const u32x4*)((const char*)ws + half);
   uint32_t* params = (uint32_t*)((char*)ws + 2 * half);
   // workgroups resident on the 32 CUs of an XCD: by registers and LDS 2, 3 to 4 or 5 to 8 per CU
@@ -1025,9 +1028,9 @@ int run_attention(const jenga_plan* p, const void* q, const void* k, void* ws, b
   } else {
     const bool paced = BLK == 128 && (c.flags & JENGA_FLAG_PACED_WALK);
     Split split = {};
-#define JENGA_ATTN(PACED, SPLIT, WGS)                                                                                 \
-  attn_h_kernel<BLK, D, PACED, SPLIT><<<dim3(WGS), 2 * BLK, 0, st>>>(qb, kp, vp, sel_count, sel_index, ob, lse, work, \
-                                                                     f.N_pad, f.pad_v, f.pad_c, scale, bias, params, split)
+#define JENGA_ATTN(PACED, SPLIT, K_ROWS, WGS)                                                                    \
+  attn_h_kernel<BLK, D, PACED, SPLIT, K_ROWS><<<dim3(WGS), 2 * BLK, 0, st>>>(                                    \
+      qb, kp, vp, sel_count, sel_index, ob, lse, work, f.N_pad, f.pad_v, f.pad_c, scale, bias, params, split)
     if (may_split && p->attn_parts > 1) {
       split.parts = p->attn_parts;
       split.chunk = p->attn_chunk;
@@ -1035,9 +1038,10 @@ int run_attention(const jenga_plan* p, const void* q, const void* k, void* ws, b
       split.o = (float*)((char*)ws + 2 * half + 256);
       split.stat = split.o + (size_t)bh * f.M * split.parts * BLK * D;
       if constexpr (BLK == 128) {
-        if (paced) JENGA_ATTN(true, true, split.parts * split.stride);
+        if (paced) JENGA_ATTN(true, true, false, split.parts * split.stride);
       }
-      if (!paced) JENGA_ATTN(false, true, split.parts * split.stride);
+      if (k_rows) JENGA_ATTN(false, true, true, split.parts * split.stride);
+      else if (!paced) JENGA_ATTN(false, true, false, split.parts * split.stride);
       merge_kernel<BLK, D><<<dim3(BLK / 32, f.M, bh), 2 * D, 0, st>>>(sel_count, ob, lse, f.M, f.M_v, f.N_pad, f.pad_v,
                                                                       f.pad_c, split);
       return hipGetLastError() == hipSuccess ? JENGA_OK : JENGA_EHIP;
@@ -1046,10 +1050,11 @@ int run_attention(const jenga_plan* p, const void* q, const void* k, void* ws, b
       if (paced) {
         // a workgroup spends about 6.3 us (D = 128; 3.6 us at D = 64) on a block of 128 keys when three share a CU
         walk_pace_kernel<<<1, 1024, 0, st>>>(sel_count, bh * f.M, f.M, D == 128 ? 630.f : 360.f, params);
-        JENGA_ATTN(true, false, work.n_wg);
+        JENGA_ATTN(true, false, false, work.n_wg);
       }
     }
-    if (!paced) JENGA_ATTN(false, false, work.n_wg);
+    if (k_rows) JENGA_ATTN(false, false, true, work.n_wg);
+    else if (!paced) JENGA_ATTN(false, false, false, work.n_wg);
 #undef JENGA_ATTN
   }
   return hipGetLastError() == hipSuccess ? JENGA_OK : JENGA_EHIP;

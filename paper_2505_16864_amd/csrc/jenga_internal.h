@@ -51,7 +51,7 @@ int launch_select(const jenga_plan* p, const void* q, const void* k, int32_t* se
 int select_scratch_init(int device);
 // with_k = false: K is left out where the attention kernel can read it in place; launch_attention then gets it.
 int launch_pack(const jenga_plan* p, const void* k, const void* v, void* ws, bool with_k, void* stream);
-// k: K, if it may have been left out of the workspace, else NULL.  may_split: the call has the workspace to itself and may
+// k: K, if it may have been left out of the workspace, else NULL (K packed).  may_split: the call has the workspace to itself and may
 // write behind the packed tiles.
 int launch_attention(const jenga_plan* p, const void* q, const void* k, void* packed_ws, bool may_split,
                      const int32_t* sel_count, const int32_t* sel_index, void* out, float* lse, void* stream);
