@@ -121,7 +121,8 @@ int jenga_plan_tables(const jenga_config* cfg, jenga_plan_info_t* info, int32_t*
 int jenga_curve_permute(const jenga_plan* plan, const void* src_thw, void* dst_curve, void* stream);
 
 /*
- * jenga_curve_permute of Q, K and V in one launch: the same results as three calls.
+ * jenga_curve_permute of Q, K and V in one launch: the same results as three calls in this order, also
+ * where a result lies over a tensor that has moved by then (K's over Q): that is done in three launches.
  */
 int jenga_curve_permute_qkv(const jenga_plan* plan, const void* q_thw, const void* k_thw, const void* v_thw,
                             void* q_curve, void* k_curve, void* v_curve, void* stream);

@@ -86,7 +86,21 @@ int jenga_curve_permute_qkv(const jenga_plan* p, const void* q_thw, const void* 
   if (!on_plan_device(p)) return JENGA_EINVAL;
   const void* src[3] = {q_thw, k_thw, v_thw};
   void* dst[3] = {q_curve, k_curve, v_curve};
-  return jenga::launch_permute(p, src, dst, 3, true, stream);
+  // One launch moves the three at the same time.  A result that lies over another tensor (K's over Q, which has moved
+  // by then) needs them one after the other.
+  const size_t rows = (size_t)p->cfg.batch * p->cfg.heads, row = (size_t)p->cfg.head_dim * 2;
+  const size_t src_bytes = rows * (p->info.N_v + p->cfg.n_text) * row, dst_bytes = rows * p->info.N_pad * row;
+  bool one_launch = true;
+  for (int t = 0; t < 3; ++t)
+    for (int u = 0; u < 3; ++u)
+      if (t != u && (overlap(dst[t], dst_bytes, src[u], src_bytes) || overlap(dst[t], dst_bytes, dst[u], dst_bytes)))
+        one_launch = false;
+  if (one_launch) return jenga::launch_permute(p, src, dst, 3, true, stream);
+  for (int t = 0; t < 3; ++t) {
+    const int rc = jenga::launch_permute(p, src + t, dst + t, 1, true, stream);
+    if (rc != JENGA_OK) return rc;
+  }
+  return JENGA_OK;
 }
 
 int jenga_curve_permute_rows(const jenga_plan* p, const void* src_rows, void* dst_rows, int32_t row_bytes,

@@ -68,3 +68,29 @@ def test_three_tensors_in_one_launch(name):
         jb.jenga_plan_destroy(plan)
     for a, b in zip(one, all3):
         assert np.array_equal(ji.bits(a), ji.bits(b))
+
+
+# Results laid over tensors that three calls in a row have finished with: K's over Q, V's over K, all three results in
+# one buffer (the last one stays).  Large enough for the three to be in flight together if they were launched as one.
+@pytest.mark.parametrize("over", ["k over q, v over k", "v over q", "one buffer"])
+def test_results_over_tensors_that_have_moved(over):
+    from paper_2505_16864_amd import binding as jb
+    w = dict(ji.WORKLOADS["small"], batch=2, heads=24, n_text=70)
+    tensors = [x.cuda().reshape(-1) for x in ji.make_qkv(w, 91)]
+    plan = jb.jenga_plan_create(jb.make_config(w["T"], w["H"], w["W"], w["n_text"], w["batch"], w["heads"],
+                                               w["head_dim"], w["block"], w["topk"], w["p"]))
+    try:
+        n = w["batch"] * w["heads"] * jb.jenga_plan_info(plan).N_pad * w["head_dim"]
+        room = [torch.cat([x, x.new_zeros(n - x.numel())]) for x in tensors]      # inputs in buffers a result fits in
+        want = [x.new_empty(n) for x in room]
+        for src, dst in zip(tensors, want):
+            jb.jenga_curve_permute(plan, src, dst)
+        own = [x.new_empty(n) for x in room]
+        dst = {"k over q, v over k": [own[0], room[0], room[1]], "v over q": [own[0], own[1], room[0]],
+               "one buffer": [own[0], own[0], own[0]]}[over]
+        jb.jenga_curve_permute_qkv(plan, *room, *dst)
+        torch.cuda.synchronize()
+    finally:
+        jb.jenga_plan_destroy(plan)
+    for t in range(2 if over == "one buffer" else 0, 3):
+        assert np.array_equal(ji.bits(dst[t]), ji.bits(want[t])), (over, t)
