@@ -94,3 +94,24 @@ def test_results_over_tensors_that_have_moved(over):
         jb.jenga_plan_destroy(plan)
     for t in range(2 if over == "one buffer" else 0, 3):
         assert np.array_equal(ji.bits(dst[t]), ji.bits(want[t])), (over, t)
+
+
+# More batches than a grid has in z for three tensors.
+def test_three_tensors_of_many_batches():
+    from paper_2505_16864_amd import binding as jb
+    cfg = jb.make_config(1, 1, 3, 1, 21846, 1, 64, 32, 0.5, 0.3)
+    plan = jb.jenga_plan_create(cfg)
+    try:
+        g = torch.Generator(device="cuda:0").manual_seed(92)
+        src = [torch.randn((21846, 4, 1, 64), generator=g, device="cuda:0").to(torch.bfloat16) for _ in range(3)]
+        shape = (21846, 1, jb.jenga_plan_info(plan).N_pad, 64)
+        one = [src[0].new_full(shape, 7.0) for _ in range(3)]
+        all3 = [src[0].new_full(shape, 8.0) for _ in range(3)]
+        for a, b in zip(src, one):
+            jb.jenga_curve_permute(plan, a, b)
+        jb.jenga_curve_permute_qkv(plan, *src, *all3)
+        torch.cuda.synchronize()
+    finally:
+        jb.jenga_plan_destroy(plan)
+    for a, b in zip(one, all3):
+        assert torch.equal(a, b)
