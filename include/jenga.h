@@ -78,7 +78,7 @@ typedef struct {
 typedef struct {
   int32_t N_v, M_v, M_c, M, N_pad, pad_v, pad_c, K_top;
   uint64_t select_workspace_bytes; /* for jenga_select_blocks                                  */
-  uint64_t attn_workspace_bytes;   /* for jenga_block_sparse_attn                              */
+  uint64_t attn_workspace_bytes;   /* for jenga_block_sparse_attn; enough for the packed entries */
 } jenga_plan_info_t;
 
 typedef struct jenga_plan jenga_plan; /* opaque, library-owned */
@@ -208,6 +208,8 @@ int jenga_block_sparse_attn(const jenga_plan* plan, const void* q, const void* k
  * block") into the matrix-core fragment order inside `workspace`; pad rows of V are zeroed.
  * A caller that attends several times to the same K and V (a sweep of k or p) packs once: what is packed
  * depends on T, H, W, n_text, batch, heads, head_dim and block alone.
+ *   workspace  : 256-byte aligned, at least 2 * B + 256 bytes with B = batch * heads * N_pad * head_dim * 2 rounded
+ *                up to a multiple of 256 (attn_workspace_bytes is never less); JENGA_EWORKSPACE below that
  */
 int jenga_pack_kv(const jenga_plan* plan, const void* k, const void* v, void* workspace,
                   size_t workspace_bytes, void* stream);
@@ -216,7 +218,8 @@ int jenga_pack_kv(const jenga_plan* plan, const void* k, const void* v, void* wo
  * Second half of jenga_block_sparse_attn: the block-sparse attention kernel itself, reading K and V
  * from a workspace filled by jenga_pack_kv for this plan or for one that differs in topk_ratio, cum_prob,
  * text_bias or flags only (jenga_block_sparse_attn leaves nothing in its workspace that could be read
- * here).  The packed tiles are only read; the 256 bytes behind them (launch parameters) may be written.
+ * here); it may be as small as that call takes it.  The packed tiles are only read; the 256 bytes behind
+ * them (launch parameters) may be written.
  * Other arguments as above.
  */
 int jenga_block_sparse_attn_packed(const jenga_plan* plan, const void* q, void* packed_kv_workspace,

@@ -1015,7 +1015,7 @@ int run_attention(const jenga_plan* p, const void* q, const void* k, void* ws, b
     if (may_split && p->attn_parts > 1) {
       split.parts = p->attn_parts;
       split.stride = (work.n_wg + 7) & ~7;
-      split.o = (float*)((char*)ws + 2 * half + 256);
+      split.o = (float*)((char*)ws + p->packed_bytes);
       split.stat = split.o + (size_t)bh * f.M * split.parts * BLK * D;
       attn_kernel<D, NS, true><<<dim3(split.parts * split.stride), 64 * NS, 0, st>>>(
           qb, kp, vp, sel_count, sel_index, ob, lse, work, f.N_pad, f.pad_v, f.pad_c, scale, bias, split);
@@ -1035,7 +1035,7 @@ int run_attention(const jenga_plan* p, const void* q, const void* k, void* ws, b
       split.parts = p->attn_parts;
       split.chunk = p->attn_chunk;
       split.stride = (work.n_wg + 7) & ~7;   // a multiple of the XCDs, which a query block's parts then share
-      split.o = (float*)((char*)ws + 2 * half + 256);
+      split.o = (float*)((char*)ws + p->packed_bytes);
       split.stat = split.o + (size_t)bh * f.M * split.parts * BLK * D;
       if constexpr (BLK == 128) {
         if (paced) JENGA_ATTN(true, true, false, split.parts * split.stride);

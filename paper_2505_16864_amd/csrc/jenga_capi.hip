@@ -148,7 +148,7 @@ int jenga_pack_kv(const jenga_plan* p, const void* k, const void* v, void* works
   if (!p || !k || !v || !workspace) return JENGA_EINVAL;
   if (!on_plan_device(p)) return JENGA_EINVAL;
   if (((uintptr_t)workspace & 255u) != 0) return JENGA_EINVAL;
-  if (workspace_bytes < p->info.attn_workspace_bytes) return JENGA_EWORKSPACE;
+  if (workspace_bytes < p->packed_bytes) return JENGA_EWORKSPACE;
   return jenga::launch_pack(p, k, v, workspace, true, stream);
 }
 
@@ -158,7 +158,7 @@ int jenga_block_sparse_attn_packed(const jenga_plan* p, const void* q, void* pac
   if (!p || !q || !packed_kv_workspace || !sel_count || !sel_index || !out_curve) return JENGA_EINVAL;
   if (!on_plan_device(p)) return JENGA_EINVAL;
   if (((uintptr_t)packed_kv_workspace & 255u) != 0) return JENGA_EINVAL;
-  if (workspace_bytes < p->info.attn_workspace_bytes) return JENGA_EWORKSPACE;
+  if (workspace_bytes < p->packed_bytes) return JENGA_EWORKSPACE;
   return jenga::launch_attention(p, q, nullptr, packed_kv_workspace, false, sel_count, sel_index, out_curve, lse_or_null, stream);
 }
 

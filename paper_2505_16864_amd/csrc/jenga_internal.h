@@ -13,6 +13,8 @@ struct jenga_plan {
   // attention: a list longer than attn_chunk entries is cut into up to attn_parts parts (1: lists stay whole);
   // attn_chunk = 0: every list into attn_parts ranges of key blocks
   int attn_parts, attn_chunk;
+  // bytes of the attention workspace that hold packed K, packed V and launch parameters; parts lie behind them
+  uint64_t packed_bytes;
   // host tables
   std::vector<int32_t> perm, inv_perm;
   std::vector<int32_t> src_of_pos;  // [N_pad] index into the thw-side sequence, -1 for a pad

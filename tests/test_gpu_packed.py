@@ -1,4 +1,5 @@
-"""A packed workspace depends on the grid and the shape alone: packed once, it serves plans with another walk."""
+"""A packed workspace depends on the grid and the shape alone: packed once, it serves plans with another walk, k or p,
+and holds the packed tiles and 256 bytes, nothing else."""
 import pytest
 import torch
 
@@ -41,3 +42,38 @@ def test_packed_under_one_walk_read_under_the_other(block, head_dim, heads, pack
         # The paced walk's last bits may differ between runs: one unit of the bf16 output, at most 2^-7 |o|, and the bf16
         # probabilities taken against another reference, 2^-8 max|v| (max|v| and max|o| are alike here).
         assert float((second.o_c.float() - want.float()).abs().max()) <= 2.0 ** -6 * float(want.float().abs().max())
+
+
+# Grids whose lists jenga_block_sparse_attn cuts, so that it needs more workspace than the packed tiles take.
+@pytest.mark.parametrize("block,head_dim,blocks,heads", [(128, 128, 9, 2), (64, 64, 20, 3), (32, 64, 1600, 2)])
+def test_packed_entries_need_the_packed_tiles_only(block, head_dim, blocks, heads):
+    w = dict(_workload(block, head_dim, heads), W=block * blocks - 9)
+    print("packed size", w, flush=True)
+    sparse, dense = CarveLayer(dict(w, topk=0.05), "cuda:0"), CarveLayer(dict(w, topk=1.0, p=0.9), "cuda:0")
+    tiles = 2 * (-(-heads * dense.info.N_pad * head_dim * 2 // 256) * 256) + 256
+    assert dense.info.attn_workspace_bytes > tiles
+    ws = torch.empty(tiles, dtype=torch.uint8, device="cuda:0")
+    stream = torch.cuda.current_stream().cuda_stream
+    q, k, v = [x.cuda() for x in ji.make_qkv(w, 82)]
+    for layer in (sparse, dense):
+        layer.permute_in(q, k, v)
+        layer.select()
+        layer.pack()
+        layer.attend_packed()
+    jb.jenga_pack_kv(sparse.plan, sparse.k_c, sparse.v_c, ws, tiles, stream)
+    for layer in (sparse, dense):                               # one pack, two k and two p
+        torch.cuda.synchronize()
+        want = layer.o_c.clone()
+        layer.o_c.view(torch.int16).fill_(0x7FC1)
+        jb.jenga_block_sparse_attn_packed(layer.plan, layer.q_c, ws, tiles, layer.sel_count, layer.sel_index, layer.o_c,
+                                          None, stream)
+        torch.cuda.synchronize()
+        assert torch.equal(layer.o_c, want)
+    for call in (lambda: jb.jenga_pack_kv(dense.plan, dense.k_c, dense.v_c, ws, tiles - 1, stream),
+                 lambda: jb.jenga_block_sparse_attn_packed(dense.plan, dense.q_c, ws, tiles - 1, dense.sel_count,
+                                                           dense.sel_index, dense.o_c, None, stream),
+                 lambda: jb.jenga_block_sparse_attn(dense.plan, dense.q_c, dense.k_c, dense.v_c, dense.sel_count,
+                                                    dense.sel_index, dense.o_c, None, ws, tiles, stream)):
+        with pytest.raises(jb.JengaError) as err:
+            call()
+        assert err.value.status == -3
