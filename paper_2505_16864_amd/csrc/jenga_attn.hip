@@ -1014,13 +1014,20 @@ int run_attention(const jenga_plan* p, const void* q, const void* k, void* ws, b
     Split split = {};
     if (may_split && p->attn_parts > 1) {
       split.parts = p->attn_parts;
-      split.stride = (work.n_wg + 7) & ~7;
       split.o = (float*)((char*)ws + p->packed_bytes);
-      split.stat = split.o + (size_t)bh * f.M * split.parts * BLK * D;
-      attn_kernel<D, NS, true><<<dim3(split.parts * split.stride), 64 * NS, 0, st>>>(
-          qb, kp, vp, sel_count, sel_index, ob, lse, work, f.N_pad, f.pad_v, f.pad_c, scale, bias, split);
-      merge_kernel<BLK, D><<<dim3(1, f.M, bh), 2 * D, 0, st>>>(sel_count, ob, lse, f.M, f.M_v, f.N_pad, f.pad_v, f.pad_c,
-                                                               split);
+      split.stat = split.o + (size_t)p->attn_heads * f.M * split.parts * BLK * D;
+      for (int first = 0; first < bh; first += p->attn_heads) {   // the launches share the area of the partial results
+        const int n = bh - first < p->attn_heads ? bh - first : p->attn_heads;
+        const size_t row0 = (size_t)first * f.N_pad, list0 = (size_t)first * f.M;
+        const WorkMap some = plan_work(n, f.M, f.M_v, 32 * PER_CU, (size_t)f.N_pad * D * 4, c.topk_ratio, c.cum_prob);
+        float* lse0 = lse != nullptr ? lse + row0 : nullptr;
+        split.stride = (some.n_wg + 7) & ~7;
+        attn_kernel<D, NS, true><<<dim3(split.parts * split.stride), 64 * NS, 0, st>>>(
+            qb + row0 * D, kp + row0 * (D / 8), vp + row0 * (D / 8), sel_count + list0, sel_index + list0 * f.M,
+            ob + row0 * D, lse0, some, f.N_pad, f.pad_v, f.pad_c, scale, bias, split);
+        merge_kernel<BLK, D><<<dim3(1, f.M, n), 2 * D, 0, st>>>(sel_count + list0, ob + row0 * D, lse0, f.M, f.M_v,
+                                                                f.N_pad, f.pad_v, f.pad_c, split);
+      }
     } else {
       attn_kernel<D, NS, false><<<dim3(work.n_wg), 64 * NS, 0, st>>>(qb, kp, vp, sel_count, sel_index, ob, lse, work,
                                                                      f.N_pad, f.pad_v, f.pad_c, scale, bias, split);

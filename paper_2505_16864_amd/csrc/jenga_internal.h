@@ -13,6 +13,7 @@ struct jenga_plan {
   // attention: a list longer than attn_chunk entries is cut into up to attn_parts parts (1: lists stay whole);
   // attn_chunk = 0: every list into attn_parts ranges of key blocks
   int attn_parts, attn_chunk;
+  int attn_heads;  // (batch, head) pairs per launch where lists are cut
   // bytes of the attention workspace that hold packed K, packed V and launch parameters; parts lie behind them
   uint64_t packed_bytes;
   // host tables

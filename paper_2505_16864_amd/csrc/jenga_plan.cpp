@@ -150,11 +150,24 @@ void curve_order(int T, int H, int W, bool use_curve, std::vector<int32_t>& perm
 //   11.1 MB (678 blocks, D = 128, lists of 138)          319 / 285* / 299 / 309 us
 //   6.5 MB (398 blocks, D = 128, lists of 137)           650 / 611* / 633 / 680 us
 //   5.0 MB (303 blocks, D = 128, lists of 77)            206* / 221 / 238 / 261 us
+//
+// The ranges' results take 2 to 3 times as much as K and V of a head.  So that the workspace does not grow with
+// batch * heads, a launch takes as many heads as RANGE_AREA_BYTES holds results of (one at least: 102 MB at most), and
+// the next launch the next heads in the same area, which then stays in the last-level cache.  Attention with packing,
+// all heads in one launch / area of 64 / 128* / 256 / 512 MB:
+//   2048 blocks x 24 heads, D = 128 (2.4 GB)     18.24 / 17.90 / 17.90* / 18.08 / 18.18 ms
+//   2048 x 40, D = 64 (2.1 GB)                   12.68 / 12.57 / 12.24* / 12.26 / 12.44 ms
+//   708 x 40, D = 128 (0.9 GB)                   3.87 / 3.74 / 3.62* / 3.71 / 3.83 ms
+//   408 x 24, D = 128 (0.3 GB)                   1.30 / 1.28 / 1.26* / 1.27 / 1.31 ms
+//   1503 x 16, D = 128 (1.2 GB)                  4.97 / 5.00 / 5.01* / 4.84 / 4.87 ms
+constexpr uint64_t RANGE_AREA_BYTES = 128ull << 20;
+
 static void split_lists(jenga_plan* plan) {
   const jenga_config& c = plan->cfg;
   const jenga_plan_info_t& f = plan->info;
   plan->attn_parts = 1;
   plan->attn_chunk = f.M;
+  plan->attn_heads = c.batch * c.heads;
   const long long rows = (long long)c.batch * c.heads * f.M;
   // expected list length: K_top and the blocks that are always on
   long long fixed = 0;
@@ -166,6 +179,10 @@ static void split_lists(jenga_plan* plan) {
     if (rows >= 512 && len >= 32 * parts) {
       plan->attn_parts = parts;
       plan->attn_chunk = 0;
+      const uint64_t head_bytes = (uint64_t)f.M * parts * 32 * (c.head_dim + 2) * 4;
+      const int most = (int)std::max<uint64_t>(1, std::min<uint64_t>(RANGE_AREA_BYTES / head_bytes, 65535));
+      const int launches = (plan->attn_heads + most - 1) / most;
+      plan->attn_heads = (plan->attn_heads + launches - 1) / launches;
     }
     return;
   }
@@ -246,7 +263,7 @@ int build_host_tables(jenga_plan* plan) {
   split_lists(plan);
   // and, where lists are cut, O and two statistics per row and part, float32
   if (plan->attn_parts > 1)
-    f.attn_workspace_bytes += align256(bh * f.M * plan->attn_parts * (uint64_t)m * (c.head_dim + 2) * 4);
+    f.attn_workspace_bytes += align256((uint64_t)plan->attn_heads * f.M * plan->attn_parts * m * (c.head_dim + 2) * 4);
   return JENGA_OK;
 }
 

@@ -172,6 +172,33 @@ def test_passes_over_key_ranges(head_dim, m_v):
         assert np.abs(got[alive] - want_lse[alive]).max() <= 1e-3     # float32 sums and one float32 logarithm
 
 
+# More heads than one launch has room for the results of: every head as in a plan that has it alone, bit for bit.
+@pytest.mark.parametrize("head_dim,m_v,heads", [(64, 1538, 7), (128, 600, 9)])
+def test_passes_over_key_ranges_in_several_launches(head_dim, m_v, heads):
+    w = dict(T=1, H=1, W=32 * m_v - 3, n_text=37, batch=1, heads=heads, head_dim=head_dim, block=32, topk=0.2, p=0.3,
+             text_bias=0.4)
+    print("several launches", w, flush=True)
+    q, k, v = [x.cuda() for x in ji.make_qkv(w, 64)]
+    layer, one = CarveLayer(w, "cuda:0", want_lse=True), CarveLayer(dict(w, heads=1), "cuda:0", want_lse=True)
+
+    def parts(of):
+        return of.info.attn_workspace_bytes - 256 - 4 * of.w["heads"] * of.info.N_pad * head_dim
+    assert 0 < parts(one) and parts(layer) < heads * parts(one)
+    layer.permute_in(q, k, v)
+    layer.select()
+    layer.o_c.view(torch.int16).fill_(0x7FC1)
+    layer.lse.fill_(7.0)
+    layer.attend()
+    for h in range(heads):
+        for to, of in ((one.q_c, layer.q_c), (one.k_c, layer.k_c), (one.v_c, layer.v_c), (one.sel_count, layer.sel_count),
+                       (one.sel_index, layer.sel_index)):
+            to.copy_(of[:, h:h + 1])
+        one.attend()
+        torch.cuda.synchronize()
+        assert torch.equal(one.o_c[:, 0].view(torch.int16), layer.o_c[:, h].view(torch.int16)), h
+        assert torch.equal(one.lse[:, 0], layer.lse[:, h]), h
+
+
 # K is read in place by some kernels: an output that lies over it must still see the K of before the call.
 @pytest.mark.parametrize("block,flags", [(32, 7), (64, 7), (128, 7), (128, 15)])
 @pytest.mark.parametrize("heads", [2, 90])

@@ -118,3 +118,18 @@ def test_null_arguments_return_einval_without_a_device():
     assert lib.jenga_block_sparse_attn_packed(None, None, None, 0, None, None, None, None, None) == -1
     assert lib.jenga_stage_switch(None, None, None, None, 1, 1, 1, 1, 1, 1, 1, 0.5, None) == -1
     assert lib.jenga_plan_destroy(None) == 0
+
+
+# Cut lists leave their parts' results in the attention workspace: 129 MB at most, however many heads there are.
+@pytest.mark.parametrize("block,head_dim", [(32, 64), (32, 128), (64, 64), (64, 128), (128, 64), (128, 128)])
+def test_attention_workspace_is_bounded(block, head_dim):
+    cut = 0
+    for tokens_h in (1, 3, 8, 20, 60, 120, 250):
+        for heads in (1, 2, 3, 8, 24, 40, 500, 65535):
+            for topk in (0.05, 0.3, 1.0):
+                cfg = J.make_config(1, tokens_h, 256, 77, 1, heads, head_dim, block, topk, 0.3, flags=2)
+                info = J.jenga_plan_tables(cfg)
+                tiles = 2 * (-(-heads * info.N_pad * head_dim * 2 // 256) * 256) + 256
+                assert tiles <= info.attn_workspace_bytes <= tiles + (129 << 20), (tokens_h, heads, topk)
+                cut += info.attn_workspace_bytes > tiles
+    assert cut > 0
