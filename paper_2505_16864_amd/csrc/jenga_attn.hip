@@ -35,6 +35,8 @@
 
 namespace {
 
+using jenga::WorkMap;
+
 typedef __bf16 bf16x8 __attribute__((ext_vector_type(8)));
 typedef float f32x16 __attribute__((ext_vector_type(16)));
 typedef uint32_t u32x4 __attribute__((ext_vector_type(4)));
@@ -120,60 +122,7 @@ __device__ inline void dma_1kb_to_lds_at(const void* uniform_base, uint32_t lane
 
 __device__ inline void wait_vmem() { __builtin_amdgcn_s_waitcnt(0x0F70); }   // vmcnt(0) only
 
-// Work mapping shared by the attention kernels.  The text query blocks of every (batch, head) are
-// dense rows, several times longer than a vision row: they are dealt out first, ahead of all vision
-// blocks, so that none of them starts late and runs on alone at the end.  The vision blocks follow.
-// Workgroups are dealt round-robin to the 8 XCDs; `share` of them (8, 4, 2 or 1) work on the same head
-// at a time and split its query blocks into contiguous runs of `chunk`, whose selections overlap; the
-// heads are divided evenly among the 8 / share groups.  plan_work() says how `share` is chosen.
-struct WorkMap {
-  int n_bh, M, M_v;
-  int share, chunk;   // XCDs per head, query blocks of a head per XCD
-  int log_share;
-  int units;          // n_bh * chunk: query blocks (with fillers) per member of a group, over all groups
-  int text_chunk;     // text blocks per XCD when share < 8
-  int text_wgs, n_wg; // workgroups of the text blocks, all workgroups
-};
-
-// Fewer XCDs on a head mean more of the workgroups that share an L2 read the same keys at about the same time: with
-// share = 8 and M_v = 234 an XCD's 128 resident workgroups belong to four heads, with share = 1 to one.  So the
-// largest share is taken that still gives an XCD enough query blocks of one head to fill it, but the heads that
-// are then in flight at once have to stay in the 256 MB last-level cache (720p: a head is 61 MB, and share = 1 costs
-// 8 %).  Attention time at share 8 / 4 / 2 / 1, the rule's choice marked:
-//   47 blocks x 16 heads, D = 64            138 / 137 / 132 / 111* us (each XCD also gets its own text rows)
-//   220 blocks of 64 x 12 heads, D = 128    511 / 476 / 469 / 472* us
-//   260 blocks x 24 heads, D = 128          4.40 / 4.35 / 4.33* / 4.33 ms
-//   2032 blocks of 32 x 2 heads, D = 64     0.75* / 0.88 / 0.90 / 0.88 ms
-//   929 blocks x 24 heads, D = 128          20.8* / 20.5 / 20.8 / 22.4 ms (k = 0.1)
-//
-// With few XCDs per head a head with long lists keeps its XCDs busy longer than the others.  Lists have about the same
-// length as long as K_top decides it; where the cumulative-probability rule does (p well above k) heads differ, and
-// a grid of several generations of workgroups stays at share = 8 (248 blocks x 12 heads, p = 0.9: share = 2 is up to
-// 2.3 % slower).
-WorkMap plan_work(int n_bh, int M, int M_v, int slots_per_xcd, size_t head_kv_bytes, double topk_ratio,
-                  double cum_prob) {
-  WorkMap w;
-  const bool even = cum_prob <= 2.0 * topk_ratio || (long long)n_bh * M <= 8ll * slots_per_xcd;
-  w.n_bh = n_bh;
-  w.M = M;
-  w.M_v = M_v;
-  int share = 8;
-  while (even && share > 1 && M_v / share < slots_per_xcd &&
-         (size_t)(16 / share) * head_kv_bytes <= (size_t)192 << 20)
-    share /= 2;
-  w.share = share;
-  w.log_share = share == 8 ? 3 : share == 4 ? 2 : share == 2 ? 1 : 0;
-  w.chunk = (M_v + share - 1) / share;
-  w.units = n_bh * w.chunk;
-  const int n_text = n_bh * (M - M_v);
-  w.text_chunk = (n_text + 7) / 8;
-  w.text_wgs = share == 8 ? n_text : 8 * w.text_chunk;
-  const int groups = 8 / share;
-  w.n_wg = w.text_wgs + 8 * ((w.units + groups - 1) / groups);
-  return w;
-}
-
-// Returns false for the filler workgroups at the end of a run.
+// The query block of workgroup n (see WorkMap).  Returns false for the filler workgroups at the end of a run.
 __device__ inline bool map_work(int n, const WorkMap& w, int* bh, int* i) {
   const int M_c = w.M - w.M_v;
   if (n < w.text_wgs) {
@@ -1002,38 +951,43 @@ int run_attention(const jenga_plan* p, const void* q, const void* k, void* ws, b
   const u32x4* kp = k_rows ? (const u32x4*)k : (const u32x4*)ws;
   const u32x4* vp = (const u32x4*)((const char*)ws + half);
   uint32_t* params = (uint32_t*)((char*)ws + 2 * half);
-  // workgroups resident on the 32 CUs of an XCD: by registers and LDS 2, 3 to 4 or 5 to 8 per CU
-  constexpr int PER_CU = BLK == 32 ? 2 : jenga::attn_h_per_cu(BLK, D);
-  const WorkMap work = plan_work(bh, f.M, f.M_v, 32 * PER_CU, (size_t)f.N_pad * D * 4, c.topk_ratio, c.cum_prob);
   const float log2e = 1.4426950408889634f;
   const float scale = log2e / sqrtf((float)D), bias = c.text_bias * log2e;
   const uint16_t* qb = (const uint16_t*)q;
   uint16_t* ob = (uint16_t*)out;
   if constexpr (BLK == 32) {   // in-order walk only
     constexpr int NS = D == 128 ? 4 : 8;
+    const bool ranges = may_split && p->attn_parts > 1;
     Split split = {};
-    if (may_split && p->attn_parts > 1) {
+    if (ranges) {   // the launches share the area of the partial results
       split.parts = p->attn_parts;
       split.o = (float*)((char*)ws + p->packed_bytes);
       split.stat = split.o + (size_t)p->attn_heads * f.M * split.parts * BLK * D;
-      for (int first = 0; first < bh; first += p->attn_heads) {   // the launches share the area of the partial results
-        const int n = bh - first < p->attn_heads ? bh - first : p->attn_heads;
-        const size_t row0 = (size_t)first * f.N_pad, list0 = (size_t)first * f.M;
-        const WorkMap some = plan_work(n, f.M, f.M_v, 32 * PER_CU, (size_t)f.N_pad * D * 4, c.topk_ratio, c.cum_prob);
-        float* lse0 = lse != nullptr ? lse + row0 : nullptr;
-        split.stride = (some.n_wg + 7) & ~7;
+    }
+    const int most = ranges ? p->attn_heads : jenga::heads_per_launch(p, 64 * NS);
+    for (int first = 0; first < bh; first += most) {
+      const int n = bh - first < most ? bh - first : most;
+      const size_t row0 = (size_t)first * f.N_pad, list0 = (size_t)first * f.M;
+      const WorkMap work = jenga::plan_work(p, n);
+      const uint16_t* q0 = qb + row0 * D;
+      const u32x4 *kp0 = kp + row0 * (D / 8), *vp0 = vp + row0 * (D / 8);
+      const int32_t *count0 = sel_count + list0, *index0 = sel_index + list0 * f.M;
+      uint16_t* ob0 = ob + row0 * D;
+      float* lse0 = lse != nullptr ? lse + row0 : nullptr;
+      if (ranges) {
+        split.stride = (work.n_wg + 7) & ~7;
         attn_kernel<D, NS, true><<<dim3(split.parts * split.stride), 64 * NS, 0, st>>>(
-            qb + row0 * D, kp + row0 * (D / 8), vp + row0 * (D / 8), sel_count + list0, sel_index + list0 * f.M,
-            ob + row0 * D, lse0, some, f.N_pad, f.pad_v, f.pad_c, scale, bias, split);
-        merge_kernel<BLK, D><<<dim3(1, f.M, n), 2 * D, 0, st>>>(sel_count + list0, ob + row0 * D, lse0, f.M, f.M_v,
-                                                                f.N_pad, f.pad_v, f.pad_c, split);
+            q0, kp0, vp0, count0, index0, ob0, lse0, work, f.N_pad, f.pad_v, f.pad_c, scale, bias, split);
+        merge_kernel<BLK, D><<<dim3(1, f.M, n), 2 * D, 0, st>>>(count0, ob0, lse0, f.M, f.M_v, f.N_pad, f.pad_v, f.pad_c,
+                                                                split);
+      } else {
+        attn_kernel<D, NS, false><<<dim3(work.n_wg), 64 * NS, 0, st>>>(q0, kp0, vp0, count0, index0, ob0, lse0, work,
+                                                                       f.N_pad, f.pad_v, f.pad_c, scale, bias, split);
       }
-    } else {
-      attn_kernel<D, NS, false><<<dim3(work.n_wg), 64 * NS, 0, st>>>(qb, kp, vp, sel_count, sel_index, ob, lse, work,
-                                                                     f.N_pad, f.pad_v, f.pad_c, scale, bias, split);
     }
   } else {
     const bool paced = BLK == 128 && (c.flags & JENGA_FLAG_PACED_WALK);
+    const WorkMap work = jenga::plan_work(p, bh);
     Split split = {};
 #define JENGA_ATTN(PACED, SPLIT, K_ROWS, WGS)                                                                    \
   attn_h_kernel<BLK, D, PACED, SPLIT, K_ROWS><<<dim3(WGS), 2 * BLK, 0, st>>>(                                    \

@@ -43,6 +43,27 @@ constexpr int attn_h_per_cu(int block, int head_dim) {
   return block == 64 ? (head_dim == 128 ? 5 : 8) : (head_dim == 128 ? 3 : 4);
 }
 
+// Work mapping shared by the attention kernels.  The text query blocks of every (batch, head) are
+// dense rows, several times longer than a vision row: they are dealt out first, ahead of all vision
+// blocks, so that none of them starts late and runs on alone at the end.  The vision blocks follow.
+// Workgroups are dealt round-robin to the 8 XCDs; `share` of them (8, 4, 2 or 1) work on the same head
+// at a time and split its query blocks into contiguous runs of `chunk`, whose selections overlap; the
+// heads are divided evenly among the 8 / share groups.  plan_work() says how `share` is chosen.
+struct WorkMap {
+  int n_bh, M, M_v;
+  int share, chunk;   // XCDs per head, query blocks of a head per XCD
+  int log_share;
+  int units;          // n_bh * chunk: query blocks (with fillers) per member of a group, over all groups
+  int text_chunk;     // text blocks per XCD when share < 8
+  int text_wgs, n_wg; // workgroups of the text blocks, all workgroups
+};
+
+// The mapping for `n_bh` (batch, head) pairs of the plan.
+WorkMap plan_work(const jenga_plan* p, int n_bh);
+
+// (batch, head) pairs of the plan that one launch with `threads` threads per query block can take.
+int heads_per_launch(const jenga_plan* p, int threads);
+
 // Kernel launchers (defined in the .hip files).  All return a jenga_status.
 // 1 to 3 tensors of the plan's shape
 int launch_permute(const jenga_plan* p, const void* const* src, void* const* dst, int tensors, bool forward,

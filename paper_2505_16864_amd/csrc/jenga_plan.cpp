@@ -130,6 +130,55 @@ void curve_order(int T, int H, int W, bool use_curve, std::vector<int32_t>& perm
   w.box({{0, 0, 0}}, v[0], v[1], v[2]);
 }
 
+// Fewer XCDs on a head mean more of the workgroups that share an L2 read the same keys at about the same time: with
+// share = 8 and M_v = 234 an XCD's 128 resident workgroups belong to four heads, with share = 1 to one.  So the
+// largest share is taken that still gives an XCD enough query blocks of one head to fill it, but the heads that
+// are then in flight at once have to stay in the 256 MB last-level cache (720p: a head is 61 MB, and share = 1 costs
+// 8 %).  Attention time at share 8 / 4 / 2 / 1, the rule's choice marked:
+//   47 blocks x 16 heads, D = 64            138 / 137 / 132 / 111* us (each XCD also gets its own text rows)
+//   220 blocks of 64 x 12 heads, D = 128    511 / 476 / 469 / 472* us
+//   260 blocks x 24 heads, D = 128          4.40 / 4.35 / 4.33* / 4.33 ms
+//   2032 blocks of 32 x 2 heads, D = 64     0.75* / 0.88 / 0.90 / 0.88 ms
+//   929 blocks x 24 heads, D = 128          20.8* / 20.5 / 20.8 / 22.4 ms (k = 0.1)
+//
+// With few XCDs per head a head with long lists keeps its XCDs busy longer than the others.  Lists have about the same
+// length as long as K_top decides it; where the cumulative-probability rule does (p well above k) heads differ, and
+// a grid of several generations of workgroups stays at share = 8 (248 blocks x 12 heads, p = 0.9: share = 2 is up to
+// 2.3 % slower).
+WorkMap plan_work(const jenga_plan* p, int n_bh) {
+  const jenga_config& c = p->cfg;
+  const int M = p->info.M, M_v = p->info.M_v;
+  // workgroups resident on the 32 CUs of an XCD: by registers and LDS 2, 3 to 4 or 5 to 8 per CU
+  const int slots_per_xcd = 32 * (c.block == 32 ? 2 : attn_h_per_cu(c.block, c.head_dim));
+  const size_t head_kv_bytes = (size_t)p->info.N_pad * c.head_dim * 4;
+  WorkMap w;
+  const bool even = c.cum_prob <= 2.0 * c.topk_ratio || (long long)n_bh * M <= 8ll * slots_per_xcd;
+  w.n_bh = n_bh;
+  w.M = M;
+  w.M_v = M_v;
+  int share = 8;
+  while (even && share > 1 && M_v / share < slots_per_xcd &&
+         (size_t)(16 / share) * head_kv_bytes <= (size_t)192 << 20)
+    share /= 2;
+  w.share = share;
+  w.log_share = share == 8 ? 3 : share == 4 ? 2 : share == 2 ? 1 : 0;
+  w.chunk = (M_v + share - 1) / share;
+  w.units = n_bh * w.chunk;
+  const int n_text = n_bh * (M - M_v);
+  w.text_chunk = (n_text + 7) / 8;
+  w.text_wgs = share == 8 ? n_text : 8 * w.text_chunk;
+  const int groups = 8 / share;
+  w.n_wg = w.text_wgs + 8 * ((w.units + groups - 1) / groups);
+  return w;
+}
+
+// A grid has fewer than 2^32 threads in x.
+int heads_per_launch(const jenga_plan* p, int threads) {
+  int heads = p->cfg.batch * p->cfg.heads;
+  while ((long long)plan_work(p, heads).n_wg * threads >= 1ll << 32) heads = (heads + 1) / 2;
+  return heads;
+}
+
 // Whether the attention kernel cuts the lists of this plan, and where.
 //
 // With fewer query blocks than resident workgroups the longest lists (the text rows see every block) decide the time:
