@@ -30,6 +30,27 @@ bool config_ok(const jenga_config& c, int* why) {
   return true;
 }
 
+// The largest group of output rows whose input rows fit the LDS tile.
+StageTiles stage_switch_tiles(long long channels, int T_in, int H_in, int W_in, int T_out, int H_out, int W_out, bool on_16) {
+  constexpr long long TILE_FLOATS = 12288;   // 48 KB of LDS for the staged clean-latent estimate
+  auto window_len_max = [](long long n_in, long long n_out) { return (n_in + n_out - 1) / n_out + 1; };
+  const unsigned quads_per_row = ((unsigned)W_out + 3u) / 4u;
+  const long long nt_max = window_len_max(T_in, T_out);
+  StageTiles s;
+  s.rows_per_wg = quads_per_row >= 256u ? 1u : 256u / quads_per_row;
+  if (s.rows_per_wg > (unsigned)H_out) s.rows_per_wg = (unsigned)H_out;
+  auto tile_floats = [&](unsigned rows) {
+    // input rows touched by `rows` consecutive output rows: at most floor((rows-1)*H_in/H_out) + window + 1
+    const long long nh = ((long long)(rows - 1) * H_in) / H_out + window_len_max(H_in, H_out) + 1;
+    return nt_max * (((nh < H_in ? nh : H_in) * W_in + 6) & ~3ll);
+  };
+  while (s.rows_per_wg > 1 && tile_floats(s.rows_per_wg) > TILE_FLOATS) --s.rows_per_wg;
+  s.floats = tile_floats(s.rows_per_wg);
+  // a workgroup of 256 threads for every (channel, t) plane: below 2^32 threads in x, which a grid has to stay under
+  s.tiled = on_16 && s.floats <= TILE_FLOATS && channels * T_out < 1ll << 24;
+  return s;
+}
+
 }  // namespace jenga
 
 extern "C" {

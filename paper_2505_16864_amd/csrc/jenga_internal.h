@@ -64,6 +64,15 @@ WorkMap plan_work(const jenga_plan* p, int n_bh);
 // (batch, head) pairs of the plan that one launch with `threads` threads per query block can take.
 int heads_per_launch(const jenga_plan* p, int threads);
 
+// How jenga_stage_switch does a shape: tiled (input rows staged in LDS) or directly from global memory.
+struct StageTiles {
+  bool tiled;
+  unsigned rows_per_wg;   // output rows of a workgroup
+  long long floats;       // LDS tile
+};
+// on_16: inputs 16-byte aligned
+StageTiles stage_switch_tiles(long long channels, int T_in, int H_in, int W_in, int T_out, int H_out, int W_out, bool on_16);
+
 // Kernel launchers (defined in the .hip files).  All return a jenga_status.
 // 1 to 3 tensors of the plan's shape
 int launch_permute(const jenga_plan* p, const void* const* src, void* const* dst, int tensors, bool forward,

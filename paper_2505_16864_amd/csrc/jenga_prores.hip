@@ -80,14 +80,12 @@ __device__ inline uint32_t div_small_quotient(uint32_t a, uint32_t b, float rcp_
   return q;
 }
 
-constexpr int TILE_FLOATS = 12288;   // 48 KB of LDS for the staged clean-latent estimate
-
 // grid (channels * T_out, row groups).  A workgroup produces `rows_per_wg` consecutive output rows h of
 // one (c, t) plane.  It first stages x0_hat = x_t - sigma eps_t of every input row these outputs touch
 // ([t0, t1) x [H0, H1) x W, contiguous per t) in LDS with 16-byte loads (from the 16-byte boundary below the first
 // row, so rows of any length will do), then every thread averages the windows of four consecutive w from LDS.  Needs
-// 16-byte aligned inputs and a tile of at most TILE_FLOATS; the host falls back to stage_switch_direct_kernel
-// otherwise.  The sums run in the same (t, h, w) order as there, so both kernels give the same bits.
+// 16-byte aligned inputs and a tile of at most 48 KB (jenga::stage_switch_tiles); the host falls back to
+// stage_switch_direct_kernel otherwise.  The sums run in the same (t, h, w) order as there, so both kernels give the same bits.
 //
 // 16 x 33 x 68 x 120 -> 90 x 160 (95 MB): 25.0 -> 20.5 us with the noise asked for before the tile is staged, one
 // quotient per quad instead of eight, and only the t cells that there are; 4.7 TB/s where a large copy reaches 5.1.
@@ -240,28 +238,18 @@ extern "C" int jenga_stage_switch(const float* x_t, const float* eps_t, const fl
   const bool vec = (W_out % 4 == 0) && ((((uintptr_t)eps_tilde) | ((uintptr_t)x_out)) & 15u) == 0;
   hipStream_t st = (hipStream_t)stream;
 
-  // Tiled path: largest group of output rows whose input rows fit the LDS tile.
-  auto window_len_max = [](long long n_in, long long n_out) { return (n_in + n_out - 1) / n_out + 1; };
-  const bool in_vec = ((((uintptr_t)x_t) | ((uintptr_t)eps_t)) & 15u) == 0;
-  unsigned rows_per_wg = quads_per_row >= 256u ? 1u : 256u / quads_per_row;
-  if (rows_per_wg > (unsigned)H_out) rows_per_wg = (unsigned)H_out;
-  const long long nt_max = window_len_max(T_in, T_out);
-  auto tile_floats = [&](unsigned rows) {
-    // input rows touched by `rows` consecutive output rows: at most floor((rows-1)*H_in/H_out) + window + 1
-    const long long nh = ((long long)(rows - 1) * H_in) / H_out + window_len_max(H_in, H_out) + 1;
-    return nt_max * (((nh < H_in ? nh : H_in) * W_in + 6) & ~3ll);
-  };
-  while (rows_per_wg > 1 && tile_floats(rows_per_wg) > TILE_FLOATS) --rows_per_wg;
-  if (in_vec && (unsigned long long)channels * T_out <= 0x7FFFFFFFull && tile_floats(rows_per_wg) <= TILE_FLOATS) {
+  const bool on_16 = ((((uintptr_t)x_t) | ((uintptr_t)eps_t)) & 15u) == 0;
+  const jenga::StageTiles tiles = jenga::stage_switch_tiles(channels, T_in, H_in, W_in, T_out, H_out, W_out, on_16);
+  if (tiles.tiled) {
+    const unsigned rows_per_wg = tiles.rows_per_wg;
     const dim3 grid((unsigned)(channels * T_out), ((unsigned)H_out + rows_per_wg - 1) / rows_per_wg);
     const bool up = T_in <= T_out && H_in <= H_out && W_in <= W_out;
-    const long long need = tile_floats(rows_per_wg);
     const size_t n_in = (size_t)channels * T_in * H_in * W_in;
-    const size_t lds_bytes = (size_t)need * sizeof(float);
+    const size_t lds_bytes = (size_t)tiles.floats * sizeof(float);
 #define JENGA_TILED(V, U)                                                                                          \
   stage_switch_tiled_kernel<V, U><<<grid, 256, lds_bytes, st>>>(x_t, eps_t, eps_tilde, x_out, quads_per_row,       \
                                                                 rows_per_wg, T_in, H_in, W_in, T_out, H_out, W_out, \
-                                                                (uint32_t)need, n_in, sigma_t)
+                                                                (uint32_t)tiles.floats, n_in, sigma_t)
     if (vec && up) JENGA_TILED(true, true);
     else if (vec) JENGA_TILED(true, false);
     else if (up) JENGA_TILED(false, true);

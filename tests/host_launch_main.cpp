@@ -1,12 +1,25 @@
 // Test driver for the host rules that shape launches (CPU only).  Reads configurations from stdin, one per line:
 //     T H W n_text batch heads head_dim block topk_ratio cum_prob threads
 // and prints for each: batch * heads, the pairs heads_per_launch() gives a launch with `threads` threads per query block,
-// and the workgroups of a launch of all pairs and of one of that many.
+// and the workgroups of a launch of all pairs and of one of that many.  With the argument "switch" the lines are
+//     channels T_in H_in W_in T_out H_out W_out aligned
+// and the output is what stage_switch_tiles() says: tiled, output rows per workgroup, floats of LDS.
 #include <cstdio>
+#include <cstring>
 
 #include "jenga_internal.h"
 
-int main() {
+static int stage_switch() {
+  int c, i[3], o[3], aligned;
+  while (std::scanf("%d %d %d %d %d %d %d %d", &c, i, i + 1, i + 2, o, o + 1, o + 2, &aligned) == 8) {
+    const jenga::StageTiles s = jenga::stage_switch_tiles(c, i[0], i[1], i[2], o[0], o[1], o[2], aligned != 0);
+    std::printf("%d %u %lld\n", (int)s.tiled, s.rows_per_wg, s.floats);
+  }
+  return 0;
+}
+
+int main(int argc, char** argv) {
+  if (argc > 1 && std::strcmp(argv[1], "switch") == 0) return stage_switch();
   jenga_plan p = {};
   jenga_config& c = p.cfg;
   int threads;

@@ -22,9 +22,9 @@ def driver(tmp_path_factory):
     return exe
 
 
-def _run(driver, rows):
+def _run(driver, rows, *args):
     lines = "".join(" ".join(str(x) for x in row) + "\n" for row in rows)
-    r = subprocess.run([driver], input=lines, capture_output=True, text=True, timeout=120)
+    r = subprocess.run([driver, *args], input=lines, capture_output=True, text=True, timeout=120)
     assert r.returncode == 0, r.stderr
     return [line.split() for line in r.stdout.strip().split("\n")]
 
@@ -44,3 +44,35 @@ def test_attention_launches_stay_below_the_grid_limit(driver):
         else:
             cut += 1
     assert cut > 4      # e.g. 65535 heads of 129 blocks at head dim 64
+
+
+# Planes of a stage switch: 2^24 of them are more than one grid takes with a workgroup each.
+def test_stage_switch_launches_stay_below_the_grid_limit(driver):
+    rows = [(channels, t, h, w, t, h, w, 1) for channels in (1, 16, 1 << 20, (1 << 24) - 1, 1 << 24, (1 << 31) - 1)
+            for t in (1, 33) for h, w in ((1, 1), (1, 4), (3, 7), (68, 120), (45, 79))]
+    for row, (tiled, rows_per_wg, _) in zip(rows, _run(driver, rows, "switch")):
+        assert not int(tiled) or row[0] * row[4] * 256 < 1 << 32, row
+        assert not int(tiled) or -(-row[5] // int(rows_per_wg)) <= 65535
+    assert all(int(got[0]) for row, got in zip(rows, _run(driver, rows, "switch")) if row[0] == 16 and row[2] > 3)
+
+
+def _window(o, n_in, n_out):
+    return o * n_in // n_out, -(-(o + 1) * n_in // n_out)
+
+
+# Every workgroup's input rows fit the tile that the launch asks for: up, down, same size, rows on and off the 16-byte grid.
+def test_stage_switch_tiles_hold_what_is_staged(driver):
+    sizes = [(1, 1), (1, 3), (2, 2), (3, 2), (4, 9), (9, 4), (13, 18), (20, 20), (33, 10), (68, 90), (45, 67), (120, 7)]
+    rows = [(2, ti, hi, wi, to, ho, wo, 1) for hi, ho in sizes for wi, wo in sizes + [(120, 160), (1031, 1033), (2048, 2560)]
+            for ti, to in ((1, 1), (3, 3), (5, 4), (4, 9), (9, 2))]
+    tiled = 0
+    for (_, ti, hi, wi, to, ho, wo, _), got in zip(rows, _run(driver, rows, "switch")):
+        per_wg, floats = int(got[1]), int(got[2])
+        if not int(got[0]):
+            continue
+        tiled += 1
+        assert floats * 4 <= 48 << 10
+        cells_t = max(b - a for a, b in (_window(t, ti, to) for t in range(to)))
+        cells_h = max(_window(min(h + per_wg, ho) - 1, hi, ho)[1] - _window(h, hi, ho)[0] for h in range(0, ho, per_wg))
+        assert cells_t * ((cells_h * wi + 6) // 4 * 4) <= floats, (ti, hi, wi, to, ho, wo)
+    assert tiled > 300
