@@ -1,6 +1,7 @@
 // The host-only half of the C ABI (see include/jenga.h): configuration checks, plan tables without a
 // device, table export, status strings.  No HIP in this file, so that it can be built and run under
 // the host sanitizers together with jenga_plan.cpp.
+#include <algorithm>
 #include <cmath>
 #include <cstring>
 #include <new>
@@ -46,8 +47,18 @@ StageTiles stage_switch_tiles(long long channels, int T_in, int H_in, int W_in, 
   };
   while (s.rows_per_wg > 1 && tile_floats(s.rows_per_wg) > TILE_FLOATS) --s.rows_per_wg;
   s.floats = tile_floats(s.rows_per_wg);
+  // Rows off the 16-byte grid: with the chip full a workgroup costs 1 to 1.8 ns however little it has to read and write,
+  // and small planes are done sooner directly.  Direct -> tiled, by the larger of the quads it reads and writes:
+  //   26214 x 8 x 2 x 5 -> 2 x 5 (4)       13 -> 214 us        1134 x 8 x 11 x 21 -> 11 x 21 (66)   10.7 -> 16.0 us
+  //   748 x 8 x 14 x 25 -> 14 x 25 (98)    10.8 -> 12.2 us    497 x 8 x 17 x 31 -> 17 x 31 (136)  10.4 -> 10.8 us
+  //   227 x 8 x 18 x 33 -> 25 x 46 (252)   18.2 -> 9.8 us     16 x 33 x 45 x 79 -> 67 x 117 (240)  30 -> 13.6 us
+  // From 192 on no shape tried (W 1 to 1001, up, down and equal) was slower tiled.
+  const long long out_quads = (long long)s.rows_per_wg * quads_per_row;
+  const long long rows_in = std::min<long long>(H_in, ((long long)s.rows_per_wg * H_in + H_out - 1) / H_out);
+  const long long in_quads = std::max(1, T_in / T_out) * rows_in * W_in / 4;
+  const bool worth_it = W_in % 4 == 0 || std::max(out_quads, in_quads) >= 192;
   // a workgroup of 256 threads for every (channel, t) plane: below 2^32 threads in x, which a grid has to stay under
-  s.tiled = on_16 && s.floats <= TILE_FLOATS && channels * T_out < 1ll << 24;
+  s.tiled = on_16 && worth_it && s.floats <= TILE_FLOATS && channels * T_out < 1ll << 24;
   return s;
 }
 
