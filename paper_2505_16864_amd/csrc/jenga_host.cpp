@@ -43,7 +43,9 @@ StageTiles stage_switch_tiles(long long channels, int T_in, int H_in, int W_in, 
   auto tile_floats = [&](unsigned rows) {
     // input rows touched by `rows` consecutive output rows: at most floor((rows-1)*H_in/H_out) + window + 1
     const long long nh = ((long long)(rows - 1) * H_in) / H_out + window_len_max(H_in, H_out) + 1;
-    return nt_max * (((nh < H_in ? nh : H_in) * W_in + 6) & ~3ll);
+    const long long plane = (nh < H_in ? nh : H_in) * W_in;
+    // rows off the 16-byte grid are read from the boundary below them
+    return nt_max * (W_in % 4 == 0 ? plane : (plane + 6) & ~3ll);
   };
   while (s.rows_per_wg > 1 && tile_floats(s.rows_per_wg) > TILE_FLOATS) --s.rows_per_wg;
   s.floats = tile_floats(s.rows_per_wg);

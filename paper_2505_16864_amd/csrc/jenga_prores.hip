@@ -108,7 +108,7 @@ __global__ __launch_bounds__(256) void stage_switch_tiled_kernel(const float* __
   area_window(t, T, To, &t0, &t1);
   area_window(hb, H, Ho, &H0, &tmp);
   area_window(he - 1, H, Ho, &tmp, &H1);
-  const uint32_t plane = (H1 - H0) * W, pitch = (plane + 6u) & ~3u;   // floats per t, and their place in LDS
+  const uint32_t plane = (H1 - H0) * W, pitch = W % 4u == 0u ? plane : (plane + 6u) & ~3u;   // floats per t, their place in LDS
   if ((t1 - t0) * pitch > tile_floats) return;   // cannot happen: the host sizes the tile for it
 
   // this thread's first quad; its noise is on the way while the tile is staged

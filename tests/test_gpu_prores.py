@@ -88,3 +88,11 @@ def test_rows_off_the_16_byte_grid(shape_in, shape_out):
                           torch.cuda.current_stream().cuda_stream)
     torch.cuda.synchronize()
     assert np.array_equal(out.cpu().numpy().astype(np.float64), got)
+
+
+# Tiles of exactly 48 KB: rows of 2048 cells, groups of 16 rows of 256.
+@pytest.mark.parametrize("shape_in,shape_out", [((3, 5, 2048), (3, 6, 2560)), ((2, 4, 2048), (2, 4, 2048)), ((2, 96, 256), (2, 72, 64))])
+def test_tiles_of_the_largest_size(shape_in, shape_out):
+    got, want = run({"channels": 2, "in": shape_in, "out": shape_out, "sigma": 0.35}, 7060)
+    assert np.isfinite(got).all()
+    assert np.abs(got - want).max() <= ATOL

@@ -84,5 +84,14 @@ def test_stage_switch_tiles_hold_what_is_staged(driver):
         assert floats * 4 <= 48 << 10
         cells_t = max(b - a for a, b in (_window(t, ti, to) for t in range(to)))
         cells_h = max(_window(min(h + per_wg, ho) - 1, hi, ho)[1] - _window(h, hi, ho)[0] for h in range(0, ho, per_wg))
-        assert cells_t * ((cells_h * wi + 6) // 4 * 4) <= floats, (ti, hi, wi, to, ho, wo)
+        pitch = cells_h * wi if wi % 4 == 0 else (cells_h * wi + 6) // 4 * 4
+        assert cells_t * pitch <= floats, (ti, hi, wi, to, ho, wo)
     assert tiled > 300
+
+
+# Rows on the 16-byte grid need no room for a boundary below them: tiles of exactly 48 KB are staged.
+@pytest.mark.parametrize("shape_in,shape_out,rows", [((33, 8, 2048), (33, 8, 2048), 1), ((33, 12, 2048), (33, 15, 2560), 1),
+                                                     ((5, 96, 256), (5, 72, 64), 16)])
+def test_stage_switch_tiles_up_to_the_limit(driver, shape_in, shape_out, rows):
+    tiled, per_wg, floats = [int(x) for x in _run(driver, [(16, *shape_in, *shape_out, 1)], "switch")[0]]
+    assert tiled and floats <= 12288 and per_wg == rows
