@@ -50,15 +50,18 @@ StageTiles stage_switch_tiles(long long channels, int T_in, int H_in, int W_in, 
   while (s.rows_per_wg > 1 && tile_floats(s.rows_per_wg) > TILE_FLOATS) --s.rows_per_wg;
   s.floats = tile_floats(s.rows_per_wg);
   // Rows off the 16-byte grid: with the chip full a workgroup costs 1 to 1.8 ns however little it has to read and write,
-  // and small planes are done sooner directly.  Direct -> tiled, by the larger of the quads it reads and writes:
-  //   26214 x 8 x 2 x 5 -> 2 x 5 (4)       13 -> 214 us        1134 x 8 x 11 x 21 -> 11 x 21 (66)   10.7 -> 16.0 us
-  //   748 x 8 x 14 x 25 -> 14 x 25 (98)    10.8 -> 12.2 us    497 x 8 x 17 x 31 -> 17 x 31 (136)  10.4 -> 10.8 us
-  //   227 x 8 x 18 x 33 -> 25 x 46 (252)   18.2 -> 9.8 us     16 x 33 x 45 x 79 -> 67 x 117 (240)  30 -> 13.6 us
-  // From 192 on no shape tried (W 1 to 1001, up, down and equal) was slower tiled.
-  const long long out_quads = (long long)s.rows_per_wg * quads_per_row;
+  // and small planes are done sooner directly, above all where every window is a single cell.  Direct -> tiled, by the
+  // larger of a quarter of the cells it reads and of those it writes:
+  //   windows of one cell: 26214 x 8 x 2 x 5 -> 2 x 5 (2)     13 -> 214 us      1134 x 8 x 11 x 21 -> 11 x 21 (57)  10.7 -> 16.0 us
+  //                        748 x 8 x 14 x 25 -> 14 x 25 (87)  10.8 -> 12.2 us   497 x 8 x 17 x 31 -> 17 x 31 (131)  10.4 -> 10.8 us
+  //   others:              2880 x 8 x 7 x 13 -> 10 x 18 (45)  24.4 -> 27.6 us   8 x 33 x 3 -> 66 x 5 (82)            7 % slower
+  //                        1134 x 8 x 11 x 21 -> 15 x 29 (109)  26 -> 16 us     227 x 8 x 18 x 33 -> 25 x 46 (252)  18.2 -> 9.8 us
+  //                        16 x 33 x 45 x 79 -> 67 x 117 (614)  30 -> 13.6 us
+  // No shape tried (W 1 to 1001, up, down and equal) was slower tiled from 192 and 96 on.
   const long long rows_in = std::min<long long>(H_in, ((long long)s.rows_per_wg * H_in + H_out - 1) / H_out);
-  const long long in_quads = std::max(1, T_in / T_out) * rows_in * W_in / 4;
-  const bool worth_it = W_in % 4 == 0 || std::max(out_quads, in_quads) >= 192;
+  const long long read = std::max(1, T_in / T_out) * rows_in * W_in / 4, written = (long long)s.rows_per_wg * W_out / 4;
+  const bool one_cell = T_out % T_in == 0 && H_out % H_in == 0 && W_out % W_in == 0;
+  const bool worth_it = W_in % 4 == 0 || std::max(read, written) >= (one_cell ? 192 : 96);
   // a workgroup of 256 threads for every (channel, t) plane: below 2^32 threads in x, which a grid has to stay under
   s.tiled = on_16 && worth_it && s.floats <= TILE_FLOATS && channels * T_out < 1ll << 24;
   return s;

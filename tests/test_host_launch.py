@@ -59,7 +59,8 @@ def test_stage_switch_launches_stay_below_the_grid_limit(driver):
 # Small planes off the 16-byte grid are not worth a workgroup each; rows on it are staged as long as they fit.
 @pytest.mark.parametrize("shape_in,shape_out,tiled", [
     ((8, 1, 1), (8, 1, 1), 0), ((8, 2, 5), (8, 3, 7), 0), ((61, 3, 3), (60, 5, 5), 0), ((8, 11, 21), (8, 11, 21), 0),
-    ((8, 7, 13), (8, 14, 26), 0), ((33, 45, 79), (33, 67, 117), 1), ((33, 91, 161), (11, 30, 53), 1), ((8, 25, 45), (8, 35, 63), 1),
+    ((8, 7, 13), (8, 14, 26), 0), ((8, 7, 13), (8, 10, 18), 0), ((8, 11, 21), (8, 15, 29), 1), ((8, 17, 31), (8, 17, 31), 0),
+    ((33, 45, 79), (33, 67, 117), 1), ((33, 91, 161), (11, 30, 53), 1), ((8, 25, 45), (8, 35, 63), 1),
     ((8, 2, 4), (8, 3, 6), 1), ((33, 68, 120), (33, 90, 160), 1), ((8, 9, 16), (8, 2, 4), 1)])
 def test_stage_switch_small_planes_are_not_staged(driver, shape_in, shape_out, tiled):
     for channels in (1, 16, 4096):
