@@ -35,6 +35,7 @@
 
 namespace {
 
+using jenga::map_work;
 using jenga::WorkMap;
 
 typedef __bf16 bf16x8 __attribute__((ext_vector_type(8)));
@@ -121,27 +122,6 @@ __device__ inline void dma_1kb_to_lds_at(const void* uniform_base, uint32_t lane
 }
 
 __device__ inline void wait_vmem() { __builtin_amdgcn_s_waitcnt(0x0F70); }   // vmcnt(0) only
-
-// The query block of workgroup n (see WorkMap).  Returns false for the filler workgroups at the end of a run.
-__device__ inline bool map_work(int n, const WorkMap& w, int* bh, int* i) {
-  const int M_c = w.M - w.M_v;
-  if (n < w.text_wgs) {
-    const int t = w.share == 8 ? n : (n & 7) * w.text_chunk + (n >> 3);
-    if (t >= w.n_bh * M_c) return false;
-    *bh = t / M_c;
-    *i = w.M_v + t % M_c;
-    return true;
-  }
-  n -= w.text_wgs;
-  const int xcd = n & 7, group = xcd >> w.log_share, member = xcd & (w.share - 1), log_groups = 3 - w.log_share;
-  const int first = (int)(((long long)w.units * group) >> log_groups);
-  const int end = (int)(((long long)w.units * (group + 1)) >> log_groups);
-  const int u = first + (n >> 3);
-  if (u >= end) return false;
-  *bh = u / w.chunk;
-  *i = member * w.chunk + u % w.chunk;
-  return *i < w.M_v;
-}
 
 // compile-time loop: f(integral_constant<int, 0>) ... f(integral_constant<int, N-1>)
 template <typename F, int... Is>

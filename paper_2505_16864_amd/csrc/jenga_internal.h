@@ -5,6 +5,12 @@
 #include <vector>
 #include "jenga.h"
 
+#ifdef __HIPCC__
+#define JENGA_HOST_DEVICE __host__ __device__
+#else   // the host-only sources and their tests
+#define JENGA_HOST_DEVICE
+#endif
+
 struct jenga_plan {
   jenga_config cfg;
   jenga_plan_info_t info;
@@ -54,9 +60,33 @@ struct WorkMap {
   int share, chunk;   // XCDs per head, query blocks of a head per XCD
   int log_share;
   int units;          // n_bh * chunk: query blocks (with fillers) per member of a group, over all groups
-  int text_chunk;     // text blocks per XCD when share < 8
   int text_wgs, n_wg; // workgroups of the text blocks, all workgroups
 };
+
+// The query block of workgroup n (see WorkMap).  Returns false for the filler workgroups at the end of a run.
+JENGA_HOST_DEVICE inline bool map_work(int n, const WorkMap& w, int* bh, int* i) {
+  const int M_c = w.M - w.M_v;
+  if (n < w.text_wgs) {
+    int t = n;
+    if (w.share < 8) {   // XCD x: eighth x of the text blocks, as of the units below, so that both are of the same heads
+      const int n_text = w.n_bh * M_c, x = n & 7;
+      t = (n_text * x >> 3) + (n >> 3);
+      if (t >= n_text * (x + 1) >> 3) return false;
+    }
+    *bh = t / M_c;
+    *i = w.M_v + t % M_c;
+    return true;
+  }
+  n -= w.text_wgs;
+  const int xcd = n & 7, group = xcd >> w.log_share, member = xcd & (w.share - 1), log_groups = 3 - w.log_share;
+  const int first = (int)(((long long)w.units * group) >> log_groups);
+  const int end = (int)(((long long)w.units * (group + 1)) >> log_groups);
+  const int u = first + (n >> 3);
+  if (u >= end) return false;
+  *bh = u / w.chunk;
+  *i = member * w.chunk + u % w.chunk;
+  return *i < w.M_v;
+}
 
 // The mapping for `n_bh` (batch, head) pairs of the plan.
 WorkMap plan_work(const jenga_plan* p, int n_bh);

@@ -165,8 +165,7 @@ WorkMap plan_work(const jenga_plan* p, int n_bh) {
   w.chunk = (M_v + share - 1) / share;
   w.units = n_bh * w.chunk;
   const int n_text = n_bh * (M - M_v);
-  w.text_chunk = (n_text + 7) / 8;
-  w.text_wgs = share == 8 ? n_text : 8 * w.text_chunk;
+  w.text_wgs = share == 8 ? n_text : 8 * ((n_text + 7) / 8);
   const int groups = 8 / share;
   w.n_wg = w.text_wgs + 8 * ((w.units + groups - 1) / groups);
   return w;

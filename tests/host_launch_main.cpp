@@ -3,9 +3,15 @@
 // and prints for each: batch * heads, the pairs heads_per_launch() gives a launch with `threads` threads per query block,
 // and the workgroups of a launch of all pairs and of one of that many.  With the argument "switch" the lines are
 //     channels T_in H_in W_in T_out H_out W_out aligned
-// and the output is what stage_switch_tiles() says: tiled, output rows per workgroup, floats of LDS.
+// and the output is what stage_switch_tiles() says: tiled, output rows per workgroup, floats of LDS.  With the argument
+// "work" the lines are configurations without the last column, and the output is how often the query block that is dealt
+// out least and most often is, the share, and how many text blocks are on an XCD without a vision block of their head.
+#include <algorithm>
 #include <cstdio>
 #include <cstring>
+#include <set>
+#include <utility>
+#include <vector>
 
 #include "jenga_internal.h"
 
@@ -18,7 +24,30 @@ static int stage_switch() {
   return 0;
 }
 
+static int work() {
+  jenga_plan p = {};
+  jenga_config& c = p.cfg;
+  while (std::scanf("%d %d %d %d %d %d %d %d %lf %lf", &c.T, &c.H, &c.W, &c.n_text, &c.batch, &c.heads, &c.head_dim,
+                    &c.block, &c.topk_ratio, &c.cum_prob) == 10) {
+    if (jenga::build_host_tables(&p) != JENGA_OK) return 1;
+    const jenga::WorkMap w = jenga::plan_work(&p, c.batch * c.heads);
+    std::vector<int> times((size_t)w.n_bh * w.M, 0);
+    std::set<std::pair<int, int>> vision;
+    int bh, i, apart = 0;
+    for (int n = w.n_wg - 1; n >= 0; --n) {   // vision blocks first
+      if (!jenga::map_work(n, w, &bh, &i)) continue;
+      ++times[(size_t)bh * w.M + i];
+      if (i < w.M_v) vision.insert({n & 7, bh});
+      else if (!vision.count({n & 7, bh})) ++apart;
+    }
+    std::printf("%d %d %d %d\n", *std::min_element(times.begin(), times.end()),
+                *std::max_element(times.begin(), times.end()), w.share, apart);
+  }
+  return 0;
+}
+
 int main(int argc, char** argv) {
+  if (argc > 1 && std::strcmp(argv[1], "work") == 0) return work();
   if (argc > 1 && std::strcmp(argv[1], "switch") == 0) return stage_switch();
   jenga_plan p = {};
   jenga_config& c = p.cfg;

@@ -46,6 +46,22 @@ def test_attention_launches_stay_below_the_grid_limit(driver):
     assert cut > 4      # e.g. 65535 heads of 129 blocks at head dim 64
 
 
+# Every query block is dealt out once, and text blocks to XCDs that work on their head: alone on another XCD a row that
+# sees every block finds no key in its L2.
+def test_work_mapping(driver):
+    rows = [(1, 1, block * m_v - 3, n_text, 1, heads, d, block, 0.3, p)
+            for block in (32, 64, 128) for d in (64, 128) for m_v in (1, 7, 8, 31, 64, 129, 300) for n_text in (0, 3, 300)
+            for heads in (1, 2, 3, 8, 13, 24, 80) for p in (0.3, 0.9)]
+    shares = set()
+    for row, got in zip(rows, _run(driver, rows, "work")):
+        least, most, share, apart = [int(x) for x in got]
+        assert (least, most) == (1, 1), row
+        shares.add(share)
+        if row[2] > 8 * row[7]:           # a vision block for every XCD of a head
+            assert apart == 0, (row, share)
+    assert shares == {1, 2, 4, 8}
+
+
 # Planes of a stage switch: 2^24 of them are more than one grid takes with a workgroup each.
 def test_stage_switch_launches_stay_below_the_grid_limit(driver):
     rows = [(channels, t, h, w, t, h, w, 1) for channels in (1, 16, 1 << 20, (1 << 24) - 1, 1 << 24, (1 << 31) - 1)
