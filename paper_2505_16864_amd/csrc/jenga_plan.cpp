@@ -189,7 +189,11 @@ int heads_per_launch(const jenga_plan* p, int threads) {
 //   D = 128, blocks of 128:  18 query blocks 31 -> 23 us, 136 52 -> 44, 368 137 -> 116, 552 171 -> 158; 736 183 -> 191
 //   D = 64, blocks of 128:   192 96 -> 54, 384 101 -> 82; 768 131 -> 139
 //   D = 128, blocks of 64:   168 35 -> 32, 608 120 -> 97; 1824 202 -> 210
-// Lists of about a dozen steps lose what they gain (408 query blocks of 11.6 entries: 75 us whole, 80 us in parts of 8).
+// Lists of about a dozen steps lose what they gain (408 query blocks of 11.6 entries: 75 us whole, 80 us in parts of 8),
+// and so do lists that are cut into halves of that length: from 3/8 of the places on nothing is cut where the longest
+// list, all blocks, is up to one and a half parts.  Attention with packing, cut -> whole, p = 0.9: 408 query blocks, 17 a head
+// 15 % less at D = 64, 12 % at D = 128; 560, 14 a head, D = 64 60.7 -> 55.4 us; 720 of 64 tokens, 30 a head, D = 128 14 % less.
+// With fewer query blocks cutting is still the better one (264 of 64 tokens, 33 a head, D = 128: 25 % less).
 //
 // Blocks of 32 tokens share their list among the wavefronts of a workgroup already; they are read 32 rows at a time, and
 // what bounds them is K and V of a head that is larger than an XCD's 4 MB L2.  There the parts are ranges of key blocks,
@@ -238,6 +242,7 @@ static void split_lists(jenga_plan* plan) {
   if (4 * rows >= 3 * places) return;
   const long long shortest = (rows <= 256 ? 6 : 24) * 64 / c.block;
   const long long chunk = std::max(shortest, (5 * rows * len + 3 * places - 1) / (3 * places));
+  if (8 * rows >= 3 * places && 2 * f.M <= 3 * chunk) return;
   plan->attn_parts = (int)std::min(std::min(8ll, 2 * places / rows), (f.M + chunk - 1) / chunk);
   plan->attn_chunk = (int)chunk;
 }

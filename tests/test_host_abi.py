@@ -133,3 +133,12 @@ def test_attention_workspace_is_bounded(block, head_dim):
                 assert tiles <= info.attn_workspace_bytes <= tiles + (129 << 20), (tokens_h, heads, topk)
                 cut += info.attn_workspace_bytes > tiles
     assert cut > 0
+
+
+# Where the chip has three workgroups for eight places or more, lists that would only make two short parts stay whole.
+@pytest.mark.parametrize("m_v,heads,block,head_dim,cut", [(14, 40, 128, 64, False), (17, 24, 128, 128, False), (33, 24, 64, 128, False),
+                                                          (49, 8, 128, 128, True), (17, 8, 128, 128, True), (33, 8, 64, 128, True)])
+def test_short_lists_stay_whole(m_v, heads, block, head_dim, cut):
+    info = J.jenga_plan_tables(J.make_config(1, 1, block * m_v, 0, 1, heads, head_dim, block, 0.3, 0.9))
+    tiles = 2 * (-(-heads * info.N_pad * head_dim * 2 // 256) * 256) + 256
+    assert (info.attn_workspace_bytes > tiles) == cut
