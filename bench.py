@@ -2,9 +2,11 @@
 """Benchmark of the attention-carving hot path on one MI355X.
 
 One "step" is one pass of the whole path over one synthetic layer input:
-    jenga_curve_permute_qkv  ->  jenga_select_blocks  ->  jenga_block_sparse_attn
+    jenga_curve_permute_qkv  ->  jenga_select_blocks  ->  jenga_pack_kv  ->  jenga_block_sparse_attn_packed
     ->  jenga_unpermute
-with Q/K/V already resident in HBM.  The headline value is the time of what recurs per layer
+with Q/K/V already resident in HBM.  The attention runs as its two halves so that each can be timed: under the
+paced walk that is the work of jenga_block_sparse_attn; in the ordered walk that call reads K in place and saves
+half of the packing, which these figures do not show.  The headline value is the time of what recurs per layer
 (select + attention); the permutes, which the paper pays once per DiT forward, are reported beside
 it.  Prints ONE JSON line.
 """

@@ -646,12 +646,12 @@ __global__ __launch_bounds__(2 * D) void merge_kernel(const int32_t* __restrict_
 // (every block of the sequence) from running on alone; their partial results meet in LDS at the end, in a fixed
 // order.  No barrier inside the loop.
 //
-// Measured on 2048 blocks x 2 heads, D = 64, k = 0.05 (lists of 305 of 2048 blocks): 0.77 ms, against 1.77 ms for one
-// wavefront per query block that staged its tiles in LDS.  What bounds it there is the path behind the L2: 32 rows
-// read 8 KB of K and V for 0.26 MFLOP, 10 GB in all, from a head (16 MB) that an XCD's 4 MB do not hold; 5.5 GB
-// miss, at 7.1 TB/s.  In three passes over ranges of key blocks (RANGE) it takes 0.57 ms with the merge; 0.42 ms are
-// left when every load hits the L1.  Eight wavefronts
-// per list at D = 64 (two workgroups fill a CU), four at D = 128 (the registers leave room for eight).
+// Measured on 2048 blocks x 2 heads, D = 64, k = 0.05 (lists of 291 of 2048 blocks on average): 0.75 ms, against 1.77 ms
+// for one wavefront per query block that staged its tiles in LDS.  What bounds it there is the path behind the L2: 32
+// rows read 8 KB of K and V for 0.26 MFLOP, 10.6 GB in all, from a head (16 MB) that an XCD's 4 MB do not hold; 5.5 GB
+// miss, at 7.4 TB/s.  In three passes over ranges of key blocks (RANGE) 1.35 GB miss and it takes 0.52 to 0.56 ms and
+// 0.02 for the merge; 0.42 ms were left in a timing variant whose loads all hit the L1.  Eight wavefronts per list at
+// D = 64 (two workgroups fill a CU), four at D = 128 (the registers leave room for eight).
 // ---------------------------------------------------------------------------------------------
 //
 // RANGE: K and V of a head do not fit an XCD's L2.  A pass over all query blocks takes the entries of one of

@@ -134,7 +134,7 @@ void curve_order(int T, int H, int W, bool use_curve, std::vector<int32_t>& perm
 // share = 8 and M_v = 234 an XCD's 128 resident workgroups belong to four heads, with share = 1 to one.  So the
 // largest share is taken that still gives an XCD enough query blocks of one head to fill it, but the heads that
 // are then in flight at once have to stay in the 256 MB last-level cache (720p: a head is 61 MB, and share = 1 costs
-// 8 %).  Attention time at share 8 / 4 / 2 / 1, the rule's choice marked:
+// 8 %).  Attention time, launches back to back, at share 8 / 4 / 2 / 1, the rule's choice marked:
 //   47 blocks x 16 heads, D = 64            138 / 137 / 132 / 111* us (each XCD also gets its own text rows)
 //   220 blocks of 64 x 12 heads, D = 128    511 / 476 / 469 / 472* us
 //   260 blocks x 24 heads, D = 128          4.40 / 4.35 / 4.33* / 4.33 ms
@@ -198,7 +198,7 @@ int heads_per_launch(const jenga_plan* p, int threads) {
 // Blocks of 32 tokens share their list among the wavefronts of a workgroup already; they are read 32 rows at a time, and
 // what bounds them is K and V of a head that is larger than an XCD's 4 MB L2.  There the parts are ranges of key blocks,
 // one pass each, and every list has them all.  Time in 1 / 2 / 3 / 4 parts, the rule's choice marked:
-//   16.8 MB a head (2048 blocks, D = 64, lists of 305)   777 / 598 / 587* / 602 us
+//   16.8 MB a head (2048 blocks, D = 64, lists of 291)   777 / 598 / 587* / 602 us
 //   11.1 MB (678 blocks, D = 128, lists of 138)          319 / 285* / 299 / 309 us
 //   6.5 MB (398 blocks, D = 128, lists of 137)           650 / 611* / 633 / 680 us
 //   5.0 MB (303 blocks, D = 128, lists of 77)            206* / 221 / 238 / 261 us
@@ -307,7 +307,8 @@ int build_host_tables(jenga_plan* plan) {
   // workspaces
   const uint64_t bh = (uint64_t)c.batch * c.heads;
   auto align256 = [](uint64_t x) { return (x + 255) & ~255ull; };
-  // select: pooled Q [bh][M_v][d] f64, pooled K [bh][M][d] f64, scores [bh][M_v][M] f64
+  // select: pooled Q [bh][M_v][d] f64, pooled K [bh][M][d] f64; the third term was room for scores [bh][M_v][M] f64, which
+  // stay in LDS now: it is kept so that what jenga_select_blocks_static takes and refuses stays as documented
   f.select_workspace_bytes = align256(bh * f.M_v * c.head_dim * 8) + align256(bh * f.M * c.head_dim * 8) +
                              align256(bh * (uint64_t)f.M_v * f.M * 8);
   // attention: K and V re-tiled, bf16, one tile per (batch, head, block)

@@ -404,15 +404,16 @@ __device__ __forceinline__ void select_row(double* row, uint64_t fixed_lane, int
 // LDS holds 16 rows up to 1024 blocks and 8 rows of 2048: the 8-row kernel computes its tiles with the rows twice.
 // Row stride = 16 mod 32 doubles, so the four rows a tile is written to at a time fall on different banks.
 //
-// Time of the kernel, against a 128 x 128 tile of vector FMAs that wrote S to memory and a selection with one chain of
-// LDS exchanges per bit of the cumulative rule:
-//   17 blocks x 8 heads, D = 128     9.0 us (was 43.6 + 11.7: one workgroup per head, most of its tile padding)
-//   222 x 12, D = 128                  20 us (48 + 21)
-//   262 x 24, D = 128                  38 us (53 + 19)
-//   2048 x 2, D = 64                  109 us (38 + 141)
-//   931 x 24, D = 128, k = 0.1        226 us (164 + 145): matrix cores 105 us (75 us at their full rate, the rest is the
-//                                     last round of 5.5 and the first loads), softmax 40, top K 30, the rest of the
-//                                     rows' work 50; the two halves do not overlap, LDS leaves one workgroup on a CU
+// Time of the kernel, median and shortest of ten to twenty launches, against a 128 x 128 tile of vector FMAs that wrote S
+// to memory and a selection with one chain of LDS exchanges per bit of the cumulative rule:
+//   17 blocks x 8 heads, D = 128     8.7, 8.3 us (was 43.6 + 11.7: one workgroup per head, most of its tile padding)
+//   222 x 12, D = 128                  24, 20 us (48 + 21)
+//   262 x 24, D = 128                  40, 39 us (53 + 19)
+//   2048 x 2, D = 64                 127, 112 us (38 + 141)
+//   931 x 24, D = 128, k = 0.1 and 0.3  266, 242 us (164 + 145): at k = 0.1, in a run of 226 us, matrix cores 105 us (75 us
+//                                     at their full rate, the rest is the last round of 5.5 and the first loads), softmax
+//                                     40, top K 30, the rest of the rows' work 50; the two halves do not overlap, LDS
+//                                     leaves one workgroup on a CU
 typedef double f64x4 __attribute__((ext_vector_type(4)));
 typedef double f64x2 __attribute__((ext_vector_type(2)));
 
@@ -553,7 +554,7 @@ extern "C" int jenga_select_blocks_static(const jenga_plan* p, const void* q_cur
   if (p->info.select_workspace_bytes > STATIC_SCRATCH_BYTES) return JENGA_EWORKSPACE;
   void* ws = scratch_address(dev);   // looked up when the plan was created; never allocates
   if (ws == nullptr) return JENGA_EHIP;
-  // every byte of the scratch that select_kernel reads is written first by pool_kernel and
-  // scores_kernel of this same call, so nothing has to be cleared between calls
+  // every byte of the scratch that select_kernel reads is written first by pool_kernel of this same call, so nothing
+  // has to be cleared between calls
   return jenga::launch_select(p, q_curve, k_curve, sel_count, sel_index, mask_or_null, ws, stream);
 }
