@@ -194,7 +194,7 @@ int jenga_select_blocks_static(const jenga_plan* plan, const void* q_curve, cons
  *                and rows of an empty list get -inf.  Fully overwritten when given
  *   workspace  : at least attn_workspace_bytes, 256-byte aligned (V and where needed K re-tiled for the
  *                matrix cores, 256 bytes of launch parameters, and on grids that leave the chip idle
- *                the results of the parts that long lists are cut into, 129 MB of them at most), contents undefined after
+ *                the results of the parts that long lists are cut into, 129 MiB of them at most), contents undefined after
  * Equivalent to jenga_pack_kv followed by jenga_block_sparse_attn_packed on the same workspace (the latter
  * never cuts lists, since calls on one packed workspace may overlap: where this call does, the two differ
  * in the last bits).

@@ -204,9 +204,9 @@ int heads_per_launch(const jenga_plan* p, int threads) {
 //   5.0 MB (303 blocks, D = 128, lists of 77)            206* / 221 / 238 / 261 us
 //
 // The ranges' results take 2 to 3 times as much as K and V of a head.  So that the workspace does not grow with
-// batch * heads, a launch takes as many heads as RANGE_AREA_BYTES holds results of (one at least: 102 MB at most), and
+// batch * heads, a launch takes as many heads as RANGE_AREA_BYTES holds results of (one at least, which is 98 MiB at most), and
 // the next launch the next heads in the same area, which then stays in the last-level cache.  Attention with packing,
-// all heads in one launch / area of 64 / 128* / 256 / 512 MB:
+// all heads in one launch / area of 64 / 128* / 256 / 512 MiB:
 //   2048 blocks x 24 heads, D = 128 (2.4 GB)     18.24 / 17.90 / 17.90* / 18.08 / 18.18 ms
 //   2048 x 40, D = 64 (2.1 GB)                   12.68 / 12.57 / 12.24* / 12.26 / 12.44 ms
 //   708 x 40, D = 128 (0.9 GB)                   3.87 / 3.74 / 3.62* / 3.71 / 3.83 ms

@@ -120,7 +120,7 @@ def test_null_arguments_return_einval_without_a_device():
     assert lib.jenga_plan_destroy(None) == 0
 
 
-# Cut lists leave their parts' results in the attention workspace: 129 MB at most, however many heads there are.
+# Cut lists leave their parts' results in the attention workspace: 129 MiB at most, however many heads there are.
 @pytest.mark.parametrize("block,head_dim", [(32, 64), (32, 128), (64, 64), (64, 128), (128, 64), (128, 128)])
 def test_attention_workspace_is_bounded(block, head_dim):
     cut = 0
