@@ -51,19 +51,25 @@ __device__ inline uint32_t pack_bf16x2(float lo, float hi) {
   return __builtin_bit_cast(uint32_t, __builtin_convertvector(v, bf16x2));
 }
 
+// Counters of a queue (see take_item), one per XCD and cache line.
+constexpr int QUEUE_STRIDE = 32, QUEUE_BYTES = 8 * QUEUE_STRIDE * 4;
+
 // grid (M, batch*heads, 2).  z = 0: K tile -> fragment order; z = 1: V tile -> transposed fragment order, pad rows zeroed.
-// grid (M, batch*heads, 1) with first = 1: V only.
+// grid (M, batch*heads, 1) with first = 1: V only.  The first workgroup sets the counters of the launch that follows.
 // A workgroup each, so that the two chains of loads and stores run side by side: 931 blocks x 24 heads (2.9 GB) 531 ->
 // 511 us = 5.7 TB/s, 262 x 24 156 -> 145 us; HBM-bound from there on.
 template <int BLK, int D>
 __global__ __launch_bounds__(256) void pack_kernel(const uint16_t* __restrict__ k, const uint16_t* __restrict__ v,
                                                    uint4* __restrict__ kp, uint4* __restrict__ vp,
-                                                   const int32_t* __restrict__ blk_valid, int M, int n_pad, int first) {
+                                                   const int32_t* __restrict__ blk_valid, int M, int n_pad, int first,
+                                                   uint32_t* __restrict__ queue, int queue_first) {
   constexpr int KS = D / 16, PS = BLK / 16, CH = D / 8;
   constexpr int TILE_CHUNKS = BLK * D / 8;
   constexpr int LDV = D + 8;   // padded row length (elements) of the staged V tile
   __shared__ uint16_t vl[BLK * LDV];
   const int j = blockIdx.x, bh = blockIdx.y;
+  if (queue != nullptr && j == 0 && bh == 0 && blockIdx.z == 0 && threadIdx.x < 8)
+    queue[threadIdx.x * QUEUE_STRIDE] = queue_first;
   const int nv = blk_valid[j];
   const size_t row0 = (size_t)bh * n_pad + (size_t)j * BLK;
   const uint4* ksrc = (const uint4*)(k + row0 * D);
@@ -201,20 +207,49 @@ constexpr int attn_h_min_waves() { return D == 128 ? 3 : 4; }   // wavefronts pe
 
 // SPLIT: grids that leave the chip idle.  The list of a query block is cut into Split::of(cnt) parts of equal length, a
 // workgroup each; the parts' O, reference and sum go to the workspace and merge_kernel puts them together.
+// With a queue (see take_item) the rows at its end are cut, all into `parts`.
 struct Split {
   int parts, chunk;   // most parts of a list, list entries from which on there is one more part (0: always all parts)
   int stride;         // workgroups per part
-  float* o;           // [batch*heads*M][parts][BLK/32][D/32][4][64][4]: O in accumulator order
-  float* stat;        // [batch*heads*M][parts][2][BLK]: reference, sum
+  int first, whole;   // with a queue: positions of an XCD that are not dealt out by it, and before the first list that is cut
+  float* o;           // [slot][parts][BLK/32][D/32][4][64][4]: O in accumulator order
+  float* stat;        // [slot][parts][2][BLK]: reference, sum; slot = batch*head*M + block, or 8 * (position - whole) + XCD
   __device__ int of(int cnt) const { return chunk == 0 ? parts : max(1, min(parts, (cnt + chunk - 1) / chunk)); }
 };
+
+// Work for one workgroup of a launch that is dealt out by counters, one per XCD (workgroup n runs on XCD n % 8): XCDs that
+// have the same work to do need up to a tenth more or less time for it than others.  The value 8 r + x stands for position r
+// of XCD x: positions below `whole` are query blocks 8 r + x of map_work(), from there on every query block has `parts`
+// positions.  An XCD whose own are all taken goes on with those of the one that has most left.  -1: all are taken.
+// A launch has a quarter more workgroups than there are positions, so that a fast XCD finds some to run; the others end
+// here, in a few us.  (One workgroup that loops over positions keeps the kernel's arguments in scalar registers over
+// the loop: 20 to 70 spilled ones.)  The workgroups of the first generation do not ask, all at once, but take the position of their
+// own number: 34 shapes of 1 to 4 generations, 0.15 to 2.8 ms, 2 % less on average, 10 % where a workgroup lasts 100 us.
+__device__ inline int take_item(uint32_t* queue, const WorkMap& work, int whole, int parts) {
+  const int n_end = 8 * (whole + parts * ((work.n_wg + 7) / 8 - whole));
+  int x = blockIdx.x & 7;
+  for (;;) {
+    const int n = 8 * (int)__hip_atomic_fetch_add(queue + x * QUEUE_STRIDE, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) + x;
+    if (n < n_end) return n;
+    int least = n_end;
+#pragma unroll
+    for (int y = 0; y < 8; ++y) {
+      const int next = 8 * (int)__hip_atomic_load(queue + y * QUEUE_STRIDE, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) + y;
+      if (next < least) {
+        least = next;
+        x = y;
+      }
+    }
+    if (least == n_end) return -1;
+  }
+}
 
 template <int BLK, int D, bool PACED, bool SPLIT, bool K_ROWS>
 __global__ __launch_bounds__(2 * BLK, (attn_h_min_waves<BLK, D>())) void attn_h_kernel(
     const uint16_t* __restrict__ q, const u32x4* __restrict__ kp, const u32x4* __restrict__ vp,
     const int32_t* __restrict__ sel_count, const int32_t* __restrict__ sel_index,
     uint16_t* __restrict__ out, float* __restrict__ lse, WorkMap work, int n_pad, int pad_v, int pad_c,
-    float scale_log2e, float bias_log2e, const uint32_t* __restrict__ pace_params, Split split) {
+    float scale_log2e, float bias_log2e, const uint32_t* __restrict__ pace_params, Split split, uint32_t* queue) {
   constexpr int KS = D / 16, DT = D / 32, PS = BLK / 16, MH = 2, PH = 4;
   constexpr int NW = BLK / 32, NTHR = 64 * NW, HALVES = BLK / 64;   // wavefronts, threads, steps per key block
   constexpr int TILE_CHUNKS = BLK * D / 8, HALF_CHUNKS = 64 * D / 8, CPT = HALF_CHUNKS / NTHR;
@@ -231,14 +266,37 @@ __global__ __launch_bounds__(2 * BLK, (attn_h_min_waves<BLK, D>())) void attn_h_
   __shared__ uint32_t rem_bits[PACED ? 64 : 1];   // PACED: bitmap of the blocks still to visit, 32 per word
   __shared__ int pace_slot[2];                    // PACED: G for the next pick, published by thread 0
 
-  int bh, i;
-  const int part = SPLIT ? blockIdx.x / split.stride : 0;
-  if (!map_work(SPLIT ? blockIdx.x - part * split.stride : blockIdx.x, work, &bh, &i)) return;
-  const int M = work.M, M_v = work.M_v;
-  int n_parts = 1;
+  int n = blockIdx.x, part = 0, n_parts = 1, slot = -1;   // slot: of the partial result, -1: the whole list
   if constexpr (SPLIT) {
+    if (queue != nullptr) {
+      if (n >= 8 * split.first) {
+        volatile int* taken = (volatile int*)Ks;   // no tile is in there yet
+        if (threadIdx.x == 0) *taken = take_item(queue, work, split.whole, split.parts);
+        __syncthreads();
+        n = __builtin_amdgcn_readfirstlane(*taken);
+        __syncthreads();
+        if (n < 0) return;
+      }
+      const int cut = (n >> 3) - split.whole;
+      if (cut >= 0) {
+        n_parts = split.parts;
+        part = cut % n_parts;
+        const int row = cut / n_parts * 8 + (n & 7);
+        slot = row * n_parts + part;
+        n = 8 * split.whole + row;
+      }
+    } else {
+      part = n / split.stride;
+      n -= part * split.stride;
+    }
+  }
+  int bh, i;
+  if (!map_work(n, work, &bh, &i)) return;
+  const int M = work.M, M_v = work.M_v;
+  if (SPLIT && queue == nullptr) {
     n_parts = split.of(min(max(sel_count[(size_t)bh * M + i], 0), M));
     if (part >= n_parts) return;
+    if (n_parts > 1) slot = (bh * M + i) * split.parts + part;
   }
 
   const int tid = threadIdx.x, lane = tid & 63;
@@ -264,7 +322,7 @@ __global__ __launch_bounds__(2 * BLK, (attn_h_min_waves<BLK, D>())) void attn_h_
   uint32_t rem = 0, pace_k = 0;
   if constexpr (PACED) {
     // the list as a bitmap (a block listed twice is visited once); lane w of every wavefront holds word w
-    if constexpr (!SPLIT) pace_k = pace_params[0];
+    if (pace_params != nullptr) pace_k = pace_params[0];   // 0: ascending order
     if (tid < 64) rem_bits[tid] = 0;
     __syncthreads();
     for (int t = tid; t < cnt; t += NTHR) {
@@ -277,8 +335,8 @@ __global__ __launch_bounds__(2 * BLK, (attn_h_min_waves<BLK, D>())) void attn_h_
 #pragma unroll
     for (int o = 32; o >= 1; o >>= 1) pc += __shfl_xor(pc, o, 64);
     cnt = __builtin_amdgcn_readfirstlane(pc);
-    if constexpr (SPLIT) {   // the same positions of the bitmap, in ascending order: less than a generation of workgroups
-      const int lo = cnt * part / n_parts, hi = cnt * (part + 1) / n_parts;   // has no use for a common pace
+    if (SPLIT && n_parts > 1) {   // the same positions of the bitmap
+      const int lo = cnt * part / n_parts, hi = cnt * (part + 1) / n_parts;
       const int own = __popc(rem);
       int before = own;
 #pragma unroll
@@ -298,7 +356,7 @@ __global__ __launch_bounds__(2 * BLK, (attn_h_min_waves<BLK, D>())) void attn_h_
     }
   }
   // G: the low 32 bits of the clock times 2^32 / lap wrap once per lap; the high half of that times M is the block
-  auto pace_now = [&]() { return SPLIT ? 0 : (int)__umulhi((uint32_t)__builtin_amdgcn_s_memrealtime() * pace_k, (uint32_t)M); };
+  auto pace_now = [&]() { return (int)__umulhi((uint32_t)__builtin_amdgcn_s_memrealtime() * pace_k, (uint32_t)M); };
   // The first remaining block at or after G, else the first one after the wrap.  Every wavefront runs this on its
   // own copy of the bitmap with the same G, so the four agree without exchanging the result.  Needs rem != 0.
   // G is wave-uniform, so most of this is scalar arithmetic.
@@ -541,17 +599,16 @@ __global__ __launch_bounds__(2 * BLK, (attn_h_min_waves<BLK, D>())) void attn_h_
   const size_t qrow_e = (size_t)bh * n_pad + (size_t)i * BLK + row_e;
   const float l_tot = l_run + __shfl_xor(l_run, 32, 64);
   if constexpr (SPLIT) {
-    if (n_parts > 1) {
-      const size_t slot = ((size_t)bh * M + i) * split.parts + part;
-      float4* o = (float4*)split.o + (slot * NW + wave) * (DT * 4 * 64) + (tid_e & 63);
+    if (slot >= 0) {
+      float4* o = (float4*)split.o + ((size_t)slot * NW + wave) * (DT * 4 * 64) + (tid_e & 63);
 #pragma unroll
       for (int dt = 0; dt < DT; ++dt)
 #pragma unroll
         for (int g = 0; g < 4; ++g)
           o[(dt * 4 + g) * 64] = make_float4(O[dt][4 * g], O[dt][4 * g + 1], O[dt][4 * g + 2], O[dt][4 * g + 3]);
       if (hl_e == 0) {
-        split.stat[(slot * 2) * BLK + row_e] = m_run;
-        split.stat[(slot * 2 + 1) * BLK + row_e] = l_tot;
+        split.stat[(size_t)slot * 2 * BLK + row_e] = m_run;
+        split.stat[((size_t)slot * 2 + 1) * BLK + row_e] = l_tot;
       }
       return;
     }
@@ -574,18 +631,26 @@ __global__ __launch_bounds__(2 * BLK, (attn_h_min_waves<BLK, D>())) void attn_h_
     }
 }
 
-// merge_kernel: grid (BLK / 32, M, batch * heads), one wavefront per channel tile of 32 query rows.  Puts the parts of
-// the lists that attn_h_kernel<.., SPLIT> cut together, in the order of the parts; the other rows are done already.
+// merge_kernel: grid (BLK / 32, M, batch * heads) or, behind a queue, (BLK / 32, slots), one wavefront per channel tile of 32
+// query rows.  Puts the parts of the lists that attn_h_kernel<.., SPLIT> cut together, in the order of the parts; the other
+// rows are done already.
 template <int BLK, int D>
 __global__ __launch_bounds__(2 * D) void merge_kernel(const int32_t* __restrict__ sel_count, uint16_t* __restrict__ out,
-                                                      float* __restrict__ lse, int M, int M_v, int n_pad, int pad_v,
+                                                      float* __restrict__ lse, WorkMap work, int n_pad, int pad_v,
                                                       int pad_c, Split split) {
   constexpr int DT = D / 32, NW = BLK / 32;
-  const int i = blockIdx.y, bh = blockIdx.z, wave = blockIdx.x;
-  const int n_parts = split.of(min(max(sel_count[(size_t)bh * M + i], 0), M));
+  const int M = work.M, M_v = work.M_v, wave = blockIdx.x;
+  int i = blockIdx.y, bh = blockIdx.z, n_parts = split.parts;
+  size_t slot = (size_t)bh * M + i;
+  if (split.first > 0) {   // slots of a queue's end
+    slot = blockIdx.y;
+    if (!map_work(8 * split.whole + (int)slot, work, &bh, &i)) return;
+  } else {
+    n_parts = split.of(min(max(sel_count[slot], 0), M));
+  }
   if (n_parts == 1) return;
+  slot *= split.parts;
   const int lane = threadIdx.x & 63, dt = threadIdx.x >> 6, hl = lane >> 5, row = 32 * wave + (lane & 31);
-  const size_t slot = ((size_t)bh * M + i) * split.parts;
   const float4* o = (const float4*)split.o + (slot * NW + wave) * (DT * 4 * 64) + dt * 4 * 64 + lane;
   const float* stat = split.stat + slot * 2 * BLK + row;
 
@@ -906,8 +971,14 @@ bool reads_k_rows(const jenga_plan* p) {
   return BLK == 64 || (BLK == 128 && !(p->cfg.flags & JENGA_FLAG_PACED_WALK));
 }
 
+// Counters of a launch that deals its query blocks out as workgroups become free, behind the packed tiles; nullptr where the
+// plan has none.
+uint32_t* attn_queue(const jenga_plan* p, void* ws) {
+  return p->attn_first > 0 ? (uint32_t*)((char*)ws + p->packed_bytes) : nullptr;
+}
+
 template <int BLK, int D>
-int run_pack(const jenga_plan* p, const void* k, const void* v, void* ws, bool with_k, hipStream_t st) {
+int run_pack(const jenga_plan* p, const void* k, const void* v, void* ws, bool with_k, uint32_t* queue, hipStream_t st) {
   const jenga_config& c = p->cfg;
   const jenga_plan_info_t& f = p->info;
   const int bh = c.batch * c.heads;
@@ -916,7 +987,7 @@ int run_pack(const jenga_plan* p, const void* k, const void* v, void* ws, bool w
   uint4* vp = (uint4*)((char*)ws + half);
   const int first = with_k || !reads_k_rows<BLK>(p) ? 0 : 1;
   pack_kernel<BLK, D><<<dim3(f.M, bh, 2 - first), 256, 0, st>>>((const uint16_t*)k, (const uint16_t*)v, kp, vp,
-                                                             p->d_blk_valid, f.M, f.N_pad, first);
+                                                             p->d_blk_valid, f.M, f.N_pad, first, queue, p->attn_first);
   return hipGetLastError() == hipSuccess ? JENGA_OK : JENGA_EHIP;
 }
 
@@ -958,7 +1029,7 @@ int run_attention(const jenga_plan* p, const void* q, const void* k, void* ws, b
         split.stride = (work.n_wg + 7) & ~7;
         attn_kernel<D, NS, true><<<dim3(split.parts * split.stride), 64 * NS, 0, st>>>(
             q0, kp0, vp0, count0, index0, ob0, lse0, work, f.N_pad, f.pad_v, f.pad_c, scale, bias, split);
-        merge_kernel<BLK, D><<<dim3(1, f.M, n), 2 * D, 0, st>>>(count0, ob0, lse0, f.M, f.M_v, f.N_pad, f.pad_v, f.pad_c,
+        merge_kernel<BLK, D><<<dim3(1, f.M, n), 2 * D, 0, st>>>(count0, ob0, lse0, work, f.N_pad, f.pad_v, f.pad_c,
                                                                 split);
       } else {
         attn_kernel<D, NS, false><<<dim3(work.n_wg), 64 * NS, 0, st>>>(q0, kp0, vp0, count0, index0, ob0, lse0, work,
@@ -969,30 +1040,44 @@ int run_attention(const jenga_plan* p, const void* q, const void* k, void* ws, b
     const bool paced = BLK == 128 && (c.flags & JENGA_FLAG_PACED_WALK);
     const WorkMap work = jenga::plan_work(p, bh);
     Split split = {};
+    uint32_t *queue = may_split ? attn_queue(p, ws) : nullptr, *pace = nullptr;
 #define JENGA_ATTN(PACED, SPLIT, K_ROWS, WGS)                                                                    \
   attn_h_kernel<BLK, D, PACED, SPLIT, K_ROWS><<<dim3(WGS), 2 * BLK, 0, st>>>(                                    \
-      qb, kp, vp, sel_count, sel_index, ob, lse, work, f.N_pad, f.pad_v, f.pad_c, scale, bias, params, split)
-    if (may_split && p->attn_parts > 1) {
+      qb, kp, vp, sel_count, sel_index, ob, lse, work, f.N_pad, f.pad_v, f.pad_c, scale, bias, pace, split, queue)
+    if (paced && !(may_split && queue == nullptr && p->attn_parts > 1)) {
+      // a workgroup spends about 6.3 us (D = 128; 3.6 us at D = 64) on a block of 128 keys when three share a CU
+      pace = params;
+      walk_pace_kernel<<<1, 1024, 0, st>>>(sel_count, bh * f.M, f.M, D == 128 ? 630.f : 360.f, pace);
+    }
+    if (may_split && (p->attn_parts > 1 || queue != nullptr)) {
       split.parts = p->attn_parts;
       split.chunk = p->attn_chunk;
       split.stride = (work.n_wg + 7) & ~7;   // a multiple of the XCDs, which a query block's parts then share
       split.o = (float*)((char*)ws + p->packed_bytes);
-      split.stat = split.o + (size_t)bh * f.M * split.parts * BLK * D;
-      if constexpr (BLK == 128) {
-        if (paced) JENGA_ATTN(true, true, false, split.parts * split.stride);
+      int wgs = split.parts * split.stride;
+      size_t slots = (size_t)bh * f.M;
+      dim3 merge(BLK / 32, f.M, bh);
+      if (queue != nullptr) {
+        split.first = p->attn_first;
+        split.whole = split.stride / 8 - p->attn_tail;
+        split.o += QUEUE_BYTES / 4;
+        slots = (size_t)8 * p->attn_tail;
+        wgs = 8 * (split.whole + split.parts * p->attn_tail);
+        wgs += (wgs + 3) / 4;
+        merge = dim3(BLK / 32, 8 * p->attn_tail, 1);
       }
-      if (k_rows) JENGA_ATTN(false, true, true, split.parts * split.stride);
-      else if (!paced) JENGA_ATTN(false, true, false, split.parts * split.stride);
-      merge_kernel<BLK, D><<<dim3(BLK / 32, f.M, bh), 2 * D, 0, st>>>(sel_count, ob, lse, f.M, f.M_v, f.N_pad, f.pad_v,
-                                                                      f.pad_c, split);
+      split.stat = split.o + slots * split.parts * BLK * D;
+      if constexpr (BLK == 128) {
+        if (paced) JENGA_ATTN(true, true, false, wgs);
+      }
+      if (k_rows) JENGA_ATTN(false, true, true, wgs);
+      else if (!paced) JENGA_ATTN(false, true, false, wgs);
+      if (split.parts > 1)
+        merge_kernel<BLK, D><<<merge, 2 * D, 0, st>>>(sel_count, ob, lse, work, f.N_pad, f.pad_v, f.pad_c, split);
       return hipGetLastError() == hipSuccess ? JENGA_OK : JENGA_EHIP;
     }
     if constexpr (BLK == 128) {
-      if (paced) {
-        // a workgroup spends about 6.3 us (D = 128; 3.6 us at D = 64) on a block of 128 keys when three share a CU
-        walk_pace_kernel<<<1, 1024, 0, st>>>(sel_count, bh * f.M, f.M, D == 128 ? 630.f : 360.f, params);
-        JENGA_ATTN(true, false, false, work.n_wg);
-      }
+      if (paced) JENGA_ATTN(true, false, false, work.n_wg);
     }
     if (k_rows) JENGA_ATTN(false, false, true, work.n_wg);
     else if (!paced) JENGA_ATTN(false, false, false, work.n_wg);
@@ -1007,11 +1092,11 @@ namespace jenga {
 
 #define JENGA_FOR_SHAPES(X) X(128, 128) X(64, 128) X(32, 128) X(128, 64) X(64, 64) X(32, 64)
 
-int launch_pack(const jenga_plan* p, const void* k, const void* v, void* ws, bool with_k, void* stream) {
+int launch_pack(const jenga_plan* p, const void* k, const void* v, void* ws, bool with_k, bool may_split, void* stream) {
   hipStream_t st = (hipStream_t)stream;
   const int blk = p->cfg.block, d = p->cfg.head_dim;
 #define X(B, DD) \
-  if (blk == B && d == DD) return run_pack<B, DD>(p, k, v, ws, with_k, st);
+  if (blk == B && d == DD) return run_pack<B, DD>(p, k, v, ws, with_k, may_split ? attn_queue(p, ws) : nullptr, st);
   JENGA_FOR_SHAPES(X)
 #undef X
   return JENGA_EUNSUPPORTED;

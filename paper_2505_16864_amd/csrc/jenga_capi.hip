@@ -137,7 +137,7 @@ int jenga_block_sparse_attn(const jenga_plan* p, const void* q, const void* k, c
   // K is read in place unless an output lies over it
   const size_t rows = (size_t)p->cfg.batch * p->cfg.heads * p->info.N_pad, bytes = rows * p->cfg.head_dim * 2;
   const bool copy_k = overlap(k, bytes, out_curve, bytes) || (lse_or_null && overlap(k, bytes, lse_or_null, rows * 4));
-  const int rc = jenga::launch_pack(p, k, v, workspace, copy_k, stream);
+  const int rc = jenga::launch_pack(p, k, v, workspace, copy_k, true, stream);
   if (rc != JENGA_OK) return rc;
   return jenga::launch_attention(p, q, copy_k ? nullptr : k, workspace, true, sel_count, sel_index, out_curve,
                                  lse_or_null, stream);
@@ -149,7 +149,7 @@ int jenga_pack_kv(const jenga_plan* p, const void* k, const void* v, void* works
   if (!on_plan_device(p)) return JENGA_EINVAL;
   if (((uintptr_t)workspace & 255u) != 0) return JENGA_EINVAL;
   if (workspace_bytes < p->packed_bytes) return JENGA_EWORKSPACE;
-  return jenga::launch_pack(p, k, v, workspace, true, stream);
+  return jenga::launch_pack(p, k, v, workspace, true, false, stream);
 }
 
 int jenga_block_sparse_attn_packed(const jenga_plan* p, const void* q, void* packed_kv_workspace,

@@ -20,6 +20,8 @@ struct jenga_plan {
   // attn_chunk = 0: every list into attn_parts ranges of key blocks
   int attn_parts, attn_chunk;
   int attn_heads;  // (batch, head) pairs per launch where lists are cut
+  int attn_first;  // > 0: query blocks are dealt out by counters; that many per XCD are not
+  int attn_tail;   // and the lists of that many at the end of each XCD's are cut
   // bytes of the attention workspace that hold packed K, packed V and launch parameters; parts lie behind them
   uint64_t packed_bytes;
   // host tables
@@ -113,7 +115,8 @@ int launch_select(const jenga_plan* p, const void* q, const void* k, int32_t* se
 // Looks up the address of the static selection scratch on `device` (the current device) once.
 int select_scratch_init(int device);
 // with_k = false: K is left out where the attention kernel can read it in place; launch_attention then gets it.
-int launch_pack(const jenga_plan* p, const void* k, const void* v, void* ws, bool with_k, void* stream);
+// may_split: as for launch_attention, whose counters are then set.
+int launch_pack(const jenga_plan* p, const void* k, const void* v, void* ws, bool with_k, bool may_split, void* stream);
 // k: K, if it may have been left out of the workspace, else NULL (K packed).  may_split: the call has the workspace to itself and may
 // write behind the packed tiles.
 int launch_attention(const jenga_plan* p, const void* q, const void* k, void* packed_ws, bool may_split,

@@ -18,7 +18,6 @@
 // Cuts are at floor(n/2), raised by one when odd and n > 2.
 #include <algorithm>
 #include <cmath>
-#include <cstdlib>
 #include <cstring>
 
 #include "jenga_internal.h"
@@ -212,12 +211,24 @@ int heads_per_launch(const jenga_plan* p, int threads) {
 //   708 x 40, D = 128 (0.9 GB)                   3.87 / 3.74 / 3.62* / 3.71 / 3.83 ms
 //   408 x 24, D = 128 (0.3 GB)                   1.30 / 1.28 / 1.26* / 1.27 / 1.31 ms
 //   1503 x 16, D = 128 (1.2 GB)                  4.97 / 5.00 / 5.01* / 4.84 / 4.87 ms
+//
+// With more query blocks than resident workgroups, all of about the same length, it is not lists that are too long: at 720p
+// XCDs that were dealt the same work took 44 to 49.5 ms for it.  There the query blocks behind the first generation of
+// workgroups are dealt out by counters (take_item in jenga_attn.hip), so that XCDs end together: 929 blocks x 24 heads
+// 49.3 -> 46.7 ms (k = 0.3, paced) and 21.0 -> 20.1 ms (k = 0.1); 20 shapes of 1.1 to 4.6 generations of 128-token blocks,
+// layers of 0.3 to 1.3 ms, 0 to 4 % less, none more.  Workgroups for 64 tokens with even lists last 50 to 200 us and lose 1 to
+// 6 % to the counter.
+// What remains is the last generation, which runs out over the time of one workgroup.  There half a generation of lists is
+// cut, into two: 1 to 3 % less from two generations on, but below two, where this reaches into the first one, up to
+// 5 % more (1416 query blocks at D = 128 601 -> 633 us).  Lists of uneven length (p well above k) into three, whatever the
+// grid: 128 tokens 1 to 13 % less (248 blocks x 12 heads 4.50 -> 4.21 ms), 64 tokens 1 to 10 % less, none more.
 constexpr uint64_t RANGE_AREA_BYTES = 128ull << 20;
 
 static void split_lists(jenga_plan* plan) {
   const jenga_config& c = plan->cfg;
   const jenga_plan_info_t& f = plan->info;
   plan->attn_parts = 1;
+  plan->attn_first = plan->attn_tail = 0;
   plan->attn_chunk = f.M;
   plan->attn_heads = c.batch * c.heads;
   const long long rows = (long long)c.batch * c.heads * f.M;
@@ -239,6 +250,18 @@ static void split_lists(jenga_plan* plan) {
     return;
   }
   const long long places = 256ll * attn_h_per_cu(c.block, c.head_dim);
+  if (rows > places) {
+    const bool uneven = c.cum_prob > 2.0 * c.topk_ratio;
+    if (c.block == 64 && !uneven) return;
+    plan->attn_first = 32 * (c.block == 64 && c.head_dim == 128 ? 4 : attn_h_per_cu(c.block, c.head_dim));
+    if (uneven || rows >= 2 * places) {
+      const int positions = (plan_work(plan, c.batch * c.heads).n_wg + 7) / 8;
+      plan->attn_tail = std::min(positions - plan->attn_first, plan->attn_first / 2);
+      plan->attn_parts = uneven ? 3 : 2;
+      plan->attn_chunk = 0;
+    }
+    return;
+  }
   if (4 * rows >= 3 * places) return;
   const long long shortest = (rows <= 256 ? 6 : 24) * 64 / c.block;
   const long long chunk = std::max(shortest, (5 * rows * len + 3 * places - 1) / (3 * places));
@@ -316,8 +339,11 @@ int build_host_tables(jenga_plan* plan) {
   f.attn_workspace_bytes = plan->packed_bytes;
   split_lists(plan);
   // and, where lists are cut, O and two statistics per row and part, float32
-  if (plan->attn_parts > 1)
-    f.attn_workspace_bytes += align256((uint64_t)plan->attn_heads * f.M * plan->attn_parts * m * (c.head_dim + 2) * 4);
+  const uint64_t part = (uint64_t)m * (c.head_dim + 2) * 4;
+  if (plan->attn_first > 0)
+    f.attn_workspace_bytes += 1024 + align256(8ull * plan->attn_tail * plan->attn_parts * part);
+  else if (plan->attn_parts > 1)
+    f.attn_workspace_bytes += align256((uint64_t)plan->attn_heads * f.M * plan->attn_parts * part);
   return JENGA_OK;
 }
 

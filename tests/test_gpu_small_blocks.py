@@ -224,3 +224,48 @@ def test_output_over_an_input(block, flags, heads):
             assert float((t[over].float() - want.float()).abs().max()) <= 2.0 ** -6 * float(want.float().abs().max())
         else:
             assert torch.equal(t[over], want)
+
+
+# More query blocks than resident workgroups: they are dealt out by counters, and the lists at the end of each XCD's are cut
+# (or not: one to two generations of even lists).  Lists shorter than the number of parts, empty and full; twice over, the
+# second time with what the first left in the workspace.  Whole lists are visited as the packed entry visits them, which
+# deals nothing out and cuts nothing.
+@pytest.mark.parametrize("block,head_dim,blocks,heads,p,paced", [
+    (128, 128, 9, 86, 0.3, False), (128, 128, 13, 120, 0.3, False), (128, 128, 13, 61, 0.9, True),
+    (128, 64, 37, 29, 0.9, False), (128, 64, 9, 230, 0.3, True), (64, 128, 29, 46, 0.9, False), (64, 64, 31, 67, 0.9, False)])
+def test_more_query_blocks_than_places(block, head_dim, blocks, heads, p, paced):
+    w = dict(T=1, H=1, W=block * (blocks - 1) - 9, n_text=5, batch=1, heads=heads, head_dim=head_dim, block=block, topk=0.3,
+             p=p, text_bias=0.4, flags=15 if paced else 7)
+    print("dealt out", w, flush=True)
+    layer = CarveLayer(w, "cuda:0", want_lse=True)
+    M = layer.info.M
+    assert M == blocks
+    layer.permute_in(*[x.cuda() for x in ji.make_qkv(w, 62)])
+    rng = np.random.default_rng(9)
+    idx = np.argsort(rng.random((1, heads, M, M)), axis=-1).astype(np.int32)
+    cnt = rng.choice([0, 1, 2, 3, M // 2, M - 1, M], size=(1, heads, M)).astype(np.int32)
+    layer.sel_count.copy_(torch.from_numpy(cnt))
+    layer.sel_index.copy_(torch.from_numpy(idx))
+    got = []
+    layer.ws_attn.fill_(0xFF)
+    for call in (layer.attend, layer.attend, layer.pack, layer.attend_packed):
+        if call != layer.pack:
+            layer.o_c.view(torch.int16).fill_(0x7FC1)
+            layer.lse.fill_(7.0)
+        call()
+        torch.cuda.synchronize()
+        if call != layer.pack:
+            got.append((layer.o_c.float().clone(), layer.lse.clone()))
+    (first, first_lse), (second, second_lse), (whole, whole_lse) = got
+    assert torch.isfinite(first).all()
+    if not paced:
+        assert torch.equal(first, second) and torch.equal(first_lse, second_lse)
+        # at most half a generation of lists is cut
+        cut = (first != whole).any(dim=-1).view(heads * M, block).any(dim=-1).sum()
+        assert int(cut) <= 256 * {(128, 128): 3, (128, 64): 4, (64, 128): 4, (64, 64): 8}[(block, head_dim)] // 2
+    # bf16 probabilities taken against another reference, 2^-8 max|v|, and one unit of the bf16 result
+    for o, lse in ((first, first_lse), (second, second_lse)):
+        assert float((o - whole).abs().max()) <= 2.0 ** -6 * float(layer.v_c.float().abs().max())
+        alive = torch.isfinite(whole_lse)
+        assert torch.equal(torch.isfinite(lse), alive) and torch.isneginf(lse[~alive]).all()
+        assert float((lse[alive] - whole_lse[alive]).abs().max()) <= 1e-3      # float32 sums and one float32 logarithm
