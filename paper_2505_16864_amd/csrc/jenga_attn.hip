@@ -51,8 +51,8 @@ __device__ inline uint32_t pack_bf16x2(float lo, float hi) {
   return __builtin_bit_cast(uint32_t, __builtin_convertvector(v, bf16x2));
 }
 
-// Counters of a queue (see take_item), one per XCD and cache line.
-constexpr int QUEUE_STRIDE = 32, QUEUE_BYTES = 8 * QUEUE_STRIDE * 4;
+// Launch parameters, behind the packed tiles: the pace of the paced walk, the eight counters of a queue (see take_item).
+constexpr int PARAM_QUEUE = 8;
 
 // grid (M, batch*heads, 2).  z = 0: K tile -> fragment order; z = 1: V tile -> transposed fragment order, pad rows zeroed.
 // grid (M, batch*heads, 1) with first = 1: V only.  The first workgroup sets the counters of the launch that follows.
@@ -69,7 +69,7 @@ __global__ __launch_bounds__(256) void pack_kernel(const uint16_t* __restrict__ 
   __shared__ uint16_t vl[BLK * LDV];
   const int j = blockIdx.x, bh = blockIdx.y;
   if (queue != nullptr && j == 0 && bh == 0 && blockIdx.z == 0 && threadIdx.x < 8)
-    queue[threadIdx.x * QUEUE_STRIDE] = queue_first;
+    queue[threadIdx.x] = queue_first;
   const int nv = blk_valid[j];
   const size_t row0 = (size_t)bh * n_pad + (size_t)j * BLK;
   const uint4* ksrc = (const uint4*)(k + row0 * D);
@@ -229,12 +229,12 @@ __device__ inline int take_item(uint32_t* queue, const WorkMap& work, int whole,
   const int n_end = 8 * (whole + parts * ((work.n_wg + 7) / 8 - whole));
   int x = blockIdx.x & 7;
   for (;;) {
-    const int n = 8 * (int)__hip_atomic_fetch_add(queue + x * QUEUE_STRIDE, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) + x;
+    const int n = 8 * (int)__hip_atomic_fetch_add(queue + x, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) + x;
     if (n < n_end) return n;
     int least = n_end;
 #pragma unroll
     for (int y = 0; y < 8; ++y) {
-      const int next = 8 * (int)__hip_atomic_load(queue + y * QUEUE_STRIDE, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) + y;
+      const int next = 8 * (int)__hip_atomic_load(queue + y, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) + y;
       if (next < least) {
         least = next;
         x = y;
@@ -971,10 +971,9 @@ bool reads_k_rows(const jenga_plan* p) {
   return BLK == 64 || (BLK == 128 && !(p->cfg.flags & JENGA_FLAG_PACED_WALK));
 }
 
-// Counters of a launch that deals its query blocks out as workgroups become free, behind the packed tiles; nullptr where the
-// plan has none.
+// Counters of a launch that deals its query blocks out as workgroups become free; nullptr where the plan has none.
 uint32_t* attn_queue(const jenga_plan* p, void* ws) {
-  return p->attn_first > 0 ? (uint32_t*)((char*)ws + p->packed_bytes) : nullptr;
+  return p->attn_first > 0 ? (uint32_t*)((char*)ws + p->packed_bytes - 256) + PARAM_QUEUE : nullptr;
 }
 
 template <int BLK, int D>
@@ -1058,13 +1057,20 @@ int run_attention(const jenga_plan* p, const void* q, const void* k, void* ws, b
       size_t slots = (size_t)bh * f.M;
       dim3 merge(BLK / 32, f.M, bh);
       if (queue != nullptr) {
+        int tail = p->attn_tail;
+        if (p->attn_over_k) {
+          split.o = (float*)ws;
+          if (!k_rows) {   // K is packed there all the same: lists stay whole
+            tail = 0;
+            split.parts = 1;
+          }
+        }
         split.first = p->attn_first;
-        split.whole = split.stride / 8 - p->attn_tail;
-        split.o += QUEUE_BYTES / 4;
-        slots = (size_t)8 * p->attn_tail;
-        wgs = 8 * (split.whole + split.parts * p->attn_tail);
+        split.whole = split.stride / 8 - tail;
+        slots = (size_t)8 * tail;
+        wgs = 8 * (split.whole + split.parts * tail);
         wgs += (wgs + 3) / 4;
-        merge = dim3(BLK / 32, 8 * p->attn_tail, 1);
+        merge = dim3(BLK / 32, 8 * tail, 1);
       }
       split.stat = split.o + slots * split.parts * BLK * D;
       if constexpr (BLK == 128) {

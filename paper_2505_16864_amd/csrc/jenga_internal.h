@@ -21,7 +21,8 @@ struct jenga_plan {
   int attn_parts, attn_chunk;
   int attn_heads;  // (batch, head) pairs per launch where lists are cut
   int attn_first;  // > 0: query blocks are dealt out by counters; that many per XCD are not
-  int attn_tail;   // and the lists of that many at the end of each XCD's are cut
+  int attn_tail;   // lists that are cut, all into attn_parts, at the end of what each XCD is dealt by counters
+  bool attn_over_k; // their results lie where packed K would, which is not needed when K is read in place
   // bytes of the attention workspace that hold packed K, packed V and launch parameters; parts lie behind them
   uint64_t packed_bytes;
   // host tables

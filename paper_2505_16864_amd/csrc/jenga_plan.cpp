@@ -339,11 +339,11 @@ int build_host_tables(jenga_plan* plan) {
   f.attn_workspace_bytes = plan->packed_bytes;
   split_lists(plan);
   // and, where lists are cut, O and two statistics per row and part, float32
-  const uint64_t part = (uint64_t)m * (c.head_dim + 2) * 4;
-  if (plan->attn_first > 0)
-    f.attn_workspace_bytes += 1024 + align256(8ull * plan->attn_tail * plan->attn_parts * part);
-  else if (plan->attn_parts > 1)
-    f.attn_workspace_bytes += align256((uint64_t)plan->attn_heads * f.M * plan->attn_parts * part);
+  const uint64_t rows = plan->attn_first > 0 ? 8ull * plan->attn_tail : (uint64_t)plan->attn_heads * f.M;
+  const uint64_t parts = plan->attn_parts > 1 ? align256(rows * plan->attn_parts * m * (c.head_dim + 2) * 4) : 0;
+  const bool k_in_place = m == 64 || (m == 128 && !(c.flags & JENGA_FLAG_PACED_WALK));
+  plan->attn_over_k = plan->attn_first > 0 && k_in_place && parts <= plan->packed_bytes / 2 - 128;
+  if (!plan->attn_over_k) f.attn_workspace_bytes += parts;
   return JENGA_OK;
 }
 
