@@ -16,12 +16,12 @@
 // accumulator, so the row maximum and row sum are lane-local (one cross-half exchange), and the
 // accumulator layout of S^T is already the B-operand layout PV needs: P never goes through LDS.
 //
-// V, and for some kernels K, are first re-tiled once per call (pack_kernel) into "fragment order": for every
+// A call that is given K and V themselves reads them as they are in the in-order kernels for blocks of 64 and 128 tokens
+// (K_ROWS).  For the others both are first re-tiled once per call (pack_kernel) into "fragment order": for every
 // block a 16-byte piece per (fragment, lane) in exactly the order the LDS reads want them, so that a tile
-// moves global -> LDS as a straight copy and every LDS read is a conflict-free 1 KB wave read.  A call that is
-// given K itself takes it as it is in the in-order kernels for blocks of 64 and 128 tokens (K_ROWS).  A packed
-// workspace always holds both in fragment order, whatever the walk: plans of one grid may share it.
-// The V tile is stored transposed, with its key index permuted to match the accumulator layout:
+// moves global -> LDS as a straight copy and every LDS read is a conflict-free 1 KB wave read.  A packed
+// workspace always holds that order, whatever the walk: plans of one grid may share it.
+// The packed V tile is transposed, with its key index permuted to match the accumulator layout:
 //     accumulator register r of kv-tile mt, lane l  <->  key 32*mt + 8*(r/4) + 4*(l/32) + r%4,
 //     query (l%32).
 #include <hip/hip_runtime.h>
@@ -40,6 +40,7 @@ using jenga::WorkMap;
 
 typedef __bf16 bf16x8 __attribute__((ext_vector_type(8)));
 typedef float f32x16 __attribute__((ext_vector_type(16)));
+typedef uint32_t u32x2 __attribute__((ext_vector_type(2)));
 typedef uint32_t u32x4 __attribute__((ext_vector_type(4)));
 
 typedef __bf16 bf16x2 __attribute__((ext_vector_type(2)));
@@ -55,21 +56,17 @@ __device__ inline uint32_t pack_bf16x2(float lo, float hi) {
 constexpr int PARAM_QUEUE = 8;
 
 // grid (M, batch*heads, 2).  z = 0: K tile -> fragment order; z = 1: V tile -> transposed fragment order, pad rows zeroed.
-// grid (M, batch*heads, 1) with first = 1: V only.  The first workgroup sets the counters of the launch that follows.
 // A workgroup each, so that the two chains of loads and stores run side by side: 931 blocks x 24 heads (2.9 GB) 531 ->
 // 511 us = 5.7 TB/s, 262 x 24 156 -> 145 us; HBM-bound from there on.
 template <int BLK, int D>
 __global__ __launch_bounds__(256) void pack_kernel(const uint16_t* __restrict__ k, const uint16_t* __restrict__ v,
                                                    uint4* __restrict__ kp, uint4* __restrict__ vp,
-                                                   const int32_t* __restrict__ blk_valid, int M, int n_pad, int first,
-                                                   uint32_t* __restrict__ queue, int queue_first) {
+                                                   const int32_t* __restrict__ blk_valid, int M, int n_pad) {
   constexpr int KS = D / 16, PS = BLK / 16, CH = D / 8;
   constexpr int TILE_CHUNKS = BLK * D / 8;
   constexpr int LDV = D + 8;   // padded row length (elements) of the staged V tile
   __shared__ uint16_t vl[BLK * LDV];
   const int j = blockIdx.x, bh = blockIdx.y;
-  if (queue != nullptr && j == 0 && bh == 0 && blockIdx.z == 0 && threadIdx.x < 8)
-    queue[threadIdx.x] = queue_first;
   const int nv = blk_valid[j];
   const size_t row0 = (size_t)bh * n_pad + (size_t)j * BLK;
   const uint4* ksrc = (const uint4*)(k + row0 * D);
@@ -77,7 +74,7 @@ __global__ __launch_bounds__(256) void pack_kernel(const uint16_t* __restrict__ 
   uint4* kdst = kp + ((size_t)bh * M + j) * TILE_CHUNKS;
   uint4* vdst = vp + ((size_t)bh * M + j) * TILE_CHUNKS;
 
-  if (blockIdx.z + first == 0) {
+  if (blockIdx.z == 0) {
 #pragma unroll
     for (int o = threadIdx.x; o < TILE_CHUNKS; o += 256) {
       const int lane = o & 63, f = o >> 6;
@@ -115,16 +112,17 @@ __global__ __launch_bounds__(256) void pack_kernel(const uint16_t* __restrict__ 
 // Written as asm so that the compiler does not track these copies: it would otherwise order every
 // later LDS read of the same array behind them with a full vmcnt(0) wait.  Completion is tracked by
 // vmcnt and waited for explicitly (wait_vmem) before the barrier that publishes a tile.
-// The LDS byte address is a number that the caller keeps in an SGPR.
-__device__ inline void dma_1kb_to_lds_at(const void* uniform_base, uint32_t lane_byte_off, uint32_t lds_addr) {
+// The LDS byte address is lds_addr, a number that the caller keeps in an SGPR, plus `lds_off`.
+__device__ __forceinline__ void dma_1kb_to_lds_at(const void* uniform_base, uint32_t lane_byte_off, uint32_t lds_addr,
+                                                  int lds_off) {
   const uint64_t b = (uint64_t)uniform_base;
   const uint32_t lo = __builtin_amdgcn_readfirstlane((uint32_t)b);
   const uint32_t hi = __builtin_amdgcn_readfirstlane((uint32_t)(b >> 32));
   const uint64_t base = ((uint64_t)hi << 32) | lo;
-  asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %1, %2"
+  asm volatile("s_add_u32 m0, %0, %3\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %1, %2"
                :
-               : "s"(lds_addr), "v"(lane_byte_off), "s"(base)
-               : "memory", "m0");
+               : "s"(lds_addr), "v"(lane_byte_off), "s"(base), "i"(lds_off)
+               : "memory", "m0", "scc");
 }
 
 __device__ inline void wait_vmem() { __builtin_amdgcn_s_waitcnt(0x0F70); }   // vmcnt(0) only
@@ -152,6 +150,26 @@ __device__ __forceinline__ void static_for(F&& f) {
 template <int BYTE_OFF>
 __device__ __forceinline__ void lds_frag(u32x4& dst, uint32_t lane_addr) {
   asm volatile("ds_read_b128 %0, %1 offset:%2" : "=v"(dst) : "v"(lane_addr), "n"(BYTE_OFF) : "memory");
+}
+// x ^ y, formed where it stands: hoisted out of a loop it would take a register there.
+__device__ __forceinline__ uint32_t xor_here(uint32_t x, int y) {
+  uint32_t r;
+  asm volatile("v_xor_b32 %0, %1, %2" : "=v"(r) : "i"(y), "v"(x));
+  return r;
+}
+
+// 64 bits per lane, transposed: the 16 lanes of a group name 4 rows of 16 bf16 each, a row by 4 lanes of 8 bytes; lane i gets
+// column i, row 0 first.
+template <int BYTE_OFF>
+__device__ __forceinline__ void lds_columns(u32x2& dst, uint32_t lane_addr) {
+  asm volatile("ds_read_b64_tr_b16 %0, %1 offset:%2" : "=v"(dst) : "v"(lane_addr), "n"(BYTE_OFF) : "memory");
+}
+__device__ __forceinline__ void lds_wait(u32x2 (&g)[4][2]) {
+  asm volatile("s_waitcnt lgkmcnt(0)"
+               : "+v"(g[0][0]), "+v"(g[0][1]), "+v"(g[1][0]), "+v"(g[1][1]), "+v"(g[2][0]), "+v"(g[2][1]), "+v"(g[3][0]),
+                 "+v"(g[3][1])
+               :
+               : "memory");
 }
 __device__ __forceinline__ void lds_wait(u32x4 (&g)[4]) {
   asm volatile("s_waitcnt lgkmcnt(0)" : "+v"(g[0]), "+v"(g[1]), "+v"(g[2]), "+v"(g[3]) : : "memory");
@@ -254,15 +272,19 @@ __global__ __launch_bounds__(2 * BLK, (attn_h_min_waves<BLK, D>())) void attn_h_
   constexpr int NW = BLK / 32, NTHR = 64 * NW, HALVES = BLK / 64;   // wavefronts, threads, steps per key block
   constexpr int TILE_CHUNKS = BLK * D / 8, HALF_CHUNKS = 64 * D / 8, CPT = HALF_CHUNKS / NTHR;
   static_assert(HALVES >= 1 && (!PACED || HALVES == 2), "64 keys a step; the paced walk needs two steps a block");
-  // The current 64 keys: fragments (m2, ks) from packed tiles, or (K_ROWS) rows of D channels as they lie in K, with the
-  // 16-byte pieces of a row rotated by an exclusive or with k_swizzle(row), so that the 16 rows that are read at a time
-  // fall on different banks.  K_ROWS needs no packed K (lowres layer of 262 blocks x 24 heads: 4505 -> 4448 us with
-  // packing, 931 blocks at k = 0.1 21.01 -> 20.74 ms, 222 blocks of 64 580 -> 570 us) but eight address instructions
-  // a step; the paced walk, which is closest to what the matrix cores can do, loses 0.6 % to them and keeps the tiles,
-  // and so does whoever has packed K already.
+  // The current 64 keys: fragments from packed tiles, or (K_ROWS) rows of D channels as they lie in K and V, with the
+  // 16-byte pieces of a row rotated by an exclusive or on the way.  K: with k_swizzle(row), so that the 16 rows that are
+  // read at a time fall on different banks.  V is read by columns, ds_read_b64_tr_b16, which hands a lane 4 keys of its
+  // channel: two of them are a fragment, in the key order of the accumulators.  There v_swizzle(row) spreads the 4 rows x
+  // 64 bytes that half a wavefront reads over the banks.  A copy brings whole rows: with 4 rows x 64 bytes for every 16 lanes
+  // of it, which would have left both reads without address arithmetic, 222 blocks of 64 x 12 took 609 instead of 493 us.
+  // The addresses are formed where they are needed (xor_here; ten instructions a step): hoisted, they cost spills.
+  // No packing, against V packed (before, with K packed too): layer of 222 blocks of 64 x 12 heads 521 -> 486 us, 17
+  // blocks x 8 59.5 -> 56.2, 48 x 16 at D = 64 133.1 -> 130.2, 262 x 24 4.48 -> 4.45 ms (the columns take twice as many LDS
+  // instructions as fragments).  The paced walk keeps packed tiles, and so does whoever has packed them already.
   static_assert(!(PACED && K_ROWS), "the paced walk reads packed tiles");
   __shared__ __align__(256) u32x4 Ks[HALF_CHUNKS];
-  __shared__ u32x4 Vs[HALF_CHUNKS];   // fragments (dt, p2) of the current 64 keys
+  __shared__ __align__(256) u32x4 Vs[HALF_CHUNKS];   // fragments (dt, p2) of the current 64 keys, or rows
   __shared__ uint32_t rem_bits[PACED ? 64 : 1];   // PACED: bitmap of the blocks still to visit, 32 per word
   __shared__ int pace_slot[2];                    // PACED: G for the next pick, published by thread 0
 
@@ -387,21 +409,23 @@ __global__ __launch_bounds__(2 * BLK, (attn_h_min_waves<BLK, D>())) void attn_h_
       (uint32_t)(uintptr_t)(const __attribute__((address_space(3))) void*)Vs + (uint32_t)wave * 1024u);
   constexpr int CH = D / 8, ROWS_PER_COPY = NTHR / CH;
   auto k_swizzle = [](int row) { return D == 128 ? row & 15 : (row >> 1) & 7; };
+  auto v_swizzle = [](int row) { return D == 128 ? (row & 3) * 4 : (row & 2) * 2; };
   const uint32_t k_off = (uint32_t)(K_ROWS ? tid / CH * CH + (tid % CH ^ k_swizzle(tid / CH)) : tid) * 16u;
+  const uint32_t v_off = (uint32_t)(K_ROWS ? tid / CH * CH + (tid % CH ^ v_swizzle(tid / CH)) : lane) * 16u;
   auto k_half_to_lds = [&](int j, int h) {
     const char* kt = (const char*)(kbase + (size_t)j * TILE_CHUNKS + h * HALF_CHUNKS);
 #pragma unroll
-    for (int c = 0; c < CPT; ++c) 
+    for (int c = 0; c < CPT; ++c)
       dma_1kb_to_lds_at(kt + (size_t)c * (NTHR * 16),
                         K_ROWS ? k_off ^ (uint32_t)k_swizzle(c * ROWS_PER_COPY) * 16u : k_off,
-                        ks_wave + c * (NTHR * 16u));
+                        ks_wave, c * (NTHR * 16));
   };
   auto v_half_to_lds = [&](int j, int h) {
-    const u32x4* vt = vbase + (size_t)j * TILE_CHUNKS + (PH * h) * 64;
+    const u32x4* vt = vbase + (size_t)j * TILE_CHUNKS + (K_ROWS ? h * HALF_CHUNKS : PH * h * 64);
 #pragma unroll
     for (int c = 0; c < CPT; ++c) {
       const int f = c * NW + wave, dt = f / PH, p2 = f % PH;
-      dma_1kb_to_lds_at(vt + (size_t)(dt * PS + p2) * 64, (uint32_t)lane * 16u, vs_wave + c * (NTHR * 16u));
+      dma_1kb_to_lds_at(vt + (size_t)(K_ROWS ? c * NTHR : (dt * PS + p2) * 64), v_off, vs_wave, c * (NTHR * 16));
     }
   };
 
@@ -412,16 +436,26 @@ __global__ __launch_bounds__(2 * BLK, (attn_h_min_waves<BLK, D>())) void attn_h_
   for (int dt = 0; dt < DT; ++dt)
 #pragma unroll
     for (int r = 0; r < 16; ++r) O[dt][r] = 0.f;
-  const uint32_t ks_lane = (uint32_t)(uintptr_t)(const __attribute__((address_space(3))) void*)Ks +
-                           (K_ROWS ? ql * (2 * D) + (hl ^ k_swizzle(ql)) * 16 : lane * 16);
-  auto k_frag = [&](u32x4& dst, auto M2, auto KSTEP) {   // fragment (m2, ks); K_ROWS: piece 2 ks + hl of row 32 m2 + ql
-    constexpr int m2 = decltype(M2)::value, ks = decltype(KSTEP)::value;
-    if constexpr (K_ROWS)
-      lds_frag<m2 * 64 * D>(dst, ks_lane ^ ks * 32);
-    else
-      lds_frag<(m2 * KS + ks) * 1024>(dst, ks_lane);
+  const uint32_t ks_lane =
+      (uint32_t)(uintptr_t)(const __attribute__((address_space(3))) void*)Ks +
+      (K_ROWS ? ql * (2 * D) + (hl ^ k_swizzle(ql)) * 16 : lane * 16);
+  auto k_frags = [&](u32x4 (&dst)[4], auto G) {   // (m2, ks) = (e & 1, 2 g + e / 2); K_ROWS: piece 2 ks + hl of row 32 m2 + ql
+    constexpr int g = decltype(G)::value;
+    uint32_t at[2] = {ks_lane, ks_lane};
+    if constexpr (K_ROWS) {
+      if constexpr (g > 0) at[0] = xor_here(ks_lane, g * 64);
+      at[1] = xor_here(ks_lane, g * 64 + 32);
+    }
+    static_for<4>([&](auto E) {
+      constexpr int e = decltype(E)::value, m2 = e & 1;
+      lds_frag<K_ROWS ? m2 * 64 * D : (m2 * KS + 2 * g + e / 2) * 1024>(dst[e], at[e / 2]);
+    });
   };
-  const uint32_t vs_lane = (uint32_t)(uintptr_t)(const __attribute__((address_space(3))) void*)Vs + lane * 16;
+  // K_ROWS: columns 32 dt + 16 (lane / 16 % 2) + lane % 16 of four rows
+  const int v_row = 4 * hl + ((lane >> 2) & 3);
+  const uint32_t vs_lane =
+      (uint32_t)(uintptr_t)(const __attribute__((address_space(3))) void*)Vs +
+      (K_ROWS ? v_row * (2 * D) + v_swizzle(v_row) * 16 + ((lane >> 4) & 1) * 32 + (lane & 3) * 8 : lane * 16);
 
   // The block index of the next step is fetched a step ahead, and the valid-token count of a
   // block follows from its index, so no step waits on a scalar load it has just issued.
@@ -455,19 +489,12 @@ __global__ __launch_bounds__(2 * BLK, (attn_h_min_waves<BLK, D>())) void attn_h_
       {
         constexpr int NG = KS / 2;
         u32x4 A[2][4];
-        static_for<4>([&](auto E) {
-          constexpr int e = decltype(E)::value;
-          k_frag(A[0][e], std::integral_constant<int, e & 1>{}, std::integral_constant<int, e / 2>{});
-        });
+        k_frags(A[0], std::integral_constant<int, 0>{});
         static_for<NG>([&](auto G) {
           constexpr int g = decltype(G)::value;
           lds_wait(A[g & 1]);
           if constexpr (g + 1 < NG)
-            static_for<4>([&](auto E) {
-              constexpr int e = decltype(E)::value;
-              k_frag(A[(g + 1) & 1][e], std::integral_constant<int, e & 1>{},
-                     std::integral_constant<int, 2 * (g + 1) + e / 2>{});
-            });
+            k_frags(A[(g + 1) & 1], std::integral_constant<int, g + 1>{});
           static_for<4>([&](auto E) {
             constexpr int e = decltype(E)::value, m2 = e & 1, ks = 2 * g + e / 2;
             S[m2] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(__builtin_bit_cast(bf16x8, A[g & 1][e]), qf[ks], S[m2],
@@ -561,16 +588,37 @@ __global__ __launch_bounds__(2 * BLK, (attn_h_min_waves<BLK, D>())) void attn_h_
     l_run += rs;
 
     wait_vmem();       // this wave's part of the V half has landed
+    if (K_ROWS && nv < BLK) {   // pad rows hold anything, and their probabilities are zero
+      asm volatile("" : : : "memory");   // a real, rarely taken branch; nothing is written before the copies have landed
+      int at = threadIdx.x;
+      asm volatile("" : "+v"(at));
+#pragma unroll 1
+      for (; at < HALF_CHUNKS; at += NTHR)
+        if (64 * h + at / CH >= nv) Vs[at] = u32x4{0, 0, 0, 0};
+    }
     __syncthreads();   // V half is in LDS; every wave is done reading the K half
     if (st + 1 < steps) k_half_to_lds(j_next, HALVES == 2 ? (st + 1) & 1 : 0);
 
     // O^T += V^T P^T, fragments (dt, p2) = (2 (g / 2) + (e & 1), 2 (g % 2) + e / 2), pipelined as above
     {
       constexpr int NG = DT;
-      u32x4 A[2][4];
+      typedef typename std::conditional<K_ROWS, u32x2[2], u32x4>::type Frag;
+      Frag A[2][4];
+      uint32_t vs_dt[DT];   // K_ROWS: formed here and now, not kept over the loop
+#pragma unroll
+      for (int dt = 0; dt < DT; ++dt) vs_dt[dt] = K_ROWS && dt > 0 ? xor_here(vs_lane, dt * 64) : vs_lane;
+      auto v_frag = [&](Frag& dst, auto DTV, auto P2V) {
+        constexpr int dt = decltype(DTV)::value, p2 = decltype(P2V)::value;
+        if constexpr (K_ROWS) {   // keys 16 p2 + 4 hl + 0..3 and the same plus 8
+          lds_columns<p2 * 32 * D>(dst[0], vs_dt[dt]);
+          lds_columns<p2 * 32 * D + 16 * D>(dst[1], vs_dt[dt]);
+        } else {
+          lds_frag<(dt * PH + p2) * 1024>(dst, vs_lane);
+        }
+      };
       static_for<4>([&](auto E) {
         constexpr int e = decltype(E)::value;
-        lds_frag<((e & 1) * PH + e / 2) * 1024>(A[0][e], vs_lane);
+        v_frag(A[0][e], std::integral_constant<int, e & 1>{}, std::integral_constant<int, e / 2>{});
       });
       static_for<NG>([&](auto G) {
         constexpr int g = decltype(G)::value;
@@ -578,12 +626,17 @@ __global__ __launch_bounds__(2 * BLK, (attn_h_min_waves<BLK, D>())) void attn_h_
         if constexpr (g + 1 < NG)
           static_for<4>([&](auto E) {
             constexpr int e = decltype(E)::value, g1 = g + 1;
-            lds_frag<((2 * (g1 / 2) + (e & 1)) * PH + 2 * (g1 % 2) + e / 2) * 1024>(A[g1 & 1][e], vs_lane);
+            v_frag(A[g1 & 1][e], std::integral_constant<int, 2 * (g1 / 2) + (e & 1)>{},
+                   std::integral_constant<int, 2 * (g1 % 2) + e / 2>{});
           });
         static_for<4>([&](auto E) {
           constexpr int e = decltype(E)::value, dt = 2 * (g / 2) + (e & 1), p2 = 2 * (g % 2) + e / 2;
-          O[dt] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(__builtin_bit_cast(bf16x8, A[g & 1][e]), pb[p2], O[dt],
-                                                          0, 0, 0);
+          u32x4 a;
+          if constexpr (K_ROWS)
+            a = __builtin_shufflevector(A[g & 1][e][0], A[g & 1][e][1], 0, 1, 2, 3);
+          else
+            a = A[g & 1][e];
+          O[dt] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(__builtin_bit_cast(bf16x8, a), pb[p2], O[dt], 0, 0, 0);
         });
       });
     }
@@ -942,8 +995,10 @@ __global__ __launch_bounds__(64 * NS, (D == 128 ? 2 : 4)) void attn_kernel(
 #define JENGA_PACE_FACTOR 0.6f
 #endif
 __global__ __launch_bounds__(1024) void walk_pace_kernel(const int32_t* __restrict__ sel_count, int n_rows, int M,
-                                                         float ticks_per_block, uint32_t* __restrict__ params) {
+                                                         float ticks_per_block, uint32_t* __restrict__ params,
+                                                         uint32_t* queue, int queue_first) {
   __shared__ float part[16];
+  if (queue != nullptr && threadIdx.x < 8) queue[threadIdx.x] = queue_first;
   float s = 0.f;
   for (int t0 = threadIdx.x; t0 < n_rows; t0 += 4096) {   // four loads in flight per thread
     int c[4];
@@ -965,11 +1020,8 @@ __global__ __launch_bounds__(1024) void walk_pace_kernel(const int32_t* __restri
   }
 }
 
-// Whether the attention kernel of a plan reads K in place (see K_ROWS) if it is given it.
-template <int BLK>
-bool reads_k_rows(const jenga_plan* p) {
-  return BLK == 64 || (BLK == 128 && !(p->cfg.flags & JENGA_FLAG_PACED_WALK));
-}
+// Sets the counters of a queue.
+__global__ void queue_kernel(uint32_t* queue, int queue_first) { queue[threadIdx.x] = queue_first; }
 
 // Counters of a launch that deals its query blocks out as workgroups become free; nullptr where the plan has none.
 uint32_t* attn_queue(const jenga_plan* p, void* ws) {
@@ -977,29 +1029,28 @@ uint32_t* attn_queue(const jenga_plan* p, void* ws) {
 }
 
 template <int BLK, int D>
-int run_pack(const jenga_plan* p, const void* k, const void* v, void* ws, bool with_k, uint32_t* queue, hipStream_t st) {
+int run_pack(const jenga_plan* p, const void* k, const void* v, void* ws, hipStream_t st) {
   const jenga_config& c = p->cfg;
   const jenga_plan_info_t& f = p->info;
   const int bh = c.batch * c.heads;
   const size_t half = (((size_t)bh * f.N_pad * D * 2) + 255) & ~(size_t)255;
   uint4* kp = (uint4*)ws;
   uint4* vp = (uint4*)((char*)ws + half);
-  const int first = with_k || !reads_k_rows<BLK>(p) ? 0 : 1;
-  pack_kernel<BLK, D><<<dim3(f.M, bh, 2 - first), 256, 0, st>>>((const uint16_t*)k, (const uint16_t*)v, kp, vp,
-                                                             p->d_blk_valid, f.M, f.N_pad, first, queue, p->attn_first);
+  pack_kernel<BLK, D><<<dim3(f.M, bh, 2), 256, 0, st>>>((const uint16_t*)k, (const uint16_t*)v, kp, vp, p->d_blk_valid,
+                                                       f.M, f.N_pad);
   return hipGetLastError() == hipSuccess ? JENGA_OK : JENGA_EHIP;
 }
 
 template <int BLK, int D>
-int run_attention(const jenga_plan* p, const void* q, const void* k, void* ws, bool may_split, const int32_t* sel_count,
-                  const int32_t* sel_index, void* out, float* lse, hipStream_t st) {
+int run_attention(const jenga_plan* p, const void* q, const void* k, const void* v, void* ws, bool may_split,
+                  const int32_t* sel_count, const int32_t* sel_index, void* out, float* lse, hipStream_t st) {
   const jenga_config& c = p->cfg;
   const jenga_plan_info_t& f = p->info;
   const int bh = c.batch * c.heads;
   const size_t half = (((size_t)bh * f.N_pad * D * 2) + 255) & ~(size_t)255;
-  const bool k_rows = reads_k_rows<BLK>(p) && k != nullptr;
+  const bool k_rows = k != nullptr;
   const u32x4* kp = k_rows ? (const u32x4*)k : (const u32x4*)ws;
-  const u32x4* vp = (const u32x4*)((const char*)ws + half);
+  const u32x4* vp = k_rows ? (const u32x4*)v : (const u32x4*)((const char*)ws + half);
   uint32_t* params = (uint32_t*)((char*)ws + 2 * half);
   const float log2e = 1.4426950408889634f;
   const float scale = log2e / sqrtf((float)D), bias = c.text_bias * log2e;
@@ -1046,7 +1097,10 @@ int run_attention(const jenga_plan* p, const void* q, const void* k, void* ws, b
     if (paced && !(may_split && queue == nullptr && p->attn_parts > 1)) {
       // a workgroup spends about 6.3 us (D = 128; 3.6 us at D = 64) on a block of 128 keys when three share a CU
       pace = params;
-      walk_pace_kernel<<<1, 1024, 0, st>>>(sel_count, bh * f.M, f.M, D == 128 ? 630.f : 360.f, pace);
+      walk_pace_kernel<<<1, 1024, 0, st>>>(sel_count, bh * f.M, f.M, D == 128 ? 630.f : 360.f, pace, queue,
+                                           p->attn_first);
+    } else if (queue != nullptr) {
+      queue_kernel<<<1, 8, 0, st>>>(queue, p->attn_first);
     }
     if (may_split && (p->attn_parts > 1 || queue != nullptr)) {
       split.parts = p->attn_parts;
@@ -1058,9 +1112,9 @@ int run_attention(const jenga_plan* p, const void* q, const void* k, void* ws, b
       dim3 merge(BLK / 32, f.M, bh);
       if (queue != nullptr) {
         int tail = p->attn_tail;
-        if (p->attn_over_k) {
+        if (p->attn_over_kv) {
           split.o = (float*)ws;
-          if (!k_rows) {   // K is packed there all the same: lists stay whole
+          if (!k_rows) {   // K and V are packed there all the same: lists stay whole
             tail = 0;
             split.parts = 1;
           }
@@ -1098,22 +1152,22 @@ namespace jenga {
 
 #define JENGA_FOR_SHAPES(X) X(128, 128) X(64, 128) X(32, 128) X(128, 64) X(64, 64) X(32, 64)
 
-int launch_pack(const jenga_plan* p, const void* k, const void* v, void* ws, bool with_k, bool may_split, void* stream) {
+int launch_pack(const jenga_plan* p, const void* k, const void* v, void* ws, void* stream) {
   hipStream_t st = (hipStream_t)stream;
   const int blk = p->cfg.block, d = p->cfg.head_dim;
 #define X(B, DD) \
-  if (blk == B && d == DD) return run_pack<B, DD>(p, k, v, ws, with_k, may_split ? attn_queue(p, ws) : nullptr, st);
+  if (blk == B && d == DD) return run_pack<B, DD>(p, k, v, ws, st);
   JENGA_FOR_SHAPES(X)
 #undef X
   return JENGA_EUNSUPPORTED;
 }
 
-int launch_attention(const jenga_plan* p, const void* q, const void* k, void* ws, bool may_split, const int32_t* sel_count,
-                     const int32_t* sel_index, void* out, float* lse, void* stream) {
+int launch_attention(const jenga_plan* p, const void* q, const void* k, const void* v, void* ws, bool may_split,
+                     const int32_t* sel_count, const int32_t* sel_index, void* out, float* lse, void* stream) {
   hipStream_t st = (hipStream_t)stream;
   const int blk = p->cfg.block, d = p->cfg.head_dim;
 #define X(B, DD) \
-  if (blk == B && d == DD) return run_attention<B, DD>(p, q, k, ws, may_split, sel_count, sel_index, out, lse, st);
+  if (blk == B && d == DD) return run_attention<B, DD>(p, q, k, v, ws, may_split, sel_count, sel_index, out, lse, st);
   JENGA_FOR_SHAPES(X)
 #undef X
   return JENGA_EUNSUPPORTED;

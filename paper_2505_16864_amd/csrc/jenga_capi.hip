@@ -134,13 +134,17 @@ int jenga_block_sparse_attn(const jenga_plan* p, const void* q, const void* k, c
   if (!on_plan_device(p)) return JENGA_EINVAL;
   if (((uintptr_t)workspace & 255u) != 0) return JENGA_EINVAL;
   if (workspace_bytes < p->info.attn_workspace_bytes) return JENGA_EWORKSPACE;
-  // K is read in place unless an output lies over it
+  // K and V are read in place unless an output lies over them
   const size_t rows = (size_t)p->cfg.batch * p->cfg.heads * p->info.N_pad, bytes = rows * p->cfg.head_dim * 2;
-  const bool copy_k = overlap(k, bytes, out_curve, bytes) || (lse_or_null && overlap(k, bytes, lse_or_null, rows * 4));
-  const int rc = jenga::launch_pack(p, k, v, workspace, copy_k, true, stream);
-  if (rc != JENGA_OK) return rc;
-  return jenga::launch_attention(p, q, copy_k ? nullptr : k, workspace, true, sel_count, sel_index, out_curve,
-                                 lse_or_null, stream);
+  bool in_place = jenga::reads_kv_in_place(p);
+  for (const void* x : {k, v})
+    if (overlap(x, bytes, out_curve, bytes) || (lse_or_null && overlap(x, bytes, lse_or_null, rows * 4))) in_place = false;
+  if (!in_place) {
+    const int rc = jenga::launch_pack(p, k, v, workspace, stream);
+    if (rc != JENGA_OK) return rc;
+    k = v = nullptr;
+  }
+  return jenga::launch_attention(p, q, k, v, workspace, true, sel_count, sel_index, out_curve, lse_or_null, stream);
 }
 
 int jenga_pack_kv(const jenga_plan* p, const void* k, const void* v, void* workspace, size_t workspace_bytes,
@@ -149,7 +153,7 @@ int jenga_pack_kv(const jenga_plan* p, const void* k, const void* v, void* works
   if (!on_plan_device(p)) return JENGA_EINVAL;
   if (((uintptr_t)workspace & 255u) != 0) return JENGA_EINVAL;
   if (workspace_bytes < p->packed_bytes) return JENGA_EWORKSPACE;
-  return jenga::launch_pack(p, k, v, workspace, true, false, stream);
+  return jenga::launch_pack(p, k, v, workspace, stream);
 }
 
 int jenga_block_sparse_attn_packed(const jenga_plan* p, const void* q, void* packed_kv_workspace,
@@ -159,7 +163,8 @@ int jenga_block_sparse_attn_packed(const jenga_plan* p, const void* q, void* pac
   if (!on_plan_device(p)) return JENGA_EINVAL;
   if (((uintptr_t)packed_kv_workspace & 255u) != 0) return JENGA_EINVAL;
   if (workspace_bytes < p->packed_bytes) return JENGA_EWORKSPACE;
-  return jenga::launch_attention(p, q, nullptr, packed_kv_workspace, false, sel_count, sel_index, out_curve, lse_or_null, stream);
+  return jenga::launch_attention(p, q, nullptr, nullptr, packed_kv_workspace, false, sel_count, sel_index, out_curve,
+                                 lse_or_null, stream);
 }
 
 }  // extern "C"

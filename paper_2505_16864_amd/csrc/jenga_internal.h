@@ -22,7 +22,7 @@ struct jenga_plan {
   int attn_heads;  // (batch, head) pairs per launch where lists are cut
   int attn_first;  // > 0: query blocks are dealt out by counters; that many per XCD are not
   int attn_tail;   // lists that are cut, all into attn_parts, at the end of what each XCD is dealt by counters
-  bool attn_over_k; // their results lie where packed K would, which is not needed when K is read in place
+  bool attn_over_kv; // their results lie where packed K and V would, which are not needed when K and V are read in place
   // bytes of the attention workspace that hold packed K, packed V and launch parameters; parts lie behind them
   uint64_t packed_bytes;
   // host tables
@@ -115,12 +115,12 @@ int launch_select(const jenga_plan* p, const void* q, const void* k, int32_t* se
                   int32_t* sel_index, uint8_t* mask, void* ws, void* stream);
 // Looks up the address of the static selection scratch on `device` (the current device) once.
 int select_scratch_init(int device);
-// with_k = false: K is left out where the attention kernel can read it in place; launch_attention then gets it.
-// may_split: as for launch_attention, whose counters are then set.
-int launch_pack(const jenga_plan* p, const void* k, const void* v, void* ws, bool with_k, bool may_split, void* stream);
-// k: K, if it may have been left out of the workspace, else NULL (K packed).  may_split: the call has the workspace to itself and may
-// write behind the packed tiles.
-int launch_attention(const jenga_plan* p, const void* q, const void* k, void* packed_ws, bool may_split,
+int launch_pack(const jenga_plan* p, const void* k, const void* v, void* ws, void* stream);
+// Whether launch_attention can read K and V as they are instead of packed.
+bool reads_kv_in_place(const jenga_plan* p);
+// k, v: to be read in place, or NULL (packed in the workspace).  may_split: the call has the workspace to itself and may write
+// behind the packed tiles, or where they would be.
+int launch_attention(const jenga_plan* p, const void* q, const void* k, const void* v, void* packed_ws, bool may_split,
                      const int32_t* sel_count, const int32_t* sel_index, void* out, float* lse, void* stream);
 
 }  // namespace jenga

@@ -270,6 +270,10 @@ static void split_lists(jenga_plan* plan) {
   plan->attn_chunk = (int)chunk;
 }
 
+bool reads_kv_in_place(const jenga_plan* p) {
+  return p->cfg.block == 64 || (p->cfg.block == 128 && !(p->cfg.flags & JENGA_FLAG_PACED_WALK));
+}
+
 int build_host_tables(jenga_plan* plan) {
   const jenga_config& c = plan->cfg;
   jenga_plan_info_t& f = plan->info;
@@ -341,9 +345,8 @@ int build_host_tables(jenga_plan* plan) {
   // and, where lists are cut, O and two statistics per row and part, float32
   const uint64_t rows = plan->attn_first > 0 ? 8ull * plan->attn_tail : (uint64_t)plan->attn_heads * f.M;
   const uint64_t parts = plan->attn_parts > 1 ? align256(rows * plan->attn_parts * m * (c.head_dim + 2) * 4) : 0;
-  const bool k_in_place = m == 64 || (m == 128 && !(c.flags & JENGA_FLAG_PACED_WALK));
-  plan->attn_over_k = plan->attn_first > 0 && k_in_place && parts <= plan->packed_bytes / 2 - 128;
-  if (!plan->attn_over_k) f.attn_workspace_bytes += parts;
+  plan->attn_over_kv = plan->attn_first > 0 && reads_kv_in_place(plan) && parts <= plan->packed_bytes - 256;
+  if (!plan->attn_over_kv) f.attn_workspace_bytes += parts;
   return JENGA_OK;
 }
 

@@ -269,3 +269,28 @@ def test_more_query_blocks_than_places(block, head_dim, blocks, heads, p, paced)
         alive = torch.isfinite(whole_lse)
         assert torch.equal(torch.isfinite(lse), alive) and torch.isneginf(lse[~alive]).all()
         assert float((lse[alive] - whole_lse[alive]).abs().max()) <= 1e-3      # float32 sums and one float32 logarithm
+
+
+# Pad rows of K and V may hold anything: in place, V's reach the second product with probabilities of zero.  Ragged blocks
+# of one row, one short, and around the 64 keys of a step.
+@pytest.mark.parametrize("head_dim,block", [(64, 64), (128, 64), (64, 128), (128, 128)])
+@pytest.mark.parametrize("tail_v,tail_c,heads", [(1, 63, 2), (127, 1, 2), (64, 65, 95), (5, 62, 95)])
+def test_pad_rows_hold_anything(head_dim, block, tail_v, tail_c, heads):
+    w = dict(T=1, H=1, W=block * 8 + min(tail_v, block - 1), n_text=block + min(tail_c, block), batch=1, heads=heads,
+             head_dim=head_dim, block=block, topk=0.9, p=0.3)
+    print("pads", w, flush=True)
+    layer = CarveLayer(w, "cuda:0", want_lse=True)
+    layer.permute_in(*[x.cuda() for x in ji.make_qkv(w, 64)])
+    layer.select()
+    layer.attend()
+    torch.cuda.synchronize()
+    want, want_lse = layer.o_c.clone(), layer.lse.clone()
+    i = layer.info
+    assert i.pad_v > 0
+    for x in (layer.k_c, layer.v_c):
+        x[:, :, i.N_v:i.M_v * block] = float("nan")
+        x[:, :, i.M_v * block + w["n_text"]:] = float("inf")
+    layer.o_c.view(torch.int16).fill_(0x7FC1)
+    layer.attend()
+    torch.cuda.synchronize()
+    assert torch.equal(layer.o_c, want) and torch.equal(layer.lse, want_lse)

@@ -67,6 +67,27 @@ def test_fragment_registers_untouched_between_read_and_wait(listing):
     assert checked >= 2 * (32 + 16)   # fragment reads per step: 32 at head dim 128, 16 at head dim 64; two walks each
 
 
+# The same for V read in place, by columns: 16 or 32 reads a step and kernel at head dim 64 or 128.
+def test_column_registers_untouched_between_read_and_wait(listing):
+    checked = {}
+    for sym, body in _kernel_bodies(listing, "attn_h_kernel"):
+        pending = set()
+        checked[sym] = 0
+        for line in body.split("\n"):
+            ins = line.split(";")[0].strip()
+            op, _, rest = ins.partition(" ")
+            if op == "s_waitcnt" and "lgkmcnt(0)" in rest:
+                pending.clear()
+            elif ins and not ins.endswith(":") and not ins.startswith("."):
+                assert not (_regs(rest) & pending), "%s: `%s` touches a column register before the wait" % (sym, ins)
+                if op == "ds_read_b64_tr_b16":
+                    pending |= _regs(rest.partition(",")[0])
+                    checked[sym] += 1
+    for block, d, paced, cut, rows in ATTN_H:
+        name = "attn_h_kernelILi%dELi%dELb%dELb%dELb%dEEE" % (block, d, paced, cut, rows)
+        assert [n for sym, n in checked.items() if name in sym] == [rows * d // 4], name
+
+
 def _step_loop(body, mfmas):
     """Text of the smallest loop with at least `mfmas` MFMAs in it, from its label to the last backward branch to it."""
     best = ""
