@@ -192,13 +192,13 @@ int jenga_select_blocks_static(const jenga_plan* plan, const void* q_curve, cons
  *                biased as above): Alg. 4's running maximum and running sum combined, the value a
  *                caller needs to merge this result with attention over other keys.  Pad query rows
  *                and rows of an empty list get -inf.  Fully overwritten when given
- *   workspace  : at least attn_workspace_bytes, 256-byte aligned (V and where needed K re-tiled for the
+ *   workspace  : at least attn_workspace_bytes, 256-byte aligned (where needed K and V re-tiled for the
  *                matrix cores, 256 bytes of launch parameters, and the results of the parts that long
  *                lists are cut into on grids that leave the chip idle, and some lists at the end of grids that
  *                do not, 129 MiB of them at most), contents undefined after
  * Equivalent to jenga_pack_kv followed by jenga_block_sparse_attn_packed on the same workspace (the latter
  * never cuts lists, since calls on one packed workspace may overlap: where this call does, the two differ
- * in the last bits; so may, where lists are cut at the end of a grid, a call whose output lies over K).
+ * in the last bits; so may a call whose outputs lie over both K and V).
  */
 int jenga_block_sparse_attn(const jenga_plan* plan, const void* q, const void* k, const void* v,
                             const int32_t* sel_count, const int32_t* sel_index, void* out_curve,

@@ -223,28 +223,27 @@ constexpr float P_SUM_MAX = 1073741824.0f;   // 2^30
 template <int BLK, int D>
 constexpr int attn_h_min_waves() { return D == 128 ? 3 : 4; }   // wavefronts per SIMD that the registers have to allow
 
-// SPLIT: grids that leave the chip idle.  The list of a query block is cut into Split::of(cnt) parts of equal length, a
-// workgroup each; the parts' O, reference and sum go to the workspace and merge_kernel puts them together.
-// With a queue (see take_item) the rows at its end are cut, all into `parts`.
+// SPLIT: lists are cut into parts, a workgroup each; the parts' O, reference and sum go to the workspace and merge_kernel puts
+// them together.  Grids that leave the chip idle: every list into Split::of(cnt) parts of equal length.  Others: what
+// the launch's Deal says.
 struct Split {
   int parts, chunk;   // most parts of a list, list entries from which on there is one more part (0: always all parts)
   int stride;         // workgroups per part
-  int first, whole;   // with a queue: positions of an XCD that are not dealt out by it, and before the first list that is cut
-  float* o;           // [slot][parts][BLK/32][D/32][4][64][4]: O in accumulator order
-  float* stat;        // [slot][parts][2][BLK]: reference, sum; slot = batch*head*M + block, or 8 * (position - whole) + XCD
+  jenga::Deal deal;   // if deal.parts > 0
+  int first;          // with a queue: positions of an XCD that it does not deal out
+  float* o;           // [slot][BLK/32][D/32][4][64][4]: O in accumulator order
+  float* stat;        // [slot][2][BLK]: reference, sum; slot = (batch*head*M + block) * parts + part, or by deal_position()
   __device__ int of(int cnt) const { return chunk == 0 ? parts : max(1, min(parts, (cnt + chunk - 1) / chunk)); }
 };
 
 // Work for one workgroup of a launch that is dealt out by counters, one per XCD (workgroup n runs on XCD n % 8): XCDs that
 // have the same work to do need up to a tenth more or less time for it than others.  The value 8 r + x stands for position r
-// of XCD x: positions below `whole` are query blocks 8 r + x of map_work(), from there on every query block has `parts`
-// positions.  An XCD whose own are all taken goes on with those of the one that has most left.  -1: all are taken.
+// of XCD x (deal_position).  An XCD whose own are all taken goes on with those of the one that has most left.  -1: all are taken.
 // A launch has a quarter more workgroups than there are positions, so that a fast XCD finds some to run; the others end
 // here, in a few us.  (One workgroup that loops over positions keeps the kernel's arguments in scalar registers over
 // the loop: 20 to 70 spilled ones.)  The workgroups of the first generation do not ask, all at once, but take the position of their
 // own number: 34 shapes of 1 to 4 generations, 0.15 to 2.8 ms, 2 % less on average, 10 % where a workgroup lasts 100 us.
-__device__ inline int take_item(uint32_t* queue, const WorkMap& work, int whole, int parts) {
-  const int n_end = 8 * (whole + parts * ((work.n_wg + 7) / 8 - whole));
+__device__ inline int take_item(uint32_t* queue, int n_end) {
   int x = blockIdx.x & 7;
   for (;;) {
     const int n = 8 * (int)__hip_atomic_fetch_add(queue + x, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) + x;
@@ -289,24 +288,18 @@ __global__ __launch_bounds__(2 * BLK, (attn_h_min_waves<BLK, D>())) void attn_h_
   __shared__ int pace_slot[2];                    // PACED: G for the next pick, published by thread 0
 
   int n = blockIdx.x, part = 0, n_parts = 1, slot = -1;   // slot: of the partial result, -1: the whole list
+  const bool dealt = SPLIT && split.deal.parts > 0;
   if constexpr (SPLIT) {
-    if (queue != nullptr) {
-      if (n >= 8 * split.first) {
+    if (dealt) {
+      if (queue != nullptr && n >= 8 * split.first) {
         volatile int* taken = (volatile int*)Ks;   // no tile is in there yet
-        if (threadIdx.x == 0) *taken = take_item(queue, work, split.whole, split.parts);
+        if (threadIdx.x == 0) *taken = take_item(queue, 8 * split.deal.positions());
         __syncthreads();
         n = __builtin_amdgcn_readfirstlane(*taken);
         __syncthreads();
         if (n < 0) return;
       }
-      const int cut = (n >> 3) - split.whole;
-      if (cut >= 0) {
-        n_parts = split.parts;
-        part = cut % n_parts;
-        const int row = cut / n_parts * 8 + (n & 7);
-        slot = row * n_parts + part;
-        n = 8 * split.whole + row;
-      }
+      if (!jenga::deal_position(n >> 3, n & 7, split.deal, work, &n, &part, &n_parts, &slot)) return;
     } else {
       part = n / split.stride;
       n -= part * split.stride;
@@ -315,7 +308,7 @@ __global__ __launch_bounds__(2 * BLK, (attn_h_min_waves<BLK, D>())) void attn_h_
   int bh, i;
   if (!map_work(n, work, &bh, &i)) return;
   const int M = work.M, M_v = work.M_v;
-  if (SPLIT && queue == nullptr) {
+  if (SPLIT && !dealt) {
     n_parts = split.of(min(max(sel_count[(size_t)bh * M + i], 0), M));
     if (part >= n_parts) return;
     if (n_parts > 1) slot = (bh * M + i) * split.parts + part;
@@ -505,12 +498,13 @@ __global__ __launch_bounds__(2 * BLK, (attn_h_min_waves<BLK, D>())) void attn_h_
 
       if (nv < BLK) {   // sequence-length mask: pad keys of a ragged block
         asm volatile("");   // a real, rarely taken branch
+        int valid = nv - 64 * h - 4 * hl;
 #pragma unroll
         for (int m2 = 0; m2 < MH; ++m2)
 #pragma unroll
           for (int r = 0; r < 16; ++r) {
-            const int kv = 64 * h + 32 * m2 + 8 * (r / 4) + 4 * hl + (r % 4);
-            if (kv >= nv) S[m2][r] = -INFINITY;
+            if (r % 4 == 0) asm volatile("" : "+v"(valid));   // four comparisons at a time: 32 masks would be 64 scalar registers
+            if (32 * m2 + 8 * (r / 4) + (r % 4) >= valid) S[m2][r] = -INFINITY;
           }
       }
     };
@@ -693,16 +687,20 @@ __global__ __launch_bounds__(2 * D) void merge_kernel(const int32_t* __restrict_
                                                       int pad_c, Split split) {
   constexpr int DT = D / 32, NW = BLK / 32;
   const int M = work.M, M_v = work.M_v, wave = blockIdx.x;
-  int i = blockIdx.y, bh = blockIdx.z, n_parts = split.parts;
+  int i = blockIdx.y, bh = blockIdx.z, n_parts;
   size_t slot = (size_t)bh * M + i;
-  if (split.first > 0) {   // slots of a queue's end
-    slot = blockIdx.y;
-    if (!map_work(8 * split.whole + (int)slot, work, &bh, &i)) return;
+  if (split.deal.parts > 0) {   // row y of those that are cut
+    const int y = blockIdx.y, text = split.deal.text_rows();
+    const bool is_text = y < text;
+    n_parts = is_text ? split.deal.text_parts : split.deal.parts;
+    slot = is_text ? (size_t)y * n_parts : (size_t)text * split.deal.text_parts + (size_t)(y - text) * n_parts;
+    if (is_text && y >= work.text_wgs) return;
+    if (!map_work(is_text ? y : work.text_wgs + 8 * split.deal.whole + y - text, work, &bh, &i)) return;
   } else {
     n_parts = split.of(min(max(sel_count[slot], 0), M));
+    if (n_parts == 1) return;
+    slot *= split.parts;
   }
-  if (n_parts == 1) return;
-  slot *= split.parts;
   const int lane = threadIdx.x & 63, dt = threadIdx.x >> 6, hl = lane >> 5, row = 32 * wave + (lane & 31);
   const float4* o = (const float4*)split.o + (slot * NW + wave) * (DT * 4 * 64) + dt * 4 * 64 + lane;
   const float* stat = split.stat + slot * 2 * BLK + row;
@@ -1020,6 +1018,10 @@ __global__ __launch_bounds__(1024) void walk_pace_kernel(const int32_t* __restri
   }
 }
 
+__global__ __launch_bounds__(256) void copy_kernel(const uint4* __restrict__ src, uint4* __restrict__ dst, size_t n) {
+  for (size_t t = (size_t)blockIdx.x * 256 + threadIdx.x; t < n; t += (size_t)gridDim.x * 256) dst[t] = src[t];
+}
+
 // Sets the counters of a queue.
 __global__ void queue_kernel(uint32_t* queue, int queue_first) { queue[threadIdx.x] = queue_first; }
 
@@ -1094,7 +1096,7 @@ int run_attention(const jenga_plan* p, const void* q, const void* k, const void*
 #define JENGA_ATTN(PACED, SPLIT, K_ROWS, WGS)                                                                    \
   attn_h_kernel<BLK, D, PACED, SPLIT, K_ROWS><<<dim3(WGS), 2 * BLK, 0, st>>>(                                    \
       qb, kp, vp, sel_count, sel_index, ob, lse, work, f.N_pad, f.pad_v, f.pad_c, scale, bias, pace, split, queue)
-    if (paced && !(may_split && queue == nullptr && p->attn_parts > 1)) {
+    if (paced && !(may_split && p->attn_first == 0 && p->attn_parts > 1)) {   // parts of short grids: ascending order
       // a workgroup spends about 6.3 us (D = 128; 3.6 us at D = 64) on a block of 128 keys when three share a CU
       pace = params;
       walk_pace_kernel<<<1, 1024, 0, st>>>(sel_count, bh * f.M, f.M, D == 128 ? 630.f : 360.f, pace, queue,
@@ -1102,37 +1104,35 @@ int run_attention(const jenga_plan* p, const void* q, const void* k, const void*
     } else if (queue != nullptr) {
       queue_kernel<<<1, 8, 0, st>>>(queue, p->attn_first);
     }
-    if (may_split && (p->attn_parts > 1 || queue != nullptr)) {
-      split.parts = p->attn_parts;
-      split.chunk = p->attn_chunk;
-      split.stride = (work.n_wg + 7) & ~7;   // a multiple of the XCDs, which a query block's parts then share
+    const bool dealt = p->attn_first > 0 || p->attn_text_parts > 1;
+    if (may_split && (dealt || p->attn_parts > 1)) {
+      int wgs, slots;
+      dim3 merge;
       split.o = (float*)((char*)ws + p->packed_bytes);
-      int wgs = split.parts * split.stride;
-      size_t slots = (size_t)bh * f.M;
-      dim3 merge(BLK / 32, f.M, bh);
-      if (queue != nullptr) {
-        int tail = p->attn_tail;
-        if (p->attn_over_kv) {
-          split.o = (float*)ws;
-          if (!k_rows) {   // K and V are packed there all the same: lists stay whole
-            tail = 0;
-            split.parts = 1;
-          }
-        }
+      if (dealt) {
+        if (p->attn_over_kv) split.o = (float*)(k == (const void*)ws ? (char*)ws + half : (char*)ws);
+        // where both K and V are packed there all the same, lists stay whole
+        split.deal = jenga::plan_deal(p, work, p->attn_over_kv && !k_rows);
         split.first = p->attn_first;
-        split.whole = split.stride / 8 - tail;
-        slots = (size_t)8 * tail;
-        wgs = 8 * (split.whole + split.parts * tail);
-        wgs += (wgs + 3) / 4;
-        merge = dim3(BLK / 32, 8 * tail, 1);
+        wgs = 8 * split.deal.positions();
+        if (queue != nullptr) wgs += (wgs + 3) / 4;
+        slots = split.deal.slots();
+        merge = dim3(BLK / 32, split.deal.text_rows() + split.deal.tail_rows(), 1);
+      } else {
+        split.parts = p->attn_parts;
+        split.chunk = p->attn_chunk;
+        split.stride = (work.n_wg + 7) & ~7;   // a multiple of the XCDs, which a query block's parts then share
+        wgs = split.parts * split.stride;
+        slots = bh * f.M * split.parts;
+        merge = dim3(BLK / 32, f.M, bh);
       }
-      split.stat = split.o + slots * split.parts * BLK * D;
+      split.stat = split.o + (size_t)slots * BLK * D;
       if constexpr (BLK == 128) {
         if (paced) JENGA_ATTN(true, true, false, wgs);
       }
       if (k_rows) JENGA_ATTN(false, true, true, wgs);
       else if (!paced) JENGA_ATTN(false, true, false, wgs);
-      if (split.parts > 1)
+      if (slots > 0)
         merge_kernel<BLK, D><<<merge, 2 * D, 0, st>>>(sel_count, ob, lse, work, f.N_pad, f.pad_v, f.pad_c, split);
       return hipGetLastError() == hipSuccess ? JENGA_OK : JENGA_EHIP;
     }
@@ -1160,6 +1160,14 @@ int launch_pack(const jenga_plan* p, const void* k, const void* v, void* ws, voi
   JENGA_FOR_SHAPES(X)
 #undef X
   return JENGA_EUNSUPPORTED;
+}
+
+int launch_keep(const jenga_plan* p, const void* src, void* ws, int which, const void** copied, void* stream) {
+  const size_t bytes = (size_t)p->cfg.batch * p->cfg.heads * p->info.N_pad * p->cfg.head_dim * 2;
+  char* dst = (char*)ws + which * ((bytes + 255) & ~(size_t)255);
+  copy_kernel<<<2048, 256, 0, (hipStream_t)stream>>>((const uint4*)src, (uint4*)dst, bytes / 16);
+  *copied = dst;
+  return hipGetLastError() == hipSuccess ? JENGA_OK : JENGA_EHIP;
 }
 
 int launch_attention(const jenga_plan* p, const void* q, const void* k, const void* v, void* ws, bool may_split,

@@ -21,8 +21,9 @@ struct jenga_plan {
   int attn_parts, attn_chunk;
   int attn_heads;  // (batch, head) pairs per launch where lists are cut
   int attn_first;  // > 0: query blocks are dealt out by counters; that many per XCD are not
-  int attn_tail;   // lists that are cut, all into attn_parts, at the end of what each XCD is dealt by counters
-  bool attn_over_kv; // their results lie where packed K and V would, which are not needed when K and V are read in place
+  int attn_text_parts;  // parts that the lists of text query blocks are cut into
+  int attn_tail;   // lists that are cut, all into attn_parts, at the end of each XCD's
+  bool attn_over_kv; // their results lie where packed K would, or packed V: not needed when K and V are read in place
   // bytes of the attention workspace that hold packed K, packed V and launch parameters; parts lie behind them
   uint64_t packed_bytes;
   // host tables
@@ -91,8 +92,46 @@ JENGA_HOST_DEVICE inline bool map_work(int n, const WorkMap& w, int* bh, int* i)
   return *i < w.M_v;
 }
 
+// Work of a launch in positions, the same number for each XCD: text query blocks in `text_parts` parts each, `whole` vision
+// blocks, `tail` vision blocks in `parts` parts each.
+struct Deal {
+  int text, text_parts, whole, tail, parts;
+  JENGA_HOST_DEVICE int positions() const { return text * text_parts + whole + tail * parts; }
+  JENGA_HOST_DEVICE int text_rows() const { return text_parts > 1 ? 8 * text : 0; }   // that are cut
+  JENGA_HOST_DEVICE int tail_rows() const { return parts > 1 ? 8 * tail : 0; }
+  JENGA_HOST_DEVICE int slots() const { return text_rows() * text_parts + tail_rows() * parts; }
+};
+
+// What position r of XCD x is: part `part` of `parts` of workgroup *n of map_work(); its partial result goes to slot *slot, -1 if
+// the list is whole.  Returns false where there is nothing to do.
+JENGA_HOST_DEVICE inline bool deal_position(int r, int x, const Deal& d, const WorkMap& w, int* n, int* part, int* parts,
+                                            int* slot) {
+  const int text = d.text * d.text_parts;
+  int row0 = 0, slot0 = 0, rows = w.text_wgs;
+  *parts = d.text_parts;
+  if (r >= text) rows = w.n_wg;
+  if (r >= text + d.whole) {
+    r -= text + d.whole;
+    row0 = w.text_wgs + 8 * d.whole;
+    slot0 = d.text_rows() * d.text_parts;
+    *parts = d.parts;
+  } else if (r >= text) {
+    r -= text;
+    row0 = w.text_wgs;
+    *parts = 1;
+  }
+  const int row = r / *parts * 8 + x;
+  *part = r % *parts;
+  *slot = *parts > 1 ? slot0 + row * *parts + *part : -1;
+  *n = row0 + row;
+  return *n < rows;
+}
+
 // The mapping for `n_bh` (batch, head) pairs of the plan.
 WorkMap plan_work(const jenga_plan* p, int n_bh);
+
+// The positions of a launch for all of them; whole: nothing is cut.
+Deal plan_deal(const jenga_plan* p, const WorkMap& work, bool whole);
 
 // (batch, head) pairs of the plan that one launch with `threads` threads per query block can take.
 int heads_per_launch(const jenga_plan* p, int threads);
@@ -118,8 +157,11 @@ int select_scratch_init(int device);
 int launch_pack(const jenga_plan* p, const void* k, const void* v, void* ws, void* stream);
 // Whether launch_attention can read K and V as they are instead of packed.
 bool reads_kv_in_place(const jenga_plan* p);
-// k, v: to be read in place, or NULL (packed in the workspace).  may_split: the call has the workspace to itself and may write
-// behind the packed tiles, or where they would be.
+// K (which = 0) or V as it is into its half of a packed workspace, for a call that reads in place but writes over it; returns
+// the copy in *copied.
+int launch_keep(const jenga_plan* p, const void* src, void* ws, int which, const void** copied, void* stream);
+// k, v: to be read in place (one of them may be a copy in the workspace), or NULL (packed in the workspace).  may_split: the
+// call has the workspace to itself and may write behind the packed tiles, or where they would be.
 int launch_attention(const jenga_plan* p, const void* q, const void* k, const void* v, void* packed_ws, bool may_split,
                      const int32_t* sel_count, const int32_t* sel_index, void* out, float* lse, void* stream);
 

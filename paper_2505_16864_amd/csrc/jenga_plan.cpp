@@ -222,13 +222,32 @@ int heads_per_launch(const jenga_plan* p, int threads) {
 // cut, into two: 1 to 3 % less from two generations on, but below two, where this reaches into the first one, up to
 // 5 % more (1416 query blocks at D = 128 601 -> 633 us).  Lists of uneven length (p well above k) into three, whatever the
 // grid: 128 tokens 1 to 13 % less (248 blocks x 12 heads 4.50 -> 4.21 ms), 64 tokens 1 to 10 % less, none more.
+//
+// From three quarters of the places on, the lists of the text rows are what can be too long: all blocks, where a vision
+// row sees `usual`.  In one generation the fullest CU decides: ceil(rows / 256) workgroups, one of them a text row.
+// Cutting text rows adds workgroups, so they get the number of parts with the least load, and none where a CU gets one more
+// for it (768 query blocks, 16 of them text: 115 -> 123 us).  With more query blocks a text row is cut where it alone lasts as
+// long as the launch.  Attention, whole -> cut: 732 query blocks, 61 a head, D = 128 201 -> 180 us; 972, 81 a head, D = 64
+// 183 -> 158; 1104, 138 a head, D = 128 507 -> 498; blocks of 64 at D = 64: 1944, 162 a head 180 -> 137, 8196, 683 a
+// head at k = 0.1 1401 -> 1270; 38 shapes 3 % less on average, none above 1 % more.
 constexpr uint64_t RANGE_AREA_BYTES = 128ull << 20;
+
+Deal plan_deal(const jenga_plan* p, const WorkMap& work, bool whole) {
+  Deal d;
+  d.text = (work.text_wgs + 7) / 8;
+  d.text_parts = whole ? 1 : p->attn_text_parts;
+  d.tail = whole ? 0 : p->attn_tail;
+  d.parts = d.tail > 0 ? p->attn_parts : 1;
+  d.whole = (work.n_wg - work.text_wgs + 7) / 8 - d.tail;
+  return d;
+}
 
 static void split_lists(jenga_plan* plan) {
   const jenga_config& c = plan->cfg;
   const jenga_plan_info_t& f = plan->info;
   plan->attn_parts = 1;
   plan->attn_first = plan->attn_tail = 0;
+  plan->attn_text_parts = 1;
   plan->attn_chunk = f.M;
   plan->attn_heads = c.batch * c.heads;
   const long long rows = (long long)c.batch * c.heads * f.M;
@@ -250,19 +269,35 @@ static void split_lists(jenga_plan* plan) {
     return;
   }
   const long long places = 256ll * attn_h_per_cu(c.block, c.head_dim);
-  if (rows > places) {
+  if (4 * rows >= 3 * places) {
     const bool uneven = c.cum_prob > 2.0 * c.topk_ratio;
-    if (c.block == 64 && !uneven) return;
-    plan->attn_first = 32 * (c.block == 64 && c.head_dim == 128 ? 4 : attn_h_per_cu(c.block, c.head_dim));
-    if (uneven || rows >= 2 * places) {
-      const int positions = (plan_work(plan, c.batch * c.heads).n_wg + 7) / 8;
-      plan->attn_tail = std::min(positions - plan->attn_first, plan->attn_first / 2);
-      plan->attn_parts = uneven ? 3 : 2;
-      plan->attn_chunk = 0;
+    const WorkMap work = plan_work(plan, c.batch * c.heads);
+    const double usual = std::max((double)len, c.cum_prob * c.cum_prob * f.M), gens = (double)rows / places;
+    const long long text_rows = (long long)c.batch * c.heads * f.M_c;
+    if (work.text_wgs <= 32768) {   // rows of a merge
+      if (gens <= 1.0) {
+        double least = f.M + ((rows + 255) / 256 - 1) * usual - 384 / c.block;
+        for (int parts = 2; parts <= 8; ++parts) {
+          const double load = std::max((double)f.M / parts, usual) + ((rows + text_rows * (parts - 1) + 255) / 256 - 1) * usual;
+          if (load < least) {
+            least = load;
+            plan->attn_text_parts = parts;
+          }
+        }
+      } else if (f.M > (gens < 1.5 ? 1.15 : 1.8) * gens * usual) {
+        plan->attn_text_parts = std::min(8, (int)std::ceil(f.M / (gens * usual)));
+      }
+    }
+    if (rows > places && (c.block == 128 || uneven)) {
+      plan->attn_first = 32 * (c.block == 64 && c.head_dim == 128 ? 4 : attn_h_per_cu(c.block, c.head_dim));
+      if (uneven || rows >= 2 * places) {
+        const int positions = (work.n_wg + 7) / 8;
+        plan->attn_tail = std::min(positions - plan->attn_first, plan->attn_first / 2);
+        plan->attn_parts = uneven ? 3 : 2;
+      }
     }
     return;
   }
-  if (4 * rows >= 3 * places) return;
   const long long shortest = (rows <= 256 ? 6 : 24) * 64 / c.block;
   const long long chunk = std::max(shortest, (5 * rows * len + 3 * places - 1) / (3 * places));
   if (8 * rows >= 3 * places && 2 * f.M <= 3 * chunk) return;
@@ -343,9 +378,12 @@ int build_host_tables(jenga_plan* plan) {
   f.attn_workspace_bytes = plan->packed_bytes;
   split_lists(plan);
   // and, where lists are cut, O and two statistics per row and part, float32
-  const uint64_t rows = plan->attn_first > 0 ? 8ull * plan->attn_tail : (uint64_t)plan->attn_heads * f.M;
-  const uint64_t parts = plan->attn_parts > 1 ? align256(rows * plan->attn_parts * m * (c.head_dim + 2) * 4) : 0;
-  plan->attn_over_kv = plan->attn_first > 0 && reads_kv_in_place(plan) && parts <= plan->packed_bytes - 256;
+  const bool dealt = plan->attn_first > 0 || plan->attn_text_parts > 1;
+  const uint64_t slots = dealt                  ? plan_deal(plan, plan_work(plan, (int)bh), false).slots()
+                         : plan->attn_parts > 1 ? (uint64_t)plan->attn_heads * f.M * plan->attn_parts
+                                                : 0;
+  const uint64_t parts = align256(slots * m * (c.head_dim + 2) * 4);
+  plan->attn_over_kv = dealt && reads_kv_in_place(plan) && parts <= (plan->packed_bytes - 256) / 2;
   if (!plan->attn_over_kv) f.attn_workspace_bytes += parts;
   return JENGA_OK;
 }

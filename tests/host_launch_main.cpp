@@ -6,6 +6,8 @@
 // and the output is what stage_switch_tiles() says: tiled, output rows per workgroup, floats of LDS.  With the argument
 // "work" the lines are configurations without the last column, and the output is how often the query block that is dealt
 // out least and most often is, the share, and how many text blocks are on an XCD without a vision block of their head.
+// With the argument "deal" the lines are the same configurations; a launch's positions are gone through as the kernel does and
+// the output is: parts of a text list, lists cut at the end, the parts dealt out least and most often, slots used and slots there are.
 #include <algorithm>
 #include <cstdio>
 #include <cstring>
@@ -46,7 +48,44 @@ static int work() {
   return 0;
 }
 
+static int deal() {
+  jenga_plan p = {};
+  jenga_config& c = p.cfg;
+  while (std::scanf("%d %d %d %d %d %d %d %d %lf %lf", &c.T, &c.H, &c.W, &c.n_text, &c.batch, &c.heads, &c.head_dim,
+                    &c.block, &c.topk_ratio, &c.cum_prob) == 10) {
+    if (jenga::build_host_tables(&p) != JENGA_OK) return 1;
+    const jenga::WorkMap w = jenga::plan_work(&p, c.batch * c.heads);
+    const jenga::Deal d = jenga::plan_deal(&p, w, false);
+    std::vector<int> done((size_t)w.n_bh * w.M, 0), parts_of((size_t)w.n_bh * w.M, 0);
+    std::set<int> slots, rows;
+    int n, part, parts, slot, bh, i, least = 1 << 30, most = 0;
+    for (int r = 0; r < d.positions(); ++r)
+      for (int x = 0; x < 8; ++x) {
+        if (!jenga::deal_position(r, x, d, w, &n, &part, &parts, &slot) || !jenga::map_work(n, w, &bh, &i)) continue;
+        const size_t row = (size_t)bh * w.M + i;
+        if (part < 0 || part >= parts || (slot >= 0) != (parts > 1)) return 2;
+        done[row] += 1;
+        parts_of[row] = parts;
+        if (slot >= 0 && (slot >= d.slots() || !slots.insert(slot).second)) return 3;
+        // where merge_kernel finds the row: text rows first, then the others
+        if (slot >= 0) {
+          const int text = d.text_rows(), y = i >= w.M_v ? n : text + n - w.text_wgs - 8 * d.whole;
+          const int first = y < text ? y * d.text_parts : text * d.text_parts + (y - text) * d.parts;
+          if (y < 0 || y >= text + d.tail_rows() || first + part != slot) return 4;
+        }
+      }
+    for (size_t row = 0; row < done.size(); ++row) {
+      least = std::min(least, done[row] - parts_of[row]);
+      most = std::max(most, done[row] - parts_of[row]);
+      if (done[row] == 0) return 5;
+    }
+    std::printf("%d %d %d %d %d %d\n", d.text_parts, d.parts > 1 ? d.tail : 0, least, most, (int)slots.size(), d.slots());
+  }
+  return 0;
+}
+
 int main(int argc, char** argv) {
+  if (argc > 1 && std::strcmp(argv[1], "deal") == 0) return deal();
   if (argc > 1 && std::strcmp(argv[1], "work") == 0) return work();
   if (argc > 1 && std::strcmp(argv[1], "switch") == 0) return stage_switch();
   jenga_plan p = {};

@@ -62,6 +62,20 @@ def test_work_mapping(driver):
     assert shares == {1, 2, 4, 8}
 
 
+# Every part of every list is dealt out once and has a slot of its own, which is where the merge looks for it.
+def test_positions_cover_every_part_once(driver):
+    rows = [(1, 1, block * m_v - 3, n_text, 1, heads, d, block, topk, p)
+            for block in (64, 128) for d in (64, 128) for m_v, heads in ((31, 27), (49, 16), (80, 12), (137, 8), (257, 9), (300, 24))
+            for n_text in (0, 3, 300) for topk, p in ((0.3, 0.3), (0.1, 0.3), (0.25, 0.9))]
+    text, tails = set(), 0
+    for row, got in zip(rows, _run(driver, rows, "deal")):
+        text_parts, tail, least, most, used, slots = [int(x) for x in got]
+        assert (least, most) == (0, 0) and used <= slots, row
+        text.add(text_parts)
+        tails += tail > 0
+    assert len(text) > 3 and tails > 10
+
+
 # Planes of a stage switch: 2^24 of them are more than one grid takes with a workgroup each.
 def test_stage_switch_launches_stay_below_the_grid_limit(driver):
     rows = [(channels, t, h, w, t, h, w, 1) for channels in (1, 16, 1 << 20, (1 << 24) - 1, 1 << 24, (1 << 31) - 1)
