@@ -397,34 +397,36 @@ __device__ __forceinline__ void select_row(double* row, uint64_t fixed_lane, int
 }
 
 // Scores and selection of ROWS query blocks of one (batch, head) against all M <= 64 * NT key blocks.  First the
-// wavefronts share the columns: S = Q^ K^T / sqrt(D) in 16 x 16 tiles of v_mfma_f64_16x16x4_f64, operands straight
-// from global memory (16 rows x 64 bytes a load, K^ of a head stays in the L2 of the XCD that works on it), results
+// wavefronts share the columns: S = Q^ K^T / sqrt(D) in 16 x 16 tiles of v_mfma_f64_16x16x4_f64, K^ straight from
+// global memory (16 rows x 64 bytes a load, K^ of a head stays in the L2 of the XCD that works on it), Q^ from LDS, which
+// every wavefront needs whole: read from memory by each it was as much for the L1 as all of K^.  Results
 // to LDS.  Then every wavefront selects for one row.  S never leaves the CU.
 //
 // LDS holds 16 rows up to 1024 blocks and 8 rows of 2048: the 8-row kernel computes its tiles with the rows twice.
 // Row stride = 16 mod 32 doubles, so the four rows a tile is written to at a time fall on different banks.
 //
-// Time of the kernel, median and shortest of ten to twenty launches, against a 128 x 128 tile of vector FMAs that wrote S
-// to memory and a selection with one chain of LDS exchanges per bit of the cumulative rule:
-//   17 blocks x 8 heads, D = 128     8.7, 8.3 us (was 43.6 + 11.7: one workgroup per head, most of its tile padding)
-//   222 x 12, D = 128                  24, 20 us (48 + 21)
-//   262 x 24, D = 128                  40, 39 us (53 + 19)
-//   2048 x 2, D = 64                 127, 112 us (38 + 141)
-//   931 x 24, D = 128, k = 0.1 and 0.3  266, 242 us (164 + 145): at k = 0.1, in a run of 226 us, matrix cores 105 us (75 us
-//                                     at their full rate, the rest is the last round of 5.5 and the first loads), softmax
-//                                     40, top K 30, the rest of the rows' work 50; the two halves do not overlap, LDS
-//                                     leaves one workgroup on a CU
+// Up to 448 blocks two workgroups fit a CU if they keep to 64 registers, hence half a row of K^ in flight at a time; then one
+// multiplies while the other selects.  NT is as many values per lane as M needs, up to 512 blocks; rounded up to a power of two,
+// 262 blocks cost a third more for the rows.
+//
+// Time of the kernel, median of ten to twenty launches, now and before Q^ went through LDS:
+//   17 blocks x 8 heads, D = 128      8.0 us (8.7; a launch alone takes 2.5)
+//   48 x 16, D = 64                  11.1 us (11.9)
+//   222 x 12, D = 128                20.3 us (24)
+//   262 x 24, D = 128                26.1 us (39.6: one workgroup per CU, two rounds of them)
+//   2048 x 2, D = 64                 114 us (115): cycles of a workgroup: products 44 k, half of them for the doubled rows, softmax
+//                                     17 k, top K 13 k, cumulative rule 20 k, lists 11 k; one workgroup a CU, two rounds
+//   931 x 24, D = 128                250 to 290 us (240 to 270): products 28 k, the last wavefront's 20 k longer, rows 21 k
 typedef double f64x4 __attribute__((ext_vector_type(4)));
 typedef double f64x2 __attribute__((ext_vector_type(2)));
 
 template <int D, int NT, int ROWS>
-__global__ __launch_bounds__(64 * ROWS) void select_kernel(const double* __restrict__ qh, const double* __restrict__ kh,
-                                                           const uint64_t* __restrict__ fixed_bits,
-                                                           int32_t* __restrict__ sel_count,
-                                                           int32_t* __restrict__ sel_index, uint8_t* __restrict__ mask,
-                                                           int M_v, int M, int n_tiles, int n_units, int K_top, double p,
-                                                           int nt64) {
+__global__ __launch_bounds__(64 * ROWS, NT < 8 ? 8 : 1) void select_kernel(
+    const double* __restrict__ qh, const double* __restrict__ kh, const uint64_t* __restrict__ fixed_bits,
+    int32_t* __restrict__ sel_count, int32_t* __restrict__ sel_index, uint8_t* __restrict__ mask, int M_v, int M, int n_tiles,
+    int n_units, int K_top, double p, int nt64) {
   __shared__ double S[ROWS][64 * NT + 16];
+  __shared__ __align__(1024) f64x2 A[ROWS * D / 2];   // the pooled query rows, as they lie in memory
   // workgroup n runs on XCD n % 8: each XCD gets a contiguous run of (head, row tile) units
   const int per_xcd = (n_units + 7) / 8;
   const int unit = (blockIdx.x & 7) * per_xcd + (blockIdx.x >> 3);
@@ -437,25 +439,35 @@ __global__ __launch_bounds__(64 * ROWS) void select_kernel(const double* __restr
   if (i < M_v && lane < nt64) fixed_lane = fixed_bits[(size_t)i * nt64 + lane];
 
   if (i0 < M_v) {
-    // lane l: row l % 16 of both operands, channels 8 s + 2 (l / 16) and the next in step s
+    // wavefront w brings row w, then takes every ROWS-th tile of columns
+    constexpr int CHUNK = D / 16 < 8 ? D / 16 : 8;   // steps whose loads are in flight at a time
     const int g = lane >> 4, c = lane & 15;
-    const int ia = min(i0 + c % ROWS, M_v - 1);
-    const double* qa = qh + ((size_t)bh * M_v + ia) * D;
-    f64x2 a[D / 8];
-#pragma unroll
-    for (int s = 0; s < D / 8; ++s) a[s] = *(const f64x2*)(qa + pooled_pos<D>(ia, 8 * s + 2 * g));
+    if (D == 128 || lane < 32) A[wave * (D / 2) + lane] = ((const f64x2*)(qh + ((size_t)bh * M_v + min(i, M_v - 1)) * D))[lane];
+    __syncthreads();
+    // lane l: row l % 16 of both operands, channels 8 s + 2 (l / 16) and the next in step s; pooled_pos() in bytes is an
+    // exclusive or of the row's place with 64 s
+    auto place = [&](int row, int j) { return (uint32_t)(row * D * 8 + (j & (D / 8 - 1)) * 64 + g * 16); };
+    const int ra = c % ROWS;
+    const uint32_t at_a = place(ra, min(i0 + ra, M_v - 1));
+    const char* k_head = (const char*)(kh + (size_t)bh * M * D);
     const double inv = 1.0 / sqrt((double)D);
     for (int j0 = 16 * wave; j0 < M; j0 += 16 * ROWS) {
       const int jb = min(j0 + c, M - 1);
-      const double* kb = kh + ((size_t)bh * M + jb) * D;
-      f64x2 b[D / 8];
-#pragma unroll
-      for (int s = 0; s < D / 8; ++s) b[s] = *(const f64x2*)(kb + pooled_pos<D>(jb, 8 * s + 2 * g));
+      const uint32_t at_b = place(jb, jb);
       f64x4 acc = {0.0, 0.0, 0.0, 0.0};
 #pragma unroll
-      for (int s = 0; s < D / 8; ++s) {
-        acc = __builtin_amdgcn_mfma_f64_16x16x4f64(a[s].x, b[s].x, acc, 0, 0, 0);
-        acc = __builtin_amdgcn_mfma_f64_16x16x4f64(a[s].y, b[s].y, acc, 0, 0, 0);
+      for (int s0 = 0; s0 < D / 8; s0 += CHUNK) {
+        f64x2 b[CHUNK];
+        uint32_t a0 = at_a;
+        asm volatile("" : "+v"(a0));   // the places are formed here and not kept over the loop
+#pragma unroll
+        for (int s = 0; s < CHUNK; ++s) b[s] = *(const f64x2*)(k_head + (at_b ^ (uint32_t)(64 * (s0 + s))));
+#pragma unroll
+        for (int s = 0; s < CHUNK; ++s) {
+          const f64x2 a = *(const f64x2*)((const char*)A + (a0 ^ (uint32_t)(64 * (s0 + s))));
+          acc = __builtin_amdgcn_mfma_f64_16x16x4f64(a.x, b[s].x, acc, 0, 0, 0);
+          acc = __builtin_amdgcn_mfma_f64_16x16x4f64(a.y, b[s].y, acc, 0, 0, 0);
+        }
       }
       // register e of lane l holds row 4 e + l / 16, column l % 16; columns past M are never read
 #pragma unroll
@@ -500,12 +512,21 @@ int run_select(const jenga_plan* p, const void* q, const void* k, int32_t* sel_c
     select_kernel<D, NTV, ROWS><<<dim3((units + 7) / 8 * 8), 64 * ROWS, 0, st>>>(                                    \
         qh, kh, p->d_fixed_bits, sel_count, sel_index, mask, f.M_v, f.M, tiles, units, f.K_top, c.cum_prob, p->nt64); \
   } while (0)
-  if (p->nt64 <= 1) JENGA_SELECT(1, 16);
-  else if (p->nt64 <= 2) JENGA_SELECT(2, 16);
-  else if (p->nt64 <= 4) JENGA_SELECT(4, 16);
-  else if (p->nt64 <= 8) JENGA_SELECT(8, 16);
-  else if (p->nt64 <= 16) JENGA_SELECT(16, 16);
-  else JENGA_SELECT(32, 8);
+  switch (p->nt64) {
+    case 1: JENGA_SELECT(1, 16); break;
+    case 2: JENGA_SELECT(2, 16); break;
+    case 3: JENGA_SELECT(3, 16); break;
+    case 4: JENGA_SELECT(4, 16); break;
+    case 5: JENGA_SELECT(5, 16); break;
+    case 6: JENGA_SELECT(6, 16); break;
+    case 7: JENGA_SELECT(7, 16); break;
+    case 8: JENGA_SELECT(8, 16); break;
+    case 9: case 10: JENGA_SELECT(10, 16); break;
+    case 11: case 12: JENGA_SELECT(12, 16); break;
+    default:
+      if (p->nt64 <= 16) JENGA_SELECT(16, 16);
+      else JENGA_SELECT(32, 8);
+  }
 #undef JENGA_SELECT
   return hipGetLastError() == hipSuccess ? JENGA_OK : JENGA_EHIP;
 }

@@ -47,6 +47,13 @@ def test_block_counts(m, head_dim, topk, p):
     _check(w, q, k)
 
 
+# First and last block count of the numbers of values per lane between the powers of two.
+@pytest.mark.parametrize("m", [192, 193, 320, 321, 384, 385, 448, 449, 512, 640, 641, 768, 769])
+@pytest.mark.parametrize("head_dim,topk,p", [(128, 0.1, 0.8), (64, 0.3, 0.3)])
+def test_block_counts_between(m, head_dim, topk, p):
+    test_block_counts(m, head_dim, topk, p)
+
+
 # Key blocks that repeat with period 7: groups of equal probabilities, larger than a wavefront from m = 512 on, resolved
 # by index.  Small whole numbers, constant over a block, keep every score exact.
 @pytest.mark.parametrize("m", [9, 64, 100, 200, 600, 1500])
