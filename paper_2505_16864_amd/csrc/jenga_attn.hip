@@ -773,14 +773,20 @@ __global__ __launch_bounds__(2 * D) void merge_kernel(const int32_t* __restrict_
 // RANGE: K and V of a head do not fit an XCD's L2.  A pass over all query blocks takes the entries of one of
 // `split.parts` ranges of key blocks, which then stays in the L2, and the next pass the next range; O, reference and sum
 // of the passes go to the workspace and merge_kernel puts them together.
-template <int D, int NS, bool RANGE>
-__global__ __launch_bounds__(64 * NS, (D == 128 ? 2 : 4)) void attn_kernel(
+//
+// ROWS (D = 64): K and V as they lie, for grids so small that packing them, a launch, is what counts (reads_kv_in_place).  K
+// fragments are then 32 rows x 32 bytes instead of 1 KB in one piece; V goes through LDS, 32 rows per wavefront, and is
+// read by columns as in attn_h_kernel, the next rows only after that.  The same bits either way.
+template <int D, int NS, bool RANGE, bool ROWS>
+__device__ __forceinline__ void attn_32(
     const uint16_t* __restrict__ q, const u32x4* __restrict__ kp, const u32x4* __restrict__ vp,
     const int32_t* __restrict__ sel_count, const int32_t* __restrict__ sel_index, uint16_t* __restrict__ out,
-    float* __restrict__ lse, WorkMap work, int n_pad, int pad_v, int pad_c, float scale_log2e, float bias_log2e,
-    Split split) {
-  constexpr int BLK = 32, KS = D / 16, DT = D / 32, PS = BLK / 16, TILE_CHUNKS = BLK * D / 8;
-  __shared__ float part[NS][16][64];   // one channel tile of every wavefront's O, accumulator order
+    float* __restrict__ lse, const WorkMap& work, int n_pad, int pad_v, int pad_c, float scale_log2e, float bias_log2e,
+    const Split& split) {
+  constexpr int BLK = 32, KS = D / 16, DT = D / 32, PS = BLK / 16, TILE_CHUNKS = BLK * D / 8, CH = D / 8;
+  // one channel tile of every wavefront's O, accumulator order; ROWS: before that, 32 rows of V for every wavefront
+  static_assert(!ROWS || D == 64, "32 rows of V take the room of a channel tile");
+  __shared__ __align__(1024) float part[NS][16][64];
   __shared__ float stat[NS][2][32];    // reference and sum of every row
 
   __shared__ uint16_t in_range[RANGE ? 2048 : 1];   // the list's entries in this pass's range, in list order
@@ -827,16 +833,29 @@ __global__ __launch_bounds__(64 * NS, (D == 128 ? 2 : 4)) void attn_kernel(
     }
     cnt = __builtin_amdgcn_readfirstlane(kept);
   }
-  const u32x4* kbase = kp + (size_t)bh * M * TILE_CHUNKS + lane;
-  const u32x4* vbase = vp + (size_t)bh * M * TILE_CHUNKS + lane;
-  u32x4 kf[KS], vf[DT * PS];
+  const u32x4* kbase = kp + (size_t)bh * M * TILE_CHUNKS + (ROWS ? ql * CH + hl : lane);
+  const u32x4* vbase = vp + (size_t)bh * M * TILE_CHUNKS + (ROWS ? 0 : lane);
+  u32x4 kf[KS], vf[ROWS ? 1 : DT * PS];
   auto load_k = [&](int j) {
 #pragma unroll
-    for (int f = 0; f < KS; ++f) kf[f] = kbase[(size_t)j * TILE_CHUNKS + f * 64];
+    for (int f = 0; f < KS; ++f) kf[f] = kbase[(size_t)j * TILE_CHUNKS + f * (ROWS ? 2 : 64)];
   };
+  // ROWS: the 16-byte pieces of a row of V rotated as in attn_h_kernel
+  auto v_swizzle = [](int row) { return (row & 2) * 2; };
+  const uint32_t v_wave = __builtin_amdgcn_readfirstlane(
+      (uint32_t)(uintptr_t)(const __attribute__((address_space(3))) void*)part + (uint32_t)wave * (TILE_CHUNKS * 16));
+  const uint32_t v_off = (uint32_t)(lane / CH * CH + (lane % CH ^ v_swizzle(lane / CH))) * 16u;
+  const int v_row = 4 * hl + ((lane >> 2) & 3);
+  const uint32_t v_lane = v_wave + v_row * (2 * D) + v_swizzle(v_row) * 16 + ((lane >> 4) & 1) * 32 + (lane & 3) * 8;
   auto load_v = [&](int j) {
+    if constexpr (ROWS) {
 #pragma unroll
-    for (int f = 0; f < DT * PS; ++f) vf[f] = vbase[(size_t)j * TILE_CHUNKS + f * 64];
+      for (int c = 0; c < TILE_CHUNKS / 64; ++c)
+        dma_1kb_to_lds_at(vbase + (size_t)j * TILE_CHUNKS + c * 64, v_off, v_wave, c * 1024);
+    } else {
+#pragma unroll
+      for (int f = 0; f < DT * PS; ++f) vf[f] = vbase[(size_t)j * TILE_CHUNKS + f * 64];
+    }
   };
   auto listed = [&](int t) {
     return RANGE ? __builtin_amdgcn_readfirstlane((int)in_range[t]) : min(max(idx[t], 0), M - 1);
@@ -922,12 +941,38 @@ __global__ __launch_bounds__(64 * NS, (D == 128 ? 2 : 4)) void attn_kernel(
     }
     l_run += rs;
 
+    if constexpr (ROWS) {
+      wait_vmem();   // this wavefront's rows of V have landed
+      if (nv < BLK) {   // pad rows hold anything, and their probabilities are zero
+        asm volatile("" : : : "memory");
+        u32x4* rows = (u32x4*)part + wave * TILE_CHUNKS;
+        for (int at = lane; at < TILE_CHUNKS; at += 64)
+          if (at / CH >= nv) rows[at] = u32x4{0, 0, 0, 0};
+        asm volatile("" : : : "memory");
+      }
+      static_for<DT / 2>([&](auto G) {   // two channel tiles at a time
+        constexpr int g = decltype(G)::value;
+        u32x2 A[4][2];
+        static_for<4>([&](auto E) {
+          constexpr int e = decltype(E)::value, dt = 2 * g + (e & 1), ps = e / 2;
+          lds_columns<ps * 32 * D>(A[e][0], v_lane ^ dt * 64);
+          lds_columns<ps * 32 * D + 16 * D>(A[e][1], v_lane ^ dt * 64);
+        });
+        lds_wait(A);
+        static_for<4>([&](auto E) {
+          constexpr int e = decltype(E)::value, dt = 2 * g + (e & 1), ps = e / 2;
+          const u32x4 a = __builtin_shufflevector(A[e][0], A[e][1], 0, 1, 2, 3);
+          O[dt] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(__builtin_bit_cast(bf16x8, a), pb[ps], O[dt], 0, 0, 0);
+        });
+      });
+    } else {
 #pragma unroll
-    for (int ps = 0; ps < PS; ++ps)
+      for (int ps = 0; ps < PS; ++ps)
 #pragma unroll
-      for (int dt = 0; dt < DT; ++dt)
-        O[dt] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(__builtin_bit_cast(bf16x8, vf[dt * PS + ps]), pb[ps], O[dt],
-                                                        0, 0, 0);
+        for (int dt = 0; dt < DT; ++dt)
+          O[dt] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(__builtin_bit_cast(bf16x8, vf[dt * PS + ps]), pb[ps], O[dt],
+                                                          0, 0, 0);
+    }
     if (more) load_v(j_next);
     j = j_next;
     j_next = j_after;
@@ -983,6 +1028,26 @@ __global__ __launch_bounds__(64 * NS, (D == 128 ? 2 : 4)) void attn_kernel(
 #pragma unroll
     for (int u = 0; u < RP; u += 2) *(uint32_t*)(o + u) = row_ok ? pack_bf16x2(sum[u], sum[u + 1]) : 0u;
   }
+}
+
+template <int D, int NS, bool RANGE>
+__global__ __launch_bounds__(64 * NS, (D == 128 ? 2 : 4)) void attn_kernel(
+    const uint16_t* __restrict__ q, const u32x4* __restrict__ kp, const u32x4* __restrict__ vp,
+    const int32_t* __restrict__ sel_count, const int32_t* __restrict__ sel_index, uint16_t* __restrict__ out,
+    float* __restrict__ lse, WorkMap work, int n_pad, int pad_v, int pad_c, float scale_log2e, float bias_log2e,
+    Split split) {
+  attn_32<D, NS, RANGE, false>(q, kp, vp, sel_count, sel_index, out, lse, work, n_pad, pad_v, pad_c, scale_log2e, bias_log2e,
+                               split);
+}
+
+// K and V in place.
+template <int D, int NS>
+__global__ __launch_bounds__(64 * NS, 4) void attn_rows_kernel(
+    const uint16_t* __restrict__ q, const u32x4* __restrict__ k, const u32x4* __restrict__ v,
+    const int32_t* __restrict__ sel_count, const int32_t* __restrict__ sel_index, uint16_t* __restrict__ out,
+    float* __restrict__ lse, WorkMap work, int n_pad, int pad_v, int pad_c, float scale_log2e, float bias_log2e) {
+  attn_32<D, NS, false, true>(q, k, v, sel_count, sel_index, out, lse, work, n_pad, pad_v, pad_c, scale_log2e, bias_log2e,
+                              Split{});
 }
 
 // Lap of the paced walk, common to all workgroups of a launch: a fixed fraction of the time a workgroup needs for
@@ -1083,10 +1148,17 @@ int run_attention(const jenga_plan* p, const void* q, const void* k, const void*
             q0, kp0, vp0, count0, index0, ob0, lse0, work, f.N_pad, f.pad_v, f.pad_c, scale, bias, split);
         merge_kernel<BLK, D><<<dim3(1, f.M, n), 2 * D, 0, st>>>(count0, ob0, lse0, work, f.N_pad, f.pad_v, f.pad_c,
                                                                 split);
-      } else {
-        attn_kernel<D, NS, false><<<dim3(work.n_wg), 64 * NS, 0, st>>>(q0, kp0, vp0, count0, index0, ob0, lse0, work,
-                                                                       f.N_pad, f.pad_v, f.pad_c, scale, bias, split);
+        continue;
       }
+      if constexpr (D == 64) {
+        if (k_rows) {
+          attn_rows_kernel<D, NS><<<dim3(work.n_wg), 64 * NS, 0, st>>>(q0, kp0, vp0, count0, index0, ob0, lse0, work, f.N_pad,
+                                                                       f.pad_v, f.pad_c, scale, bias);
+          continue;
+        }
+      }
+      attn_kernel<D, NS, false><<<dim3(work.n_wg), 64 * NS, 0, st>>>(q0, kp0, vp0, count0, index0, ob0, lse0, work, f.N_pad,
+                                                                     f.pad_v, f.pad_c, scale, bias, split);
     }
   } else {
     const bool paced = BLK == 128 && (c.flags & JENGA_FLAG_PACED_WALK);

@@ -275,7 +275,7 @@ def test_more_query_blocks_than_places(block, head_dim, blocks, heads, p, paced)
 
 # Pad rows of K and V may hold anything: in place, V's reach the second product with probabilities of zero.  Ragged blocks
 # of one row, one short, and around the 64 keys of a step.
-@pytest.mark.parametrize("head_dim,block", [(64, 64), (128, 64), (64, 128), (128, 128)])
+@pytest.mark.parametrize("head_dim,block", [(64, 32), (64, 64), (128, 64), (64, 128), (128, 128)])
 @pytest.mark.parametrize("tail_v,tail_c,heads", [(1, 63, 2), (127, 1, 2), (64, 65, 95), (5, 62, 95)])
 def test_pad_rows_hold_anything(head_dim, block, tail_v, tail_c, heads):
     w = dict(T=1, H=1, W=block * 8 + min(tail_v, block - 1), n_text=block + min(tail_c, block), batch=1, heads=heads,
@@ -296,3 +296,9 @@ def test_pad_rows_hold_anything(head_dim, block, tail_v, tail_c, heads):
     layer.attend()
     torch.cuda.synchronize()
     assert torch.equal(layer.o_c, want) and torch.equal(layer.lse, want_lse)
+    if block == 32:   # nothing is cut there: in place and packed give the same bits
+        layer.pack()
+        layer.o_c.view(torch.int16).fill_(0x7FC1)
+        layer.attend_packed()
+        torch.cuda.synchronize()
+        assert torch.equal(layer.o_c, want) and torch.equal(layer.lse, want_lse)
