@@ -402,7 +402,9 @@ __device__ __forceinline__ void select_row(double* row, uint64_t fixed_lane, int
 // every wavefront needs whole: read from memory by each it was as much for the L1 as all of K^.  Results
 // to LDS.  Then every wavefront selects for one row.  S never leaves the CU.
 //
-// LDS holds 16 rows up to 1024 blocks and 8 rows of 2048: the 8-row kernel computes its tiles with the rows twice.
+// LDS holds 16 rows up to 1024 blocks and 8 rows of 2048.  The 8-row kernel multiplies four rows of Q^ at a time by the same 16
+// columns (v_mfma_f64_4x4x4_4b_f64, Q^'s rows in each of the four blocks), so that no row is computed twice, which 16 x 16
+// tiles did (2048 x 2: 114 us); K^ of the next tile asked for ahead of this one's products changed nothing.
 // Row stride = 16 mod 32 doubles, so the four rows a tile is written to at a time fall on different banks.
 //
 // Up to 448 blocks two workgroups fit a CU if they keep to 64 registers, hence half a row of K^ in flight at a time; then one
@@ -414,8 +416,8 @@ __device__ __forceinline__ void select_row(double* row, uint64_t fixed_lane, int
 //   48 x 16, D = 64                  11.1 us (11.9)
 //   222 x 12, D = 128                20.3 us (24)
 //   262 x 24, D = 128                26.1 us (39.6: one workgroup per CU, two rounds of them)
-//   2048 x 2, D = 64                 114 us (115): cycles of a workgroup: products 44 k, half of them for the doubled rows, softmax
-//                                     17 k, top K 13 k, cumulative rule 20 k, lists 11 k; one workgroup a CU, two rounds
+//   2048 x 2, D = 64                 106 us (115): cycles of a workgroup beside the products: softmax 17 k, top K 13 k,
+//                                     cumulative rule 20 k, lists 11 k; one workgroup a CU, two rounds
 //   931 x 24, D = 128                250 to 290 us (240 to 270): products 28 k, the last wavefront's 20 k longer, rows 21 k
 typedef double f64x4 __attribute__((ext_vector_type(4)));
 typedef double f64x2 __attribute__((ext_vector_type(2)));
@@ -447,31 +449,41 @@ __global__ __launch_bounds__(64 * ROWS, NT < 8 ? 8 : 1) void select_kernel(
     // lane l: row l % 16 of both operands, channels 8 s + 2 (l / 16) and the next in step s; pooled_pos() in bytes is an
     // exclusive or of the row's place with 64 s
     auto place = [&](int row, int j) { return (uint32_t)(row * D * 8 + (j & (D / 8 - 1)) * 64 + g * 16); };
-    const int ra = c % ROWS;
-    const uint32_t at_a = place(ra, min(i0 + ra, M_v - 1));
+    constexpr bool QUADS = ROWS == 8;   // tiles of 4 x 16: rows l % 4 of Q^, and those four further
+    const int ra = QUADS ? c & 3 : c;
+    const uint32_t at_a = place(ra, min(i0 + ra, M_v - 1)), at_a4 = place(ra + 4, min(i0 + ra + 4, M_v - 1));
     const char* k_head = (const char*)(kh + (size_t)bh * M * D);
     const double inv = 1.0 / sqrt((double)D);
     for (int j0 = 16 * wave; j0 < M; j0 += 16 * ROWS) {
       const int jb = min(j0 + c, M - 1);
       const uint32_t at_b = place(jb, jb);
       f64x4 acc = {0.0, 0.0, 0.0, 0.0};
+      double quad[2][2] = {{0.0, 0.0}, {0.0, 0.0}};   // [four rows][even and odd channels]
 #pragma unroll
       for (int s0 = 0; s0 < D / 8; s0 += CHUNK) {
         f64x2 b[CHUNK];
-        uint32_t a0 = at_a;
-        asm volatile("" : "+v"(a0));   // the places are formed here and not kept over the loop
+        uint32_t a0 = at_a, a4 = at_a4;
+        asm volatile("" : "+v"(a0), "+v"(a4));   // the places are formed here and not kept over the loop
 #pragma unroll
         for (int s = 0; s < CHUNK; ++s) b[s] = *(const f64x2*)(k_head + (at_b ^ (uint32_t)(64 * (s0 + s))));
 #pragma unroll
         for (int s = 0; s < CHUNK; ++s) {
           const f64x2 a = *(const f64x2*)((const char*)A + (a0 ^ (uint32_t)(64 * (s0 + s))));
-          acc = __builtin_amdgcn_mfma_f64_16x16x4f64(a.x, b[s].x, acc, 0, 0, 0);
-          acc = __builtin_amdgcn_mfma_f64_16x16x4f64(a.y, b[s].y, acc, 0, 0, 0);
+          if constexpr (QUADS) {
+            const f64x2 a_up = *(const f64x2*)((const char*)A + (a4 ^ (uint32_t)(64 * (s0 + s))));
+            quad[0][0] = __builtin_amdgcn_mfma_f64_4x4x4f64(a.x, b[s].x, quad[0][0], 0, 0, 0);
+            quad[1][0] = __builtin_amdgcn_mfma_f64_4x4x4f64(a_up.x, b[s].x, quad[1][0], 0, 0, 0);
+            quad[0][1] = __builtin_amdgcn_mfma_f64_4x4x4f64(a.y, b[s].y, quad[0][1], 0, 0, 0);
+            quad[1][1] = __builtin_amdgcn_mfma_f64_4x4x4f64(a_up.y, b[s].y, quad[1][1], 0, 0, 0);
+          } else {
+            acc = __builtin_amdgcn_mfma_f64_16x16x4f64(a.x, b[s].x, acc, 0, 0, 0);
+            acc = __builtin_amdgcn_mfma_f64_16x16x4f64(a.y, b[s].y, acc, 0, 0, 0);
+          }
         }
       }
-      // register e of lane l holds row 4 e + l / 16, column l % 16; columns past M are never read
+      // register e, or four rows e, of lane l: row 4 e + l / 16, column l % 16; columns past M are never read
 #pragma unroll
-      for (int e = 0; e < ROWS / 4; ++e) S[4 * e + g][j0 + c] = acc[e] * inv;
+      for (int e = 0; e < ROWS / 4; ++e) S[4 * e + g][j0 + c] = (QUADS ? quad[e & 1][0] + quad[e & 1][1] : acc[e]) * inv;
     }
   }
   __syncthreads();
