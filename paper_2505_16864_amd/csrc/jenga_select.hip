@@ -160,21 +160,17 @@ __device__ __forceinline__ uint64_t values_inside(const double (&r)[NT], const I
   return key;
 }
 
-// One row of the selection by one wavefront: softmax of the scores in `row` (LDS, overwritten), N_k, the top N_k, the
-// union with `fixed_lane` (lane t holds word t of the row's fixed mask), compaction.  See the head of this file.
+// One row of the selection by one wavefront: softmax of the scores r (value t of lane l: block 64 t + l, -inf past M), N_k, the
+// top N_k (`row`: LDS for 64 of the values), the union with `fixed_lane` (lane t holds word t of the row's fixed mask),
+// compaction.  See the head of this file.
 template <int NT>
-__device__ __forceinline__ void select_row(double* row, uint64_t fixed_lane, int32_t* idx_out, uint8_t* mask_out, int* count,
-                                  int M, int K_top, double p) {
+__device__ __forceinline__ void select_row(double (&r)[NT], double* row, uint64_t fixed_lane, int32_t* idx_out,
+                                           uint8_t* mask_out, int* count, int M, int K_top, double p) {
   const int lane = threadIdx.x & 63;
   const uint64_t lt_mask = (1ull << lane) - 1ull;
-  double r[NT];
   double mx = -INFINITY;
 #pragma unroll
-  for (int t = 0; t < NT; ++t) {
-    const int j = t * 64 + lane;
-    r[t] = j < M ? row[j] : -INFINITY;
-    mx = fmax(mx, r[t]);
-  }
+  for (int t = 0; t < NT; ++t) mx = fmax(mx, r[t]);
   mx = wave_max(mx);
   double z = 0.0;
 #pragma unroll
@@ -402,32 +398,43 @@ __device__ __forceinline__ void select_row(double* row, uint64_t fixed_lane, int
 // every wavefront needs whole: read from memory by each it was as much for the L1 as all of K^.  Results
 // to LDS.  Then every wavefront selects for one row.  S never leaves the CU.
 //
-// LDS holds 16 rows up to 1024 blocks and 8 rows of 2048.  The 8-row kernel multiplies four rows of Q^ at a time by the same 16
-// columns (v_mfma_f64_4x4x4_4b_f64, Q^'s rows in each of the four blocks), so that no row is computed twice, which 16 x 16
-// tiles did (2048 x 2: 114 us); K^ of the next tile asked for ahead of this one's products changed nothing.
+// A row goes to the registers of its wavefront a range of columns at a time, so that LDS need not hold all of S and two
+// workgroups fit a CU: one multiplies while the other selects.  That takes 64 registers, hence half a row of K^ in flight at
+// a time, and up to 448 blocks (one range) and from there to 768 (ranges of 256 columns) they are enough.  Up to 1024 the values alone
+// are 32 of them: one range, one workgroup a CU.  Above, 16 rows have no room at all; 8 rows in two ranges do, in 128 registers.
+// 8 rows for 1024 too: 88 us (16 rows 102) on 800 blocks x 12 heads, D = 64, but 57 (47) on 1000 x 3 and 282 (278) on 931 x 24,
+// D = 128, for which K^ is read twice as often.
+// The 8-row kernel multiplies four rows of Q^ at a time by the same 16 columns (v_mfma_f64_4x4x4_4b_f64, Q^'s rows in each of
+// the four blocks), so that no row is computed twice as in 16 x 16 tiles (2048 x 2: 114 -> 106 us); K^ of the next tile asked
+// for ahead of this one's products changed nothing.
 // Row stride = 16 mod 32 doubles, so the four rows a tile is written to at a time fall on different banks.
 //
-// Up to 448 blocks two workgroups fit a CU if they keep to 64 registers, hence half a row of K^ in flight at a time; then one
-// multiplies while the other selects.  NT is as many values per lane as M needs, up to 512 blocks; rounded up to a power of two,
-// 262 blocks cost a third more for the rows.
+// NT is as many values per lane as M needs, up to 512 blocks; rounded up to a power of two, 262 blocks cost a third more for the
+// rows.
 //
-// Time of the kernel, median of ten to twenty launches, now and before Q^ went through LDS:
+// Time of the kernel, median of ten to twenty launches, now and before (Q^ from memory, unless it says so):
 //   17 blocks x 8 heads, D = 128      8.0 us (8.7; a launch alone takes 2.5)
 //   48 x 16, D = 64                  11.1 us (11.9)
 //   222 x 12, D = 128                20.3 us (24)
 //   262 x 24, D = 128                26.1 us (39.6: one workgroup per CU, two rounds of them)
-//   2048 x 2, D = 64                 106 us (115): cycles of a workgroup beside the products: softmax 17 k, top K 13 k,
-//                                     cumulative rule 20 k, lists 11 k; one workgroup a CU, two rounds
+//   600 x 24, D = 128               111 us (135: all of S in LDS, one workgroup a CU); 760 x 12 96 (112), 500 x 24 90 (91)
+//   2048 x 2, D = 64                 95 us (115); before, with the products above, one workgroup a CU and two rounds of them: 103
+//   1500 x 8, D = 128               295 us (330 likewise)
 //   931 x 24, D = 128                250 to 290 us (240 to 270): products 28 k, the last wavefront's 20 k longer, rows 21 k
 typedef double f64x4 __attribute__((ext_vector_type(4)));
 typedef double f64x2 __attribute__((ext_vector_type(2)));
 
+// Columns of S that are in LDS at a time
+template <int NT, int ROWS>
+constexpr int select_cols() { return ROWS == 8 ? 32 * NT : NT < 8 || NT == 16 ? 64 * NT : 256; }
+
 template <int D, int NT, int ROWS>
-__global__ __launch_bounds__(64 * ROWS, NT < 8 ? 8 : 1) void select_kernel(
+__global__ __launch_bounds__(64 * ROWS, NT == 16 ? 1 : ROWS == 8 ? 4 : 8) void select_kernel(
     const double* __restrict__ qh, const double* __restrict__ kh, const uint64_t* __restrict__ fixed_bits,
     int32_t* __restrict__ sel_count, int32_t* __restrict__ sel_index, uint8_t* __restrict__ mask, int M_v, int M, int n_tiles,
     int n_units, int K_top, double p, int nt64) {
-  __shared__ double S[ROWS][64 * NT + 16];
+  constexpr int COLS = select_cols<NT, ROWS>(), PASSES = (64 * NT + COLS - 1) / COLS;
+  __shared__ double S[ROWS][COLS + 16];
   __shared__ __align__(1024) f64x2 A[ROWS * D / 2];   // the pooled query rows, as they lie in memory
   // workgroup n runs on XCD n % 8: each XCD gets a contiguous run of (head, row tile) units
   const int per_xcd = (n_units + 7) / 8;
@@ -440,53 +447,65 @@ __global__ __launch_bounds__(64 * ROWS, NT < 8 ? 8 : 1) void select_kernel(
   uint64_t fixed_lane = 0;   // asked for here, needed at the end
   if (i < M_v && lane < nt64) fixed_lane = fixed_bits[(size_t)i * nt64 + lane];
 
-  if (i0 < M_v) {
-    // wavefront w brings row w, then takes every ROWS-th tile of columns
-    constexpr int CHUNK = D / 16 < 8 ? D / 16 : 8;   // steps whose loads are in flight at a time
-    const int g = lane >> 4, c = lane & 15;
-    if (D == 128 || lane < 32) A[wave * (D / 2) + lane] = ((const f64x2*)(qh + ((size_t)bh * M_v + min(i, M_v - 1)) * D))[lane];
-    __syncthreads();
-    // lane l: row l % 16 of both operands, channels 8 s + 2 (l / 16) and the next in step s; pooled_pos() in bytes is an
-    // exclusive or of the row's place with 64 s
-    auto place = [&](int row, int j) { return (uint32_t)(row * D * 8 + (j & (D / 8 - 1)) * 64 + g * 16); };
-    constexpr bool QUADS = ROWS == 8;   // tiles of 4 x 16: rows l % 4 of Q^, and those four further
-    const int ra = QUADS ? c & 3 : c;
-    const uint32_t at_a = place(ra, min(i0 + ra, M_v - 1)), at_a4 = place(ra + 4, min(i0 + ra + 4, M_v - 1));
-    const char* k_head = (const char*)(kh + (size_t)bh * M * D);
-    const double inv = 1.0 / sqrt((double)D);
-    for (int j0 = 16 * wave; j0 < M; j0 += 16 * ROWS) {
-      const int jb = min(j0 + c, M - 1);
-      const uint32_t at_b = place(jb, jb);
-      f64x4 acc = {0.0, 0.0, 0.0, 0.0};
-      double quad[2][2] = {{0.0, 0.0}, {0.0, 0.0}};   // [four rows][even and odd channels]
+  double r[NT];
 #pragma unroll
-      for (int s0 = 0; s0 < D / 8; s0 += CHUNK) {
-        f64x2 b[CHUNK];
-        uint32_t a0 = at_a, a4 = at_a4;
-        asm volatile("" : "+v"(a0), "+v"(a4));   // the places are formed here and not kept over the loop
+  for (int pass = 0; pass < PASSES; ++pass) {
+    if (i0 < M_v) {
+      // wavefront w brings row w (in the first pass), then takes every ROWS-th tile of columns
+      constexpr int CHUNK = D / 16 < 8 ? D / 16 : 8;   // steps whose loads are in flight at a time
+      const int g = lane >> 4, c = lane & 15;
+      if (pass == 0 && (D == 128 || lane < 32))
+        A[wave * (D / 2) + lane] = ((const f64x2*)(qh + ((size_t)bh * M_v + min(i, M_v - 1)) * D))[lane];
+      __syncthreads();
+      // lane l: row l % 16 of both operands, channels 8 s + 2 (l / 16) and the next in step s; pooled_pos() in bytes is an
+      // exclusive or of the row's place with 64 s
+      auto place = [&](int row, int j) { return (uint32_t)(row * D * 8 + (j & (D / 8 - 1)) * 64 + g * 16); };
+      constexpr bool QUADS = ROWS == 8;   // tiles of 4 x 16: rows l % 4 of Q^, and those four further
+      const int ra = QUADS ? c & 3 : c;
+      const uint32_t at_a = place(ra, min(i0 + ra, M_v - 1)), at_a4 = place(ra + 4, min(i0 + ra + 4, M_v - 1));
+      const char* k_head = (const char*)(kh + (size_t)bh * M * D);
+      const double inv = 1.0 / sqrt((double)D);
+      for (int j0 = pass * COLS + 16 * wave; j0 < min(M, (pass + 1) * COLS); j0 += 16 * ROWS) {
+        const int jb = min(j0 + c, M - 1);
+        const uint32_t at_b = place(jb, jb);
+        f64x4 acc = {0.0, 0.0, 0.0, 0.0};
+        double quad[2][2] = {{0.0, 0.0}, {0.0, 0.0}};   // [four rows][even and odd channels]
 #pragma unroll
-        for (int s = 0; s < CHUNK; ++s) b[s] = *(const f64x2*)(k_head + (at_b ^ (uint32_t)(64 * (s0 + s))));
+        for (int s0 = 0; s0 < D / 8; s0 += CHUNK) {
+          f64x2 b[CHUNK];
+          uint32_t a0 = at_a, a4 = at_a4;
+          asm volatile("" : "+v"(a0), "+v"(a4));   // the places are formed here and not kept over the loop
 #pragma unroll
-        for (int s = 0; s < CHUNK; ++s) {
-          const f64x2 a = *(const f64x2*)((const char*)A + (a0 ^ (uint32_t)(64 * (s0 + s))));
-          if constexpr (QUADS) {
-            const f64x2 a_up = *(const f64x2*)((const char*)A + (a4 ^ (uint32_t)(64 * (s0 + s))));
-            quad[0][0] = __builtin_amdgcn_mfma_f64_4x4x4f64(a.x, b[s].x, quad[0][0], 0, 0, 0);
-            quad[1][0] = __builtin_amdgcn_mfma_f64_4x4x4f64(a_up.x, b[s].x, quad[1][0], 0, 0, 0);
-            quad[0][1] = __builtin_amdgcn_mfma_f64_4x4x4f64(a.y, b[s].y, quad[0][1], 0, 0, 0);
-            quad[1][1] = __builtin_amdgcn_mfma_f64_4x4x4f64(a_up.y, b[s].y, quad[1][1], 0, 0, 0);
-          } else {
-            acc = __builtin_amdgcn_mfma_f64_16x16x4f64(a.x, b[s].x, acc, 0, 0, 0);
-            acc = __builtin_amdgcn_mfma_f64_16x16x4f64(a.y, b[s].y, acc, 0, 0, 0);
+          for (int s = 0; s < CHUNK; ++s) b[s] = *(const f64x2*)(k_head + (at_b ^ (uint32_t)(64 * (s0 + s))));
+#pragma unroll
+          for (int s = 0; s < CHUNK; ++s) {
+            const f64x2 a = *(const f64x2*)((const char*)A + (a0 ^ (uint32_t)(64 * (s0 + s))));
+            if constexpr (QUADS) {
+              const f64x2 a_up = *(const f64x2*)((const char*)A + (a4 ^ (uint32_t)(64 * (s0 + s))));
+              quad[0][0] = __builtin_amdgcn_mfma_f64_4x4x4f64(a.x, b[s].x, quad[0][0], 0, 0, 0);
+              quad[1][0] = __builtin_amdgcn_mfma_f64_4x4x4f64(a_up.x, b[s].x, quad[1][0], 0, 0, 0);
+              quad[0][1] = __builtin_amdgcn_mfma_f64_4x4x4f64(a.y, b[s].y, quad[0][1], 0, 0, 0);
+              quad[1][1] = __builtin_amdgcn_mfma_f64_4x4x4f64(a_up.y, b[s].y, quad[1][1], 0, 0, 0);
+            } else {
+              acc = __builtin_amdgcn_mfma_f64_16x16x4f64(a.x, b[s].x, acc, 0, 0, 0);
+              acc = __builtin_amdgcn_mfma_f64_16x16x4f64(a.y, b[s].y, acc, 0, 0, 0);
+            }
           }
         }
-      }
-      // register e, or four rows e, of lane l: row 4 e + l / 16, column l % 16; columns past M are never read
+        // register e, or four rows e, of lane l: row 4 e + l / 16, column l % 16; columns past M are never read
 #pragma unroll
-      for (int e = 0; e < ROWS / 4; ++e) S[4 * e + g][j0 + c] = (QUADS ? quad[e & 1][0] + quad[e & 1][1] : acc[e]) * inv;
+        for (int e = 0; e < ROWS / 4; ++e)
+          S[4 * e + g][j0 - pass * COLS + c] = (QUADS ? quad[e & 1][0] + quad[e & 1][1] : acc[e]) * inv;
+      }
     }
+    __syncthreads();
+#pragma unroll
+    for (int t = 0; t < COLS / 64 && pass * (COLS / 64) + t < NT; ++t) {
+      const int j = pass * COLS + t * 64 + lane;
+      r[pass * (COLS / 64) + t] = j < M ? S[wave][t * 64 + lane] : -INFINITY;
+    }
+    if (pass + 1 < PASSES) __syncthreads();
   }
-  __syncthreads();
 
   if (i >= M) return;
   const size_t out_row = (size_t)bh * M + i;
@@ -500,7 +519,7 @@ __global__ __launch_bounds__(64 * ROWS, NT < 8 ? 8 : 1) void select_kernel(
     if (lane == 0) sel_count[out_row] = M;
     return;
   }
-  select_row<NT>(S[wave], fixed_lane, idx_out, mask_out, sel_count + out_row, M, K_top, p);
+  select_row<NT>(r, S[wave], fixed_lane, idx_out, mask_out, sel_count + out_row, M, K_top, p);
 }
 
 template <int D>
