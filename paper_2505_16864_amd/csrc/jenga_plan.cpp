@@ -216,8 +216,11 @@ int heads_per_launch(const jenga_plan* p, int threads) {
 // XCDs that were dealt the same work took 44 to 49.5 ms for it.  There the query blocks behind the first generation of
 // workgroups are dealt out by counters (take_item in jenga_attn.hip), so that XCDs end together: 929 blocks x 24 heads
 // 49.3 -> 46.7 ms (k = 0.3, paced) and 21.0 -> 20.1 ms (k = 0.1); 20 shapes of 1.1 to 4.6 generations of 128-token blocks,
-// layers of 0.3 to 1.3 ms, 0 to 4 % less, none more.  Workgroups for 64 tokens with even lists last 50 to 200 us and lose 1 to
-// 6 % to the counter.
+// layers of 0.3 to 1.3 ms, 0 to 4 % less, none more.  Workgroups that last less than about 200 us (their blocks at the time a
+// block takes on a full chip) lose to the counter and to the cuts.  Layer, as dealt out by map_work -> by counters, on lists of
+// 52 us (29 blocks of 64 x 80 heads, D = 128) 204 -> 252 us, 106 us (297 of 64 x 40, D = 64) 1127 -> 1300, 120 us (36 x 48, D = 64)
+// 326 -> 358, 150 to 180 us (four shapes) 2 to 4 % more; 200 to 220 us the same, from 260 us on 1 to 14 % less.  Even lists of
+// 64-token blocks last longer than that only where heads are large, and lose 1 to 6 % there too.
 // What remains is the last generation, which runs out over the time of one workgroup.  There half a generation of lists is
 // cut, into two: 1 to 3 % less from two generations on, but below two, where this reaches into the first one, up to
 // 5 % more (1416 query blocks at D = 128 601 -> 633 us).  Lists of uneven length (p well above k) into three, whatever the
@@ -229,7 +232,8 @@ int heads_per_launch(const jenga_plan* p, int threads) {
 // for it (768 query blocks, 16 of them text: 115 -> 123 us).  With more query blocks a text row is cut where it alone lasts as
 // long as the launch.  Attention, whole -> cut: 732 query blocks, 61 a head, D = 128 201 -> 180 us; 972, 81 a head, D = 64
 // 183 -> 158; 1104, 138 a head, D = 128 507 -> 498; blocks of 64 at D = 64: 1944, 162 a head 180 -> 137, 8196, 683 a
-// head at k = 0.1 1401 -> 1270; 38 shapes 3 % less on average, none above 1 % more.
+// head at k = 0.1 1401 -> 1270; 38 shapes 3 % less on average, none above 1 % more.  A text row has to last 400 us for it, beyond
+// one generation: with 920 query blocks of 128, 23 a head (145 us), a layer took 241 whole and 250 us cut, 888, 37 a head 211 and 215.
 constexpr uint64_t RANGE_AREA_BYTES = 128ull << 20;
 
 Deal plan_deal(const jenga_plan* p, const WorkMap& work, bool whole) {
@@ -273,6 +277,7 @@ static void split_lists(jenga_plan* plan) {
     const bool uneven = c.cum_prob > 2.0 * c.topk_ratio;
     const WorkMap work = plan_work(plan, c.batch * c.heads);
     const double usual = std::max((double)len, c.cum_prob * c.cum_prob * f.M), gens = (double)rows / places;
+    const double block_us = c.block == 128 ? (c.head_dim == 128 ? 6.3 : 3.6) : (c.head_dim == 128 ? 2.6 : 1.8);
     const long long text_rows = (long long)c.batch * c.heads * f.M_c;
     if (work.text_wgs <= 32768) {   // rows of a merge
       if (gens <= 1.0) {
@@ -284,11 +289,11 @@ static void split_lists(jenga_plan* plan) {
             plan->attn_text_parts = parts;
           }
         }
-      } else if (f.M > (gens < 1.5 ? 1.15 : 1.8) * gens * usual) {
+      } else if (f.M * block_us >= 400.0 && f.M > (gens < 1.5 ? 1.15 : 1.8) * gens * usual) {
         plan->attn_text_parts = std::min(8, (int)std::ceil(f.M / (gens * usual)));
       }
     }
-    if (rows > places && (c.block == 128 || uneven)) {
+    if (rows > places && (c.block == 128 || uneven) && usual * block_us >= 200.0) {
       plan->attn_first = 32 * (c.block == 64 && c.head_dim == 128 ? 4 : attn_h_per_cu(c.block, c.head_dim));
       if (uneven || rows >= 2 * places) {
         const int positions = (work.n_wg + 7) / 8;
