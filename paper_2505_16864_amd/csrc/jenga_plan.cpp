@@ -219,7 +219,8 @@ int heads_per_launch(const jenga_plan* p, int threads) {
 // layers of 0.3 to 1.3 ms, 0 to 4 % less, none more.  Workgroups that last less than about 200 us (their blocks at the time a
 // block takes on a full chip) lose to the counter and to the cuts.  Layer, as dealt out by map_work -> by counters, on lists of
 // 52 us (29 blocks of 64 x 80 heads, D = 128) 204 -> 252 us, 106 us (297 of 64 x 40, D = 64) 1127 -> 1300, 120 us (36 x 48, D = 64)
-// 326 -> 358, 150 to 180 us (four shapes) 2 to 4 % more; 200 to 220 us the same, from 260 us on 1 to 14 % less.  Even lists of
+// 326 -> 358, 150 to 180 us (four shapes) 2 to 4 % more; 200 to 220 us the same, from 260 us on 1 to 14 % less.  At D = 64 the line
+// lies higher: four shapes of 205 to 252 us 0.4 to 2.5 % more, 273 us 1 % and from 400 us on 0.3 to 14 % less.  Even lists of
 // 64-token blocks last longer than that only where heads are large, and lose 1 to 6 % there too.
 // What remains is the last generation, which runs out over the time of one workgroup.  There half a generation of lists is
 // cut, into two: 1 to 3 % less from two generations on, but below two, where this reaches into the first one, up to
@@ -293,7 +294,7 @@ static void split_lists(jenga_plan* plan) {
         plan->attn_text_parts = std::min(8, (int)std::ceil(f.M / (gens * usual)));
       }
     }
-    if (rows > places && (c.block == 128 || uneven) && usual * block_us >= 200.0) {
+    if (rows > places && (c.block == 128 || uneven) && usual * block_us >= (c.head_dim == 128 ? 200.0 : 320.0)) {
       plan->attn_first = 32 * (c.block == 64 && c.head_dim == 128 ? 4 : attn_h_per_cu(c.block, c.head_dim));
       if (uneven || rows >= 2 * places) {
         const int positions = (work.n_wg + 7) / 8;

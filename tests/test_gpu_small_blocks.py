@@ -236,8 +236,8 @@ def test_output_over_an_input(block, flags, heads):
     # text rows cut: in one generation, behind a counter, 64 tokens
     (128, 64, 67, 13, 0.3, True), (128, 64, 67, 13, 0.3, False), (128, 128, 113, 8, 0.3, False), (64, 64, 121, 14, 0.3, False),
     # lists long enough for the counters: one to two generations, two and more, lists of uneven length, the paced walk
-    (128, 128, 97, 9, 0.3, False), (128, 128, 97, 17, 0.3, True), (128, 128, 37, 24, 0.97, False), (128, 64, 61, 18, 0.97, True),
-    (64, 128, 83, 16, 0.97, False), (64, 64, 121, 17, 0.97, False)])
+    (128, 128, 97, 9, 0.3, False), (128, 128, 97, 17, 0.3, True), (128, 128, 37, 24, 0.97, False), (128, 64, 97, 11, 0.97, True),
+    (64, 128, 83, 16, 0.97, False), (64, 64, 193, 11, 0.97, False)])
 def test_more_query_blocks_than_places(block, head_dim, blocks, heads, p, paced):
     w = dict(T=1, H=1, W=block * (blocks - 1) - 9, n_text=5, batch=1, heads=heads, head_dim=head_dim, block=block, topk=0.3,
              p=p, text_bias=0.4, flags=15 if paced else 7)
