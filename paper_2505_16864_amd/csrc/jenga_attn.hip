@@ -280,8 +280,8 @@ __global__ __launch_bounds__(2 * BLK, (attn_h_min_waves<BLK, D>())) void attn_h_
   // The addresses are formed where they are needed (xor_here; ten instructions a step): hoisted, they cost spills.
   // No packing, against V packed (before, with K packed too): layer of 222 blocks of 64 x 12 heads 521 -> 486 us, 17
   // blocks x 8 59.5 -> 56.2, 48 x 16 at D = 64 133.1 -> 130.2, 262 x 24 4.48 -> 4.45 ms (the columns take twice as many LDS
-  // instructions as fragments).  The paced walk keeps packed tiles, and so does whoever has packed them already.
-  static_assert(!(PACED && K_ROWS), "the paced walk reads packed tiles");
+  // instructions as fragments).  The paced walk keeps packed tiles where it is paced, and so does whoever has packed them already.
+  static_assert(!(PACED && K_ROWS) || SPLIT, "only cut lists, which are visited in ascending order");
   __shared__ __align__(256) u32x4 Ks[HALF_CHUNKS];
   __shared__ __align__(256) u32x4 Vs[HALF_CHUNKS];   // fragments (dt, p2) of the current 64 keys, or rows
   __shared__ uint32_t rem_bits[PACED ? 64 : 1];   // PACED: bitmap of the blocks still to visit, 32 per word
@@ -1200,9 +1200,10 @@ int run_attention(const jenga_plan* p, const void* q, const void* k, const void*
       }
       split.stat = split.o + (size_t)slots * BLK * D;
       if constexpr (BLK == 128) {
-        if (paced) JENGA_ATTN(true, true, false, wgs);
+        if (paced && k_rows) JENGA_ATTN(true, true, true, wgs);
+        else if (paced) JENGA_ATTN(true, true, false, wgs);
       }
-      if (k_rows) JENGA_ATTN(false, true, true, wgs);
+      if (k_rows && !paced) JENGA_ATTN(false, true, true, wgs);
       else if (!paced) JENGA_ATTN(false, true, false, wgs);
       if (slots > 0)
         merge_kernel<BLK, D><<<merge, 2 * D, 0, st>>>(sel_count, ob, lse, work, f.N_pad, f.pad_v, f.pad_c, split);

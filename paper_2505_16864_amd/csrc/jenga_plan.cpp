@@ -314,9 +314,13 @@ static void split_lists(jenga_plan* plan) {
 // Blocks of 32 tokens: packing is a launch of 2.5 us, and reading in place costs more a block.  At head dim 64 attention takes,
 // packed / in place: 9 blocks x 2 heads 8.4 / 6.5 us, 14 x 2 8.9 / 7.5, 23 x 3 8.6 / 8.1, 23 x 8 9.0 / 8.7, 44 x 8 15.7 /
 // 18.8; at 128 it is never shorter (14 x 2 9.1 / 9.4).
+// A plan with the paced walk reads in place where the grid is so short that its lists are cut and visited in ascending order: layer,
+// packed / in place, 8 blocks x 12 heads 42.4 / 37.8 us, 40 x 3 78 / 73, 110 x 2 150 / 143.  Paced, the address arithmetic costs
+// as much as the packing.
 bool reads_kv_in_place(const jenga_plan* p) {
   if (p->cfg.block == 32) return p->cfg.head_dim == 64 && p->info.M <= 24 && p->cfg.batch * p->cfg.heads * p->info.M <= 256;
-  return p->cfg.block == 64 || !(p->cfg.flags & JENGA_FLAG_PACED_WALK);
+  const bool short_grid = p->attn_first == 0 && p->attn_text_parts == 1 && p->attn_parts > 1;
+  return p->cfg.block == 64 || !(p->cfg.flags & JENGA_FLAG_PACED_WALK) || short_grid;
 }
 
 int build_host_tables(jenga_plan* plan) {

@@ -279,10 +279,11 @@ def test_more_query_blocks_than_places(block, head_dim, blocks, heads, p, paced)
 # Pad rows of K and V may hold anything: in place, V's reach the second product with probabilities of zero.  Ragged blocks
 # of one row, one short, and around the 64 keys of a step.
 @pytest.mark.parametrize("head_dim,block", [(64, 32), (64, 64), (128, 64), (64, 128), (128, 128)])
-@pytest.mark.parametrize("tail_v,tail_c,heads", [(1, 63, 2), (127, 1, 2), (64, 65, 95), (5, 62, 95)])
-def test_pad_rows_hold_anything(head_dim, block, tail_v, tail_c, heads):
+@pytest.mark.parametrize("tail_v,tail_c,heads,flags", [(1, 63, 2, 7), (127, 1, 2, 7), (64, 65, 95, 7), (5, 62, 95, 7),
+                                                       (1, 63, 2, 15), (127, 1, 2, 15)])   # 15: short grids are not paced
+def test_pad_rows_hold_anything(head_dim, block, tail_v, tail_c, heads, flags):
     w = dict(T=1, H=1, W=block * 8 + min(tail_v, block - 1), n_text=block + min(tail_c, block), batch=1, heads=heads,
-             head_dim=head_dim, block=block, topk=0.9, p=0.3)
+             head_dim=head_dim, block=block, topk=0.9, p=0.3, flags=flags)
     print("pads", w, flush=True)
     layer = CarveLayer(w, "cuda:0", want_lse=True)
     layer.permute_in(*[x.cuda() for x in ji.make_qkv(w, 64)])

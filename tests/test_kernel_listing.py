@@ -104,7 +104,7 @@ def _step_loop(body, mfmas):
 
 # block, head dim, paced, cut, K in place
 ATTN_H = [(block, d, paced, cut, rows) for block in (128, 64) for d in (128, 64) for paced in (0, 1) for cut in (0, 1)
-          for rows in (0, 1) if not (paced and (rows or block == 64))]
+          for rows in (0, 1) if not (paced and (block == 64 or (rows and not cut)))]
 
 
 def _attention_kernels(listing):
