@@ -420,7 +420,7 @@ __device__ __forceinline__ void select_row(double (&r)[NT], double* row, uint64_
 //   600 x 24, D = 128               111 us (135: all of S in LDS, one workgroup a CU); 760 x 12 96 (112), 500 x 24 90 (91)
 //   2048 x 2, D = 64                 95 us (115); before, with the products above, one workgroup a CU and two rounds of them: 103
 //   1500 x 8, D = 128               295 us (330 likewise)
-//   931 x 24, D = 128                250 to 290 us (240 to 270): products 28 k, the last wavefront's 20 k longer, rows 21 k
+//   931 x 24, D = 128                220 to 290 us (240 to 270): products 28 k, the last wavefront's 20 k longer, rows 21 k
 typedef double f64x4 __attribute__((ext_vector_type(4)));
 typedef double f64x2 __attribute__((ext_vector_type(2)));
 
