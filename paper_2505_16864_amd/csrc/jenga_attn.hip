@@ -689,13 +689,10 @@ __global__ __launch_bounds__(2 * D) void merge_kernel(const int32_t* __restrict_
   const int M = work.M, M_v = work.M_v, wave = blockIdx.x;
   int i = blockIdx.y, bh = blockIdx.z, n_parts;
   size_t slot = (size_t)bh * M + i;
-  if (split.deal.parts > 0) {   // row y of those that are cut
-    const int y = blockIdx.y, text = split.deal.text_rows();
-    const bool is_text = y < text;
-    n_parts = is_text ? split.deal.text_parts : split.deal.parts;
-    slot = is_text ? (size_t)y * n_parts : (size_t)text * split.deal.text_parts + (size_t)(y - text) * n_parts;
-    if (is_text && y >= work.text_wgs) return;
-    if (!map_work(is_text ? y : work.text_wgs + 8 * split.deal.whole + y - text, work, &bh, &i)) return;
+  if (split.deal.parts > 0) {
+    int n, first;
+    if (!jenga::merge_row(blockIdx.y, split.deal, work, &n, &n_parts, &first) || !map_work(n, work, &bh, &i)) return;
+    slot = first;
   } else {
     n_parts = split.of(min(max(sel_count[slot], 0), M));
     if (n_parts == 1) return;

@@ -127,6 +127,17 @@ JENGA_HOST_DEVICE inline bool deal_position(int r, int x, const Deal& d, const W
   return *n < rows;
 }
 
+// Row y of those that are cut, text rows first: workgroup *n of map_work(), whose *parts results start at slot *slot.
+// Returns false where there is none.
+JENGA_HOST_DEVICE inline bool merge_row(int y, const Deal& d, const WorkMap& w, int* n, int* parts, int* slot) {
+  const int text = d.text_rows();
+  const bool is_text = y < text;
+  *parts = is_text ? d.text_parts : d.parts;
+  *slot = is_text ? y * *parts : text * d.text_parts + (y - text) * *parts;
+  *n = is_text ? y : w.text_wgs + 8 * d.whole + y - text;
+  return *n < (is_text ? w.text_wgs : w.n_wg);
+}
+
 // The mapping for `n_bh` (batch, head) pairs of the plan.
 WorkMap plan_work(const jenga_plan* p, int n_bh);
 

@@ -297,8 +297,9 @@ static void split_lists(jenga_plan* plan) {
     if (rows > places && (c.block == 128 || uneven) && usual * block_us >= (c.head_dim == 128 ? 200.0 : 320.0)) {
       plan->attn_first = 32 * (c.block == 64 && c.head_dim == 128 ? 4 : attn_h_per_cu(c.block, c.head_dim));
       if (uneven || rows >= 2 * places) {
-        const int positions = (work.n_wg + 7) / 8;
-        plan->attn_tail = std::min(positions - plan->attn_first, plan->attn_first / 2);
+        // beyond the first generation, and vision lists: text rows, dealt out first, may be most of the grid
+        const int positions = (work.n_wg + 7) / 8, vision = (work.n_wg - work.text_wgs + 7) / 8;
+        plan->attn_tail = std::min({positions - plan->attn_first, plan->attn_first / 2, vision});
         plan->attn_parts = uneven ? 3 : 2;
       }
     }

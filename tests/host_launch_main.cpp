@@ -6,10 +6,13 @@
 // and the output is what stage_switch_tiles() says: tiled, output rows per workgroup, floats of LDS.  With the argument
 // "work" the lines are configurations without the last column, and the output is how often the query block that is dealt
 // out least and most often is, the share, and how many text blocks are on an XCD without a vision block of their head.
-// With the argument "deal" the lines are the same configurations; a launch's positions are gone through as the kernel does and
-// the output is: parts of a text list, lists cut at the end, the parts dealt out least and most often, slots used and slots there are.
+// With the argument "deal" and optionally the flags of all plans the lines are the same configurations; a launch's positions are
+// gone through as the kernel does, then the rows of its merge: every row has to be written once, from slots that hold its parts.
+// The output is: parts of a text list, lists cut at the end, the parts dealt out least and most often, slots used and slots there
+// are, positions of an XCD that its counter does not deal out, bytes of the workspace beside packed K and V.
 #include <algorithm>
 #include <cstdio>
+#include <cstdlib>
 #include <cstring>
 #include <set>
 #include <utility>
@@ -48,44 +51,59 @@ static int work() {
   return 0;
 }
 
-static int deal() {
+// Positions of a launch as the kernel goes through them, then the rows of its merge.
+static int deal(unsigned flags) {
   jenga_plan p = {};
   jenga_config& c = p.cfg;
+  c.flags = flags;
   while (std::scanf("%d %d %d %d %d %d %d %d %lf %lf", &c.T, &c.H, &c.W, &c.n_text, &c.batch, &c.heads, &c.head_dim,
                     &c.block, &c.topk_ratio, &c.cum_prob) == 10) {
-    if (jenga::build_host_tables(&p) != JENGA_OK) return 1;
+    int why = 0;
+    if (!jenga::config_ok(c, &why) || jenga::build_host_tables(&p) != JENGA_OK) return 1;
     const jenga::WorkMap w = jenga::plan_work(&p, c.batch * c.heads);
     const jenga::Deal d = jenga::plan_deal(&p, w, false);
-    std::vector<int> done((size_t)w.n_bh * w.M, 0), parts_of((size_t)w.n_bh * w.M, 0);
-    std::set<int> slots, rows;
-    int n, part, parts, slot, bh, i, least = 1 << 30, most = 0;
+    if (d.whole < 0 || d.tail < 0) return 2;
+    const size_t all = (size_t)w.n_bh * w.M;
+    std::vector<int> done(all, 0), parts_of(all, 0), written(all, 0);
+    std::vector<long long> slot_row(d.slots(), -1);   // row whose part is in a slot
+    std::vector<int> slot_part(d.slots(), -1);
+    int n, part, parts, slot, bh, i, least = 1 << 30, most = 0, used = 0;
     for (int r = 0; r < d.positions(); ++r)
       for (int x = 0; x < 8; ++x) {
         if (!jenga::deal_position(r, x, d, w, &n, &part, &parts, &slot) || !jenga::map_work(n, w, &bh, &i)) continue;
         const size_t row = (size_t)bh * w.M + i;
-        if (part < 0 || part >= parts || (slot >= 0) != (parts > 1)) return 2;
+        if (part < 0 || part >= parts || (slot >= 0) != (parts > 1)) return 3;
         done[row] += 1;
         parts_of[row] = parts;
-        if (slot >= 0 && (slot >= d.slots() || !slots.insert(slot).second)) return 3;
-        // where merge_kernel finds the row: text rows first, then the others
-        if (slot >= 0) {
-          const int text = d.text_rows(), y = i >= w.M_v ? n : text + n - w.text_wgs - 8 * d.whole;
-          const int first = y < text ? y * d.text_parts : text * d.text_parts + (y - text) * d.parts;
-          if (y < 0 || y >= text + d.tail_rows() || first + part != slot) return 4;
+        if (slot < 0) {
+          written[row] += 1;
+          continue;
         }
+        if (slot >= d.slots() || slot_row[slot] >= 0) return 4;
+        slot_row[slot] = (long long)row;
+        slot_part[slot] = part;
+        ++used;
       }
-    for (size_t row = 0; row < done.size(); ++row) {
+    for (int y = 0; y < d.text_rows() + d.tail_rows(); ++y) {
+      if (!jenga::merge_row(y, d, w, &n, &parts, &slot) || !jenga::map_work(n, w, &bh, &i)) continue;
+      const size_t row = (size_t)bh * w.M + i;
+      written[row] += 1;
+      for (int s = 0; s < parts; ++s)
+        if (slot + s >= d.slots() || slot_row[slot + s] != (long long)row || slot_part[slot + s] != s) return 5;
+    }
+    for (size_t row = 0; row < all; ++row) {
       least = std::min(least, done[row] - parts_of[row]);
       most = std::max(most, done[row] - parts_of[row]);
-      if (done[row] == 0) return 5;
+      if (done[row] == 0 || written[row] != 1) return 6;
     }
-    std::printf("%d %d %d %d %d %d\n", d.text_parts, d.parts > 1 ? d.tail : 0, least, most, (int)slots.size(), d.slots());
+    std::printf("%d %d %d %d %d %d %d %llu\n", d.text_parts, d.parts > 1 ? d.tail : 0, least, most, used, d.slots(), p.attn_first,
+                (unsigned long long)(p.info.attn_workspace_bytes - p.packed_bytes));
   }
   return 0;
 }
 
 int main(int argc, char** argv) {
-  if (argc > 1 && std::strcmp(argv[1], "deal") == 0) return deal();
+  if (argc > 1 && std::strcmp(argv[1], "deal") == 0) return deal(argc > 2 ? (unsigned)std::atoi(argv[2]) : 0u);
   if (argc > 1 && std::strcmp(argv[1], "work") == 0) return work();
   if (argc > 1 && std::strcmp(argv[1], "switch") == 0) return stage_switch();
   jenga_plan p = {};

@@ -276,6 +276,44 @@ def test_more_query_blocks_than_places(block, head_dim, blocks, heads, p, paced)
         assert float((lse[alive] - whole_lse[alive]).abs().max()) <= 1e-3      # float32 sums and one float32 logarithm
 
 
+# More text than vision blocks, text rows and the vision lists at the end both cut: every row comes from its own parts, also
+# where the output lies over Q, which only the row itself may still read.
+@pytest.mark.parametrize("block,vision,text,heads,topk,flags", [
+    (64, 2333, 9726, 7, 0.1, 7), (128, 1003, 25540, 4, 0.2, 4), (64, 6754, 16434, 4, 0.05, 7)])
+def test_more_text_than_vision(block, vision, text, heads, topk, flags):
+    from paper_2505_16864_amd import binding as jb
+    w = dict(T=1, H=1, W=vision, n_text=text, batch=1, heads=heads, head_dim=128, block=block, topk=topk, p=0.5, flags=flags)
+    print("more text than vision", w, flush=True)
+    layer = CarveLayer(w, "cuda:0", want_lse=True)
+    layer.permute_in(*[x.cuda() for x in ji.make_qkv(w, 65)])
+    layer.select()
+    got = []
+    layer.ws_attn.fill_(0xFF)
+    for call in (layer.attend, layer.attend, layer.pack, layer.attend_packed):
+        if call != layer.pack:
+            layer.o_c.view(torch.int16).fill_(0x7FC1)
+            layer.lse.fill_(7.0)
+        call()
+        torch.cuda.synchronize()
+        if call != layer.pack:
+            got.append((layer.o_c.clone(), layer.lse.clone()))
+    (first, first_lse), (second, second_lse), (whole, whole_lse) = got
+    assert torch.equal(first, second) and torch.equal(first_lse, second_lse)
+    q = layer.q_c.clone()
+    jb.jenga_block_sparse_attn(layer.plan, q, layer.k_c, layer.v_c, layer.sel_count, layer.sel_index, q, None,
+                               layer.ws_attn, layer.ws_attn.numel(), torch.cuda.current_stream().cuda_stream)
+    torch.cuda.synchronize()
+    assert torch.equal(q, first)
+    # bf16 probabilities taken against another reference, 2^-8 max|v|, and one unit of the bf16 result
+    err = (first.float() - whole.float()).abs()
+    assert float(err.max()) <= 2.0 ** -6 * float(layer.v_c.float().abs().max())
+    alive = torch.isfinite(whole_lse)
+    assert torch.equal(torch.isfinite(first_lse), alive)
+    assert float((first_lse[alive] - whole_lse[alive]).abs().max()) <= 1e-3      # float32 sums and one float32 logarithm
+    n_v = layer.info.M_v * block
+    assert bool((err[:, :, :n_v] > 0).any()) and bool((err[:, :, n_v:] > 0).any())   # of both some were cut
+
+
 # Pad rows of K and V may hold anything: in place, V's reach the second product with probabilities of zero.  Ragged blocks
 # of one row, one short, and around the 64 keys of a step.
 @pytest.mark.parametrize("head_dim,block", [(64, 32), (64, 64), (128, 64), (64, 128), (128, 128)])

@@ -25,7 +25,7 @@ def driver(tmp_path_factory):
 def _run(driver, rows, *args):
     lines = "".join(" ".join(str(x) for x in row) + "\n" for row in rows)
     r = subprocess.run([driver, *args], input=lines, capture_output=True, text=True, timeout=120)
-    assert r.returncode == 0, r.stderr
+    assert r.returncode == 0, (r.returncode, rows[r.stdout.count("\n")], r.stderr)
     return [line.split() for line in r.stdout.strip().split("\n")]
 
 
@@ -69,11 +69,30 @@ def test_positions_cover_every_part_once(driver):
             for n_text in (0, 3, 300) for topk, p in ((0.3, 0.3), (0.1, 0.3), (0.25, 0.9))]
     text, tails = set(), 0
     for row, got in zip(rows, _run(driver, rows, "deal")):
-        text_parts, tail, least, most, used, slots = [int(x) for x in got]
+        text_parts, tail, least, most, used, slots = [int(x) for x in got[:6]]
         assert (least, most) == (0, 0) and used <= slots, row
         text.add(text_parts)
         tails += tail > 0
     assert len(text) > 3 and tails > 10
+
+
+# The same where text blocks outnumber vision blocks, down to a single one: the lists cut at the end are vision lists, of which
+# an XCD then has fewer than it has places for.
+@pytest.mark.parametrize("flags", [0, 4, 5, 7, 15])
+def test_positions_cover_every_part_once_with_more_text_than_vision(driver, flags):
+    rows = [(1, 1, block * m_v - 3, block * m_c - 7, 1, heads, d, block, topk, p)
+            for block in (64, 128) for d in (64, 128) for m_c in (36, 77, 120, 500, 1064)
+            for m_v in sorted({min(2048 - m_c, max(1, m_c * part // 100)) for part in (0, 3, 7, 17, 40, 100)})
+            for heads in (1, 4, 7, 12, 24) for topk, p in ((0.05, 0.5), (0.2, 0.5), (0.3, 0.3), (0.25, 0.9))]
+    rows += [(1, 1, 6754, 16434, 1, 4, 128, 64, 0.05, 0.5), (1, 1, 2333, 9726, 1, 7, 128, 64, 0.1, 0.5),
+             (1, 1, 2560, 13824, 1, 12, 128, 128, 0.2, 0.5), (1, 1, 46327, 136099, 1, 1, 128, 128, 0.05, 0.5),
+             (1, 1, 1024, 15360, 1, 8, 128, 128, 0.2, 0.5), (1, 1, 3840, 15360, 1, 8, 128, 128, 0.2, 0.5)]
+    both = 0
+    for row, got in zip(rows, _run(driver, rows, "deal", str(flags))):
+        text_parts, tail, least, most, used, slots, _, _ = [int(x) for x in got]
+        assert (least, most) == (0, 0) and used <= slots, row
+        both += tail > 0 and text_parts > 1
+    assert both > 0
 
 
 # Planes of a stage switch: 2^24 of them are more than one grid takes with a workgroup each.
