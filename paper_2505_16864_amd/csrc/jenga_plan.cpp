@@ -280,20 +280,6 @@ static void split_lists(jenga_plan* plan) {
     const double usual = std::max((double)len, c.cum_prob * c.cum_prob * f.M), gens = (double)rows / places;
     const double block_us = c.block == 128 ? (c.head_dim == 128 ? 6.3 : 3.6) : (c.head_dim == 128 ? 2.6 : 1.8);
     const long long text_rows = (long long)c.batch * c.heads * f.M_c;
-    if (work.text_wgs <= 32768) {   // rows of a merge
-      if (gens <= 1.0) {
-        double least = f.M + ((rows + 255) / 256 - 1) * usual - 384 / c.block;
-        for (int parts = 2; parts <= 8; ++parts) {
-          const double load = std::max((double)f.M / parts, usual) + ((rows + text_rows * (parts - 1) + 255) / 256 - 1) * usual;
-          if (load < least) {
-            least = load;
-            plan->attn_text_parts = parts;
-          }
-        }
-      } else if (f.M * block_us >= 400.0 && f.M > (gens < 1.5 ? 1.15 : 1.8) * gens * usual) {
-        plan->attn_text_parts = std::min(8, (int)std::ceil(f.M / (gens * usual)));
-      }
-    }
     if (rows > places && (c.block == 128 || uneven) && usual * block_us >= (c.head_dim == 128 ? 200.0 : 320.0)) {
       plan->attn_first = 32 * (c.block == 64 && c.head_dim == 128 ? 4 : attn_h_per_cu(c.block, c.head_dim));
       if (uneven || rows >= 2 * places) {
@@ -302,6 +288,26 @@ static void split_lists(jenga_plan* plan) {
         plan->attn_tail = std::min({positions - plan->attn_first, plan->attn_first / 2, vision});
         plan->attn_parts = uneven ? 3 : 2;
       }
+    }
+    // Text rows may be most of the grid too: as many parts as there is room for beside the lists cut at the end, in the area
+    // or where packed K would lie.
+    const bool in_place = c.block == 64 || !(c.flags & JENGA_FLAG_PACED_WALK);
+    const uint64_t room = std::max<uint64_t>(RANGE_AREA_BYTES, in_place ? (plan->packed_bytes - 256) / 2 : 0);
+    const uint64_t part_bytes = (uint64_t)c.block * (c.head_dim + 2) * 4;
+    const uint64_t text_slots = room / part_bytes - 8ull * plan->attn_tail * plan->attn_parts;
+    const int most = work.text_wgs > 0 && work.text_wgs <= 32768   // rows of a merge
+                         ? (int)std::min<uint64_t>(8, text_slots / ((work.text_wgs + 7) / 8 * 8)) : 1;
+    if (gens <= 1.0) {
+      double least = f.M + ((rows + 255) / 256 - 1) * usual - 384 / c.block;
+      for (int parts = 2; parts <= most; ++parts) {
+        const double load = std::max((double)f.M / parts, usual) + ((rows + text_rows * (parts - 1) + 255) / 256 - 1) * usual;
+        if (load < least) {
+          least = load;
+          plan->attn_text_parts = parts;
+        }
+      }
+    } else if (f.M * block_us >= 400.0 && f.M > (gens < 1.5 ? 1.15 : 1.8) * gens * usual) {
+      plan->attn_text_parts = std::max(1, std::min(most, (int)std::ceil(f.M / (gens * usual))));
     }
     return;
   }

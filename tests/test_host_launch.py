@@ -95,6 +95,22 @@ def test_positions_cover_every_part_once_with_more_text_than_vision(driver, flag
     assert both > 0
 
 
+# Results of parts take 129 MiB of the workspace at most, also of text rows, of which there may be tens of thousands.
+@pytest.mark.parametrize("flags", [0, 7, 15])
+def test_parts_of_text_rows_are_bounded(driver, flags):
+    rows = [(1, 1, vision, n_text, batch, heads, d, block, topk, p)
+            for block in (64, 128) for d in (64, 128) for n_text in (10000, 27348, 64000, 109477, 128000)
+            for vision in (100, 893, 2068, 15000) for batch, heads in ((1, 1), (1, 3), (1, 14), (2, 40))
+            for topk, p in ((0.05, 0.0), (0.05, 0.5), (0.3, 0.2), (0.2, 0.9))
+            if -(-vision // block) + -(-n_text // block) <= 2048]
+    rows += [(1, 1, 8330, 9838, 1, 8, 128, 128, 0.05, 0.5), (33, 45, 80, 256, 1, 24, 128, 128, 0.1, 0.3)]
+    cut = 0
+    for row, got in zip(rows, _run(driver, rows, "deal", str(flags))):
+        assert int(got[7]) <= 129 << 20, (row, got)
+        cut += int(got[0]) > 1
+    assert cut > 0
+
+
 # Planes of a stage switch: 2^24 of them are more than one grid takes with a workgroup each.
 def test_stage_switch_launches_stay_below_the_grid_limit(driver):
     rows = [(channels, t, h, w, t, h, w, 1) for channels in (1, 16, 1 << 20, (1 << 24) - 1, 1 << 24, (1 << 31) - 1)
