@@ -198,7 +198,7 @@ int jenga_select_blocks_static(const jenga_plan* plan, const void* q_curve, cons
  *                do not, 129 MiB of them at most), contents undefined after
  * Equivalent to jenga_pack_kv followed by jenga_block_sparse_attn_packed on the same workspace (the latter
  * never cuts lists, since calls on one packed workspace may overlap: where this call does, the two differ
- * in the last bits; so may a call whose outputs lie over both K and V).
+ * in the last bits; so may a call whose outputs lie over both K and V, or with both off the 16-byte grid).
  */
 int jenga_block_sparse_attn(const jenga_plan* plan, const void* q, const void* k, const void* v,
                             const int32_t* sel_count, const int32_t* sel_index, void* out_curve,

@@ -134,19 +134,21 @@ int jenga_block_sparse_attn(const jenga_plan* p, const void* q, const void* k, c
   if (!on_plan_device(p)) return JENGA_EINVAL;
   if (((uintptr_t)workspace & 255u) != 0) return JENGA_EINVAL;
   if (workspace_bytes < p->info.attn_workspace_bytes) return JENGA_EWORKSPACE;
-  // Where K and V are read in place, one that an output lies over is copied first; if both are, they are packed.
+  // Where K and V are read in place, one that an output lies over, or that is off the 16-byte grid, which the copies into LDS
+  // want (ordinary loads take any address), is copied first; if both are, they are packed.
   const size_t rows = (size_t)p->cfg.batch * p->cfg.heads * p->info.N_pad, bytes = rows * p->cfg.head_dim * 2;
-  auto written = [&](const void* x) {
-    return overlap(x, bytes, out_curve, bytes) || (lse_or_null && overlap(x, bytes, lse_or_null, rows * 4));
+  auto moved = [&](const void* x) {
+    return ((uintptr_t)x & 15u) != 0 || overlap(x, bytes, out_curve, bytes) ||
+           (lse_or_null && overlap(x, bytes, lse_or_null, rows * 4));
   };
-  const bool k_written = written(k), v_written = written(v);
+  const bool k_moved = moved(k), v_moved = moved(v);
   int rc = JENGA_OK;
-  if (!jenga::reads_kv_in_place(p) || (k_written && v_written)) {
+  if (!jenga::reads_kv_in_place(p) || (k_moved && v_moved)) {
     rc = jenga::launch_pack(p, k, v, workspace, stream);
     k = v = nullptr;
-  } else if (k_written) {
+  } else if (k_moved) {
     rc = jenga::launch_keep(p, k, workspace, 0, &k, stream);
-  } else if (v_written) {
+  } else if (v_moved) {
     rc = jenga::launch_keep(p, v, workspace, 1, &v, stream);
   }
   if (rc != JENGA_OK) return rc;

@@ -168,8 +168,8 @@ int select_scratch_init(int device);
 int launch_pack(const jenga_plan* p, const void* k, const void* v, void* ws, void* stream);
 // Whether launch_attention can read K and V as they are instead of packed.
 bool reads_kv_in_place(const jenga_plan* p);
-// K (which = 0) or V as it is into its half of a packed workspace, for a call that reads in place but writes over it; returns
-// the copy in *copied.
+// K (which = 0) or V as it is into its half of a packed workspace, for a call that reads in place but cannot read this one
+// there; returns the copy in *copied.
 int launch_keep(const jenga_plan* p, const void* src, void* ws, int which, const void** copied, void* stream);
 // k, v: to be read in place (one of them may be a copy in the workspace), or NULL (packed in the workspace).  may_split: the
 // call has the workspace to itself and may write behind the packed tiles, or where they would be.

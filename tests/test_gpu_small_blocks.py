@@ -226,6 +226,32 @@ def test_output_over_an_input(block, flags, heads):
             assert torch.equal(t[over], want)
 
 
+# K and V anywhere in a buffer: the copies into LDS want 16-byte addresses, so either is copied or both are packed first.
+@pytest.mark.parametrize("block,heads,flags", [(32, 2, 7), (64, 2, 7), (64, 90, 7), (128, 2, 7), (128, 90, 7), (128, 2, 15)])
+@pytest.mark.parametrize("off_k,off_v", [(0, 1), (4, 0), (0, 4), (1, 4), (8, 8)])
+def test_inputs_off_the_16_byte_grid(block, heads, flags, off_k, off_v):
+    from paper_2505_16864_amd import binding as jb
+    w = dict(T=1, H=1, W=block * 11 - 9, n_text=block + 5, batch=1, heads=heads, head_dim=64, block=block, topk=0.4, p=0.3,
+             flags=flags)
+    print("off the grid", w, off_k, off_v, flush=True)
+    layer = CarveLayer(w, "cuda:0")
+    layer.permute_in(*[x.cuda() for x in ji.make_qkv(w, 66)])
+    layer.select()
+    layer.attend()
+    torch.cuda.synchronize()
+    want = layer.o_c.clone()
+    at = []
+    for x, off in ((layer.k_c, off_k), (layer.v_c, off_v)):
+        room = torch.empty(x.numel() + 8, dtype=x.dtype, device=x.device)
+        at.append(room[off:off + x.numel()].view(x.shape).copy_(x))
+        assert at[-1].data_ptr() % 16 == 2 * off % 16
+    layer.o_c.view(torch.int16).fill_(0x7FC1)
+    jb.jenga_block_sparse_attn(layer.plan, layer.q_c, at[0], at[1], layer.sel_count, layer.sel_index, layer.o_c, None,
+                               layer.ws_attn, layer.ws_attn.numel(), torch.cuda.current_stream().cuda_stream)
+    torch.cuda.synchronize()
+    assert torch.equal(layer.o_c, want)
+
+
 # More query blocks than resident workgroups: they are dealt out by counters, and the lists at the end of each XCD's are cut
 # (or not: one to two generations of even lists).  Lists shorter than the number of parts, empty and full; twice over, the
 # second time with what the first left in the workspace.  Whole lists are visited as the packed entry visits them, which
