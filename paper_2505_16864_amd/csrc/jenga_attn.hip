@@ -52,8 +52,9 @@ __device__ inline uint32_t pack_bf16x2(float lo, float hi) {
   return __builtin_bit_cast(uint32_t, __builtin_convertvector(v, bf16x2));
 }
 
-// Launch parameters, behind the packed tiles: the pace of the paced walk, the eight counters of a queue (see take_item).
-constexpr int PARAM_QUEUE = 8;
+// Launch parameters, behind the packed tiles: the pace of the paced walk, the eight counters of a queue (see take_item) and
+// behind them whether it is used.
+constexpr int PARAM_QUEUE = 8, QUEUE_USED = 8;
 
 // grid (M, batch*heads, 2).  z = 0: K tile -> fragment order; z = 1: V tile -> transposed fragment order, pad rows zeroed.
 // A workgroup each, so that the two chains of loads and stores run side by side: 931 blocks x 24 heads (2.9 GB) 531 ->
@@ -291,15 +292,18 @@ __global__ __launch_bounds__(2 * BLK, (attn_h_min_waves<BLK, D>())) void attn_h_
   const bool dealt = SPLIT && split.deal.parts > 0;
   if constexpr (SPLIT) {
     if (dealt) {
-      if (queue != nullptr && n >= 8 * split.first) {
+      jenga::Deal deal = split.deal;
+      if (queue != nullptr && __builtin_amdgcn_readfirstlane((int)queue[QUEUE_USED]) == 0) {
+        deal = deal.vision_whole();
+      } else if (queue != nullptr && n >= 8 * split.first) {
         volatile int* taken = (volatile int*)Ks;   // no tile is in there yet
-        if (threadIdx.x == 0) *taken = take_item(queue, 8 * split.deal.positions());
+        if (threadIdx.x == 0) *taken = take_item(queue, 8 * deal.positions());
         __syncthreads();
         n = __builtin_amdgcn_readfirstlane(*taken);
         __syncthreads();
         if (n < 0) return;
       }
-      if (!jenga::deal_position(n >> 3, n & 7, split.deal, work, &n, &part, &n_parts, &slot)) return;
+      if (!jenga::deal_position(n >> 3, n & 7, deal, work, &n, &part, &n_parts, &slot)) return;
     } else {
       part = n / split.stride;
       n -= part * split.stride;
@@ -678,20 +682,21 @@ __global__ __launch_bounds__(2 * BLK, (attn_h_min_waves<BLK, D>())) void attn_h_
     }
 }
 
-// merge_kernel: grid (BLK / 32, M, batch * heads) or, behind a queue, (BLK / 32, slots), one wavefront per channel tile of 32
-// query rows.  Puts the parts of the lists that attn_h_kernel<.., SPLIT> cut together, in the order of the parts; the other
+// merge_kernel: grid (BLK / 32, M, batch * heads) or, with a Deal, (BLK / 32, rows that are cut), one wavefront per channel tile
+// of 32 query rows.  Puts the parts of the lists that attn_h_kernel<.., SPLIT> cut together, in the order of the parts; the other
 // rows are done already.
 template <int BLK, int D>
 __global__ __launch_bounds__(2 * D) void merge_kernel(const int32_t* __restrict__ sel_count, uint16_t* __restrict__ out,
                                                       float* __restrict__ lse, WorkMap work, int n_pad, int pad_v,
-                                                      int pad_c, Split split) {
+                                                      int pad_c, Split split, const uint32_t* __restrict__ queue) {
   constexpr int DT = D / 32, NW = BLK / 32;
   const int M = work.M, M_v = work.M_v, wave = blockIdx.x;
   int i = blockIdx.y, bh = blockIdx.z, n_parts;
   size_t slot = (size_t)bh * M + i;
   if (split.deal.parts > 0) {
     int n, first;
-    if (!jenga::merge_row(blockIdx.y, split.deal, work, &n, &n_parts, &first) || !map_work(n, work, &bh, &i)) return;
+    const jenga::Deal deal = queue != nullptr && queue[QUEUE_USED] == 0 ? split.deal.vision_whole() : split.deal;
+    if (!jenga::merge_row(blockIdx.y, deal, work, &n, &n_parts, &first) || !map_work(n, work, &bh, &i)) return;
     slot = first;
   } else {
     n_parts = split.of(min(max(sel_count[slot], 0), M));
@@ -1047,45 +1052,61 @@ __global__ __launch_bounds__(64 * NS, 4) void attn_rows_kernel(
                               Split{});
 }
 
+// What a launch has to know of the lists' lengths.  One workgroup.
 // Lap of the paced walk, common to all workgroups of a launch: a fixed fraction of the time a workgroup needs for
 // a list of mean length (a tuning constant: between 0.45 and 0.9 the measured time is flat, at 1.0 and above the
 // workgroups run ahead of the sweep and the gain goes).  Writes 2^32 / lap (in ticks of
-// the 100 MHz clock) to params[0].  One workgroup.
+// the 100 MHz clock) to params[0].
+// A queue, if there is one: its counters, and whether it is used, which takes vision lists of `long_list` blocks on average.  The
+// plan goes by the length it expects (split_lists), but lists are the caller's: on lists of 2 to 30 blocks counters and cuts cost
+// up to 360 us a call.  492 blocks of 64 x 12 heads, D = 64, p = 0.9, lists of 2 / 8 / 30 / 60: with them 218 / 257 / 407 / 617 us,
+// lists dealt out in order and whole 45 / 84 / 229 / 435; 736 x 12 likewise, selected lists of 153: 2405 -> 2279.
 #ifndef JENGA_PACE_FACTOR
 #define JENGA_PACE_FACTOR 0.6f
 #endif
-__global__ __launch_bounds__(1024) void walk_pace_kernel(const int32_t* __restrict__ sel_count, int n_rows, int M,
-                                                         float ticks_per_block, uint32_t* __restrict__ params,
-                                                         uint32_t* queue, int queue_first) {
-  __shared__ float part[16];
+__global__ __launch_bounds__(1024) void list_lengths_kernel(const int32_t* __restrict__ sel_count, int n_rows, int M, int M_v,
+                                                            float ticks_per_block, uint32_t* __restrict__ params,
+                                                            uint32_t* queue, int queue_first, float long_list) {
+  __shared__ float part[2][16];
   if (queue != nullptr && threadIdx.x < 8) queue[threadIdx.x] = queue_first;
-  float s = 0.f;
+  float s = 0.f, vision = 0.f;
   for (int t0 = threadIdx.x; t0 < n_rows; t0 += 4096) {   // four loads in flight per thread
     int c[4];
 #pragma unroll
     for (int u = 0; u < 4; ++u) c[u] = t0 + u * 1024 < n_rows ? sel_count[t0 + u * 1024] : 0;
 #pragma unroll
-    for (int u = 0; u < 4; ++u) s += (float)min(max(c[u], 0), M);
+    for (int u = 0; u < 4; ++u) {
+      const float len = (float)min(max(c[u], 0), M);
+      s += len;
+      if ((t0 + u * 1024) % M < M_v) vision += len;
+    }
   }
 #pragma unroll
-  for (int o = 32; o >= 1; o >>= 1) s += __shfl_xor(s, o, 64);
-  if ((threadIdx.x & 63) == 0) part[threadIdx.x >> 6] = s;
+  for (int o = 32; o >= 1; o >>= 1) {
+    s += __shfl_xor(s, o, 64);
+    vision += __shfl_xor(vision, o, 64);
+  }
+  if ((threadIdx.x & 63) == 0) {
+    part[0][threadIdx.x >> 6] = s;
+    part[1][threadIdx.x >> 6] = vision;
+  }
   __syncthreads();
   if (threadIdx.x == 0) {
-    float total = 0.f;
-    for (int w = 0; w < 16; ++w) total += part[w];
+    float total = 0.f, total_vision = 0.f;
+    for (int w = 0; w < 16; ++w) {
+      total += part[0][w];
+      total_vision += part[1][w];
+    }
     const float mean = total / (float)max(n_rows, 1);
     const float lap = fminf(fmaxf(JENGA_PACE_FACTOR * mean * ticks_per_block, 1024.f), 1e9f);
     params[0] = (uint32_t)(4294967296.0 / (double)lap);
+    if (queue != nullptr) queue[QUEUE_USED] = total_vision >= long_list * (float)(n_rows / M * M_v);
   }
 }
 
 __global__ __launch_bounds__(256) void copy_kernel(const uint4* __restrict__ src, uint4* __restrict__ dst, size_t n) {
   for (size_t t = (size_t)blockIdx.x * 256 + threadIdx.x; t < n; t += (size_t)gridDim.x * 256) dst[t] = src[t];
 }
-
-// Sets the counters of a queue.
-__global__ void queue_kernel(uint32_t* queue, int queue_first) { queue[threadIdx.x] = queue_first; }
 
 // Counters of a launch that deals its query blocks out as workgroups become free; nullptr where the plan has none.
 uint32_t* attn_queue(const jenga_plan* p, void* ws) {
@@ -1144,7 +1165,7 @@ int run_attention(const jenga_plan* p, const void* q, const void* k, const void*
         attn_kernel<D, NS, true><<<dim3(split.parts * split.stride), 64 * NS, 0, st>>>(
             q0, kp0, vp0, count0, index0, ob0, lse0, work, f.N_pad, f.pad_v, f.pad_c, scale, bias, split);
         merge_kernel<BLK, D><<<dim3(1, f.M, n), 2 * D, 0, st>>>(count0, ob0, lse0, work, f.N_pad, f.pad_v, f.pad_c,
-                                                                split);
+                                                                split, nullptr);
         continue;
       }
       if constexpr (D == 64) {
@@ -1165,13 +1186,11 @@ int run_attention(const jenga_plan* p, const void* q, const void* k, const void*
 #define JENGA_ATTN(PACED, SPLIT, K_ROWS, WGS)                                                                    \
   attn_h_kernel<BLK, D, PACED, SPLIT, K_ROWS><<<dim3(WGS), 2 * BLK, 0, st>>>(                                    \
       qb, kp, vp, sel_count, sel_index, ob, lse, work, f.N_pad, f.pad_v, f.pad_c, scale, bias, pace, split, queue)
-    if (paced && !(may_split && p->attn_first == 0 && p->attn_parts > 1)) {   // parts of short grids: ascending order
+    if (paced && !(may_split && p->attn_first == 0 && p->attn_parts > 1)) pace = params;   // parts of short grids: ascending order
+    if (pace != nullptr || queue != nullptr) {
       // a workgroup spends about 6.3 us (D = 128; 3.6 us at D = 64) on a block of 128 keys when three share a CU
-      pace = params;
-      walk_pace_kernel<<<1, 1024, 0, st>>>(sel_count, bh * f.M, f.M, D == 128 ? 630.f : 360.f, pace, queue,
-                                           p->attn_first);
-    } else if (queue != nullptr) {
-      queue_kernel<<<1, 8, 0, st>>>(queue, p->attn_first);
+      list_lengths_kernel<<<1, 1024, 0, st>>>(sel_count, bh * f.M, f.M, f.M_v, D == 128 ? 630.f : 360.f, params, queue,
+                                              p->attn_first, p->attn_long);
     }
     const bool dealt = p->attn_first > 0 || p->attn_text_parts > 1;
     if (may_split && (dealt || p->attn_parts > 1)) {
@@ -1203,7 +1222,7 @@ int run_attention(const jenga_plan* p, const void* q, const void* k, const void*
       if (k_rows && !paced) JENGA_ATTN(false, true, true, wgs);
       else if (!paced) JENGA_ATTN(false, true, false, wgs);
       if (slots > 0)
-        merge_kernel<BLK, D><<<merge, 2 * D, 0, st>>>(sel_count, ob, lse, work, f.N_pad, f.pad_v, f.pad_c, split);
+        merge_kernel<BLK, D><<<merge, 2 * D, 0, st>>>(sel_count, ob, lse, work, f.N_pad, f.pad_v, f.pad_c, split, queue);
       return hipGetLastError() == hipSuccess ? JENGA_OK : JENGA_EHIP;
     }
     if constexpr (BLK == 128) {

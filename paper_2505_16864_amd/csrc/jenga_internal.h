@@ -20,7 +20,8 @@ struct jenga_plan {
   // attn_chunk = 0: every list into attn_parts ranges of key blocks
   int attn_parts, attn_chunk;
   int attn_heads;  // (batch, head) pairs per launch where lists are cut
-  int attn_first;  // > 0: query blocks are dealt out by counters; that many per XCD are not
+  int attn_first;  // > 0: query blocks are dealt out by counters, and attn_tail lists cut; that many per XCD are not
+  float attn_long; // if a call's vision lists have that many blocks on average
   int attn_text_parts;  // parts that the lists of text query blocks are cut into
   int attn_tail;   // lists that are cut, all into attn_parts, at the end of each XCD's
   bool attn_over_kv; // their results lie where packed K would, or packed V: not needed when K and V are read in place
@@ -97,6 +98,8 @@ JENGA_HOST_DEVICE inline bool map_work(int n, const WorkMap& w, int* bh, int* i)
 struct Deal {
   int text, text_parts, whole, tail, parts;
   JENGA_HOST_DEVICE int positions() const { return text * text_parts + whole + tail * parts; }
+  // the same launch where the counters are not used: workgroups beyond the positions have nothing to do
+  JENGA_HOST_DEVICE Deal vision_whole() const { return {text, text_parts, whole + tail, 0, 1}; }
   JENGA_HOST_DEVICE int text_rows() const { return text_parts > 1 ? 8 * text : 0; }   // that are cut
   JENGA_HOST_DEVICE int tail_rows() const { return parts > 1 ? 8 * tail : 0; }
   JENGA_HOST_DEVICE int slots() const { return text_rows() * text_parts + tail_rows() * parts; }

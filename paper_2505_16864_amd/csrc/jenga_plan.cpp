@@ -252,6 +252,7 @@ static void split_lists(jenga_plan* plan) {
   const jenga_plan_info_t& f = plan->info;
   plan->attn_parts = 1;
   plan->attn_first = plan->attn_tail = 0;
+  plan->attn_long = 0.f;
   plan->attn_text_parts = 1;
   plan->attn_chunk = f.M;
   plan->attn_heads = c.batch * c.heads;
@@ -280,7 +281,9 @@ static void split_lists(jenga_plan* plan) {
     const double usual = std::max((double)len, c.cum_prob * c.cum_prob * f.M), gens = (double)rows / places;
     const double block_us = c.block == 128 ? (c.head_dim == 128 ? 6.3 : 3.6) : (c.head_dim == 128 ? 2.6 : 1.8);
     const long long text_rows = (long long)c.batch * c.heads * f.M_c;
-    if (rows > places && (c.block == 128 || uneven) && usual * block_us >= (c.head_dim == 128 ? 200.0 : 320.0)) {
+    const double long_list = (c.head_dim == 128 ? 200.0 : 320.0) / block_us;
+    if (rows > places && (c.block == 128 || uneven) && usual >= long_list) {
+      plan->attn_long = (float)long_list;
       plan->attn_first = 32 * (c.block == 64 && c.head_dim == 128 ? 4 : attn_h_per_cu(c.block, c.head_dim));
       if (uneven || rows >= 2 * places) {
         // beyond the first generation, and vision lists: text rows, dealt out first, may be most of the grid

@@ -61,42 +61,46 @@ static int deal(unsigned flags) {
     int why = 0;
     if (!jenga::config_ok(c, &why) || jenga::build_host_tables(&p) != JENGA_OK) return 1;
     const jenga::WorkMap w = jenga::plan_work(&p, c.batch * c.heads);
-    const jenga::Deal d = jenga::plan_deal(&p, w, false);
-    if (d.whole < 0 || d.tail < 0) return 2;
+    const jenga::Deal cut = jenga::plan_deal(&p, w, false);
+    if (cut.whole < 0 || cut.tail < 0) return 2;
     const size_t all = (size_t)w.n_bh * w.M;
-    std::vector<int> done(all, 0), parts_of(all, 0), written(all, 0);
-    std::vector<long long> slot_row(d.slots(), -1);   // row whose part is in a slot
-    std::vector<int> slot_part(d.slots(), -1);
-    int n, part, parts, slot, bh, i, least = 1 << 30, most = 0, used = 0;
-    for (int r = 0; r < d.positions(); ++r)
-      for (int x = 0; x < 8; ++x) {
-        if (!jenga::deal_position(r, x, d, w, &n, &part, &parts, &slot) || !jenga::map_work(n, w, &bh, &i)) continue;
-        const size_t row = (size_t)bh * w.M + i;
-        if (part < 0 || part >= parts || (slot >= 0) != (parts > 1)) return 3;
-        done[row] += 1;
-        parts_of[row] = parts;
-        if (slot < 0) {
-          written[row] += 1;
-          continue;
+    int least = 1 << 30, most = 0, used = 0;
+    for (const jenga::Deal& d : {cut.vision_whole(), cut}) {   // the same workgroups, without and with the counters
+      used = 0;
+      std::vector<int> done(all, 0), parts_of(all, 0), written(all, 0);
+      std::vector<long long> slot_row(d.slots(), -1);   // row whose part is in a slot
+      std::vector<int> slot_part(d.slots(), -1);
+      int n, part, parts, slot, bh, i;
+      for (int r = 0; r < cut.positions() + (cut.positions() + 3) / 4; ++r)
+        for (int x = 0; x < 8; ++x) {
+          if (!jenga::deal_position(r, x, d, w, &n, &part, &parts, &slot) || !jenga::map_work(n, w, &bh, &i)) continue;
+          const size_t row = (size_t)bh * w.M + i;
+          if (part < 0 || part >= parts || (slot >= 0) != (parts > 1)) return 3;
+          done[row] += 1;
+          parts_of[row] = parts;
+          if (slot < 0) {
+            written[row] += 1;
+            continue;
+          }
+          if (slot >= d.slots() || slot_row[slot] >= 0) return 4;
+          slot_row[slot] = (long long)row;
+          slot_part[slot] = part;
+          ++used;
         }
-        if (slot >= d.slots() || slot_row[slot] >= 0) return 4;
-        slot_row[slot] = (long long)row;
-        slot_part[slot] = part;
-        ++used;
+      for (int y = 0; y < cut.text_rows() + cut.tail_rows(); ++y) {
+        if (!jenga::merge_row(y, d, w, &n, &parts, &slot) || !jenga::map_work(n, w, &bh, &i)) continue;
+        const size_t row = (size_t)bh * w.M + i;
+        written[row] += 1;
+        for (int s = 0; s < parts; ++s)
+          if (slot + s >= d.slots() || slot_row[slot + s] != (long long)row || slot_part[slot + s] != s) return 5;
       }
-    for (int y = 0; y < d.text_rows() + d.tail_rows(); ++y) {
-      if (!jenga::merge_row(y, d, w, &n, &parts, &slot) || !jenga::map_work(n, w, &bh, &i)) continue;
-      const size_t row = (size_t)bh * w.M + i;
-      written[row] += 1;
-      for (int s = 0; s < parts; ++s)
-        if (slot + s >= d.slots() || slot_row[slot + s] != (long long)row || slot_part[slot + s] != s) return 5;
+      for (size_t row = 0; row < all; ++row) {
+        least = std::min(least, done[row] - parts_of[row]);
+        most = std::max(most, done[row] - parts_of[row]);
+        if (done[row] == 0 || written[row] != 1) return 6;
+      }
     }
-    for (size_t row = 0; row < all; ++row) {
-      least = std::min(least, done[row] - parts_of[row]);
-      most = std::max(most, done[row] - parts_of[row]);
-      if (done[row] == 0 || written[row] != 1) return 6;
-    }
-    std::printf("%d %d %d %d %d %d %d %llu\n", d.text_parts, d.parts > 1 ? d.tail : 0, least, most, used, d.slots(), p.attn_first,
+    std::printf("%d %d %d %d %d %d %d %llu\n", cut.text_parts, cut.parts > 1 ? cut.tail : 0, least, most, used, cut.slots(), p.attn_first,
                 (unsigned long long)(p.info.attn_workspace_bytes - p.packed_bytes));
   }
   return 0;

@@ -252,19 +252,9 @@ def test_inputs_off_the_16_byte_grid(block, heads, flags, off_k, off_v):
     assert torch.equal(layer.o_c, want)
 
 
-# More query blocks than resident workgroups: they are dealt out by counters, and the lists at the end of each XCD's are cut
-# (or not: one to two generations of even lists).  Lists shorter than the number of parts, empty and full; twice over, the
-# second time with what the first left in the workspace.  Whole lists are visited as the packed entry visits them, which
-# deals nothing out and cuts nothing.
-@pytest.mark.parametrize("block,head_dim,blocks,heads,p,paced", [
-    (128, 128, 9, 86, 0.3, False), (128, 128, 13, 120, 0.3, False), (128, 128, 13, 61, 0.9, True),
-    (128, 64, 37, 29, 0.9, False), (128, 64, 9, 230, 0.3, True), (64, 128, 29, 46, 0.9, False), (64, 64, 31, 67, 0.9, False),
-    # text rows cut: in one generation, behind a counter, 64 tokens
-    (128, 64, 67, 13, 0.3, True), (128, 64, 67, 13, 0.3, False), (128, 128, 113, 8, 0.3, False), (64, 64, 121, 14, 0.3, False),
-    # lists long enough for the counters: one to two generations, two and more, lists of uneven length, the paced walk
-    (128, 128, 97, 9, 0.3, False), (128, 128, 97, 17, 0.3, True), (128, 128, 37, 24, 0.97, False), (128, 64, 97, 11, 0.97, True),
-    (64, 128, 83, 16, 0.97, False), (64, 64, 193, 11, 0.97, False)])
-def test_more_query_blocks_than_places(block, head_dim, blocks, heads, p, paced):
+# The direct entry twice, the second time with what the first left in the workspace, and the packed entry, which deals nothing
+# out and cuts nothing: output and log-sum-exp of each, and the layer.  Lists of random blocks, of the given lengths.
+def _direct_twice_and_packed(block, head_dim, blocks, heads, p, paced, lengths):
     w = dict(T=1, H=1, W=block * (blocks - 1) - 9, n_text=5, batch=1, heads=heads, head_dim=head_dim, block=block, topk=0.3,
              p=p, text_bias=0.4, flags=15 if paced else 7)
     print("dealt out", w, flush=True)
@@ -274,7 +264,7 @@ def test_more_query_blocks_than_places(block, head_dim, blocks, heads, p, paced)
     layer.permute_in(*[x.cuda() for x in ji.make_qkv(w, 62)])
     rng = np.random.default_rng(9)
     idx = np.argsort(rng.random((1, heads, M, M)), axis=-1).astype(np.int32)
-    cnt = rng.choice([0, 1, 2, 3, M // 2, M - 1, M], size=(1, heads, M)).astype(np.int32)
+    cnt = rng.choice([int(x) for x in lengths(M)], size=(1, heads, M)).astype(np.int32)
     layer.sel_count.copy_(torch.from_numpy(cnt))
     layer.sel_index.copy_(torch.from_numpy(idx))
     got = []
@@ -287,19 +277,57 @@ def test_more_query_blocks_than_places(block, head_dim, blocks, heads, p, paced)
         torch.cuda.synchronize()
         if call != layer.pack:
             got.append((layer.o_c.float().clone(), layer.lse.clone()))
-    (first, first_lse), (second, second_lse), (whole, whole_lse) = got
+    (first, first_lse), _, (whole, whole_lse) = got
     assert torch.isfinite(first).all()
-    if not paced:
-        assert torch.equal(first, second) and torch.equal(first_lse, second_lse)
-        # at most half a generation of lists is cut, and the text rows
-        cut = (first != whole).any(dim=-1).view(heads * M, block).any(dim=-1).sum()
-        assert int(cut) <= 256 * {(128, 128): 3, (128, 64): 4, (64, 128): 4, (64, 64): 8}[(block, head_dim)] // 2 + heads
     # bf16 probabilities taken against another reference, 2^-8 max|v|, and one unit of the bf16 result
-    for o, lse in ((first, first_lse), (second, second_lse)):
+    for o, lse in got[:2]:
         assert float((o - whole).abs().max()) <= 2.0 ** -6 * float(layer.v_c.float().abs().max())
         alive = torch.isfinite(whole_lse)
         assert torch.equal(torch.isfinite(lse), alive) and torch.isneginf(lse[~alive]).all()
         assert float((lse[alive] - whole_lse[alive]).abs().max()) <= 1e-3      # float32 sums and one float32 logarithm
+    if not paced:
+        assert torch.equal(first, got[1][0]) and torch.equal(first_lse, got[1][1])
+    differ = (first != whole).any(dim=-1).view(heads, M, block).any(dim=-1)
+    return differ[:, :M - 1], differ[:, M - 1:]       # vision rows, text rows
+
+
+# Workgroups of the first generation, half of which is how many vision lists are cut at most.
+FIRST = {(128, 128): 768, (128, 64): 1024, (64, 128): 1024, (64, 64): 2048}
+
+
+# More query blocks than resident workgroups, lists shorter than the number of parts, empty and full.
+@pytest.mark.parametrize("block,head_dim,blocks,heads,p,paced", [
+    # short lists: dealt out in the order of their numbers, whole
+    (128, 128, 9, 86, 0.3, False), (128, 128, 13, 120, 0.3, False), (128, 128, 13, 61, 0.9, True),
+    (128, 64, 37, 29, 0.9, False), (128, 64, 9, 230, 0.3, True), (64, 128, 29, 46, 0.9, False), (64, 64, 31, 67, 0.9, False),
+    # text rows cut: in one generation, behind a counter, 64 tokens
+    (128, 64, 67, 13, 0.3, True), (128, 64, 67, 13, 0.3, False), (128, 128, 113, 8, 0.3, False), (64, 64, 121, 14, 0.3, False),
+    # long enough for the counters or about so: one to two generations, two and more, lists of uneven length, the paced walk
+    (128, 128, 97, 9, 0.3, False), (128, 128, 97, 17, 0.3, True), (128, 128, 37, 24, 0.97, False), (128, 64, 97, 11, 0.97, True),
+    (64, 128, 83, 16, 0.97, False), (64, 64, 193, 11, 0.97, False)])
+def test_more_query_blocks_than_places(block, head_dim, blocks, heads, p, paced):
+    vision, text = _direct_twice_and_packed(block, head_dim, blocks, heads, p, paced,
+                                            lambda M: (0, 1, 2, 3, M // 2, M - 1, M))
+    if not paced:   # at most half a generation of lists is cut, and the text rows
+        assert int(vision.sum()) <= FIRST[(block, head_dim)] // 2
+
+
+# Lists that last long enough for the counters: those at the end are cut, and text rows where they alone would last as long.
+# With short lists on the same plan every vision list stays whole: the call's own lists decide.
+@pytest.mark.parametrize("block,head_dim,blocks,heads,p,paced,vision_cut,text_cut", [
+    (128, 128, 97, 9, 0.3, False, False, True), (128, 128, 97, 17, 0.3, False, True, False),
+    (128, 128, 97, 17, 0.3, True, True, False), (128, 128, 61, 14, 0.97, False, True, False),
+    (128, 64, 161, 7, 0.97, False, True, False), (128, 64, 161, 7, 0.97, True, True, False),
+    (64, 128, 137, 10, 0.97, False, True, False), (64, 64, 301, 7, 0.97, False, True, False)])
+def test_lists_decide_about_counters_and_cuts(block, head_dim, blocks, heads, p, paced, vision_cut, text_cut):
+    vision, text = _direct_twice_and_packed(block, head_dim, blocks, heads, p, paced,
+                                            lambda M: (0, 1, 2, M // 2, M - 1, M, M, M, M, M))
+    if not paced:   # paced, last bits differ between runs
+        assert (8 if vision_cut else 0) <= int(vision.sum()) <= (FIRST[(block, head_dim)] // 2 if vision_cut else 0)
+        assert int(text.sum()) > heads // 3 if text_cut else not text.any()
+    vision, _ = _direct_twice_and_packed(block, head_dim, blocks, heads, p, paced, lambda M: (0, 1, 2, 3, 8))
+    if not paced:
+        assert not vision.any()
 
 
 # More text than vision blocks, text rows and the vision lists at the end both cut: every row comes from its own parts, also
