@@ -4,9 +4,9 @@
 One "step" is one pass of the whole path over one synthetic layer input:
     jenga_curve_permute_qkv  ->  jenga_select_blocks  ->  jenga_pack_kv  ->  jenga_block_sparse_attn_packed
     ->  jenga_unpermute
-with Q/K/V already resident in HBM.  The attention runs as its two halves so that each can be timed: under the
-paced walk that is the work of jenga_block_sparse_attn; in the ordered walk that call reads K in place and saves
-half of the packing, which these figures do not show.  The headline value is the time of what recurs per layer
+with Q/K/V already resident in HBM.  The attention runs as its two halves so that each can be timed.  What
+jenga_block_sparse_attn does beside them these figures do not show: in the ordered walk it reads K and V in place and
+packs nothing, and in either walk it deals long lists out by counters and cuts the last of them.  The headline value is the time of what recurs per layer
 (select + attention); the permutes, which the paper pays once per DiT forward, are reported beside
 it.  Prints ONE JSON line.
 """

@@ -222,10 +222,16 @@ int heads_per_launch(const jenga_plan* p, int threads) {
 // 326 -> 358, 150 to 180 us (four shapes) 2 to 4 % more; 200 to 220 us the same, from 260 us on 1 to 14 % less.  At D = 64 the line
 // lies higher: four shapes of 205 to 252 us 0.4 to 2.5 % more, 273 us 1 % and from 400 us on 0.3 to 14 % less.  Even lists of
 // 64-token blocks last longer than that only where heads are large, and lose 1 to 6 % there too.
+// The plan goes by an expected length: K_top and the fixed blocks, or p^2 of all blocks where the cumulative rule decides, an estimate
+// for low-frequency activations (their lists hold 0.76 to 0.81 of all blocks at p = 0.9, 0.26 at 0.45, 0.21 to 0.37 at 0.5).  Whether
+// lists are dealt out by counters and cut at the end the lists of the call then decide (list_lengths_kernel).
+// The first generation is the resident workgroups; of 64 tokens at D = 128 four a CU, and the fifth asks the counter: with five
+// seven of ten shapes of 0.9 to 29 ms took 0.3 to 1.2 % more and three 0.6 to 1.5 % less.
 // What remains is the last generation, which runs out over the time of one workgroup.  There half a generation of lists is
 // cut, into two: 1 to 3 % less from two generations on, but below two, where this reaches into the first one, up to
 // 5 % more (1416 query blocks at D = 128 601 -> 633 us).  Lists of uneven length (p well above k) into three, whatever the
-// grid: 128 tokens 1 to 13 % less (248 blocks x 12 heads 4.50 -> 4.21 ms), 64 tokens 1 to 10 % less, none more.
+// grid: 128 tokens 1 to 13 % less (248 blocks x 12 heads 4.50 -> 4.21 ms), 64 tokens 1 to 10 % less, none more.  With more text
+// than vision blocks all vision lists may be cut: 10 grids with 2 to 86 % as many vision as text blocks took 13 % less to 2 % more.
 //
 // From three quarters of the places on, the lists of the text rows are what can be too long: all blocks, where a vision
 // row sees `usual`.  In one generation the fullest CU decides: ceil(rows / 256) workgroups, one of them a text row.

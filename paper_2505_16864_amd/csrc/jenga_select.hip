@@ -421,6 +421,8 @@ __device__ __forceinline__ void select_row(double (&r)[NT], double* row, uint64_
 //   2048 x 2, D = 64                 95 us (115); before, with the products above, one workgroup a CU and two rounds of them: 103
 //   1500 x 8, D = 128               295 us (330 likewise)
 //   931 x 24, D = 128                220 to 290 us (240 to 270): products 28 k, the last wavefront's 20 k longer, rows 21 k
+// Registers that do not fit go to scratch: 1 at 10 values a lane, 11 at 12 (2 at D = 64), 24 at 32, where a wavefront's row alone
+// takes 64 of its 128.
 typedef double f64x4 __attribute__((ext_vector_type(4)));
 typedef double f64x2 __attribute__((ext_vector_type(2)));
 

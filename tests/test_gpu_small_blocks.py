@@ -12,9 +12,10 @@ from gpu_util import oracle_layout, to_f64, check_output
 pytestmark = pytest.mark.gpu
 
 
-@pytest.mark.parametrize("head_dim,block", [(64, 32), (128, 32), (64, 64), (128, 64)])
-def test_list_lengths(head_dim, block):
-    w = dict(T=3, H=13, W=block // 2 + 3, n_text=2 * block + 5, batch=1, heads=2, head_dim=head_dim, block=block,
+@pytest.mark.parametrize("head_dim,block,width", [(64, 32, 19), (128, 32, 19), (64, 64, 35), (128, 64, 35),
+                                                  (64, 32, 13)])   # the last: 19 blocks, read in place
+def test_list_lengths(head_dim, block, width):
+    w = dict(T=3, H=13, W=width, n_text=2 * block + 5, batch=1, heads=2, head_dim=head_dim, block=block,
              topk=0.3, p=0.3, text_bias=0.4)
     print("list lengths", w, flush=True)
     q, k, v = ji.make_qkv(w, 51)
