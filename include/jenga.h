@@ -235,6 +235,17 @@ int jenga_block_sparse_attn_packed(const jenga_plan* plan, const void* q, void* 
 int jenga_unpermute(const jenga_plan* plan, const void* src_curve, void* dst_thw, void* stream);
 
 /*
+ * A whole layer on thw-side tensors: jenga_curve_permute_qkv, jenga_select_blocks, jenga_block_sparse_attn and jenga_unpermute
+ * in one call and fewer launches, with the same results in the same places (all of those calls' arguments are outputs here too).
+ * Refuses what they refuse, before anything is launched.  An output that lies over an input is taken as those calls one after the
+ * other take it.
+ */
+int jenga_forward(const jenga_plan* plan, const void* q_thw, const void* k_thw, const void* v_thw, void* q_curve,
+                  void* k_curve, void* v_curve, int32_t* sel_count, int32_t* sel_index, uint8_t* mask_or_null,
+                  void* select_workspace, size_t select_workspace_bytes, void* out_curve, float* lse_or_null,
+                  void* attn_workspace, size_t attn_workspace_bytes, void* out_thw, void* stream);
+
+/*
  * Progressive-resolution stage switch (Sec. 3.2, Eq. 4), one fused elementwise pass:
  *   x_out = (1 - sigma_t) * U(x_t - sigma_t * eps_t) + sigma_t * eps_tilde
  * U is 3D area interpolation from (T_in, H_in, W_in) to (T_out, H_out, W_out): along each axis with I

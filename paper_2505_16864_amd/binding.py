@@ -18,7 +18,7 @@ EXPORTS = ["jenga_plan_create", "jenga_plan_destroy", "jenga_plan_info", "jenga_
            "jenga_curve_permute", "jenga_curve_permute_qkv", "jenga_curve_permute_rows", "jenga_select_blocks",
            "jenga_select_blocks_static",
            "jenga_block_sparse_attn", "jenga_pack_kv",
-           "jenga_block_sparse_attn_packed", "jenga_unpermute", "jenga_stage_switch", "jenga_strerror"]
+           "jenga_block_sparse_attn_packed", "jenga_unpermute", "jenga_forward", "jenga_stage_switch", "jenga_strerror"]
 
 
 class jenga_config(ctypes.Structure):
@@ -60,6 +60,7 @@ def _load():
     lib.jenga_block_sparse_attn.argtypes = [vp, vp, vp, vp, vp, vp, vp, vp, vp, ctypes.c_size_t, vp]
     lib.jenga_pack_kv.argtypes = [vp, vp, vp, vp, ctypes.c_size_t, vp]
     lib.jenga_block_sparse_attn_packed.argtypes = [vp, vp, vp, ctypes.c_size_t, vp, vp, vp, vp, vp]
+    lib.jenga_forward.argtypes = [vp] * 11 + [ctypes.c_size_t, vp, vp, vp, ctypes.c_size_t, vp, vp]
     lib.jenga_stage_switch.argtypes = [vp, vp, vp, vp] + [ctypes.c_int32] * 7 + [ctypes.c_float, vp]
     lib.jenga_strerror.argtypes = [ctypes.c_int]
     lib.jenga_strerror.restype = ctypes.c_char_p
@@ -167,6 +168,14 @@ def jenga_block_sparse_attn_packed(plan, q, workspace, workspace_bytes, sel_coun
     _check(_lib.jenga_block_sparse_attn_packed(plan, _ptr(q), _ptr(workspace), workspace_bytes, _ptr(sel_count),
                                                _ptr(sel_index), _ptr(out_curve), _ptr(lse), stream),
            "jenga_block_sparse_attn_packed")
+
+
+def jenga_forward(plan, q_thw, k_thw, v_thw, q_curve, k_curve, v_curve, sel_count, sel_index, mask, select_workspace,
+                  select_workspace_bytes, out_curve, lse, attn_workspace, attn_workspace_bytes, out_thw, stream=None):
+    _check(_lib.jenga_forward(plan, _ptr(q_thw), _ptr(k_thw), _ptr(v_thw), _ptr(q_curve), _ptr(k_curve), _ptr(v_curve),
+                              _ptr(sel_count), _ptr(sel_index), _ptr(mask), _ptr(select_workspace), select_workspace_bytes,
+                              _ptr(out_curve), _ptr(lse), _ptr(attn_workspace), attn_workspace_bytes, _ptr(out_thw), stream),
+           "jenga_forward")
 
 
 def jenga_stage_switch(x_t, eps_t, eps_tilde, x_out, channels, in_shape, out_shape, sigma_t, stream=None):

@@ -56,6 +56,32 @@ __device__ inline uint32_t pack_bf16x2(float lo, float hi) {
 // behind them whether it is used.
 constexpr int PARAM_QUEUE = 8, QUEUE_USED = 8;
 
+// jenga_forward: rows go to the thw side from the kernel that has them in registers, beside the curve side.
+// thw: [batch][n_src][heads][D], or nullptr; first: (batch, head) pair that the launch's first one is.
+struct ThwRows {
+  uint16_t* thw;
+  const int32_t* src_of_pos;
+  int n_src, heads, first;
+  // channel 0 of row `pos` of the launch's pair bh; nullptr: a pad, or nothing is to be written there
+  template <int D>
+  __device__ __forceinline__ uint16_t* row(int bh, int pos) const {
+    if (thw == nullptr) return nullptr;
+    const int s = src_of_pos[pos], b = (first + bh) / heads, h = first + bh - b * heads;
+    return s < 0 ? nullptr : thw + (((size_t)b * n_src + s) * heads + h) * D;
+  }
+  // The kernel's first argument, read again where it is called: kept over attn_h_kernel's loop it would cost scalar registers there
+  // (up to 9 more, spilled ones in four of the kernels).
+  __device__ __forceinline__ static ThwRows argument() {
+    ThwRows t = {};
+#if defined(__HIP_DEVICE_COMPILE__)
+    uint64_t at = (uint64_t)__builtin_amdgcn_kernarg_segment_ptr();
+    asm volatile("" : "+s"(at));
+    t = *(const __attribute__((address_space(4))) ThwRows*)at;
+#endif
+    return t;
+  }
+};
+
 // grid (M, batch*heads, 2).  z = 0: K tile -> fragment order; z = 1: V tile -> transposed fragment order, pad rows zeroed.
 // A workgroup each, so that the two chains of loads and stores run side by side: 931 blocks x 24 heads (2.9 GB) 531 ->
 // 511 us = 5.7 TB/s, 262 x 24 156 -> 145 us; HBM-bound from there on.
@@ -264,7 +290,7 @@ __device__ inline int take_item(uint32_t* queue, int n_end) {
 
 template <int BLK, int D, bool PACED, bool SPLIT, bool K_ROWS>
 __global__ __launch_bounds__(2 * BLK, (attn_h_min_waves<BLK, D>())) void attn_h_kernel(
-    const uint16_t* __restrict__ q, const u32x4* __restrict__ kp, const u32x4* __restrict__ vp,
+    ThwRows, const uint16_t* __restrict__ q, const u32x4* __restrict__ kp, const u32x4* __restrict__ vp,
     const int32_t* __restrict__ sel_count, const int32_t* __restrict__ sel_index,
     uint16_t* __restrict__ out, float* __restrict__ lse, WorkMap work, int n_pad, int pad_v, int pad_c,
     float scale_log2e, float bias_log2e, const uint32_t* __restrict__ pace_params, Split split, uint32_t* queue) {
@@ -670,7 +696,7 @@ __global__ __launch_bounds__(2 * BLK, (attn_h_min_waves<BLK, D>())) void attn_h_
   // natural-log sum of exp(logit) over the visited keys: the running maximum is in base-2 units
   if (lse != nullptr && hl_e == 0)
     lse[qrow_e] = row_ok ? (m_run + __builtin_amdgcn_logf(l_tot)) * 0.6931471805599453f : -INFINITY;
-  uint16_t* orow = out + qrow_e * D;
+  uint16_t *orow = out + qrow_e * D, *trow = ThwRows::argument().row<D>(bh, i * BLK + row_e);
 #pragma unroll
   for (int dt = 0; dt < DT; ++dt)
 #pragma unroll
@@ -679,6 +705,7 @@ __global__ __launch_bounds__(2 * BLK, (attn_h_min_waves<BLK, D>())) void attn_h_
       w.x = row_ok ? pack_bf16x2(O[dt][4 * g] * inv, O[dt][4 * g + 1] * inv) : 0u;
       w.y = row_ok ? pack_bf16x2(O[dt][4 * g + 2] * inv, O[dt][4 * g + 3] * inv) : 0u;
       *(uint2*)(orow + 32 * dt + 8 * g + 4 * hl_e) = w;
+      if (trow != nullptr) *(uint2*)(trow + 32 * dt + 8 * g + 4 * hl_e) = w;
     }
 }
 
@@ -688,7 +715,8 @@ __global__ __launch_bounds__(2 * BLK, (attn_h_min_waves<BLK, D>())) void attn_h_
 template <int BLK, int D>
 __global__ __launch_bounds__(2 * D) void merge_kernel(const int32_t* __restrict__ sel_count, uint16_t* __restrict__ out,
                                                       float* __restrict__ lse, WorkMap work, int n_pad, int pad_v,
-                                                      int pad_c, Split split, const uint32_t* __restrict__ queue) {
+                                                      int pad_c, Split split, const uint32_t* __restrict__ queue,
+                                                      ThwRows thw_rows) {
   constexpr int DT = D / 32, NW = BLK / 32;
   const int M = work.M, M_v = work.M_v, wave = blockIdx.x;
   int i = blockIdx.y, bh = blockIdx.z, n_parts;
@@ -743,13 +771,14 @@ __global__ __launch_bounds__(2 * D) void merge_kernel(const int32_t* __restrict_
   const size_t qrow = (size_t)bh * n_pad + (size_t)i * BLK + row;
   if (lse != nullptr && threadIdx.x < 32)
     lse[qrow] = row_ok ? (m + __builtin_amdgcn_logf(l)) * 0.6931471805599453f : -INFINITY;
-  uint16_t* orow = out + qrow * D + 32 * dt + 4 * hl;
+  uint16_t *orow = out + qrow * D + 32 * dt + 4 * hl, *trow = thw_rows.row<D>(bh, i * BLK + row);
 #pragma unroll
   for (int g = 0; g < 4; ++g) {
     uint2 w;
     w.x = row_ok ? pack_bf16x2(sum[4 * g] * inv, sum[4 * g + 1] * inv) : 0u;
     w.y = row_ok ? pack_bf16x2(sum[4 * g + 2] * inv, sum[4 * g + 3] * inv) : 0u;
     *(uint2*)(orow + 8 * g) = w;
+    if (trow != nullptr) *(uint2*)(trow + 32 * dt + 4 * hl + 8 * g) = w;
   }
 }
 
@@ -784,7 +813,7 @@ __device__ __forceinline__ void attn_32(
     const uint16_t* __restrict__ q, const u32x4* __restrict__ kp, const u32x4* __restrict__ vp,
     const int32_t* __restrict__ sel_count, const int32_t* __restrict__ sel_index, uint16_t* __restrict__ out,
     float* __restrict__ lse, const WorkMap& work, int n_pad, int pad_v, int pad_c, float scale_log2e, float bias_log2e,
-    const Split& split) {
+    const Split& split, const ThwRows& thw_rows) {
   constexpr int BLK = 32, KS = D / 16, DT = D / 32, PS = BLK / 16, TILE_CHUNKS = BLK * D / 8, CH = D / 8;
   // one channel tile of every wavefront's O, accumulator order; ROWS: before that, 32 rows of V for every wavefront
   static_assert(!ROWS || D == 64, "32 rows of V take the room of a channel tile");
@@ -1005,6 +1034,7 @@ __device__ __forceinline__ void attn_32(
   // weight of this wavefront's part
   const float mine = RANGE ? __builtin_amdgcn_exp2f(m_run - ref) : row_ok ? __builtin_amdgcn_exp2f(m_run - ref) / l_all : 0.f;
   constexpr int RP = 16 / NS;   // accumulator registers of a channel tile that one wavefront adds up
+  uint16_t* trow = RANGE ? nullptr : thw_rows.row<D>(bh, i * BLK + ql);
 #pragma unroll
   for (int dt = 0; dt < DT; ++dt) {
     if (dt > 0) __syncthreads();   // the previous tile has been read
@@ -1026,9 +1056,14 @@ __device__ __forceinline__ void attn_32(
       for (int u = 0; u < RP; u += 2) *(float2*)(o + u) = make_float2(sum[u], sum[u + 1]);
       continue;
     }
-    uint16_t* o = out + qrow * D + 32 * dt + 8 * (r0 / 4) + 4 * hl + r0 % 4;
+    const int channel = 32 * dt + 8 * (r0 / 4) + 4 * hl + r0 % 4;
+    uint16_t* o = out + qrow * D + channel;
 #pragma unroll
-    for (int u = 0; u < RP; u += 2) *(uint32_t*)(o + u) = row_ok ? pack_bf16x2(sum[u], sum[u + 1]) : 0u;
+    for (int u = 0; u < RP; u += 2) {
+      const uint32_t w = row_ok ? pack_bf16x2(sum[u], sum[u + 1]) : 0u;
+      *(uint32_t*)(o + u) = w;
+      if (trow != nullptr) *(uint32_t*)(trow + channel + u) = w;
+    }
   }
 }
 
@@ -1037,9 +1072,9 @@ __global__ __launch_bounds__(64 * NS, (D == 128 ? 2 : 4)) void attn_kernel(
     const uint16_t* __restrict__ q, const u32x4* __restrict__ kp, const u32x4* __restrict__ vp,
     const int32_t* __restrict__ sel_count, const int32_t* __restrict__ sel_index, uint16_t* __restrict__ out,
     float* __restrict__ lse, WorkMap work, int n_pad, int pad_v, int pad_c, float scale_log2e, float bias_log2e,
-    Split split) {
+    Split split, ThwRows thw_rows) {
   attn_32<D, NS, RANGE, false>(q, kp, vp, sel_count, sel_index, out, lse, work, n_pad, pad_v, pad_c, scale_log2e, bias_log2e,
-                               split);
+                               split, thw_rows);
 }
 
 // K and V in place.
@@ -1047,9 +1082,10 @@ template <int D, int NS>
 __global__ __launch_bounds__(64 * NS, 4) void attn_rows_kernel(
     const uint16_t* __restrict__ q, const u32x4* __restrict__ k, const u32x4* __restrict__ v,
     const int32_t* __restrict__ sel_count, const int32_t* __restrict__ sel_index, uint16_t* __restrict__ out,
-    float* __restrict__ lse, WorkMap work, int n_pad, int pad_v, int pad_c, float scale_log2e, float bias_log2e) {
+    float* __restrict__ lse, WorkMap work, int n_pad, int pad_v, int pad_c, float scale_log2e, float bias_log2e,
+    ThwRows thw_rows) {
   attn_32<D, NS, false, true>(q, k, v, sel_count, sel_index, out, lse, work, n_pad, pad_v, pad_c, scale_log2e, bias_log2e,
-                              Split{});
+                              Split{}, thw_rows);
 }
 
 // What a launch has to know of the lists' lengths.  One workgroup.
@@ -1128,7 +1164,7 @@ int run_pack(const jenga_plan* p, const void* k, const void* v, void* ws, hipStr
 
 template <int BLK, int D>
 int run_attention(const jenga_plan* p, const void* q, const void* k, const void* v, void* ws, bool may_split,
-                  const int32_t* sel_count, const int32_t* sel_index, void* out, float* lse, hipStream_t st) {
+                  const int32_t* sel_count, const int32_t* sel_index, void* out, float* lse, void* thw, hipStream_t st) {
   const jenga_config& c = p->cfg;
   const jenga_plan_info_t& f = p->info;
   const int bh = c.batch * c.heads;
@@ -1141,6 +1177,7 @@ int run_attention(const jenga_plan* p, const void* q, const void* k, const void*
   const float scale = log2e / sqrtf((float)D), bias = c.text_bias * log2e;
   const uint16_t* qb = (const uint16_t*)q;
   uint16_t* ob = (uint16_t*)out;
+  ThwRows thw_rows = {(uint16_t*)thw, p->d_src_of_pos, f.N_v + c.n_text, c.heads, 0};
   if constexpr (BLK == 32) {   // in-order walk only
     constexpr int NS = D == 128 ? 4 : 8;
     const bool ranges = may_split && p->attn_parts > 1;
@@ -1160,23 +1197,24 @@ int run_attention(const jenga_plan* p, const void* q, const void* k, const void*
       const int32_t *count0 = sel_count + list0, *index0 = sel_index + list0 * f.M;
       uint16_t* ob0 = ob + row0 * D;
       float* lse0 = lse != nullptr ? lse + row0 : nullptr;
+      thw_rows.first = first;
       if (ranges) {
         split.stride = (work.n_wg + 7) & ~7;
         attn_kernel<D, NS, true><<<dim3(split.parts * split.stride), 64 * NS, 0, st>>>(
-            q0, kp0, vp0, count0, index0, ob0, lse0, work, f.N_pad, f.pad_v, f.pad_c, scale, bias, split);
+            q0, kp0, vp0, count0, index0, ob0, lse0, work, f.N_pad, f.pad_v, f.pad_c, scale, bias, split, thw_rows);
         merge_kernel<BLK, D><<<dim3(1, f.M, n), 2 * D, 0, st>>>(count0, ob0, lse0, work, f.N_pad, f.pad_v, f.pad_c,
-                                                                split, nullptr);
+                                                                split, nullptr, thw_rows);
         continue;
       }
       if constexpr (D == 64) {
         if (k_rows) {
           attn_rows_kernel<D, NS><<<dim3(work.n_wg), 64 * NS, 0, st>>>(q0, kp0, vp0, count0, index0, ob0, lse0, work, f.N_pad,
-                                                                       f.pad_v, f.pad_c, scale, bias);
+                                                                       f.pad_v, f.pad_c, scale, bias, thw_rows);
           continue;
         }
       }
       attn_kernel<D, NS, false><<<dim3(work.n_wg), 64 * NS, 0, st>>>(q0, kp0, vp0, count0, index0, ob0, lse0, work, f.N_pad,
-                                                                     f.pad_v, f.pad_c, scale, bias, split);
+                                                                     f.pad_v, f.pad_c, scale, bias, split, thw_rows);
     }
   } else {
     const bool paced = BLK == 128 && (c.flags & JENGA_FLAG_PACED_WALK);
@@ -1185,7 +1223,7 @@ int run_attention(const jenga_plan* p, const void* q, const void* k, const void*
     uint32_t *queue = may_split ? attn_queue(p, ws) : nullptr, *pace = nullptr;
 #define JENGA_ATTN(PACED, SPLIT, K_ROWS, WGS)                                                                    \
   attn_h_kernel<BLK, D, PACED, SPLIT, K_ROWS><<<dim3(WGS), 2 * BLK, 0, st>>>(                                    \
-      qb, kp, vp, sel_count, sel_index, ob, lse, work, f.N_pad, f.pad_v, f.pad_c, scale, bias, pace, split, queue)
+      thw_rows, qb, kp, vp, sel_count, sel_index, ob, lse, work, f.N_pad, f.pad_v, f.pad_c, scale, bias, pace, split, queue)
     if (paced && !(may_split && p->attn_first == 0 && p->attn_parts > 1)) pace = params;   // parts of short grids: ascending order
     if (pace != nullptr || queue != nullptr) {
       // a workgroup spends about 6.3 us (D = 128; 3.6 us at D = 64) on a block of 128 keys when three share a CU
@@ -1222,7 +1260,8 @@ int run_attention(const jenga_plan* p, const void* q, const void* k, const void*
       if (k_rows && !paced) JENGA_ATTN(false, true, true, wgs);
       else if (!paced) JENGA_ATTN(false, true, false, wgs);
       if (slots > 0)
-        merge_kernel<BLK, D><<<merge, 2 * D, 0, st>>>(sel_count, ob, lse, work, f.N_pad, f.pad_v, f.pad_c, split, queue);
+        merge_kernel<BLK, D><<<merge, 2 * D, 0, st>>>(sel_count, ob, lse, work, f.N_pad, f.pad_v, f.pad_c, split, queue,
+                                                     thw_rows);
       return hipGetLastError() == hipSuccess ? JENGA_OK : JENGA_EHIP;
     }
     if constexpr (BLK == 128) {
@@ -1260,11 +1299,11 @@ int launch_keep(const jenga_plan* p, const void* src, void* ws, int which, const
 }
 
 int launch_attention(const jenga_plan* p, const void* q, const void* k, const void* v, void* ws, bool may_split,
-                     const int32_t* sel_count, const int32_t* sel_index, void* out, float* lse, void* stream) {
+                     const int32_t* sel_count, const int32_t* sel_index, void* out, float* lse, void* thw, void* stream) {
   hipStream_t st = (hipStream_t)stream;
   const int blk = p->cfg.block, d = p->cfg.head_dim;
 #define X(B, DD) \
-  if (blk == B && d == DD) return run_attention<B, DD>(p, q, k, v, ws, may_split, sel_count, sel_index, out, lse, st);
+  if (blk == B && d == DD) return run_attention<B, DD>(p, q, k, v, ws, may_split, sel_count, sel_index, out, lse, thw, st);
   JENGA_FOR_SHAPES(X)
 #undef X
   return JENGA_EUNSUPPORTED;

@@ -20,6 +20,30 @@ bool overlap(const void* a, size_t a_bytes, const void* b, size_t b_bytes) {
   return (uintptr_t)a < (uintptr_t)b + b_bytes && (uintptr_t)b < (uintptr_t)a + a_bytes;
 }
 
+// The work of jenga_block_sparse_attn; out_thw: the rows in the thw-side order too, or NULL.
+int attention(const jenga_plan* p, const void* q, const void* k, const void* v, const int32_t* sel_count,
+              const int32_t* sel_index, void* out_curve, float* lse_or_null, void* workspace, void* out_thw, void* stream) {
+  // Where K and V are read in place, one that an output lies over, or that is off the 16-byte grid, which the copies into LDS
+  // want (ordinary loads take any address), is copied first; if both are, they are packed.
+  const size_t rows = (size_t)p->cfg.batch * p->cfg.heads * p->info.N_pad, bytes = rows * p->cfg.head_dim * 2;
+  auto moved = [&](const void* x) {
+    return ((uintptr_t)x & 15u) != 0 || overlap(x, bytes, out_curve, bytes) ||
+           (lse_or_null && overlap(x, bytes, lse_or_null, rows * 4));
+  };
+  const bool k_moved = moved(k), v_moved = moved(v);
+  int rc = JENGA_OK;
+  if (!jenga::reads_kv_in_place(p) || (k_moved && v_moved)) {
+    rc = jenga::launch_pack(p, k, v, workspace, stream);
+    k = v = nullptr;
+  } else if (k_moved) {
+    rc = jenga::launch_keep(p, k, workspace, 0, &k, stream);
+  } else if (v_moved) {
+    rc = jenga::launch_keep(p, v, workspace, 1, &v, stream);
+  }
+  if (rc != JENGA_OK) return rc;
+  return jenga::launch_attention(p, q, k, v, workspace, true, sel_count, sel_index, out_curve, lse_or_null, out_thw, stream);
+}
+
 template <typename T>
 int to_device(const std::vector<T>& h, T** d) {
   *d = nullptr;
@@ -124,7 +148,7 @@ int jenga_select_blocks(const jenga_plan* p, const void* q_curve, const void* k_
   if (!on_plan_device(p)) return JENGA_EINVAL;
   if (((uintptr_t)workspace & 255u) != 0) return JENGA_EINVAL;
   if (workspace_bytes < p->info.select_workspace_bytes) return JENGA_EWORKSPACE;
-  return jenga::launch_select(p, q_curve, k_curve, sel_count, sel_index, mask_or_null, workspace, stream);
+  return jenga::launch_select(p, q_curve, k_curve, sel_count, sel_index, mask_or_null, workspace, false, stream);
 }
 
 int jenga_block_sparse_attn(const jenga_plan* p, const void* q, const void* k, const void* v,
@@ -134,25 +158,50 @@ int jenga_block_sparse_attn(const jenga_plan* p, const void* q, const void* k, c
   if (!on_plan_device(p)) return JENGA_EINVAL;
   if (((uintptr_t)workspace & 255u) != 0) return JENGA_EINVAL;
   if (workspace_bytes < p->info.attn_workspace_bytes) return JENGA_EWORKSPACE;
-  // Where K and V are read in place, one that an output lies over, or that is off the 16-byte grid, which the copies into LDS
-  // want (ordinary loads take any address), is copied first; if both are, they are packed.
-  const size_t rows = (size_t)p->cfg.batch * p->cfg.heads * p->info.N_pad, bytes = rows * p->cfg.head_dim * 2;
-  auto moved = [&](const void* x) {
-    return ((uintptr_t)x & 15u) != 0 || overlap(x, bytes, out_curve, bytes) ||
-           (lse_or_null && overlap(x, bytes, lse_or_null, rows * 4));
-  };
-  const bool k_moved = moved(k), v_moved = moved(v);
-  int rc = JENGA_OK;
-  if (!jenga::reads_kv_in_place(p) || (k_moved && v_moved)) {
-    rc = jenga::launch_pack(p, k, v, workspace, stream);
-    k = v = nullptr;
-  } else if (k_moved) {
-    rc = jenga::launch_keep(p, k, workspace, 0, &k, stream);
-  } else if (v_moved) {
-    rc = jenga::launch_keep(p, v, workspace, 1, &v, stream);
+  return attention(p, q, k, v, sel_count, sel_index, out_curve, lse_or_null, workspace, nullptr, stream);
+}
+
+int jenga_forward(const jenga_plan* p, const void* q_thw, const void* k_thw, const void* v_thw, void* q_curve,
+                  void* k_curve, void* v_curve, int32_t* sel_count, int32_t* sel_index, uint8_t* mask_or_null,
+                  void* select_workspace, size_t select_workspace_bytes, void* out_curve, float* lse_or_null,
+                  void* attn_workspace, size_t attn_workspace_bytes, void* out_thw, void* stream) {
+  if (!p || !q_thw || !k_thw || !v_thw || !q_curve || !k_curve || !v_curve || !sel_count || !sel_index ||
+      !select_workspace || !out_curve || !attn_workspace || !out_thw)
+    return JENGA_EINVAL;
+  if (!on_plan_device(p)) return JENGA_EINVAL;
+  if ((((uintptr_t)select_workspace | (uintptr_t)attn_workspace) & 255u) != 0) return JENGA_EINVAL;
+  if (select_workspace_bytes < p->info.select_workspace_bytes || attn_workspace_bytes < p->info.attn_workspace_bytes)
+    return JENGA_EWORKSPACE;
+  const size_t bh = (size_t)p->cfg.batch * p->cfg.heads, row = (size_t)p->cfg.head_dim * 2, M = (size_t)p->info.M;
+  const size_t thw_bytes = bh * (p->info.N_v + p->cfg.n_text) * row, curve_bytes = bh * p->info.N_pad * row;
+  // The fused launches write what the calls for the single steps would write a launch later: a tensor that lies over one that is
+  // still being read there goes through those calls.
+  const void* src[3] = {q_thw, k_thw, v_thw};
+  void* dst[3] = {q_curve, k_curve, v_curve};
+  bool fused_in = 3ll * p->cfg.batch <= 65535, fused_out = true;
+  for (int t = 0; t < 3; ++t) {
+    for (int u = 0; u < 3; ++u)
+      if (overlap(dst[t], curve_bytes, src[u], thw_bytes) || (t != u && overlap(dst[t], curve_bytes, dst[u], curve_bytes)))
+        fused_in = false;
+    if (overlap(select_workspace, p->info.select_workspace_bytes, src[t], thw_bytes) ||
+        overlap(select_workspace, p->info.select_workspace_bytes, dst[t], curve_bytes))
+      fused_in = false;
+    if (overlap(out_thw, thw_bytes, dst[t], curve_bytes)) fused_out = false;
   }
-  if (rc != JENGA_OK) return rc;
-  return jenga::launch_attention(p, q, k, v, workspace, true, sel_count, sel_index, out_curve, lse_or_null, stream);
+  if (overlap(out_thw, thw_bytes, out_curve, curve_bytes) ||
+      overlap(out_thw, thw_bytes, attn_workspace, p->info.attn_workspace_bytes) ||
+      overlap(out_thw, thw_bytes, sel_count, bh * M * 4) || overlap(out_thw, thw_bytes, sel_index, bh * M * M * 4) ||
+      (lse_or_null && overlap(out_thw, thw_bytes, lse_or_null, bh * p->info.N_pad * 4)))
+    fused_out = false;
+  int rc = fused_in ? jenga::launch_permute_pool(p, src, dst, select_workspace, stream)
+                    : jenga_curve_permute_qkv(p, q_thw, k_thw, v_thw, q_curve, k_curve, v_curve, stream);
+  if (rc == JENGA_OK)
+    rc = jenga::launch_select(p, q_curve, k_curve, sel_count, sel_index, mask_or_null, select_workspace, fused_in, stream);
+  if (rc == JENGA_OK)
+    rc = attention(p, q_curve, k_curve, v_curve, sel_count, sel_index, out_curve, lse_or_null, attn_workspace,
+                   fused_out ? out_thw : nullptr, stream);
+  if (rc == JENGA_OK && !fused_out) rc = jenga_unpermute(p, out_curve, out_thw, stream);
+  return rc;
 }
 
 int jenga_pack_kv(const jenga_plan* p, const void* k, const void* v, void* workspace, size_t workspace_bytes,
@@ -172,7 +221,7 @@ int jenga_block_sparse_attn_packed(const jenga_plan* p, const void* q, void* pac
   if (((uintptr_t)packed_kv_workspace & 255u) != 0) return JENGA_EINVAL;
   if (workspace_bytes < p->packed_bytes) return JENGA_EWORKSPACE;
   return jenga::launch_attention(p, q, nullptr, nullptr, packed_kv_workspace, false, sel_count, sel_index, out_curve,
-                                 lse_or_null, stream);
+                                 lse_or_null, nullptr, stream);
 }
 
 }  // extern "C"

@@ -164,8 +164,11 @@ StageTiles stage_switch_tiles(long long channels, int T_in, int H_in, int W_in, 
 int launch_permute(const jenga_plan* p, const void* const* src, void* const* dst, int tensors, bool forward,
                    void* stream);
 int launch_permute_rows(const jenga_plan* p, const void* src, void* dst, int row_bytes, void* stream);
+// pooled: the block means are in the workspace already (launch_permute_pool)
 int launch_select(const jenga_plan* p, const void* q, const void* k, int32_t* sel_count,
-                  int32_t* sel_index, uint8_t* mask, void* ws, void* stream);
+                  int32_t* sel_index, uint8_t* mask, void* ws, bool pooled, void* stream);
+// Q, K and V into curve order, and the block means of Q and K into the selection's workspace.
+int launch_permute_pool(const jenga_plan* p, const void* const src[3], void* const dst[3], void* select_ws, void* stream);
 // Looks up the address of the static selection scratch on `device` (the current device) once.
 int select_scratch_init(int device);
 int launch_pack(const jenga_plan* p, const void* k, const void* v, void* ws, void* stream);
@@ -175,8 +178,9 @@ bool reads_kv_in_place(const jenga_plan* p);
 // there; returns the copy in *copied.
 int launch_keep(const jenga_plan* p, const void* src, void* ws, int which, const void** copied, void* stream);
 // k, v: to be read in place (one of them may be a copy in the workspace), or NULL (packed in the workspace).  may_split: the
-// call has the workspace to itself and may write behind the packed tiles, or where they would be.
+// call has the workspace to itself and may write behind the packed tiles, or where they would be.  thw: where the rows go on the
+// thw side, or NULL.
 int launch_attention(const jenga_plan* p, const void* q, const void* k, const void* v, void* packed_ws, bool may_split,
-                     const int32_t* sel_count, const int32_t* sel_index, void* out, float* lse, void* stream);
+                     const int32_t* sel_count, const int32_t* sel_index, void* out, float* lse, void* thw, void* stream);
 
 }  // namespace jenga

@@ -89,6 +89,64 @@ __global__ __launch_bounds__(256) void pool_kernel(const uint16_t* __restrict__ 
   }
 }
 
+// Q, K and V of jenga_forward into curve order, and the means of Q and K from the same rows: the pooling's pass over both, and
+// its launch.  A workgroup moves one block of one (batch, head); grid (heads, M, 3 * batch), so that neighbours read neighbouring heads
+// of the same tokens.  Sums in pool_kernel's order, so the means are the same bits.
+// Whole jenga_forward (this, and rows written to the thw side by the attention kernels), four calls -> one: 9 blocks of 32 x 2 heads,
+// D = 64, 22.9 -> 14.4 us (five launches -> three, of which each is 2.5 us however little it does), 17 of 128 x 8, D = 128, 56.8 ->
+// 52.2 us, 931 x 24 48.06 -> 47.82 ms.
+struct Moves {
+  const uint4* src[3];
+  uint4* dst[3];
+  double* mean[2];
+};
+template <int M_TOK, int D>
+__global__ __launch_bounds__(256) void permute_pool_kernel(Moves moves, const int32_t* __restrict__ src_of_pos,
+                                                           const int32_t* __restrict__ blk_valid, int n_src, int M_v,
+                                                           int batch) {
+  constexpr int CH = D / 8, G = 256 / CH, ROWS = M_TOK / G;   // pieces of a row, rows at a time, rows of a thread
+  __shared__ double red[G][D];
+  const int h = blockIdx.x, j = blockIdx.y, heads = gridDim.x, M = gridDim.y;
+  const int tensor = blockIdx.z / batch, b = blockIdx.z - tensor * batch;
+  const int c = threadIdx.x % CH, g = threadIdx.x / CH;
+  const uint4* src = moves.src[tensor] + ((size_t)b * n_src * heads + h) * CH + c;
+  uint4* dst = moves.dst[tensor] + (((size_t)b * heads + h) * M + j) * (M_TOK * CH) + threadIdx.x;
+  int s[ROWS];
+#pragma unroll
+  for (int u = 0; u < ROWS; ++u) s[u] = src_of_pos[j * M_TOK + u * G + g];
+  uint4 v[ROWS];
+#pragma unroll
+  for (int u = 0; u < ROWS; ++u) {
+    v[u] = make_uint4(0, 0, 0, 0);
+    if (s[u] >= 0) v[u] = src[(size_t)s[u] * heads * CH];
+  }
+#pragma unroll
+  for (int u = 0; u < ROWS; ++u) dst[u * 256] = v[u];
+  if (tensor == 2 || (tensor == 0 && j >= M_v)) return;
+  double acc[8];
+#pragma unroll
+  for (int e = 0; e < 8; ++e) acc[e] = 0.0;
+#pragma unroll
+  for (int u = 0; u < ROWS; ++u) {
+    const uint32_t w[4] = {v[u].x, v[u].y, v[u].z, v[u].w};
+#pragma unroll
+    for (int e = 0; e < 4; ++e) {
+      acc[2 * e] += bf16_bits_to_double(w[e] & 0xFFFFu);
+      acc[2 * e + 1] += bf16_bits_to_double(w[e] >> 16);
+    }
+  }
+#pragma unroll
+  for (int e = 0; e < 8; ++e) red[g][c * 8 + e] = acc[e];
+  __syncthreads();
+  if (threadIdx.x < D) {
+    double sum = 0.0;
+#pragma unroll
+    for (int gg = 0; gg < G; ++gg) sum += red[gg][threadIdx.x];
+    const size_t row = ((size_t)b * heads + h) * (tensor == 0 ? M_v : M) + j;
+    moves.mean[tensor][row * D + pooled_pos<D>(j, threadIdx.x)] = sum / (double)blk_valid[j];
+  }
+}
+
 // Wave-wide reductions in the vector ALU (DPP): six dependent steps of a few cycles each, where the same through
 // __shfl_xor is twelve LDS round trips.  The result is uniform.
 template <int CTRL, int ROW_MASK>
@@ -524,19 +582,23 @@ __global__ __launch_bounds__(64 * ROWS, NT == 16 ? 1 : ROWS == 8 ? 4 : 8) void s
   select_row<NT>(r, S[wave], fixed_lane, idx_out, mask_out, sel_count + out_row, M, K_top, p);
 }
 
+// Where the pooled rows of Q and K lie in the workspace.
+template <int D>
+void pooled_rows(const jenga_plan* p, void* ws, double** qh, double** kh) {
+  const size_t q_bytes = (size_t)p->cfg.batch * p->cfg.heads * p->info.M_v * D * 8;
+  *qh = (double*)ws;
+  *kh = (double*)((char*)ws + ((q_bytes + 255) & ~(size_t)255));
+}
+
 template <int D>
 int run_select(const jenga_plan* p, const void* q, const void* k, int32_t* sel_count, int32_t* sel_index,
-               uint8_t* mask, void* ws, hipStream_t st) {
+               uint8_t* mask, void* ws, bool pooled, hipStream_t st) {
   const jenga_config& c = p->cfg;
   const jenga_plan_info_t& f = p->info;
   const int bh = c.batch * c.heads;
-  auto align256 = [](size_t x) { return (x + 255) & ~(size_t)255; };
-  char* w = (char*)ws;
-  double* qh = (double*)w;
-  w += align256((size_t)bh * f.M_v * D * 8);
-  double* kh = (double*)w;
-  w += align256((size_t)bh * f.M * D * 8);
-  if (f.M_v > 0)
+  double *qh, *kh;
+  pooled_rows<D>(p, ws, &qh, &kh);
+  if (f.M_v > 0 && !pooled)
     pool_kernel<D><<<dim3(f.M, bh, 2), 256, 0, st>>>((const uint16_t*)q, (const uint16_t*)k, qh, kh, p->d_blk_valid,
                                                     f.N_pad, c.block, f.M_v, f.M);
 #define JENGA_SELECT(NTV, ROWS)                                                                                      \
@@ -591,10 +653,34 @@ namespace jenga {
 int select_scratch_init(int device) { return scratch_address(device) != nullptr ? JENGA_OK : JENGA_EHIP; }
 
 int launch_select(const jenga_plan* p, const void* q, const void* k, int32_t* sel_count, int32_t* sel_index,
-                  uint8_t* mask, void* ws, void* stream) {
+                  uint8_t* mask, void* ws, bool pooled, void* stream) {
   hipStream_t st = (hipStream_t)stream;
-  if (p->cfg.head_dim == 128) return run_select<128>(p, q, k, sel_count, sel_index, mask, ws, st);
-  return run_select<64>(p, q, k, sel_count, sel_index, mask, ws, st);
+  if (p->cfg.head_dim == 128) return run_select<128>(p, q, k, sel_count, sel_index, mask, ws, pooled, st);
+  return run_select<64>(p, q, k, sel_count, sel_index, mask, ws, pooled, st);
+}
+
+template <int D>
+static int run_permute_pool(const jenga_plan* p, const void* const src[3], void* const dst[3], void* ws, hipStream_t st) {
+  const jenga_config& c = p->cfg;
+  const jenga_plan_info_t& f = p->info;
+  double *qh, *kh;
+  pooled_rows<D>(p, ws, &qh, &kh);
+  Moves moves = {{(const uint4*)src[0], (const uint4*)src[1], (const uint4*)src[2]},
+                 {(uint4*)dst[0], (uint4*)dst[1], (uint4*)dst[2]},
+                 {qh, kh}};
+  const dim3 grid(c.heads, f.M, 3 * c.batch);
+  if (c.block == 128)
+    permute_pool_kernel<128, D><<<grid, 256, 0, st>>>(moves, p->d_src_of_pos, p->d_blk_valid, f.N_v + c.n_text, f.M_v, c.batch);
+  else if (c.block == 64)
+    permute_pool_kernel<64, D><<<grid, 256, 0, st>>>(moves, p->d_src_of_pos, p->d_blk_valid, f.N_v + c.n_text, f.M_v, c.batch);
+  else
+    permute_pool_kernel<32, D><<<grid, 256, 0, st>>>(moves, p->d_src_of_pos, p->d_blk_valid, f.N_v + c.n_text, f.M_v, c.batch);
+  return hipGetLastError() == hipSuccess ? JENGA_OK : JENGA_EHIP;
+}
+
+int launch_permute_pool(const jenga_plan* p, const void* const src[3], void* const dst[3], void* select_ws, void* stream) {
+  if (p->cfg.head_dim == 128) return run_permute_pool<128>(p, src, dst, select_ws, (hipStream_t)stream);
+  return run_permute_pool<64>(p, src, dst, select_ws, (hipStream_t)stream);
 }
 
 }  // namespace jenga
@@ -610,5 +696,5 @@ extern "C" int jenga_select_blocks_static(const jenga_plan* p, const void* q_cur
   if (ws == nullptr) return JENGA_EHIP;
   // every byte of the scratch that select_kernel reads is written first by pool_kernel of this same call, so nothing
   // has to be cleared between calls
-  return jenga::launch_select(p, q_curve, k_curve, sel_count, sel_index, mask_or_null, ws, stream);
+  return jenga::launch_select(p, q_curve, k_curve, sel_count, sel_index, mask_or_null, ws, false, stream);
 }

@@ -6,7 +6,7 @@ from . import binding as B
 
 class CarveLayer:
     """Allocates the curve-side tensors, index lists and workspaces of one configuration once and
-    runs the four calls on torch's current stream."""
+    runs the four calls, or all of them as one (forward), on torch's current stream."""
 
     def __init__(self, w, device="cuda:0", text_bias=None, flags=None, want_mask=False, want_lse=False):
         self.w = dict(w)
@@ -61,10 +61,9 @@ class CarveLayer:
 
     def forward(self, q, k, v):
         """Whole path on thw-side bf16 tensors [batch, N_v+N_c, heads, d]; returns the thw-side output."""
-        self.permute_in(q, k, v)
-        self.select()
-        self.attend()
-        self.permute_out()
+        B.jenga_forward(self.plan, q, k, v, self.q_c, self.k_c, self.v_c, self.sel_count, self.sel_index, self.mask,
+                        self.ws_select, self.ws_select.numel(), self.o_c, self.lse, self.ws_attn, self.ws_attn.numel(),
+                        self.out_thw, self._stream())
         return self.out_thw
 
     def close(self):
