@@ -233,10 +233,13 @@ constexpr float P_SUM_MAX = 1073741824.0f;   // 2^30
 // the S and P registers and half the LDS of a step over 128, which lets three workgroups (twelve
 // wavefronts) live on a CU instead of two.
 //
-// Blocks of 64 tokens run the same loop with one step per block and two wavefronts: 32 KB of LDS at D = 128, five
-// workgroups on a CU.  12 heads x 14040 tokens, D = 128, k = 0.25 (0.41 TFLOP of tiles): 0.55 ms, 0.79 ms before
-// this loop replaced one that left every LDS read and the row maximum open.  At D = 64 the softmax, not the matrix
-// core, is the longer part of a step, and four wavefronts per SIMD (128 registers) fit.
+// Blocks of 64 tokens run the same loop with two wavefronts, at D = 64 one step per block.  At D = 128 steps of 64 keys take 32 KB
+// of LDS, which is given out in pieces of 1280 bytes: four workgroups on a CU, two wavefronts per SIMD, where registers allow three.
+// Steps of 32 keys take half and put six there; their barriers cost a lone workgroup a third more time a block.  Attention, 64 -> 32 keys
+// a step with text rows and the last lists cut for either: 222 blocks x 12 heads (0.41 TFLOP of tiles) 461 -> 430 us, x 24 882 -> 830,
+// 492 x 24 4.50 -> 4.08 ms, 120 x 12 172 -> 148 us, 76 x 8 76 -> 68, 41 x 8 41.6 -> 43.6.
+// At D = 64 the softmax, not the matrix core, is the longer part of a step (32 exponentials of 16 cycles and 80 other vector
+// instructions of 4 against 512 cycles of MFMA; 1100 cycles are measured), and four wavefronts per SIMD (128 registers) fit.
 //
 // PACED (JENGA_FLAG_PACED_WALK): the selected blocks are not visited in list order.  A position G sweeps
 // over the key blocks once per lap, derived from the constant-frequency clock that every CU reads
@@ -247,6 +250,8 @@ constexpr float P_SUM_MAX = 1073741824.0f;   // 2^30
 // tile reads of the in-order walk, catches more than half of them (measured on the 720p workload).
 // The price: the order, and with it the last bits of the output, can differ from run to run.
 // ---------------------------------------------------------------------------------------------
+template <int BLK, int D>
+constexpr int attn_h_keys() { return BLK == 64 && D == 128 ? 32 : 64; }   // of a step
 template <int BLK, int D>
 constexpr int attn_h_min_waves() { return D == 128 ? 3 : 4; }   // wavefronts per SIMD that the registers have to allow
 
@@ -294,11 +299,12 @@ __global__ __launch_bounds__(2 * BLK, (attn_h_min_waves<BLK, D>())) void attn_h_
     const int32_t* __restrict__ sel_count, const int32_t* __restrict__ sel_index,
     uint16_t* __restrict__ out, float* __restrict__ lse, WorkMap work, int n_pad, int pad_v, int pad_c,
     float scale_log2e, float bias_log2e, const uint32_t* __restrict__ pace_params, Split split, uint32_t* queue) {
-  constexpr int KS = D / 16, DT = D / 32, PS = BLK / 16, MH = 2, PH = 4;
-  constexpr int NW = BLK / 32, NTHR = 64 * NW, HALVES = BLK / 64;   // wavefronts, threads, steps per key block
-  constexpr int TILE_CHUNKS = BLK * D / 8, HALF_CHUNKS = 64 * D / 8, CPT = HALF_CHUNKS / NTHR;
-  static_assert(HALVES >= 1 && (!PACED || HALVES == 2), "64 keys a step; the paced walk needs two steps a block");
-  // The current 64 keys: fragments from packed tiles, or (K_ROWS) rows of D channels as they lie in K and V, with the
+  constexpr int KEYS = attn_h_keys<BLK, D>();   // a step
+  constexpr int KS = D / 16, DT = D / 32, PS = BLK / 16, MH = KEYS / 32, PH = KEYS / 16;
+  constexpr int NW = BLK / 32, NTHR = 64 * NW, HALVES = BLK / KEYS;   // wavefronts, threads, steps per key block
+  constexpr int TILE_CHUNKS = BLK * D / 8, HALF_CHUNKS = KEYS * D / 8, CPT = HALF_CHUNKS / NTHR;
+  static_assert(HALVES >= 1 && (!PACED || HALVES == 2), "the paced walk needs two steps a block");
+  // The current keys: fragments from packed tiles, or (K_ROWS) rows of D channels as they lie in K and V, with the
   // 16-byte pieces of a row rotated by an exclusive or on the way.  K: with k_swizzle(row), so that the 16 rows that are
   // read at a time fall on different banks.  V is read by columns, ds_read_b64_tr_b16, which hands a lane 4 keys of its
   // channel: two of them are a fragment, in the key order of the accumulators.  There v_swizzle(row) spreads the 4 rows x
@@ -462,16 +468,17 @@ __global__ __launch_bounds__(2 * BLK, (attn_h_min_waves<BLK, D>())) void attn_h_
   const uint32_t ks_lane =
       (uint32_t)(uintptr_t)(const __attribute__((address_space(3))) void*)Ks +
       (K_ROWS ? ql * (2 * D) + (hl ^ k_swizzle(ql)) * 16 : lane * 16);
-  auto k_frags = [&](u32x4 (&dst)[4], auto G) {   // (m2, ks) = (e & 1, 2 g + e / 2); K_ROWS: piece 2 ks + hl of row 32 m2 + ql
-    constexpr int g = decltype(G)::value;
-    uint32_t at[2] = {ks_lane, ks_lane};
-    if constexpr (K_ROWS) {
-      if constexpr (g > 0) at[0] = xor_here(ks_lane, g * 64);
-      at[1] = xor_here(ks_lane, g * 64 + 32);
-    }
+  // (m2, ks) = (e & 1, 2 g + e / 2), or (0, 4 g + e) in steps of 32 keys; K_ROWS: piece 2 ks + hl of row 32 m2 + ql
+  auto k_frags = [&](u32x4 (&dst)[4], auto G) {
+    constexpr int g = decltype(G)::value, PER = 4 / MH;   // values of ks in a group
+    uint32_t at[PER];
+    static_for<PER>([&](auto U) {
+      constexpr int ks = PER * g + decltype(U)::value;
+      at[decltype(U)::value] = K_ROWS && ks > 0 ? xor_here(ks_lane, ks * 32) : ks_lane;
+    });
     static_for<4>([&](auto E) {
-      constexpr int e = decltype(E)::value, m2 = e & 1;
-      lds_frag<K_ROWS ? m2 * 64 * D : (m2 * KS + 2 * g + e / 2) * 1024>(dst[e], at[e / 2]);
+      constexpr int e = decltype(E)::value, m2 = e % MH, ks = PER * g + e / MH;
+      lds_frag<K_ROWS ? m2 * 64 * D : (m2 * KS + ks) * 1024>(dst[e], at[e / MH]);
     });
   };
   // K_ROWS: columns 32 dt + 16 (lane / 16 % 2) + lane % 16 of four rows
@@ -492,8 +499,7 @@ __global__ __launch_bounds__(2 * BLK, (attn_h_min_waves<BLK, D>())) void attn_h_
   }
   if (cnt > 0) k_half_to_lds(j_next, 0);
 
-  for (int st = 0; st < steps; ++st) {
-    const int h = HALVES == 2 ? st & 1 : 0;
+  auto step = [&](int st, int h) __attribute__((always_inline)) {
     const int j = j_next;
     wait_vmem();       // this wave's part of the K half has landed
     __syncthreads();   // K half of this step is in LDS; every wave is past the previous PV
@@ -510,7 +516,7 @@ __global__ __launch_bounds__(2 * BLK, (attn_h_min_waves<BLK, D>())) void attn_h_
 #pragma unroll
         for (int r = 0; r < 16; ++r) S[m2][r] = 0.f;
       {
-        constexpr int NG = KS / 2;
+        constexpr int NG = KS * MH / 4;
         u32x4 A[2][4];
         k_frags(A[0], std::integral_constant<int, 0>{});
         static_for<NG>([&](auto G) {
@@ -519,7 +525,7 @@ __global__ __launch_bounds__(2 * BLK, (attn_h_min_waves<BLK, D>())) void attn_h_
           if constexpr (g + 1 < NG)
             k_frags(A[(g + 1) & 1], std::integral_constant<int, g + 1>{});
           static_for<4>([&](auto E) {
-            constexpr int e = decltype(E)::value, m2 = e & 1, ks = 2 * g + e / 2;
+            constexpr int e = decltype(E)::value, m2 = e % MH, ks = 4 / MH * g + e / MH;
             S[m2] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(__builtin_bit_cast(bf16x8, A[g & 1][e]), qf[ks], S[m2],
                                                             0, 0, 0);
           });
@@ -528,7 +534,7 @@ __global__ __launch_bounds__(2 * BLK, (attn_h_min_waves<BLK, D>())) void attn_h_
 
       if (nv < BLK) {   // sequence-length mask: pad keys of a ragged block
         asm volatile("");   // a real, rarely taken branch
-        int valid = nv - 64 * h - 4 * hl;
+        int valid = nv - KEYS * h - 4 * hl;
 #pragma unroll
         for (int m2 = 0; m2 < MH; ++m2)
 #pragma unroll
@@ -618,14 +624,15 @@ __global__ __launch_bounds__(2 * BLK, (attn_h_min_waves<BLK, D>())) void attn_h_
       asm volatile("" : "+v"(at));
 #pragma unroll 1
       for (; at < HALF_CHUNKS; at += NTHR)
-        if (64 * h + at / CH >= nv) Vs[at] = u32x4{0, 0, 0, 0};
+        if (KEYS * h + at / CH >= nv) Vs[at] = u32x4{0, 0, 0, 0};
     }
     __syncthreads();   // V half is in LDS; every wave is done reading the K half
     if (st + 1 < steps) k_half_to_lds(j_next, HALVES == 2 ? (st + 1) & 1 : 0);
 
-    // O^T += V^T P^T, fragments (dt, p2) = (2 (g / 2) + (e & 1), 2 (g % 2) + e / 2), pipelined as above
+    // O^T += V^T P^T, fragments (dt, p2) = (2 (g / 2) + (e & 1), 2 (g % 2) + e / 2), in steps of 32 keys (2 g + (e & 1), e / 2),
+    // pipelined as above
     {
-      constexpr int NG = DT;
+      constexpr int NG = DT * PH / 4;
       typedef typename std::conditional<K_ROWS, u32x2[2], u32x4>::type Frag;
       Frag A[2][4];
       uint32_t vs_dt[DT];   // K_ROWS: formed here and now, not kept over the loop
@@ -640,6 +647,9 @@ __global__ __launch_bounds__(2 * BLK, (attn_h_min_waves<BLK, D>())) void attn_h_
           lds_frag<(dt * PH + p2) * 1024>(dst, vs_lane);
         }
       };
+      // of group g
+      auto dt_of = [](int g, int e) { return (PH == 4 ? 2 * (g / 2) : 2 * g) + (e & 1); };
+      auto p2_of = [](int g, int e) { return (PH == 4 ? 2 * (g % 2) : 0) + e / 2; };
       static_for<4>([&](auto E) {
         constexpr int e = decltype(E)::value;
         v_frag(A[0][e], std::integral_constant<int, e & 1>{}, std::integral_constant<int, e / 2>{});
@@ -650,11 +660,10 @@ __global__ __launch_bounds__(2 * BLK, (attn_h_min_waves<BLK, D>())) void attn_h_
         if constexpr (g + 1 < NG)
           static_for<4>([&](auto E) {
             constexpr int e = decltype(E)::value, g1 = g + 1;
-            v_frag(A[g1 & 1][e], std::integral_constant<int, 2 * (g1 / 2) + (e & 1)>{},
-                   std::integral_constant<int, 2 * (g1 % 2) + e / 2>{});
+            v_frag(A[g1 & 1][e], std::integral_constant<int, dt_of(g1, e)>{}, std::integral_constant<int, p2_of(g1, e)>{});
           });
         static_for<4>([&](auto E) {
-          constexpr int e = decltype(E)::value, dt = 2 * (g / 2) + (e & 1), p2 = 2 * (g % 2) + e / 2;
+          constexpr int e = decltype(E)::value, dt = dt_of(g, e), p2 = p2_of(g, e);
           u32x4 a;
           if constexpr (K_ROWS)
             a = __builtin_shufflevector(A[g & 1][e][0], A[g & 1][e][1], 0, 1, 2, 3);
@@ -664,6 +673,14 @@ __global__ __launch_bounds__(2 * BLK, (attn_h_min_waves<BLK, D>())) void attn_h_
         });
       });
     }
+  };
+  if constexpr (KEYS == 32) {   // a block an iteration
+    for (int st = 0; st < steps; st += 2) {
+      step(st, 0);
+      step(st + 1, 1);
+    }
+  } else {
+    for (int st = 0; st < steps; ++st) step(st, HALVES == 2 ? st & 1 : 0);
   }
 
   // ---- normalise and store: lane holds row qrow, channels 32*dt + 8*g + 4*hl + {0..3} ----
@@ -1241,7 +1258,7 @@ int run_attention(const jenga_plan* p, const void* q, const void* k, const void*
         split.deal = jenga::plan_deal(p, work, p->attn_over_kv && !k_rows);
         split.first = p->attn_first;
         wgs = 8 * split.deal.positions();
-        if (queue != nullptr) wgs += (wgs + 3) / 4;
+        if (queue != nullptr && split.first < split.deal.positions()) wgs += (wgs + 3) / 4;
         slots = split.deal.slots();
         merge = dim3(BLK / 32, split.deal.text_rows() + split.deal.tail_rows(), 1);
       } else {

@@ -20,7 +20,7 @@ struct jenga_plan {
   // attn_chunk = 0: every list into attn_parts ranges of key blocks
   int attn_parts, attn_chunk;
   int attn_heads;  // (batch, head) pairs per launch where lists are cut
-  int attn_first;  // > 0: query blocks are dealt out by counters, and attn_tail lists cut; that many per XCD are not
+  int attn_first;  // > 0: attn_tail lists are cut, and the positions of an XCD behind that many dealt out by counters
   float attn_long; // if a call's vision lists have that many blocks on average
   int attn_text_parts;  // parts that the lists of text query blocks are cut into
   int attn_tail;   // lists that are cut, all into attn_parts, at the end of each XCD's
@@ -49,9 +49,10 @@ void curve_order(int T, int H, int W, bool use_curve, std::vector<int32_t>& perm
 // Host tables of a plan (no device work).  Returns a jenga_status.
 int build_host_tables(jenga_plan* plan);
 
-// Workgroups of the attention kernel for blocks of 64 and 128 tokens that are resident on a CU, by registers and LDS.
+// Workgroups of the attention kernel for blocks of 64 and 128 tokens that are resident on a CU, by registers and LDS (which is given
+// out in pieces of 1280 bytes).
 constexpr int attn_h_per_cu(int block, int head_dim) {
-  return block == 64 ? (head_dim == 128 ? 5 : 8) : (head_dim == 128 ? 3 : 4);
+  return block == 64 ? (head_dim == 128 ? 6 : 8) : (head_dim == 128 ? 3 : 4);
 }
 
 // Work mapping shared by the attention kernels.  The text query blocks of every (batch, head) are

@@ -225,8 +225,8 @@ int heads_per_launch(const jenga_plan* p, int threads) {
 // The plan goes by an expected length: K_top and the fixed blocks, or p^2 of all blocks where the cumulative rule decides, an estimate
 // for low-frequency activations (their lists hold 0.76 to 0.81 of all blocks at p = 0.9, 0.26 at 0.45, 0.21 to 0.37 at 0.5).  Whether
 // lists are dealt out by counters and cut at the end the lists of the call then decide (list_lengths_kernel).
-// The first generation is the resident workgroups; of 64 tokens at D = 128 four a CU, and the fifth asks the counter: with five
-// seven of ten shapes of 0.9 to 29 ms took 0.3 to 1.2 % more and three 0.6 to 1.5 % less.
+// The first generation is the resident workgroups; of 64 tokens at D = 128 four a CU of the six, the others ask the counter (with all six
+// 0.5 to 0.8 % less on 222 x 24 and x 40, p = 0.9, and with that half a generation cut 2 % more on x 12).
 // What remains is the last generation, which runs out over the time of one workgroup.  There half a generation of lists is
 // cut, into two: 1 to 3 % less from two generations on, but below two, where this reaches into the first one, up to
 // 5 % more (1416 query blocks at D = 128 601 -> 633 us).  Lists of uneven length (p well above k) into three, whatever the
@@ -241,6 +241,13 @@ int heads_per_launch(const jenga_plan* p, int threads) {
 // 183 -> 158; 1104, 138 a head, D = 128 507 -> 498; blocks of 64 at D = 64: 1944, 162 a head 180 -> 137, 8196, 683 a
 // head at k = 0.1 1401 -> 1270; 38 shapes 3 % less on average, none above 1 % more.  A text row has to last 400 us for it, beyond
 // one generation: with 920 query blocks of 128, 23 a head (145 us), a layer took 241 whole and 250 us cut, 888, 37 a head 211 and 215.
+//
+// Even lists of blocks of 64 tokens at D = 128 (six workgroups a CU, 2.2 us a block then, 1.8 alone): a text row lasts as long as the launch sooner than
+// that, and with one to two generations a cut of 64 lists per XCD at the end evens out how many workgroups the CUs are left with, without
+// counters.  It pays where no text row is left whole.  Attention, whole -> text rows cut -> lists at the end too, k = 0.25: 222 blocks x 12 heads
+// 486 -> 439 -> 426 us, x 8 416 -> 332 -> 297, 121 x 16 252 -> 222 -> 208, x 13 247 -> 200 -> 175, x 20 271 -> 261 -> 258; text rows whole, 121 x 24
+// 298 -> 307, 92 x 24 204 -> 218.  No text: 120 x 14 203 -> 186, x 20 245 -> 253.  Lists of 24 blocks: 62 x 32 136 -> 152.  From 2.3 generations
+// on nothing changes (222 x 16, x 24).  Text rows of 200 us: 92 x 24 204 -> 206; 62 x 32 (136 us) 137 -> 141. 
 constexpr uint64_t RANGE_AREA_BYTES = 128ull << 20;
 
 Deal plan_deal(const jenga_plan* p, const WorkMap& work, bool whole) {
@@ -280,23 +287,27 @@ static void split_lists(jenga_plan* plan) {
     }
     return;
   }
-  const long long places = 256ll * attn_h_per_cu(c.block, c.head_dim);
-  if (4 * rows >= 3 * places) {
-    const bool uneven = c.cum_prob > 2.0 * c.topk_ratio;
+  const bool b64_d128 = c.block == 64 && c.head_dim == 128, uneven = c.cum_prob > 2.0 * c.topk_ratio, fine_even = b64_d128 && !uneven;
+  const long long cut_places = 256ll * (b64_d128 ? 5 : attn_h_per_cu(c.block, c.head_dim));   // what short grids' lists are cut by
+  const long long places = fine_even ? 256ll * attn_h_per_cu(c.block, c.head_dim) : cut_places;
+  if (4 * rows >= 3 * cut_places) {
     const WorkMap work = plan_work(plan, c.batch * c.heads);
     const double usual = std::max((double)len, c.cum_prob * c.cum_prob * f.M), gens = (double)rows / places;
-    const double block_us = c.block == 128 ? (c.head_dim == 128 ? 6.3 : 3.6) : (c.head_dim == 128 ? 2.6 : 1.8);
+    const double block_us = c.block == 128 ? (c.head_dim == 128 ? 6.3 : 3.6) : (c.head_dim == 128 ? (uneven ? 2.6 : 2.2) : 1.8);
     const long long text_rows = (long long)c.batch * c.heads * f.M_c;
     const double long_list = (c.head_dim == 128 ? 200.0 : 320.0) / block_us;
     if (rows > places && (c.block == 128 || uneven) && usual >= long_list) {
       plan->attn_long = (float)long_list;
-      plan->attn_first = 32 * (c.block == 64 && c.head_dim == 128 ? 4 : attn_h_per_cu(c.block, c.head_dim));
+      plan->attn_first = 32 * (b64_d128 ? 4 : attn_h_per_cu(c.block, c.head_dim));
       if (uneven || rows >= 2 * places) {
         // beyond the first generation, and vision lists: text rows, dealt out first, may be most of the grid
         const int positions = (work.n_wg + 7) / 8, vision = (work.n_wg - work.text_wgs + 7) / 8;
         plan->attn_tail = std::min({positions - plan->attn_first, plan->attn_first / 2, vision});
         plan->attn_parts = uneven ? 3 : 2;
       }
+    } else if (fine_even && rows > places && gens < (text_rows > 0 ? 2.25 : 1.3) && usual >= 28) {
+      plan->attn_tail = std::min(64, (work.n_wg - work.text_wgs + 7) / 8);
+      plan->attn_parts = 2;
     }
     // Text rows may be most of the grid too: as many parts as there is room for beside the lists cut at the end, in the area
     // or where packed K would lie.
@@ -315,15 +326,24 @@ static void split_lists(jenga_plan* plan) {
           plan->attn_text_parts = parts;
         }
       }
-    } else if (f.M * block_us >= 400.0 && f.M > (gens < 1.5 ? 1.15 : 1.8) * gens * usual) {
+    } else if (f.M * block_us >= (fine_even ? 240.0 : 400.0) && f.M > (gens < 1.5 ? 1.15 : fine_even ? 1.55 : 1.8) * gens * usual) {
       plan->attn_text_parts = std::max(1, std::min(most, (int)std::ceil(f.M / (gens * usual))));
+    }
+    if (plan->attn_tail > 0 && plan->attn_first == 0) {
+      if (text_rows > 0 && plan->attn_text_parts == 1) {
+        plan->attn_tail = 0;
+        plan->attn_parts = 1;
+      } else {
+        plan->attn_long = 28.f;
+        plan->attn_first = plan_deal(plan, work, false).positions();   // all of them: no counter is asked
+      }
     }
     return;
   }
   const long long shortest = (rows <= 256 ? 6 : 24) * 64 / c.block;
-  const long long chunk = std::max(shortest, (5 * rows * len + 3 * places - 1) / (3 * places));
-  if (8 * rows >= 3 * places && 2 * f.M <= 3 * chunk) return;
-  plan->attn_parts = (int)std::min(std::min(8ll, 2 * places / rows), (f.M + chunk - 1) / chunk);
+  const long long chunk = std::max(shortest, (5 * rows * len + 3 * cut_places - 1) / (3 * cut_places));
+  if (8 * rows >= 3 * cut_places && 2 * f.M <= 3 * chunk) return;
+  plan->attn_parts = (int)std::min(std::min(8ll, 2 * cut_places / rows), (f.M + chunk - 1) / chunk);
   plan->attn_chunk = (int)chunk;
 }
 
