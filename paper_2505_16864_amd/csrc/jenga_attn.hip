@@ -62,10 +62,9 @@ struct ThwRows {
   uint16_t* thw;
   const int32_t* src_of_pos;
   int n_src, heads, first;
-  // channel 0 of row `pos` of the launch's pair bh; nullptr: a pad, or nothing is to be written there
+  // channel 0 of row `pos` of the launch's pair bh; nullptr: a pad.  thw is not nullptr.
   template <int D>
   __device__ __forceinline__ uint16_t* row(int bh, int pos) const {
-    if (thw == nullptr) return nullptr;
     const int s = src_of_pos[pos], b = (first + bh) / heads, h = first + bh - b * heads;
     return s < 0 ? nullptr : thw + (((size_t)b * n_src + s) * heads + h) * D;
   }
@@ -713,17 +712,24 @@ __global__ __launch_bounds__(2 * BLK, (attn_h_min_waves<BLK, D>())) void attn_h_
   // natural-log sum of exp(logit) over the visited keys: the running maximum is in base-2 units
   if (lse != nullptr && hl_e == 0)
     lse[qrow_e] = row_ok ? (m_run + __builtin_amdgcn_logf(l_tot)) * 0.6931471805599453f : -INFINITY;
-  uint16_t *orow = out + qrow_e * D, *trow = ThwRows::argument().row<D>(bh, i * BLK + row_e);
+  uint16_t* orow = out + qrow_e * D;
+  uint2 w[DT][4];
 #pragma unroll
   for (int dt = 0; dt < DT; ++dt)
 #pragma unroll
     for (int g = 0; g < 4; ++g) {
-      uint2 w;
-      w.x = row_ok ? pack_bf16x2(O[dt][4 * g] * inv, O[dt][4 * g + 1] * inv) : 0u;
-      w.y = row_ok ? pack_bf16x2(O[dt][4 * g + 2] * inv, O[dt][4 * g + 3] * inv) : 0u;
-      *(uint2*)(orow + 32 * dt + 8 * g + 4 * hl_e) = w;
-      if (trow != nullptr) *(uint2*)(trow + 32 * dt + 8 * g + 4 * hl_e) = w;
+      w[dt][g].x = row_ok ? pack_bf16x2(O[dt][4 * g] * inv, O[dt][4 * g + 1] * inv) : 0u;
+      w[dt][g].y = row_ok ? pack_bf16x2(O[dt][4 * g + 2] * inv, O[dt][4 * g + 3] * inv) : 0u;
+      *(uint2*)(orow + 32 * dt + 8 * g + 4 * hl_e) = w[dt][g];
     }
+  const ThwRows thw_rows = ThwRows::argument();
+  if (thw_rows.thw == nullptr) return;
+  uint16_t* trow = thw_rows.row<D>(bh, i * BLK + row_e);
+  if (trow == nullptr) return;
+#pragma unroll
+  for (int dt = 0; dt < DT; ++dt)
+#pragma unroll
+    for (int g = 0; g < 4; ++g) *(uint2*)(trow + 32 * dt + 8 * g + 4 * hl_e) = w[dt][g];
 }
 
 // merge_kernel: grid (BLK / 32, M, batch * heads) or, with a Deal, (BLK / 32, rows that are cut), one wavefront per channel tile
@@ -788,15 +794,19 @@ __global__ __launch_bounds__(2 * D) void merge_kernel(const int32_t* __restrict_
   const size_t qrow = (size_t)bh * n_pad + (size_t)i * BLK + row;
   if (lse != nullptr && threadIdx.x < 32)
     lse[qrow] = row_ok ? (m + __builtin_amdgcn_logf(l)) * 0.6931471805599453f : -INFINITY;
-  uint16_t *orow = out + qrow * D + 32 * dt + 4 * hl, *trow = thw_rows.row<D>(bh, i * BLK + row);
+  uint16_t* orow = out + qrow * D + 32 * dt + 4 * hl;
+  uint2 packed[4];
 #pragma unroll
   for (int g = 0; g < 4; ++g) {
-    uint2 w;
-    w.x = row_ok ? pack_bf16x2(sum[4 * g] * inv, sum[4 * g + 1] * inv) : 0u;
-    w.y = row_ok ? pack_bf16x2(sum[4 * g + 2] * inv, sum[4 * g + 3] * inv) : 0u;
-    *(uint2*)(orow + 8 * g) = w;
-    if (trow != nullptr) *(uint2*)(trow + 32 * dt + 4 * hl + 8 * g) = w;
+    packed[g].x = row_ok ? pack_bf16x2(sum[4 * g] * inv, sum[4 * g + 1] * inv) : 0u;
+    packed[g].y = row_ok ? pack_bf16x2(sum[4 * g + 2] * inv, sum[4 * g + 3] * inv) : 0u;
+    *(uint2*)(orow + 8 * g) = packed[g];
   }
+  if (thw_rows.thw == nullptr) return;
+  uint16_t* trow = thw_rows.row<D>(bh, i * BLK + row);
+  if (trow == nullptr) return;
+#pragma unroll
+  for (int g = 0; g < 4; ++g) *(uint2*)(trow + 32 * dt + 4 * hl + 8 * g) = packed[g];
 }
 
 // ---------------------------------------------------------------------------------------------
@@ -1051,7 +1061,8 @@ __device__ __forceinline__ void attn_32(
   // weight of this wavefront's part
   const float mine = RANGE ? __builtin_amdgcn_exp2f(m_run - ref) : row_ok ? __builtin_amdgcn_exp2f(m_run - ref) / l_all : 0.f;
   constexpr int RP = 16 / NS;   // accumulator registers of a channel tile that one wavefront adds up
-  uint16_t* trow = RANGE ? nullptr : thw_rows.row<D>(bh, i * BLK + ql);
+  uint16_t* trow = nullptr;
+  if (!RANGE && thw_rows.thw != nullptr) trow = thw_rows.row<D>(bh, i * BLK + ql);
 #pragma unroll
   for (int dt = 0; dt < DT; ++dt) {
     if (dt > 0) __syncthreads();   // the previous tile has been read
@@ -1075,11 +1086,15 @@ __device__ __forceinline__ void attn_32(
     }
     const int channel = 32 * dt + 8 * (r0 / 4) + 4 * hl + r0 % 4;
     uint16_t* o = out + qrow * D + channel;
+    uint32_t w[RP / 2];
 #pragma unroll
     for (int u = 0; u < RP; u += 2) {
-      const uint32_t w = row_ok ? pack_bf16x2(sum[u], sum[u + 1]) : 0u;
-      *(uint32_t*)(o + u) = w;
-      if (trow != nullptr) *(uint32_t*)(trow + channel + u) = w;
+      w[u / 2] = row_ok ? pack_bf16x2(sum[u], sum[u + 1]) : 0u;
+      *(uint32_t*)(o + u) = w[u / 2];
+    }
+    if (thw_rows.thw != nullptr && trow != nullptr) {
+#pragma unroll
+      for (int u = 0; u < RP; u += 2) *(uint32_t*)(trow + channel + u) = w[u / 2];
     }
   }
 }
