@@ -56,19 +56,22 @@ __device__ inline uint32_t pack_bf16x2(float lo, float hi) {
 // behind them whether it is used.
 constexpr int PARAM_QUEUE = 8, QUEUE_USED = 8;
 
-// jenga_forward: rows go to the thw side from the kernel that has them in registers, beside the curve side.
-// thw: [batch][n_src][heads][D], or nullptr; first: (batch, head) pair that the launch's first one is.
+// jenga_forward: rows go to the thw side from the kernel that has them in registers, beside the curve side.  These are instances of
+// their own: as a branch in one kernel for all, small calls that have no such rows took 2 to 4 % longer (30 blocks of 32 x 3 heads,
+// D = 64, 8.8 -> 9.1 us, 20 of 128 x 8, D = 64, 26.0 -> 26.6).
+// thw: [batch][n_src][heads][D]; first: (batch, head) pair that the launch's first one is.
+struct NoThwRows {};
 struct ThwRows {
   uint16_t* thw;
   const int32_t* src_of_pos;
   int n_src, heads, first;
-  // channel 0 of row `pos` of the launch's pair bh; nullptr: a pad.  thw is not nullptr.
+  // channel 0 of row `pos` of the launch's pair bh; nullptr: a pad
   template <int D>
   __device__ __forceinline__ uint16_t* row(int bh, int pos) const {
     const int s = src_of_pos[pos], b = (first + bh) / heads, h = first + bh - b * heads;
     return s < 0 ? nullptr : thw + (((size_t)b * n_src + s) * heads + h) * D;
   }
-  // The kernel's first argument, read again where it is called: kept over attn_h_kernel's loop it would cost scalar registers there
+  // The kernel's first argument, read again where it is called: kept over attn_h's loop it would cost scalar registers there
   // (up to 9 more, spilled ones in four of the kernels).
   __device__ __forceinline__ static ThwRows argument() {
     ThwRows t = {};
@@ -292,12 +295,13 @@ __device__ inline int take_item(uint32_t* queue, int n_end) {
   }
 }
 
-template <int BLK, int D, bool PACED, bool SPLIT, bool K_ROWS>
-__global__ __launch_bounds__(2 * BLK, (attn_h_min_waves<BLK, D>())) void attn_h_kernel(
-    ThwRows, const uint16_t* __restrict__ q, const u32x4* __restrict__ kp, const u32x4* __restrict__ vp,
+// THW: the kernel's first argument is a ThwRows.
+template <int BLK, int D, bool PACED, bool SPLIT, bool K_ROWS, bool THW>
+__device__ __forceinline__ void attn_h(
+    const uint16_t* __restrict__ q, const u32x4* __restrict__ kp, const u32x4* __restrict__ vp,
     const int32_t* __restrict__ sel_count, const int32_t* __restrict__ sel_index,
-    uint16_t* __restrict__ out, float* __restrict__ lse, WorkMap work, int n_pad, int pad_v, int pad_c,
-    float scale_log2e, float bias_log2e, const uint32_t* __restrict__ pace_params, Split split, uint32_t* queue) {
+    uint16_t* __restrict__ out, float* __restrict__ lse, const WorkMap& work, int n_pad, int pad_v, int pad_c,
+    float scale_log2e, float bias_log2e, const uint32_t* __restrict__ pace_params, const Split& split, uint32_t* queue) {
   constexpr int KEYS = attn_h_keys<BLK, D>();   // a step
   constexpr int KS = D / 16, DT = D / 32, PS = BLK / 16, MH = KEYS / 32, PH = KEYS / 16;
   constexpr int NW = BLK / 32, NTHR = 64 * NW, HALVES = BLK / KEYS;   // wavefronts, threads, steps per key block
@@ -722,24 +726,41 @@ __global__ __launch_bounds__(2 * BLK, (attn_h_min_waves<BLK, D>())) void attn_h_
       w[dt][g].y = row_ok ? pack_bf16x2(O[dt][4 * g + 2] * inv, O[dt][4 * g + 3] * inv) : 0u;
       *(uint2*)(orow + 32 * dt + 8 * g + 4 * hl_e) = w[dt][g];
     }
-  const ThwRows thw_rows = ThwRows::argument();
-  if (thw_rows.thw == nullptr) return;
-  uint16_t* trow = thw_rows.row<D>(bh, i * BLK + row_e);
-  if (trow == nullptr) return;
+  if constexpr (THW) {
+    uint16_t* trow = ThwRows::argument().row<D>(bh, i * BLK + row_e);
+    if (trow == nullptr) return;
 #pragma unroll
-  for (int dt = 0; dt < DT; ++dt)
+    for (int dt = 0; dt < DT; ++dt)
 #pragma unroll
-    for (int g = 0; g < 4; ++g) *(uint2*)(trow + 32 * dt + 8 * g + 4 * hl_e) = w[dt][g];
+      for (int g = 0; g < 4; ++g) *(uint2*)(trow + 32 * dt + 8 * g + 4 * hl_e) = w[dt][g];
+  }
+}
+
+#define JENGA_ATTN_H_PARAMETERS                                                                                       \
+  const uint16_t *__restrict__ q, const u32x4 *__restrict__ kp, const u32x4 *__restrict__ vp,                         \
+      const int32_t *__restrict__ sel_count, const int32_t *__restrict__ sel_index, uint16_t *__restrict__ out,       \
+      float *__restrict__ lse, WorkMap work, int n_pad, int pad_v, int pad_c, float scale_log2e, float bias_log2e,    \
+      const uint32_t *__restrict__ pace_params, Split split, uint32_t *queue
+#define JENGA_ATTN_H_ARGUMENTS \
+  q, kp, vp, sel_count, sel_index, out, lse, work, n_pad, pad_v, pad_c, scale_log2e, bias_log2e, pace_params, split, queue
+
+template <int BLK, int D, bool PACED, bool SPLIT, bool K_ROWS>
+__global__ __launch_bounds__(2 * BLK, (attn_h_min_waves<BLK, D>())) void attn_h_kernel(JENGA_ATTN_H_PARAMETERS) {
+  attn_h<BLK, D, PACED, SPLIT, K_ROWS, false>(JENGA_ATTN_H_ARGUMENTS);
+}
+template <int BLK, int D, bool PACED, bool SPLIT, bool K_ROWS>
+__global__ __launch_bounds__(2 * BLK, (attn_h_min_waves<BLK, D>())) void attn_h_thw_kernel(ThwRows, JENGA_ATTN_H_PARAMETERS) {
+  attn_h<BLK, D, PACED, SPLIT, K_ROWS, true>(JENGA_ATTN_H_ARGUMENTS);
 }
 
 // merge_kernel: grid (BLK / 32, M, batch * heads) or, with a Deal, (BLK / 32, rows that are cut), one wavefront per channel tile
 // of 32 query rows.  Puts the parts of the lists that attn_h_kernel<.., SPLIT> cut together, in the order of the parts; the other
 // rows are done already.
-template <int BLK, int D>
+template <int BLK, int D, typename Thw>
 __global__ __launch_bounds__(2 * D) void merge_kernel(const int32_t* __restrict__ sel_count, uint16_t* __restrict__ out,
                                                       float* __restrict__ lse, WorkMap work, int n_pad, int pad_v,
                                                       int pad_c, Split split, const uint32_t* __restrict__ queue,
-                                                      ThwRows thw_rows) {
+                                                      Thw thw_rows) {
   constexpr int DT = D / 32, NW = BLK / 32;
   const int M = work.M, M_v = work.M_v, wave = blockIdx.x;
   int i = blockIdx.y, bh = blockIdx.z, n_parts;
@@ -802,11 +823,12 @@ __global__ __launch_bounds__(2 * D) void merge_kernel(const int32_t* __restrict_
     packed[g].y = row_ok ? pack_bf16x2(sum[4 * g + 2] * inv, sum[4 * g + 3] * inv) : 0u;
     *(uint2*)(orow + 8 * g) = packed[g];
   }
-  if (thw_rows.thw == nullptr) return;
-  uint16_t* trow = thw_rows.row<D>(bh, i * BLK + row);
-  if (trow == nullptr) return;
+  if constexpr (std::is_same<Thw, ThwRows>::value) {
+    uint16_t* trow = thw_rows.template row<D>(bh, i * BLK + row);
+    if (trow == nullptr) return;
 #pragma unroll
-  for (int g = 0; g < 4; ++g) *(uint2*)(trow + 32 * dt + 4 * hl + 8 * g) = packed[g];
+    for (int g = 0; g < 4; ++g) *(uint2*)(trow + 32 * dt + 4 * hl + 8 * g) = packed[g];
+  }
 }
 
 // ---------------------------------------------------------------------------------------------
@@ -835,12 +857,13 @@ __global__ __launch_bounds__(2 * D) void merge_kernel(const int32_t* __restrict_
 // ROWS (D = 64): K and V as they lie, for grids so small that packing them, a launch, is what counts (reads_kv_in_place).  K
 // fragments are then 32 rows x 32 bytes instead of 1 KB in one piece; V goes through LDS, 32 rows per wavefront, and is
 // read by columns as in attn_h_kernel, the next rows only after that.  The same bits either way.
-template <int D, int NS, bool RANGE, bool ROWS>
+template <int D, int NS, bool RANGE, bool ROWS, typename Thw>
 __device__ __forceinline__ void attn_32(
     const uint16_t* __restrict__ q, const u32x4* __restrict__ kp, const u32x4* __restrict__ vp,
     const int32_t* __restrict__ sel_count, const int32_t* __restrict__ sel_index, uint16_t* __restrict__ out,
     float* __restrict__ lse, const WorkMap& work, int n_pad, int pad_v, int pad_c, float scale_log2e, float bias_log2e,
-    const Split& split, const ThwRows& thw_rows) {
+    const Split& split, const Thw& thw_rows) {
+  constexpr bool THW = std::is_same<Thw, ThwRows>::value;
   constexpr int BLK = 32, KS = D / 16, DT = D / 32, PS = BLK / 16, TILE_CHUNKS = BLK * D / 8, CH = D / 8;
   // one channel tile of every wavefront's O, accumulator order; ROWS: before that, 32 rows of V for every wavefront
   static_assert(!ROWS || D == 64, "32 rows of V take the room of a channel tile");
@@ -1062,7 +1085,7 @@ __device__ __forceinline__ void attn_32(
   const float mine = RANGE ? __builtin_amdgcn_exp2f(m_run - ref) : row_ok ? __builtin_amdgcn_exp2f(m_run - ref) / l_all : 0.f;
   constexpr int RP = 16 / NS;   // accumulator registers of a channel tile that one wavefront adds up
   uint16_t* trow = nullptr;
-  if (!RANGE && thw_rows.thw != nullptr) trow = thw_rows.row<D>(bh, i * BLK + ql);
+  if constexpr (THW) trow = thw_rows.template row<D>(bh, i * BLK + ql);
 #pragma unroll
   for (int dt = 0; dt < DT; ++dt) {
     if (dt > 0) __syncthreads();   // the previous tile has been read
@@ -1092,32 +1115,33 @@ __device__ __forceinline__ void attn_32(
       w[u / 2] = row_ok ? pack_bf16x2(sum[u], sum[u + 1]) : 0u;
       *(uint32_t*)(o + u) = w[u / 2];
     }
-    if (thw_rows.thw != nullptr && trow != nullptr) {
+    if (THW && trow != nullptr) {
 #pragma unroll
       for (int u = 0; u < RP; u += 2) *(uint32_t*)(trow + channel + u) = w[u / 2];
     }
   }
 }
 
+#define JENGA_ATTN_32_PARAMETERS                                                                                      \
+  const uint16_t *__restrict__ q, const u32x4 *__restrict__ kp, const u32x4 *__restrict__ vp,                         \
+      const int32_t *__restrict__ sel_count, const int32_t *__restrict__ sel_index, uint16_t *__restrict__ out,       \
+      float *__restrict__ lse, WorkMap work, int n_pad, int pad_v, int pad_c, float scale_log2e, float bias_log2e
+#define JENGA_ATTN_32_ARGUMENTS \
+  q, kp, vp, sel_count, sel_index, out, lse, work, n_pad, pad_v, pad_c, scale_log2e, bias_log2e
+
 template <int D, int NS, bool RANGE>
-__global__ __launch_bounds__(64 * NS, (D == 128 ? 2 : 4)) void attn_kernel(
-    const uint16_t* __restrict__ q, const u32x4* __restrict__ kp, const u32x4* __restrict__ vp,
-    const int32_t* __restrict__ sel_count, const int32_t* __restrict__ sel_index, uint16_t* __restrict__ out,
-    float* __restrict__ lse, WorkMap work, int n_pad, int pad_v, int pad_c, float scale_log2e, float bias_log2e,
-    Split split, ThwRows thw_rows) {
-  attn_32<D, NS, RANGE, false>(q, kp, vp, sel_count, sel_index, out, lse, work, n_pad, pad_v, pad_c, scale_log2e, bias_log2e,
-                               split, thw_rows);
+__global__ __launch_bounds__(64 * NS, (D == 128 ? 2 : 4)) void attn_kernel(JENGA_ATTN_32_PARAMETERS, Split split) {
+  attn_32<D, NS, RANGE, false>(JENGA_ATTN_32_ARGUMENTS, split, NoThwRows{});
+}
+template <int D, int NS>
+__global__ __launch_bounds__(64 * NS, (D == 128 ? 2 : 4)) void attn_32_thw_kernel(JENGA_ATTN_32_PARAMETERS, ThwRows thw_rows) {
+  attn_32<D, NS, false, false>(JENGA_ATTN_32_ARGUMENTS, Split{}, thw_rows);
 }
 
 // K and V in place.
-template <int D, int NS>
-__global__ __launch_bounds__(64 * NS, 4) void attn_rows_kernel(
-    const uint16_t* __restrict__ q, const u32x4* __restrict__ k, const u32x4* __restrict__ v,
-    const int32_t* __restrict__ sel_count, const int32_t* __restrict__ sel_index, uint16_t* __restrict__ out,
-    float* __restrict__ lse, WorkMap work, int n_pad, int pad_v, int pad_c, float scale_log2e, float bias_log2e,
-    ThwRows thw_rows) {
-  attn_32<D, NS, false, true>(q, k, v, sel_count, sel_index, out, lse, work, n_pad, pad_v, pad_c, scale_log2e, bias_log2e,
-                              Split{}, thw_rows);
+template <int D, int NS, typename Thw>
+__global__ __launch_bounds__(64 * NS, 4) void attn_rows_kernel(JENGA_ATTN_32_PARAMETERS, Thw thw_rows) {
+  attn_32<D, NS, false, true>(JENGA_ATTN_32_ARGUMENTS, Split{}, thw_rows);
 }
 
 // What a launch has to know of the lists' lengths.  One workgroup.
@@ -1194,9 +1218,10 @@ int run_pack(const jenga_plan* p, const void* k, const void* v, void* ws, hipStr
   return hipGetLastError() == hipSuccess ? JENGA_OK : JENGA_EHIP;
 }
 
-template <int BLK, int D>
+template <int BLK, int D, typename Thw>
 int run_attention(const jenga_plan* p, const void* q, const void* k, const void* v, void* ws, bool may_split,
-                  const int32_t* sel_count, const int32_t* sel_index, void* out, float* lse, void* thw, hipStream_t st) {
+                  const int32_t* sel_count, const int32_t* sel_index, void* out, float* lse, Thw thw_rows, hipStream_t st) {
+  constexpr bool THW = std::is_same<Thw, ThwRows>::value;
   const jenga_config& c = p->cfg;
   const jenga_plan_info_t& f = p->info;
   const int bh = c.batch * c.heads;
@@ -1209,7 +1234,6 @@ int run_attention(const jenga_plan* p, const void* q, const void* k, const void*
   const float scale = log2e / sqrtf((float)D), bias = c.text_bias * log2e;
   const uint16_t* qb = (const uint16_t*)q;
   uint16_t* ob = (uint16_t*)out;
-  ThwRows thw_rows = {(uint16_t*)thw, p->d_src_of_pos, f.N_v + c.n_text, c.heads, 0};
   if constexpr (BLK == 32) {   // in-order walk only
     constexpr int NS = D == 128 ? 4 : 8;
     const bool ranges = may_split && p->attn_parts > 1;
@@ -1229,11 +1253,11 @@ int run_attention(const jenga_plan* p, const void* q, const void* k, const void*
       const int32_t *count0 = sel_count + list0, *index0 = sel_index + list0 * f.M;
       uint16_t* ob0 = ob + row0 * D;
       float* lse0 = lse != nullptr ? lse + row0 : nullptr;
-      thw_rows.first = first;
+      if constexpr (THW) thw_rows.first = first;
       if (ranges) {
         split.stride = (work.n_wg + 7) & ~7;
         attn_kernel<D, NS, true><<<dim3(split.parts * split.stride), 64 * NS, 0, st>>>(
-            q0, kp0, vp0, count0, index0, ob0, lse0, work, f.N_pad, f.pad_v, f.pad_c, scale, bias, split, thw_rows);
+            q0, kp0, vp0, count0, index0, ob0, lse0, work, f.N_pad, f.pad_v, f.pad_c, scale, bias, split);
         merge_kernel<BLK, D><<<dim3(1, f.M, n), 2 * D, 0, st>>>(count0, ob0, lse0, work, f.N_pad, f.pad_v, f.pad_c,
                                                                 split, nullptr, thw_rows);
         continue;
@@ -1245,17 +1269,27 @@ int run_attention(const jenga_plan* p, const void* q, const void* k, const void*
           continue;
         }
       }
-      attn_kernel<D, NS, false><<<dim3(work.n_wg), 64 * NS, 0, st>>>(q0, kp0, vp0, count0, index0, ob0, lse0, work, f.N_pad,
-                                                                     f.pad_v, f.pad_c, scale, bias, split, thw_rows);
+      if constexpr (THW)
+        attn_32_thw_kernel<D, NS><<<dim3(work.n_wg), 64 * NS, 0, st>>>(q0, kp0, vp0, count0, index0, ob0, lse0, work, f.N_pad,
+                                                                       f.pad_v, f.pad_c, scale, bias, thw_rows);
+      else
+        attn_kernel<D, NS, false><<<dim3(work.n_wg), 64 * NS, 0, st>>>(q0, kp0, vp0, count0, index0, ob0, lse0, work, f.N_pad,
+                                                                       f.pad_v, f.pad_c, scale, bias, split);
     }
   } else {
     const bool paced = BLK == 128 && (c.flags & JENGA_FLAG_PACED_WALK);
     const WorkMap work = jenga::plan_work(p, bh);
     Split split = {};
     uint32_t *queue = may_split ? attn_queue(p, ws) : nullptr, *pace = nullptr;
+#define JENGA_ATTN_H_VALUES \
+  qb, kp, vp, sel_count, sel_index, ob, lse, work, f.N_pad, f.pad_v, f.pad_c, scale, bias, pace, split, queue
 #define JENGA_ATTN(PACED, SPLIT, K_ROWS, WGS)                                                                    \
-  attn_h_kernel<BLK, D, PACED, SPLIT, K_ROWS><<<dim3(WGS), 2 * BLK, 0, st>>>(                                    \
-      thw_rows, qb, kp, vp, sel_count, sel_index, ob, lse, work, f.N_pad, f.pad_v, f.pad_c, scale, bias, pace, split, queue)
+  do {                                                                                                           \
+    if constexpr (THW)                                                                                           \
+      attn_h_thw_kernel<BLK, D, PACED, SPLIT, K_ROWS><<<dim3(WGS), 2 * BLK, 0, st>>>(thw_rows, JENGA_ATTN_H_VALUES); \
+    else                                                                                                         \
+      attn_h_kernel<BLK, D, PACED, SPLIT, K_ROWS><<<dim3(WGS), 2 * BLK, 0, st>>>(JENGA_ATTN_H_VALUES);            \
+  } while (0)
     if (paced && !(may_split && p->attn_first == 0 && p->attn_parts > 1)) pace = params;   // parts of short grids: ascending order
     if (pace != nullptr || queue != nullptr) {
       // a workgroup spends about 6.3 us (D = 128; 3.6 us at D = 64) on a block of 128 keys when three share a CU
@@ -1302,6 +1336,7 @@ int run_attention(const jenga_plan* p, const void* q, const void* k, const void*
     if (k_rows) JENGA_ATTN(false, false, true, work.n_wg);
     else if (!paced) JENGA_ATTN(false, false, false, work.n_wg);
 #undef JENGA_ATTN
+#undef JENGA_ATTN_H_VALUES
   }
   return hipGetLastError() == hipSuccess ? JENGA_OK : JENGA_EHIP;
 }
@@ -1334,8 +1369,12 @@ int launch_attention(const jenga_plan* p, const void* q, const void* k, const vo
                      const int32_t* sel_count, const int32_t* sel_index, void* out, float* lse, void* thw, void* stream) {
   hipStream_t st = (hipStream_t)stream;
   const int blk = p->cfg.block, d = p->cfg.head_dim;
-#define X(B, DD) \
-  if (blk == B && d == DD) return run_attention<B, DD>(p, q, k, v, ws, may_split, sel_count, sel_index, out, lse, thw, st);
+  const ThwRows rows = {(uint16_t*)thw, p->d_src_of_pos, p->info.N_v + p->cfg.n_text, p->cfg.heads, 0};
+#define X(B, DD)                                                                                                      \
+  if (blk == B && d == DD)                                                                                            \
+    return thw != nullptr                                                                                             \
+               ? run_attention<B, DD>(p, q, k, v, ws, may_split, sel_count, sel_index, out, lse, rows, st)            \
+               : run_attention<B, DD>(p, q, k, v, ws, may_split, sel_count, sel_index, out, lse, NoThwRows{}, st);
   JENGA_FOR_SHAPES(X)
 #undef X
   return JENGA_EUNSUPPORTED;

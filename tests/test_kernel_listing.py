@@ -153,3 +153,28 @@ def test_attention_kernels_keep_their_occupancy(listing):
         # some of those go to lanes of a vector register.  No other kernel is short of scalar registers.
         assert of("sgpr_spill_count") <= (33 if "ILi64ELi128E" in name else 17 if "ILi64ELi64E" in name else 0), name
     assert len(seen) == len(limits)
+
+
+# Rows for the token order are stored by instances of their own: the others store a row of results once and read no table for it.
+def test_only_kernels_with_token_order_rows_store_rows_twice(listing):
+    for suffix, copies in (("", 1), ("_thw", 2)):
+        seen = set()
+        for sym, body in _kernel_bodies(listing, "attn_h%s_kernel" % suffix):
+            d = int(re.search(r"ILi\d+ELi(\d+)E", sym).group(1))
+            assert body.count("global_store_dwordx2") == copies * d // 8, sym
+            seen.add(sym)
+        assert len(seen) == len(ATTN_H), suffix
+
+
+# The instances that store rows of both orders run the same loops: nothing spilled there, and the registers leave as many wavefronts.
+def test_kernels_with_token_order_rows_keep_their_loops(listing):
+    seen = 0
+    for sym, body in list(_kernel_bodies(listing, "attn_h_thw_kernel")) + list(_kernel_bodies(listing, "attn_32_thw_kernel")):
+        d = int(re.findall(r"Li(\d+)E", sym)["attn_h" in sym])
+        mfmas, limit = (3 * (d // 8), 168 if d == 128 else 128) if "attn_h" in sym else (d // 8, 256 if d == 128 else 128)
+        loop = _step_loop(body, mfmas)
+        assert loop.count("v_mfma") == mfmas and "scratch_" not in loop, sym
+        meta = re.search(r"\.name:\s+%s\n.*?\.vgpr_count:\s+(\d+)" % re.escape(sym), listing, re.S)
+        assert int(meta.group(1)) <= limit, sym
+        seen += 1
+    assert seen == len(ATTN_H) + 2
