@@ -57,8 +57,8 @@ __device__ inline uint32_t pack_bf16x2(float lo, float hi) {
 constexpr int PARAM_QUEUE = 8, QUEUE_USED = 8;
 
 // jenga_forward: rows go to the thw side from the kernel that has them in registers, beside the curve side.  These are instances of
-// their own: as a branch in one kernel for all, small calls that have no such rows took 2 to 4 % longer (30 blocks of 32 x 3 heads,
-// D = 64, 8.8 -> 9.1 us, 20 of 128 x 8, D = 64, 26.0 -> 26.6).
+// their own: as a branch in one kernel for all, small calls that have no such rows took 1 to 4 % longer (attention, 9 blocks of 64 x
+// 3 heads, D = 64, 12.0 -> 12.6 us, 20 of 32 x 3, D = 128, 9.7 -> 10.1).
 // thw: [batch][n_src][heads][D]; first: (batch, head) pair that the launch's first one is.
 struct NoThwRows {};
 struct ThwRows {
@@ -235,11 +235,11 @@ constexpr float P_SUM_MAX = 1073741824.0f;   // 2^30
 // the S and P registers and half the LDS of a step over 128, which lets three workgroups (twelve
 // wavefronts) live on a CU instead of two.
 //
-// Blocks of 64 tokens run the same loop with two wavefronts, at D = 64 one step per block.  At D = 128 steps of 64 keys take 32 KB
-// of LDS, which is given out in pieces of 1280 bytes: four workgroups on a CU, two wavefronts per SIMD, where registers allow three.
-// Steps of 32 keys take half and put six there; their barriers cost a lone workgroup a third more time a block.  Attention, 64 -> 32 keys
-// a step with text rows and the last lists cut for either: 222 blocks x 12 heads (0.41 TFLOP of tiles) 461 -> 430 us, x 24 882 -> 830,
-// 492 x 24 4.50 -> 4.08 ms, 120 x 12 172 -> 148 us, 76 x 8 76 -> 68, 41 x 8 41.6 -> 43.6.
+// Blocks of 64 tokens run the same loop with two wavefronts, one step per block.  At D = 128 that takes 32 KB of LDS, which is given
+// out in pieces of 1280 bytes: four workgroups on a CU, two wavefronts per SIMD, where registers allow three.  Steps of 32 keys
+// (attn_keys32_kernel) take half and put six there; their barriers cost a lone workgroup 1.3 times the time a block (1.2 us ->
+// 1.6), and with all places taken a workgroup needs 3.6 us a block instead of 2.5, so that a text row ends later.  attn_keys32() in
+// jenga_plan.cpp says which calls take them.
 // At D = 64 the softmax, not the matrix core, is the longer part of a step (32 exponentials of 16 cycles and 80 other vector
 // instructions of 4 against 512 cycles of MFMA; 1100 cycles are measured), and four wavefronts per SIMD (128 registers) fit.
 //
@@ -252,8 +252,10 @@ constexpr float P_SUM_MAX = 1073741824.0f;   // 2^30
 // tile reads of the in-order walk, catches more than half of them (measured on the 720p workload).
 // The price: the order, and with it the last bits of the output, can differ from run to run.
 // ---------------------------------------------------------------------------------------------
-template <int BLK, int D>
-constexpr int attn_h_keys() { return BLK == 64 && D == 128 ? 32 : 64; }   // of a step
+template <int FIRST, int N>
+struct Tiles {   // of 32 keys
+  static constexpr int first = FIRST, n = N;
+};
 template <int BLK, int D>
 constexpr int attn_h_min_waves() { return D == 128 ? 3 : 4; }   // wavefronts per SIMD that the registers have to allow
 
@@ -295,19 +297,21 @@ __device__ inline int take_item(uint32_t* queue, int n_end) {
   }
 }
 
-// THW: the kernel's first argument is a ThwRows.
-template <int BLK, int D, bool PACED, bool SPLIT, bool K_ROWS, bool THW>
+// KEYS: of a step.  THW: the kernel's first argument is a ThwRows.
+template <int BLK, int D, int KEYS, bool PACED, bool SPLIT, bool K_ROWS, bool THW>
 __device__ __forceinline__ void attn_h(
     const uint16_t* __restrict__ q, const u32x4* __restrict__ kp, const u32x4* __restrict__ vp,
     const int32_t* __restrict__ sel_count, const int32_t* __restrict__ sel_index,
     uint16_t* __restrict__ out, float* __restrict__ lse, const WorkMap& work, int n_pad, int pad_v, int pad_c,
     float scale_log2e, float bias_log2e, const uint32_t* __restrict__ pace_params, const Split& split, uint32_t* queue) {
-  constexpr int KEYS = attn_h_keys<BLK, D>();   // a step
   constexpr int KS = D / 16, DT = D / 32, PS = BLK / 16, MH = KEYS / 32, PH = KEYS / 16;
   constexpr int NW = BLK / 32, NTHR = 64 * NW, HALVES = BLK / KEYS;   // wavefronts, threads, steps per key block
+  // Sets of keys that a step forms and adds up probabilities in, against a reference that may move between them.  Blocks of 64
+  // tokens at D = 128: sets of 32 keys in either kind of step, so that results are the same bits whichever a call takes.
+  constexpr int SETS = BLK == 64 && D == 128 && KEYS == 64 ? 2 : 1;
   constexpr int TILE_CHUNKS = BLK * D / 8, HALF_CHUNKS = KEYS * D / 8, CPT = HALF_CHUNKS / NTHR;
   static_assert(HALVES >= 1 && (!PACED || HALVES == 2), "the paced walk needs two steps a block");
-  // The current keys: fragments from packed tiles, or (K_ROWS) rows of D channels as they lie in K and V, with the
+  // The keys of the step: fragments from packed tiles, or (K_ROWS) rows of D channels as they lie in K and V, with the
   // 16-byte pieces of a row rotated by an exclusive or on the way.  K: with k_swizzle(row), so that the 16 rows that are
   // read at a time fall on different banks.  V is read by columns, ds_read_b64_tr_b16, which hands a lane 4 keys of its
   // channel: two of them are a fragment, in the key order of the accumulators.  There v_swizzle(row) spreads the 4 rows x
@@ -319,7 +323,7 @@ __device__ __forceinline__ void attn_h(
   // instructions as fragments).  The paced walk keeps packed tiles where it is paced, and so does whoever has packed them already.
   static_assert(!(PACED && K_ROWS) || SPLIT, "only cut lists, which are visited in ascending order");
   __shared__ __align__(256) u32x4 Ks[HALF_CHUNKS];
-  __shared__ __align__(256) u32x4 Vs[HALF_CHUNKS];   // fragments (dt, p2) of the current 64 keys, or rows
+  __shared__ __align__(256) u32x4 Vs[HALF_CHUNKS];   // fragments (dt, p2) of the same keys, or rows
   __shared__ uint32_t rem_bits[PACED ? 64 : 1];   // PACED: bitmap of the blocks still to visit, 32 per word
   __shared__ int pace_slot[2];                    // PACED: G for the next pick, published by thread 0
 
@@ -471,17 +475,18 @@ __device__ __forceinline__ void attn_h(
   const uint32_t ks_lane =
       (uint32_t)(uintptr_t)(const __attribute__((address_space(3))) void*)Ks +
       (K_ROWS ? ql * (2 * D) + (hl ^ k_swizzle(ql)) * 16 : lane * 16);
-  // (m2, ks) = (e & 1, 2 g + e / 2), or (0, 4 g + e) in steps of 32 keys; K_ROWS: piece 2 ks + hl of row 32 m2 + ql
-  auto k_frags = [&](u32x4 (&dst)[4], auto G) {
-    constexpr int g = decltype(G)::value, PER = 4 / MH;   // values of ks in a group
+  // (m2, ks) = (e & 1, 2 g + e / 2) of two tiles, (first, 4 g + e) of one; K_ROWS: piece 2 ks + hl of row 32 m2 + ql
+  auto k_frags = [&](u32x4 (&dst)[4], auto G, auto TILES) {
+    typedef decltype(TILES) T;
+    constexpr int g = decltype(G)::value, PER = 4 / T::n;   // values of ks in a group
     uint32_t at[PER];
     static_for<PER>([&](auto U) {
       constexpr int ks = PER * g + decltype(U)::value;
       at[decltype(U)::value] = K_ROWS && ks > 0 ? xor_here(ks_lane, ks * 32) : ks_lane;
     });
     static_for<4>([&](auto E) {
-      constexpr int e = decltype(E)::value, m2 = e % MH, ks = PER * g + e / MH;
-      lds_frag<K_ROWS ? m2 * 64 * D : (m2 * KS + ks) * 1024>(dst[e], at[e / MH]);
+      constexpr int e = decltype(E)::value, m2 = T::first + e % T::n, ks = PER * g + e / T::n;
+      lds_frag<K_ROWS ? m2 * 64 * D : (m2 * KS + ks) * 1024>(dst[e], at[e / T::n]);
     });
   };
   // K_ROWS: columns 32 dt + 16 (lane / 16 % 2) + lane % 16 of four rows
@@ -508,27 +513,27 @@ __device__ __forceinline__ void attn_h(
     __syncthreads();   // K half of this step is in LDS; every wave is past the previous PV
     v_half_to_lds(j, h);
 
-    // S^T = K Q^T for the 64 keys of this step, with the pad keys of a ragged block set to -inf.  Fragments come in
-    // groups of four, (m2, ks) = (e & 1, 2g + e / 2); group g + 1 is in flight while the MFMAs of group g run, and
-    // the two accumulators alternate.
+    // S^T = K Q^T for tiles of this step's keys, with the pad keys of a ragged block set to -inf.  Fragments come in groups of
+    // four (k_frags); group g + 1 is in flight while the MFMAs of group g run, and the accumulators of two tiles alternate.
     f32x16 S[MH];
     const int nv = BLK - (j == M_v - 1 ? pad_v : (j == M - 1 ? pad_c : 0));
-    auto logits = [&]() {
+    auto logits = [&](auto TILES) {
+      typedef decltype(TILES) T;
 #pragma unroll
-      for (int m2 = 0; m2 < MH; ++m2)
+      for (int m2 = T::first; m2 < T::first + T::n; ++m2)
 #pragma unroll
         for (int r = 0; r < 16; ++r) S[m2][r] = 0.f;
       {
-        constexpr int NG = KS * MH / 4;
+        constexpr int NG = KS * T::n / 4;
         u32x4 A[2][4];
-        k_frags(A[0], std::integral_constant<int, 0>{});
+        k_frags(A[0], std::integral_constant<int, 0>{}, TILES);
         static_for<NG>([&](auto G) {
           constexpr int g = decltype(G)::value;
           lds_wait(A[g & 1]);
           if constexpr (g + 1 < NG)
-            k_frags(A[(g + 1) & 1], std::integral_constant<int, g + 1>{});
+            k_frags(A[(g + 1) & 1], std::integral_constant<int, g + 1>{}, TILES);
           static_for<4>([&](auto E) {
-            constexpr int e = decltype(E)::value, m2 = e % MH, ks = 4 / MH * g + e / MH;
+            constexpr int e = decltype(E)::value, m2 = T::first + e % T::n, ks = 4 / T::n * g + e / T::n;
             S[m2] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(__builtin_bit_cast(bf16x8, A[g & 1][e]), qf[ks], S[m2],
                                                             0, 0, 0);
           });
@@ -539,7 +544,7 @@ __device__ __forceinline__ void attn_h(
         asm volatile("");   // a real, rarely taken branch
         int valid = nv - KEYS * h - 4 * hl;
 #pragma unroll
-        for (int m2 = 0; m2 < MH; ++m2)
+        for (int m2 = T::first; m2 < T::first + T::n; ++m2)
 #pragma unroll
           for (int r = 0; r < 16; ++r) {
             if (r % 4 == 0) asm volatile("" : "+v"(valid));   // four comparisons at a time: 32 masks would be 64 scalar registers
@@ -551,11 +556,12 @@ __device__ __forceinline__ void attn_h(
     // ---- online softmax on S^T (lane = query row, registers = keys) ----
     const float bias = (i < M_v && j >= M_v) ? bias_log2e : 0.f;
     bf16x8 pb[PH];
-    // P = 2^(S * scale + off) as bf16 fragments for the second product; returns this lane's sum of them
-    auto probabilities = [&](float off) {
+    // P = 2^(S * scale + off) of set G as bf16 fragments for the second product; returns this lane's sum of them
+    auto probabilities = [&](float off, auto G) {
+      constexpr int P_SET = PH / SETS, p_first = decltype(G)::value * P_SET;
       float rs0 = 0.f, rs1 = 0.f;
 #pragma unroll
-      for (int p2 = 0; p2 < PH; ++p2) {
+      for (int p2 = p_first; p2 < p_first + P_SET; ++p2) {
         uint32_t w[4];
 #pragma unroll
         for (int e2 = 0; e2 < 4; ++e2) {
@@ -588,37 +594,66 @@ __device__ __forceinline__ void attn_h(
     // path: the logits again, the reference moved to the row maximum (the rescaling step of Alg. 4), and
     // probabilities <= 1 in place of the first attempt.  Each branch forms and consumes its own S, so S never
     // occupies registers beside a finished P.
-    float rs = 0.f;
-    bool in_range = false;
+    typedef std::integral_constant<int, 0> Set0;
+    typedef std::integral_constant<int, SETS - 1> Set1;
+    typedef Tiles<0, MH> All;
+    float rs[SETS], alpha_mid;   // set where they are used: a value from before the products would take a register there
+    bool in_range = false, mid = false;   // mid: O is to be rescaled by alpha_mid between the sets
     const bool first = unset;
     if (!first) {
-      logits();
+      logits(All{});
       advance();
-      rs = probabilities(bias - m_run);
-      in_range = __ballot(!(rs <= P_SUM_MAX)) == 0;
+      rs[0] = probabilities(bias - m_run, Set0{});
+      if constexpr (SETS == 2) rs[1] = probabilities(bias - m_run, Set1{});
+      in_range = __ballot(!((SETS == 2 ? rs[0] + rs[SETS - 1] : rs[0]) <= P_SUM_MAX)) == 0;
     }
     if (!in_range) {
       asm volatile("");   // a real branch: the first step of a row, then almost never
-      logits();
-      if (first) advance();
-      float mx = -INFINITY;
+      // the reference moved to the maximum of a set; returns the factor for what has been added up so far
+      auto move_reference = [&](auto TILES) {
+        typedef decltype(TILES) T;
+        float mx = -INFINITY;
 #pragma unroll
-      for (int m2 = 0; m2 < MH; ++m2)
+        for (int m2 = T::first; m2 < T::first + T::n; ++m2)
 #pragma unroll
-        for (int r = 0; r < 16; ++r) mx = fmaxf(mx, S[m2][r]);
-      mx = max_with_other_half(mx);
-      const float m_new = fmaxf(m_run, fmaf(mx, scale_log2e, bias));
-      const float alpha = m_new == m_run ? 1.0f : __builtin_amdgcn_exp2f(m_run - m_new);
-      l_run *= alpha;
-      m_run = m_new;
+          for (int r = 0; r < 16; ++r) mx = fmaxf(mx, S[m2][r]);
+        mx = max_with_other_half(mx);
+        const float m_new = fmaxf(m_run, fmaf(mx, scale_log2e, bias));
+        const float alpha = m_new == m_run ? 1.0f : __builtin_amdgcn_exp2f(m_run - m_new);
+        l_run *= alpha;
+        m_run = m_new;
+        unset = __ballot(m_run == -INFINITY) != 0;
+        return alpha;
+      };
+      auto finite = [&]() { return m_run == -INFINITY ? 0.f : bias - m_run; };   // every key so far was padding: keep it finite
+      auto rescale = [&](float alpha) {
 #pragma unroll
-      for (int dt = 0; dt < DT; ++dt)
+        for (int dt = 0; dt < DT; ++dt)
 #pragma unroll
-        for (int r = 0; r < 16; ++r) O[dt][r] *= alpha;
-      rs = probabilities(m_run == -INFINITY ? 0.f : bias - m_run);   // every key so far was padding: keep it finite
-      unset = __ballot(m_run == -INFINITY) != 0;
+          for (int r = 0; r < 16; ++r) O[dt][r] *= alpha;
+      };
+      if constexpr (SETS == 1) {
+        logits(All{});
+        if (first) advance();
+        rescale(move_reference(All{}));
+        rs[0] = probabilities(finite(), Set0{});
+      } else {   // one set after the other, and only if it is the one that is out of range
+        logits(Tiles<0, 1>{});
+        if (first) advance();
+        if (first || __ballot(!(rs[0] <= P_SUM_MAX)) != 0) rescale(move_reference(Tiles<0, 1>{}));
+        l_run += probabilities(finite(), Set0{});
+        rs[0] = 0.f;
+        logits(Tiles<1, 1>{});
+        rs[1] = probabilities(finite(), Set1{});
+        mid = unset || __ballot(!(rs[1] <= P_SUM_MAX)) != 0;
+        if (mid) {
+          alpha_mid = move_reference(Tiles<1, 1>{});
+          rs[1] = probabilities(finite(), Set1{});
+        }
+      }
     }
-    l_run += rs;
+    l_run += rs[0];
+    if constexpr (SETS == 2) l_run += rs[1];
 
     wait_vmem();       // this wave's part of the V half has landed
     if (K_ROWS && nv < BLK) {   // pad rows hold anything, and their probabilities are zero
@@ -632,8 +667,7 @@ __device__ __forceinline__ void attn_h(
     __syncthreads();   // V half is in LDS; every wave is done reading the K half
     if (st + 1 < steps) k_half_to_lds(j_next, HALVES == 2 ? (st + 1) & 1 : 0);
 
-    // O^T += V^T P^T, fragments (dt, p2) = (2 (g / 2) + (e & 1), 2 (g % 2) + e / 2), in steps of 32 keys (2 g + (e & 1), e / 2),
-    // pipelined as above
+    // O^T += V^T P^T, fragments (dt, p2) in groups of four, pipelined as above
     {
       constexpr int NG = DT * PH / 4;
       typedef typename std::conditional<K_ROWS, u32x2[2], u32x4>::type Frag;
@@ -650,9 +684,10 @@ __device__ __forceinline__ void attn_h(
           lds_frag<(dt * PH + p2) * 1024>(dst, vs_lane);
         }
       };
-      // of group g
-      auto dt_of = [](int g, int e) { return (PH == 4 ? 2 * (g / 2) : 2 * g) + (e & 1); };
-      auto p2_of = [](int g, int e) { return (PH == 4 ? 2 * (g % 2) : 0) + e / 2; };
+      // of group g: a set after the other, of each two channel tiles at a time
+      constexpr int NG_SET = NG / SETS, RUN = PH / SETS / 2;
+      constexpr auto dt_of = [](int g, int e) { return 2 * (g % NG_SET / RUN) + (e & 1); };
+      constexpr auto p2_of = [](int g, int e) { return g / NG_SET * (PH / SETS) + 2 * (g % RUN) + e / 2; };
       static_for<4>([&](auto E) {
         constexpr int e = decltype(E)::value;
         v_frag(A[0][e], std::integral_constant<int, e & 1>{}, std::integral_constant<int, e / 2>{});
@@ -660,6 +695,15 @@ __device__ __forceinline__ void attn_h(
       static_for<NG>([&](auto G) {
         constexpr int g = decltype(G)::value;
         lds_wait(A[g & 1]);
+        if constexpr (SETS == 2 && g == NG / 2) {   // the first set has been added up
+          if (mid) {
+            asm volatile("");   // a real, rarely taken branch
+#pragma unroll
+            for (int dt = 0; dt < DT; ++dt)
+#pragma unroll
+              for (int r = 0; r < 16; ++r) O[dt][r] *= alpha_mid;
+          }
+        }
         if constexpr (g + 1 < NG)
           static_for<4>([&](auto E) {
             constexpr int e = decltype(E)::value, g1 = g + 1;
@@ -746,11 +790,21 @@ __device__ __forceinline__ void attn_h(
 
 template <int BLK, int D, bool PACED, bool SPLIT, bool K_ROWS>
 __global__ __launch_bounds__(2 * BLK, (attn_h_min_waves<BLK, D>())) void attn_h_kernel(JENGA_ATTN_H_PARAMETERS) {
-  attn_h<BLK, D, PACED, SPLIT, K_ROWS, false>(JENGA_ATTN_H_ARGUMENTS);
+  attn_h<BLK, D, 64, PACED, SPLIT, K_ROWS, false>(JENGA_ATTN_H_ARGUMENTS);
 }
 template <int BLK, int D, bool PACED, bool SPLIT, bool K_ROWS>
 __global__ __launch_bounds__(2 * BLK, (attn_h_min_waves<BLK, D>())) void attn_h_thw_kernel(ThwRows, JENGA_ATTN_H_PARAMETERS) {
-  attn_h<BLK, D, PACED, SPLIT, K_ROWS, true>(JENGA_ATTN_H_ARGUMENTS);
+  attn_h<BLK, D, 64, PACED, SPLIT, K_ROWS, true>(JENGA_ATTN_H_ARGUMENTS);
+}
+
+// Blocks of 64 tokens at D = 128 in steps of 32 keys.  The same bits as in steps of 64.
+template <bool SPLIT, bool K_ROWS>
+__global__ __launch_bounds__(128, (attn_h_min_waves<64, 128>())) void attn_keys32_kernel(JENGA_ATTN_H_PARAMETERS) {
+  attn_h<64, 128, 32, false, SPLIT, K_ROWS, false>(JENGA_ATTN_H_ARGUMENTS);
+}
+template <bool SPLIT, bool K_ROWS>
+__global__ __launch_bounds__(128, (attn_h_min_waves<64, 128>())) void attn_keys32_thw_kernel(ThwRows, JENGA_ATTN_H_PARAMETERS) {
+  attn_h<64, 128, 32, false, SPLIT, K_ROWS, true>(JENGA_ATTN_H_ARGUMENTS);
 }
 
 // merge_kernel: grid (BLK / 32, M, batch * heads) or, with a Deal, (BLK / 32, rows that are cut), one wavefront per channel tile
@@ -1279,12 +1333,22 @@ int run_attention(const jenga_plan* p, const void* q, const void* k, const void*
   } else {
     const bool paced = BLK == 128 && (c.flags & JENGA_FLAG_PACED_WALK);
     const WorkMap work = jenga::plan_work(p, bh);
+    const bool keys32 = jenga::attn_keys32(p, may_split);
     Split split = {};
     uint32_t *queue = may_split ? attn_queue(p, ws) : nullptr, *pace = nullptr;
 #define JENGA_ATTN_H_VALUES \
   qb, kp, vp, sel_count, sel_index, ob, lse, work, f.N_pad, f.pad_v, f.pad_c, scale, bias, pace, split, queue
 #define JENGA_ATTN(PACED, SPLIT, K_ROWS, WGS)                                                                    \
   do {                                                                                                           \
+    if constexpr (BLK == 64 && D == 128) {                                                                       \
+      if (keys32) {                                                                                              \
+        if constexpr (THW)                                                                                       \
+          attn_keys32_thw_kernel<SPLIT, K_ROWS><<<dim3(WGS), 2 * BLK, 0, st>>>(thw_rows, JENGA_ATTN_H_VALUES);   \
+        else                                                                                                     \
+          attn_keys32_kernel<SPLIT, K_ROWS><<<dim3(WGS), 2 * BLK, 0, st>>>(JENGA_ATTN_H_VALUES);                 \
+        break;                                                                                                   \
+      }                                                                                                          \
+    }                                                                                                            \
     if constexpr (THW)                                                                                           \
       attn_h_thw_kernel<BLK, D, PACED, SPLIT, K_ROWS><<<dim3(WGS), 2 * BLK, 0, st>>>(thw_rows, JENGA_ATTN_H_VALUES); \
     else                                                                                                         \

@@ -23,6 +23,7 @@ struct jenga_plan {
   int attn_first;  // > 0: attn_tail lists are cut, and the positions of an XCD behind that many dealt out by counters
   float attn_long; // if a call's vision lists have that many blocks on average
   int attn_text_parts;  // parts that the lists of text query blocks are cut into
+  int attn_len;    // expected blocks of a vision list: K_top and the fixed ones
   int attn_tail;   // lists that are cut, all into attn_parts, at the end of each XCD's
   bool attn_over_kv; // their results lie where packed K would, or packed V: not needed when K and V are read in place
   // bytes of the attention workspace that hold packed K, packed V and launch parameters; parts lie behind them
@@ -50,7 +51,7 @@ void curve_order(int T, int H, int W, bool use_curve, std::vector<int32_t>& perm
 int build_host_tables(jenga_plan* plan);
 
 // Workgroups of the attention kernel for blocks of 64 and 128 tokens that are resident on a CU, by registers and LDS (which is given
-// out in pieces of 1280 bytes).
+// out in pieces of 1280 bytes); 64 tokens at D = 128: in steps of 32 keys, four in steps of 64.
 constexpr int attn_h_per_cu(int block, int head_dim) {
   return block == 64 ? (head_dim == 128 ? 6 : 8) : (head_dim == 128 ? 3 : 4);
 }
@@ -147,6 +148,9 @@ WorkMap plan_work(const jenga_plan* p, int n_bh);
 
 // The positions of a launch for all of them; whole: nothing is cut.
 Deal plan_deal(const jenga_plan* p, const WorkMap& work, bool whole);
+
+// Whether a call takes steps of 32 keys (blocks of 64 tokens, D = 128); may_cut: the call cuts the lists that the plan says.
+bool attn_keys32(const jenga_plan* p, bool may_cut);
 
 // (batch, head) pairs of the plan that one launch with `threads` threads per query block can take.
 int heads_per_launch(const jenga_plan* p, int threads);

@@ -260,6 +260,33 @@ Deal plan_deal(const jenga_plan* p, const WorkMap& work, bool whole) {
   return d;
 }
 
+// Blocks of 64 tokens at D = 128, steps of 32 keys or of 64: six workgroups a CU or four, each slower (attn_h in jenga_attn.hip).  Up to
+// 1024 workgroups all are resident in either kind, and those of 64 keys end first; up to 1536 only those of 32 do without a second
+// generation; up to 2048 those of 64 have two full ones; from there on the matrix cores are busier with six.  A text row that stays
+// whole ends after the others where it has more than 1.5 times the blocks that a place works off in the launch, and then it counts how
+// fast one workgroup is.  Attention, 64 -> 32 keys a step, k = 0.25:
+//   up to 1024:  41 blocks x 8 heads 38.1 -> 41.5 us, 84 x 10 72 -> 78, 300 x 3 248 -> 285, no text 40 x 24 34.0 -> 35.4, 100 x 10 67 -> 70
+//   up to 1536:  no text 62 x 20 68 -> 59, 120 x 12 137 -> 115; text rows cut 30 x 40 50.5 -> 44.8, 120 x 9 119 -> 104, 160 x 9 184 -> 153
+//   up to 2048:  no text 62 x 28 84 -> 88, 92 x 18 113 -> 118, 40 x 40 60 -> 63; 90 x 20, k = 0.7, 283 -> 297
+//   above:       no text 62 x 40 115 -> 108, 120 x 20 196 -> 182, 222 x 16 478 -> 463; 62 x 60 178 -> 171, 222 x 24 776 -> 735, 492 x 24
+//                4.41 -> 4.05 ms, text rows cut 222 x 12 402 -> 387
+//   text rows whole (packed entry, short text rows, uneven lists): 120 x 12 packed 171 -> 221, 222 x 12 packed 392 -> 464, 62 x 32 106 ->
+//                130, 92 x 24 151 -> 187, 222 x 40 at k = 0.05 440 -> 583, 138 x 10 at p = 0.9 209 -> 264
+// Lists that p decides about are taken at the K_top that they have at least; without text rows they pay from 3072 workgroups on (92 x 24,
+// p = 0.9, 175 -> 183; 222 x 12 473 -> 483; 222 x 24 862 -> 841, 222 x 40 1141 -> 1073).
+bool attn_keys32(const jenga_plan* p, bool may_cut) {
+  const jenga_config& c = p->cfg;
+  const jenga_plan_info_t& f = p->info;
+  if (c.block != 64 || c.head_dim != 128) return false;
+  const long long bh = (long long)c.batch * c.heads, rows = bh * f.M;
+  const bool text_cut = may_cut && p->attn_text_parts > 1, uneven = c.cum_prob > 2.0 * c.topk_ratio;
+  const long long wgs = rows + (text_cut ? bh * f.M_c * (p->attn_text_parts - 1) : 0);
+  if (wgs <= 1024) return false;
+  if (f.M_c > 0 && !text_cut && 2 * 1536 * (long long)f.M > 3 * rows * p->attn_len) return false;
+  if (may_cut && !uneven && p->attn_tail > 0) return true;
+  return wgs <= 1536 || wgs > (uneven ? 3072 : 2048);
+}
+
 static void split_lists(jenga_plan* plan) {
   const jenga_config& c = plan->cfg;
   const jenga_plan_info_t& f = plan->info;
@@ -274,6 +301,7 @@ static void split_lists(jenga_plan* plan) {
   long long fixed = 0;
   for (uint64_t w : plan->fixed_bits) fixed += __builtin_popcountll(w);
   const long long len = std::min<long long>(f.M, f.K_top + (fixed + f.M_v - 1) / f.M_v);
+  plan->attn_len = (int)len;
   if (c.block == 32) {
     const long long bytes = 4ll * f.N_pad * c.head_dim;   // K and V of a head
     const int parts = bytes >= 12 << 20 ? 3 : bytes >= 6 << 20 ? 2 : 1;

@@ -9,7 +9,8 @@
 // With the argument "deal" and optionally the flags of all plans the lines are the same configurations; a launch's positions are
 // gone through as the kernel does, then the rows of its merge: every row has to be written once, from slots that hold its parts.
 // The output is: parts of a text list, lists cut at the end, the parts dealt out least and most often, slots used and slots there
-// are, positions of an XCD that its counter does not deal out, bytes of the workspace beside packed K and V.
+// are, positions of an XCD that its counter does not deal out, bytes of the workspace beside packed K and V.  With the argument "keys"
+// the output is whether attention takes steps of 32 keys in a call that cuts lists and in one that does not.
 #include <algorithm>
 #include <cstdio>
 #include <cstdlib>
@@ -106,7 +107,21 @@ static int deal(unsigned flags) {
   return 0;
 }
 
+static int keys() {
+  jenga_plan p = {};
+  jenga_config& c = p.cfg;
+  c.flags = 7;
+  while (std::scanf("%d %d %d %d %d %d %d %d %lf %lf", &c.T, &c.H, &c.W, &c.n_text, &c.batch, &c.heads, &c.head_dim,
+                    &c.block, &c.topk_ratio, &c.cum_prob) == 10) {
+    int why = 0;
+    if (!jenga::config_ok(c, &why) || jenga::build_host_tables(&p) != JENGA_OK) return 1;
+    std::printf("%d %d\n", (int)jenga::attn_keys32(&p, true), (int)jenga::attn_keys32(&p, false));
+  }
+  return 0;
+}
+
 int main(int argc, char** argv) {
+  if (argc > 1 && std::strcmp(argv[1], "keys") == 0) return keys();
   if (argc > 1 && std::strcmp(argv[1], "deal") == 0) return deal(argc > 2 ? (unsigned)std::atoi(argv[2]) : 0u);
   if (argc > 1 && std::strcmp(argv[1], "work") == 0) return work();
   if (argc > 1 && std::strcmp(argv[1], "switch") == 0) return stage_switch();

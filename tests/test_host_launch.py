@@ -111,6 +111,24 @@ def test_parts_of_text_rows_are_bounded(driver, flags):
     assert cut > 0
 
 
+# Blocks of 64 tokens at head dim 128 take steps of 32 keys only where the chip is full of them and no whole text row runs on alone: in
+# a call that may cut lists, and in the packed entry, which cuts nothing.
+@pytest.mark.parametrize("blocks,heads,text,topk,p,cuts,whole", [
+    (8, 2, 1, 0.25, 0.3, 0, 0), (41, 8, 1, 0.25, 0.3, 0, 0), (84, 10, 1, 0.25, 0.3, 0, 0), (40, 24, 0, 0.25, 0.3, 0, 0),
+    (62, 20, 0, 0.25, 0.3, 1, 1), (120, 12, 0, 0.25, 0.3, 1, 1), (120, 12, 1, 0.25, 0.3, 1, 0), (30, 40, 1, 0.25, 0.3, 1, 0),
+    (40, 40, 0, 0.25, 0.3, 0, 0), (62, 28, 0, 0.25, 0.3, 0, 0), (120, 14, 0, 0.25, 0.3, 1, 0), (62, 40, 0, 0.25, 0.3, 1, 1),
+    (62, 24, 1, 0.1, 0.3, 0, 0), (62, 32, 1, 0.25, 0.3, 0, 0), (92, 24, 1, 0.25, 0.3, 0, 0), (222, 40, 2, 0.05, 0.3, 0, 0),
+    (222, 8, 2, 0.25, 0.3, 1, 0), (222, 12, 2, 0.25, 0.3, 1, 0), (222, 24, 2, 0.25, 0.3, 1, 1), (492, 24, 4, 0.3, 0.3, 1, 1),
+    (40, 40, 1, 0.25, 0.9, 0, 0), (138, 10, 1, 0.25, 0.9, 0, 0), (150, 12, 1, 0.1, 0.5, 0, 0), (222, 12, 1, 0.25, 0.9, 0, 0),
+    (222, 12, 0, 0.25, 0.9, 0, 0), (222, 24, 2, 0.25, 0.9, 1, 1), (700, 12, 4, 0.1, 0.9, 0, 0)])
+def test_steps_of_32_keys(driver, blocks, heads, text, topk, p, cuts, whole):
+    row = (1, 1, 64 * (blocks - text) - 3, 64 * text, 1, heads, 128, 64, topk, p)
+    assert _run(driver, [row], "keys") == [[str(cuts), str(whole)]]
+    for head_dim, block in ((64, 64), (128, 128), (64, 128), (128, 32)):
+        assert _run(driver, [(1, 1, block * (blocks - text) - 3, 64 * text, 1, heads, head_dim, block, topk, p)],
+                    "keys") == [["0", "0"]]
+
+
 # Planes of a stage switch: 2^24 of them are more than one grid takes with a workgroup each.
 def test_stage_switch_launches_stay_below_the_grid_limit(driver):
     rows = [(channels, t, h, w, t, h, w, 1) for channels in (1, 16, 1 << 20, (1 << 24) - 1, 1 << 24, (1 << 31) - 1)
