@@ -225,8 +225,8 @@ int heads_per_launch(const jenga_plan* p, int threads) {
 // The plan goes by an expected length: K_top and the fixed blocks, or p^2 of all blocks where the cumulative rule decides, an estimate
 // for low-frequency activations (their lists hold 0.76 to 0.81 of all blocks at p = 0.9, 0.26 at 0.45, 0.21 to 0.37 at 0.5).  Whether
 // lists are dealt out by counters and cut at the end the lists of the call then decide (list_lengths_kernel).
-// The first generation is the resident workgroups; of 64 tokens at D = 128 four a CU of the six, the others ask the counter (with all six
-// 0.5 to 0.8 % less on 222 x 24 and x 40, p = 0.9, and with that half a generation cut 2 % more on x 12).
+// The first generation is the resident workgroups; of 64 tokens at D = 128 the four a CU of steps of 64 keys, also where steps of 32 leave
+// room for six (then the others ask the counter: with all six 0.5 to 0.8 % less on 222 x 24 and x 40, p = 0.9).
 // What remains is the last generation, which runs out over the time of one workgroup.  There half a generation of lists is
 // cut, into two: 1 to 3 % less from two generations on, but below two, where this reaches into the first one, up to
 // 5 % more (1416 query blocks at D = 128 601 -> 633 us).  Lists of uneven length (p well above k) into three, whatever the
@@ -242,12 +242,18 @@ int heads_per_launch(const jenga_plan* p, int threads) {
 // head at k = 0.1 1401 -> 1270; 38 shapes 3 % less on average, none above 1 % more.  A text row has to last 400 us for it, beyond
 // one generation: with 920 query blocks of 128, 23 a head (145 us), a layer took 241 whole and 250 us cut, 888, 37 a head 211 and 215.
 //
-// Even lists of blocks of 64 tokens at D = 128 (six workgroups a CU, 2.2 us a block then, 1.8 alone): a text row lasts as long as the launch sooner than
-// that, and with one to two generations a cut of 64 lists per XCD at the end evens out how many workgroups the CUs are left with, without
+// Even lists of blocks of 64 tokens at D = 128 that take steps of 32 keys (attn_keys32): a text row lasts as long as the launch sooner,
+// and with one to two generations a cut of 64 lists per XCD at the end evens out how many workgroups the CUs are left with, without
 // counters.  It pays where no text row is left whole.  Attention, whole -> text rows cut -> lists at the end too, k = 0.25: 222 blocks x 12 heads
-// 486 -> 439 -> 426 us, x 8 416 -> 332 -> 297, 121 x 16 252 -> 222 -> 208, x 13 247 -> 200 -> 175, x 20 271 -> 261 -> 258; text rows whole, 121 x 24
-// 298 -> 307, 92 x 24 204 -> 218.  No text: 120 x 14 203 -> 186, x 20 245 -> 253.  Lists of 24 blocks: 62 x 32 136 -> 152.  From 2.3 generations
-// on nothing changes (222 x 16, x 24).  Text rows of 200 us: 92 x 24 204 -> 206; 62 x 32 (136 us) 137 -> 141. 
+// 486 -> 439 -> 426 us, x 8 416 -> 332 -> 297, 121 x 16 252 -> 222 -> 208, x 13 247 -> 200 -> 175, x 20 271 -> 261 -> 258.  No text: 120 x 14
+// 203 -> 186, x 20 245 -> 253.  Lists of 24 blocks: 62 x 32 136 -> 152.  From 2.3 generations on nothing changes (222 x 16, x 24).
+// Text rows of less than 110 blocks: 92 x 24 204 -> 206; 62 x 32 137 -> 141.
+// The parts of text rows are what a call with short lists of its own waits for: alone on a CU a block takes 1.3 times as long in
+// these steps (1.6 us), so there are a third more parts than above, as far as one generation takes them, and two where text rows would
+// stay whole.  Lists of 1 to 4 blocks, steps of 64 keys / of 32 without this / with it: 222 x 8 103 / 108 / 92 us, 120 x 9 49 / 61 / 52,
+// 300 x 5 105 / 136 / 114, 222 x 16 at k = 0.1 126 / 159 / 134, 222 x 24 318 / 470 / 258, 492 x 24 778 / 1194 / 659; 160 x 9, whose generation
+// is full, 64 / 81 / 81.  Selected lists are the same to 1 % (120 x 9 102.7 -> 102.9, 222 x 24 716 -> 717, 300 x 16 846 -> 838, 110 x 15
+// 122.7 -> 125.1); whole text rows of less than 150 blocks lose 2 % (62 x 60, 92 x 40) and stay whole.
 constexpr uint64_t RANGE_AREA_BYTES = 128ull << 20;
 
 Deal plan_deal(const jenga_plan* p, const WorkMap& work, bool whole) {
@@ -316,12 +322,14 @@ static void split_lists(jenga_plan* plan) {
     return;
   }
   const bool b64_d128 = c.block == 64 && c.head_dim == 128, uneven = c.cum_prob > 2.0 * c.topk_ratio, fine_even = b64_d128 && !uneven;
-  const long long cut_places = 256ll * (b64_d128 ? 5 : attn_h_per_cu(c.block, c.head_dim));   // what short grids' lists are cut by
+  // What the lists of short grids and uneven ones are cut by.  Five a CU of 64 tokens at D = 128, which take steps of 64 keys there and have
+  // four: the rules were measured with it.
+  const long long cut_places = 256ll * (b64_d128 ? 5 : attn_h_per_cu(c.block, c.head_dim));
   const long long places = fine_even ? 256ll * attn_h_per_cu(c.block, c.head_dim) : cut_places;
   if (4 * rows >= 3 * cut_places) {
     const WorkMap work = plan_work(plan, c.batch * c.heads);
     const double usual = std::max((double)len, c.cum_prob * c.cum_prob * f.M), gens = (double)rows / places;
-    const double block_us = c.block == 128 ? (c.head_dim == 128 ? 6.3 : 3.6) : (c.head_dim == 128 ? (uneven ? 2.6 : 2.2) : 1.8);
+    const double block_us = c.block == 128 ? (c.head_dim == 128 ? 6.3 : 3.6) : (c.head_dim == 128 ? 2.6 : 1.8);
     const long long text_rows = (long long)c.batch * c.heads * f.M_c;
     const double long_list = (c.head_dim == 128 ? 200.0 : 320.0) / block_us;
     if (rows > places && (c.block == 128 || uneven) && usual >= long_list) {
@@ -354,17 +362,22 @@ static void split_lists(jenga_plan* plan) {
           plan->attn_text_parts = parts;
         }
       }
-    } else if (f.M * block_us >= (fine_even ? 240.0 : 400.0) && f.M > (gens < 1.5 ? 1.15 : fine_even ? 1.55 : 1.8) * gens * usual) {
+    } else if ((fine_even ? f.M >= 110 : f.M * block_us >= 400.0) && f.M > (gens < 1.5 ? 1.15 : fine_even ? 1.55 : 1.8) * gens * usual) {
       plan->attn_text_parts = std::max(1, std::min(most, (int)std::ceil(f.M / (gens * usual))));
     }
+    if (plan->attn_first == 0 && text_rows > 0 && plan->attn_text_parts == 1) {
+      plan->attn_tail = 0;
+      plan->attn_parts = 1;
+    }
+    if (f.M >= 110 && text_rows > 0 && attn_keys32(plan, true)) {
+      const int parts = plan->attn_text_parts, more = parts > 1 ? parts + (parts + 1) / 3 : f.M >= 150 ? 2 : 1;
+      plan->attn_text_parts = std::max(parts, std::min(most, more));
+      while (gens <= 1.0 && plan->attn_text_parts > parts && 8ll * plan_deal(plan, work, false).positions() > places)
+        --plan->attn_text_parts;
+    }
     if (plan->attn_tail > 0 && plan->attn_first == 0) {
-      if (text_rows > 0 && plan->attn_text_parts == 1) {
-        plan->attn_tail = 0;
-        plan->attn_parts = 1;
-      } else {
-        plan->attn_long = 28.f;
-        plan->attn_first = plan_deal(plan, work, false).positions();   // all of them: no counter is asked
-      }
+      plan->attn_long = 28.f;
+      plan->attn_first = plan_deal(plan, work, false).positions();   // all of them: no counter is asked
     }
     return;
   }

@@ -129,6 +129,16 @@ def test_steps_of_32_keys(driver, blocks, heads, text, topk, p, cuts, whole):
                     "keys") == [["0", "0"]]
 
 
+# Text rows of such calls are cut into parts that a call with short lists of its own does not wait for: no longer than they were in steps
+# of 64 keys, which take three quarters of the time a block, where one generation has room for them.
+@pytest.mark.parametrize("blocks,heads,text,topk,parts", [
+    (120, 9, 1, 0.25, 5), (222, 8, 2, 0.25, 5), (222, 12, 2, 0.25, 4), (300, 5, 1, 0.25, 5), (222, 16, 2, 0.1, 4), (160, 9, 2, 0.25, 4),
+    (222, 24, 2, 0.25, 2), (492, 24, 4, 0.3, 2), (62, 60, 1, 0.25, 1), (120, 13, 1, 0.1, 1)])
+def test_parts_of_text_rows_in_steps_of_32_keys(driver, blocks, heads, text, topk, parts):
+    row = (1, 1, 64 * (blocks - text) - 3, 64 * text, 1, heads, 128, 64, topk, 0.3)
+    assert int(_run(driver, [row], "deal", "7")[0][0]) == parts
+
+
 # Planes of a stage switch: 2^24 of them are more than one grid takes with a workgroup each.
 def test_stage_switch_launches_stay_below_the_grid_limit(driver):
     rows = [(channels, t, h, w, t, h, w, 1) for channels in (1, 16, 1 << 20, (1 << 24) - 1, 1 << 24, (1 << 31) - 1)
