@@ -266,7 +266,7 @@ struct Split {
   int parts, chunk;   // most parts of a list, list entries from which on there is one more part (0: always all parts)
   int stride;         // workgroups per part
   jenga::Deal deal;   // if deal.parts > 0
-  int first;          // with a queue: positions of an XCD that it does not deal out
+  int first;          // with a queue: positions of an XCD that it does not deal out (all, where the plan has no counters)
   float* o;           // [slot][BLK/32][D/32][4][64][4]: O in accumulator order
   float* stat;        // [slot][2][BLK]: reference, sum; slot = (batch*head*M + block) * parts + part, or by deal_position()
   __device__ int of(int cnt) const { return chunk == 0 ? parts : max(1, min(parts, (cnt + chunk - 1) / chunk)); }
@@ -1254,9 +1254,10 @@ __global__ __launch_bounds__(256) void copy_kernel(const uint4* __restrict__ src
   for (size_t t = (size_t)blockIdx.x * 256 + threadIdx.x; t < n; t += (size_t)gridDim.x * 256) dst[t] = src[t];
 }
 
-// Counters of a launch that deals its query blocks out as workgroups become free; nullptr where the plan has none.
+// Counters of a launch that deals its query blocks out as workgroups become free, and whether the call's lists are long (QUEUE_USED);
+// nullptr where the plan does not ask.
 uint32_t* attn_queue(const jenga_plan* p, void* ws) {
-  return p->attn_first > 0 ? (uint32_t*)((char*)ws + p->packed_bytes - 256) + PARAM_QUEUE : nullptr;
+  return p->attn_long > 0.f ? (uint32_t*)((char*)ws + p->packed_bytes - 256) + PARAM_QUEUE : nullptr;
 }
 
 template <int BLK, int D>
@@ -1354,13 +1355,13 @@ int run_attention(const jenga_plan* p, const void* q, const void* k, const void*
     else                                                                                                         \
       attn_h_kernel<BLK, D, PACED, SPLIT, K_ROWS><<<dim3(WGS), 2 * BLK, 0, st>>>(JENGA_ATTN_H_VALUES);            \
   } while (0)
-    if (paced && !(may_split && p->attn_first == 0 && p->attn_parts > 1)) pace = params;   // parts of short grids: ascending order
+    if (paced && !(may_split && p->attn_long == 0.f && p->attn_parts > 1)) pace = params;   // parts of short grids: ascending order
     if (pace != nullptr || queue != nullptr) {
       // a workgroup spends about 6.3 us (D = 128; 3.6 us at D = 64) on a block of 128 keys when three share a CU
       list_lengths_kernel<<<1, 1024, 0, st>>>(sel_count, bh * f.M, f.M, f.M_v, D == 128 ? 630.f : 360.f, params, queue,
                                               p->attn_first, p->attn_long);
     }
-    const bool dealt = p->attn_first > 0 || p->attn_text_parts > 1;
+    const bool dealt = p->attn_long > 0.f || p->attn_text_parts > 1;
     if (may_split && (dealt || p->attn_parts > 1)) {
       int wgs, slots;
       dim3 merge;
@@ -1369,9 +1370,9 @@ int run_attention(const jenga_plan* p, const void* q, const void* k, const void*
         if (p->attn_over_kv) split.o = (float*)(k == (const void*)ws ? (char*)ws + half : (char*)ws);
         // where both K and V are packed there all the same, lists stay whole
         split.deal = jenga::plan_deal(p, work, p->attn_over_kv && !k_rows);
-        split.first = p->attn_first;
         wgs = 8 * split.deal.positions();
-        if (queue != nullptr && split.first < split.deal.positions()) wgs += (wgs + 3) / 4;
+        split.first = p->attn_first > 0 ? p->attn_first : split.deal.positions();
+        if (p->attn_first > 0) wgs += (wgs + 3) / 4;
         slots = split.deal.slots();
         merge = dim3(BLK / 32, split.deal.text_rows() + split.deal.tail_rows(), 1);
       } else {

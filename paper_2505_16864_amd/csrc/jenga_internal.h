@@ -20,8 +20,8 @@ struct jenga_plan {
   // attn_chunk = 0: every list into attn_parts ranges of key blocks
   int attn_parts, attn_chunk;
   int attn_heads;  // (batch, head) pairs per launch where lists are cut
-  int attn_first;  // > 0: attn_tail lists are cut, and the positions of an XCD behind that many dealt out by counters
-  float attn_long; // if a call's vision lists have that many blocks on average
+  float attn_long; // > 0: attn_tail lists are cut if the call's vision lists have that many blocks on average
+  int attn_first;  // > 0: then the positions of an XCD behind that many are dealt out by counters too
   int attn_text_parts;  // parts that the lists of text query blocks are cut into
   int attn_len;    // expected blocks of a vision list: K_top and the fixed ones
   int attn_tail;   // lists that are cut, all into attn_parts, at the end of each XCD's

@@ -375,10 +375,7 @@ static void split_lists(jenga_plan* plan) {
       while (gens <= 1.0 && plan->attn_text_parts > parts && 8ll * plan_deal(plan, work, false).positions() > places)
         --plan->attn_text_parts;
     }
-    if (plan->attn_tail > 0 && plan->attn_first == 0) {
-      plan->attn_long = 28.f;
-      plan->attn_first = plan_deal(plan, work, false).positions();   // all of them: no counter is asked
-    }
+    if (plan->attn_tail > 0 && plan->attn_first == 0) plan->attn_long = 28.f;
     return;
   }
   const long long shortest = (rows <= 256 ? 6 : 24) * 64 / c.block;
@@ -396,7 +393,7 @@ static void split_lists(jenga_plan* plan) {
 // as much as the packing.
 bool reads_kv_in_place(const jenga_plan* p) {
   if (p->cfg.block == 32) return p->cfg.head_dim == 64 && p->info.M <= 24 && p->cfg.batch * p->cfg.heads * p->info.M <= 256;
-  const bool short_grid = p->attn_first == 0 && p->attn_text_parts == 1 && p->attn_parts > 1;
+  const bool short_grid = p->attn_long == 0.f && p->attn_text_parts == 1 && p->attn_parts > 1;
   return p->cfg.block == 64 || !(p->cfg.flags & JENGA_FLAG_PACED_WALK) || short_grid;
 }
 
@@ -469,7 +466,7 @@ int build_host_tables(jenga_plan* plan) {
   f.attn_workspace_bytes = plan->packed_bytes;
   split_lists(plan);
   // and, where lists are cut, O and two statistics per row and part, float32
-  const bool dealt = plan->attn_first > 0 || plan->attn_text_parts > 1;
+  const bool dealt = plan->attn_long > 0.f || plan->attn_text_parts > 1;
   const uint64_t slots = dealt                  ? plan_deal(plan, plan_work(plan, (int)bh), false).slots()
                          : plan->attn_parts > 1 ? (uint64_t)plan->attn_heads * f.M * plan->attn_parts
                                                 : 0;
