@@ -251,7 +251,7 @@ int heads_per_launch(const jenga_plan* p, int threads) {
 // The parts of text rows are what a call with short lists of its own waits for: alone on a CU a block takes 1.3 times as long in
 // these steps (1.6 us), so there are a third more parts than above, as far as one generation takes them, and two where text rows would
 // stay whole.  Lists of 1 to 4 blocks, steps of 64 keys / of 32 without this / with it: 222 x 8 103 / 108 / 92 us, 120 x 9 49 / 61 / 52,
-// 300 x 5 105 / 136 / 114, 222 x 16 at k = 0.1 126 / 159 / 134, 222 x 24 318 / 470 / 258, 492 x 24 778 / 1194 / 659; 160 x 9, whose generation
+// 300 x 5 105 / 136 / 114, 222 x 24 318 / 470 / 258, 492 x 24 778 / 1194 / 659; 160 x 9, whose generation
 // is full, 64 / 81 / 81.  Selected lists are the same to 1 % (120 x 9 102.7 -> 102.9, 222 x 24 716 -> 717, 300 x 16 846 -> 838, 110 x 15
 // 122.7 -> 125.1); whole text rows of less than 150 blocks lose 2 % (62 x 60, 92 x 40) and stay whole.
 constexpr uint64_t RANGE_AREA_BYTES = 128ull << 20;
@@ -269,28 +269,47 @@ Deal plan_deal(const jenga_plan* p, const WorkMap& work, bool whole) {
 // Blocks of 64 tokens at D = 128, steps of 32 keys or of 64: six workgroups a CU or four, each slower (attn_h in jenga_attn.hip).  Up to
 // 1024 workgroups all are resident in either kind, and those of 64 keys end first; up to 1536 only those of 32 do without a second
 // generation; up to 2048 those of 64 have two full ones; from there on the matrix cores are busier with six.  A text row that stays
-// whole ends after the others where it has more than 1.5 times the blocks that a place works off in the launch, and then it counts how
-// fast one workgroup is.  Attention, 64 -> 32 keys a step, k = 0.25:
+// whole ends after the others where it has more than 1.5 times the blocks that a place works off in the launch (in one generation 2.2
+// times the blocks of a list), and then it counts how fast one workgroup is.  Attention, 64 -> 32 keys a step, k = 0.25:
 //   up to 1024:  41 blocks x 8 heads 38.1 -> 41.5 us, 84 x 10 72 -> 78, 300 x 3 248 -> 285, no text 40 x 24 34.0 -> 35.4, 100 x 10 67 -> 70
-//   up to 1536:  no text 62 x 20 68 -> 59, 120 x 12 137 -> 115; text rows cut 30 x 40 50.5 -> 44.8, 120 x 9 119 -> 104, 160 x 9 184 -> 153
+//   up to 1536:  lists cut into parts 120 x 6 106 -> 103, 305 x 2 218 -> 200, 369 x 2 326 -> 298, 71 x 3 42.3 -> 39.6; no text 62 x 20 68 -> 59, 120 x 12 137 -> 115; text rows cut 30 x 40 50.5 -> 44.8, 120 x 9 119 -> 104, 160 x 9 184 -> 153
 //   up to 2048:  no text 62 x 28 84 -> 88, 92 x 18 113 -> 118, 40 x 40 60 -> 63; 90 x 20, k = 0.7, 283 -> 297
 //   above:       no text 62 x 40 115 -> 108, 120 x 20 196 -> 182, 222 x 16 478 -> 463; 62 x 60 178 -> 171, 222 x 24 776 -> 735, 492 x 24
 //                4.41 -> 4.05 ms, text rows cut 222 x 12 402 -> 387
 //   text rows whole (packed entry, short text rows, uneven lists): 120 x 12 packed 171 -> 221, 222 x 12 packed 392 -> 464, 62 x 32 106 ->
 //                130, 92 x 24 151 -> 187, 222 x 40 at k = 0.05 440 -> 583, 138 x 10 at p = 0.9 209 -> 264
-// Lists that p decides about are taken at the K_top that they have at least; without text rows they pay from 3072 workgroups on (92 x 24,
-// p = 0.9, 175 -> 183; 222 x 12 473 -> 483; 222 x 24 862 -> 841, 222 x 40 1141 -> 1073).
+// Lists that p decides about are taken at the K_top that they have at least, from p = 0.7 on and in one generation at the p^2 of all blocks that
+// they are expected to have (98 x 12, p = 0.9, packed, 298 -> 261; lists of 0.28 of the blocks all the same 138 x 10 209 -> 264).  Their
+// heads are spread over all XCDs (plan_work), and with more than one generation six workgroups a CU then read more of a head's tiles
+// past the L2 than four do, except where a list holds most blocks of a head of up to 8 MB.  64 -> 32 keys: p = 0.3, k = 0.1, 220 x 40
+// 1319 -> 1456 us, 94 x 40 328 -> 366; p = 0.5 440 x 24 4.28 -> 4.58 ms; p = 0.7 444 x 24 6.78 -> 7.15, 220 x 24 1.96 -> 1.93; p = 0.9 96 x 40
+// 921 -> 874 us, 222 x 24 2.61 -> 2.44 ms, 304 x 24 4.76 -> 4.67, 319 x 12 2.36 -> 2.60, 444 x 24 9.75 -> 10.05; one generation: p = 0.3
+// 94 x 16 154 -> 135 us, p = 0.5 220 x 6 413 -> 374.
 bool attn_keys32(const jenga_plan* p, bool may_cut) {
   const jenga_config& c = p->cfg;
   const jenga_plan_info_t& f = p->info;
   if (c.block != 64 || c.head_dim != 128) return false;
   const long long bh = (long long)c.batch * c.heads, rows = bh * f.M;
-  const bool text_cut = may_cut && p->attn_text_parts > 1, uneven = c.cum_prob > 2.0 * c.topk_ratio;
-  const long long wgs = rows + (text_cut ? bh * f.M_c * (p->attn_text_parts - 1) : 0);
-  if (wgs <= 1024) return false;
-  if (f.M_c > 0 && !text_cut && 2 * 1536 * (long long)f.M > 3 * rows * p->attn_len) return false;
+  const bool short_grid = p->attn_long == 0.f && p->attn_text_parts == 1 && p->attn_parts > 1;   // all lists are cut
+  const bool text_cut = may_cut && (short_grid || p->attn_text_parts > 1), uneven = c.cum_prob > 2.0 * c.topk_ratio;
+  const double usual = std::max((double)p->attn_len, c.cum_prob * c.cum_prob * f.M);
+  long long wgs = rows, resident = 1024;
+  if (may_cut && short_grid) {
+    auto parts = [&](double len) { return std::max(1ll, std::min<long long>(p->attn_parts, (long long)std::ceil(len / p->attn_chunk))); };
+    wgs = bh * (f.M_v * parts(usual) + f.M_c * parts(f.M));
+    if (parts(usual) > 1) resident = 900;   // expected workgroups; those of the longer lists come on top
+  } else if (text_cut) {
+    wgs += bh * f.M_c * (p->attn_text_parts - 1);
+  }
+  if (wgs <= resident) return false;
+  const bool dense = c.cum_prob >= 0.7;
+  if (f.M_c > 0 && !text_cut) {
+    const double blocks = wgs <= 1536 ? 2.2 * (dense ? usual : p->attn_len) : 1.5 * rows / 1536 * p->attn_len;
+    if (f.M > blocks) return false;
+  }
   if (may_cut && !uneven && p->attn_tail > 0) return true;
-  return wgs <= 1536 || wgs > (uneven ? 3072 : 2048);
+  if (wgs > 1536 && uneven && (!dense || 4ll * f.N_pad * c.head_dim > 8 << 20)) return false;
+  return wgs <= 1536 || wgs > 2048;
 }
 
 static void split_lists(jenga_plan* plan) {

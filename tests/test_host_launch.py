@@ -114,13 +114,15 @@ def test_parts_of_text_rows_are_bounded(driver, flags):
 # Blocks of 64 tokens at head dim 128 take steps of 32 keys only where the chip is full of them and no whole text row runs on alone: in
 # a call that may cut lists, and in the packed entry, which cuts nothing.
 @pytest.mark.parametrize("blocks,heads,text,topk,p,cuts,whole", [
-    (8, 2, 1, 0.25, 0.3, 0, 0), (41, 8, 1, 0.25, 0.3, 0, 0), (84, 10, 1, 0.25, 0.3, 0, 0), (40, 24, 0, 0.25, 0.3, 0, 0),
+    (8, 2, 1, 0.25, 0.3, 0, 0), (41, 8, 1, 0.25, 0.3, 0, 0), (84, 10, 1, 0.25, 0.3, 0, 0), (150, 6, 1, 0.25, 0.3, 0, 0),
+    (145, 2, 2, 0.25, 0.3, 0, 0), (120, 6, 1, 0.25, 0.3, 1, 0), (305, 2, 0, 0.3, 0.5, 1, 0), (76, 6, 1, 0.2, 0.9, 1, 0), (40, 24, 0, 0.25, 0.3, 0, 0),
     (62, 20, 0, 0.25, 0.3, 1, 1), (120, 12, 0, 0.25, 0.3, 1, 1), (120, 12, 1, 0.25, 0.3, 1, 0), (30, 40, 1, 0.25, 0.3, 1, 0),
     (40, 40, 0, 0.25, 0.3, 0, 0), (62, 28, 0, 0.25, 0.3, 0, 0), (120, 14, 0, 0.25, 0.3, 1, 0), (62, 40, 0, 0.25, 0.3, 1, 1),
     (62, 24, 1, 0.1, 0.3, 0, 0), (62, 32, 1, 0.25, 0.3, 0, 0), (92, 24, 1, 0.25, 0.3, 0, 0), (222, 40, 2, 0.05, 0.3, 0, 0),
     (222, 8, 2, 0.25, 0.3, 1, 0), (222, 12, 2, 0.25, 0.3, 1, 0), (222, 24, 2, 0.25, 0.3, 1, 1), (492, 24, 4, 0.3, 0.3, 1, 1),
-    (40, 40, 1, 0.25, 0.9, 0, 0), (138, 10, 1, 0.25, 0.9, 0, 0), (150, 12, 1, 0.1, 0.5, 0, 0), (222, 12, 1, 0.25, 0.9, 0, 0),
-    (222, 12, 0, 0.25, 0.9, 0, 0), (222, 24, 2, 0.25, 0.9, 1, 1), (700, 12, 4, 0.1, 0.9, 0, 0)])
+    (40, 40, 1, 0.25, 0.9, 0, 0), (138, 10, 1, 0.25, 0.9, 1, 1), (150, 12, 1, 0.1, 0.5, 0, 0), (222, 12, 1, 0.25, 0.9, 0, 0),
+    (220, 40, 0, 0.1, 0.3, 0, 0), (94, 16, 0, 0.1, 0.3, 1, 1), (220, 24, 0, 0.2, 0.5, 0, 0), (222, 24, 2, 0.25, 0.9, 1, 1),
+    (444, 24, 4, 0.25, 0.9, 0, 0), (700, 12, 4, 0.1, 0.9, 0, 0)])
 def test_steps_of_32_keys(driver, blocks, heads, text, topk, p, cuts, whole):
     row = (1, 1, 64 * (blocks - text) - 3, 64 * text, 1, heads, 128, 64, topk, p)
     assert _run(driver, [row], "keys") == [[str(cuts), str(whole)]]
@@ -132,7 +134,7 @@ def test_steps_of_32_keys(driver, blocks, heads, text, topk, p, cuts, whole):
 # Text rows of such calls are cut into parts that a call with short lists of its own does not wait for: no longer than they were in steps
 # of 64 keys, which take three quarters of the time a block, where one generation has room for them.
 @pytest.mark.parametrize("blocks,heads,text,topk,parts", [
-    (120, 9, 1, 0.25, 5), (222, 8, 2, 0.25, 5), (222, 12, 2, 0.25, 4), (300, 5, 1, 0.25, 5), (222, 16, 2, 0.1, 4), (160, 9, 2, 0.25, 4),
+    (120, 9, 1, 0.25, 5), (222, 8, 2, 0.25, 5), (222, 12, 2, 0.25, 4), (300, 5, 1, 0.25, 5), (222, 16, 2, 0.2, 3), (160, 9, 2, 0.25, 4),
     (222, 24, 2, 0.25, 2), (492, 24, 4, 0.3, 2), (62, 60, 1, 0.25, 1), (120, 13, 1, 0.1, 1)])
 def test_parts_of_text_rows_in_steps_of_32_keys(driver, blocks, heads, text, topk, parts):
     row = (1, 1, 64 * (blocks - text) - 3, 64 * text, 1, heads, 128, 64, topk, 0.3)
