@@ -249,8 +249,8 @@ int heads_per_launch(const jenga_plan* p, int threads) {
 // 203 -> 186, x 20 245 -> 253.  Lists of 24 blocks: 62 x 32 136 -> 152.  From 2.3 generations on nothing changes (222 x 16, x 24).
 // Text rows of less than 110 blocks: 92 x 24 204 -> 206; 62 x 32 137 -> 141.
 // The parts of text rows are what a call with short lists of its own waits for: alone on a CU a block takes 1.3 times as long in
-// these steps (1.6 us), so there are a third more parts than above, as far as one generation takes them, and two where text rows would
-// stay whole.  Lists of 1 to 4 blocks, steps of 64 keys / of 32 without this / with it: 222 x 8 103 / 108 / 92 us, 120 x 9 49 / 61 / 52,
+// these steps (1.6 us), so there are a third more parts than above, and two where text rows would stay whole, as far as one generation takes
+// them and they are no more than an eightieth of the rows (268 x 8, 64 text rows in 4 parts instead of 3, 456 -> 470 us).  Lists of 1 to 4 blocks, steps of 64 keys / of 32 without this / with it: 222 x 8 103 / 108 / 92 us, 120 x 9 49 / 61 / 52,
 // 300 x 5 105 / 136 / 114, 222 x 24 318 / 470 / 258, 492 x 24 778 / 1194 / 659; 160 x 9, whose generation
 // is full, 64 / 81 / 81.  Selected lists are the same to 1 % (120 x 9 102.7 -> 102.9, 222 x 24 716 -> 717, 300 x 16 846 -> 838, 110 x 15
 // 122.7 -> 125.1); whole text rows of less than 150 blocks lose 2 % (62 x 60, 92 x 40) and stay whole.
@@ -391,7 +391,8 @@ static void split_lists(jenga_plan* plan) {
     if (f.M >= 110 && text_rows > 0 && attn_keys32(plan, true)) {
       const int parts = plan->attn_text_parts, more = parts > 1 ? parts + (parts + 1) / 3 : f.M >= 150 ? 2 : 1;
       plan->attn_text_parts = std::max(parts, std::min(most, more));
-      while (gens <= 1.0 && plan->attn_text_parts > parts && 8ll * plan_deal(plan, work, false).positions() > places)
+      while (plan->attn_text_parts > parts && (80 * text_rows * (plan->attn_text_parts - parts) > rows ||
+                                               (gens <= 1.0 && 8ll * plan_deal(plan, work, false).positions() > places)))
         --plan->attn_text_parts;
     }
     if (plan->attn_tail > 0 && plan->attn_first == 0) plan->attn_long = 28.f;
