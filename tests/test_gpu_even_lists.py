@@ -13,5 +13,6 @@ def test_lists_at_the_end_are_cut_where_they_are_long(blocks, heads, cut):
     vision, text = _direct_twice_and_packed(64, 128, blocks, heads, 0.3, False,
                                             lambda M: (0, 1, 2, M // 2, M - 1, M, M, M, M, M))
     assert (8 if cut else 0) <= int(vision.sum()) <= (512 if cut else 0)
+    assert bool(text.any()) == cut
     vision, _ = _direct_twice_and_packed(64, 128, blocks, heads, 0.3, False, lambda M: (0, 1, 2, 3, 8))
     assert not vision.any()

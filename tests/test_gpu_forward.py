@@ -27,8 +27,8 @@ def _results(layer):
                                 layer.lse, layer.out_thw)]
 
 
-# every attention kernel: in place and packed, lists whole, cut into parts and cut at the end, passes over key ranges in
-# several launches; ragged blocks, no text, odd head counts
+# in place and packed, lists whole and all cut into parts, passes over key ranges; ragged blocks, no text, odd head counts (lists
+# cut at the end, counters, the paced walk and several launches: test_gpu_forward_routes.py)
 @pytest.mark.parametrize("block,head_dim,tokens,heads,batch,n_text", [
     (32, 64, 256, 2, 1, 32), (32, 64, 6, 1, 1, 0), (32, 128, 700, 3, 2, 37), (32, 64, 32 * 1600 - 9, 3, 1, 5),
     (64, 128, 64 * 20 - 1, 3, 2, 70), (64, 64, 64 * 9 + 1, 70, 1, 0), (128, 128, 128 * 16, 8, 1, 64),
