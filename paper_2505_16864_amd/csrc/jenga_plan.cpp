@@ -147,7 +147,7 @@ void curve_order(int T, int H, int W, bool use_curve, std::vector<int32_t>& perm
 WorkMap plan_work(const jenga_plan* p, int n_bh) {
   const jenga_config& c = p->cfg;
   const int M = p->info.M, M_v = p->info.M_v;
-  // workgroups resident on the 32 CUs of an XCD: by registers and LDS 2, 3 to 4 or 5 to 8 per CU
+  // workgroups resident on the 32 CUs of an XCD: by registers and LDS 2, 3 to 4 or 6 to 8 per CU
   const int slots_per_xcd = 32 * (c.block == 32 ? 2 : attn_h_per_cu(c.block, c.head_dim));
   const size_t head_kv_bytes = (size_t)p->info.N_pad * c.head_dim * 4;
   WorkMap w;
@@ -278,8 +278,8 @@ Deal plan_deal(const jenga_plan* p, const WorkMap& work, bool whole) {
 //                4.41 -> 4.05 ms, text rows cut 222 x 12 402 -> 387
 //   text rows whole (packed entry, short text rows, uneven lists): 120 x 12 packed 171 -> 221, 222 x 12 packed 392 -> 464, 62 x 32 106 ->
 //                130, 92 x 24 151 -> 187, 222 x 40 at k = 0.05 440 -> 583, 138 x 10 at p = 0.9 209 -> 264
-// Lists that p decides about are taken at the K_top that they have at least, from p = 0.7 on and in one generation at the p^2 of all blocks that
-// they are expected to have (98 x 12, p = 0.9, packed, 298 -> 261; lists of 0.28 of the blocks all the same 138 x 10 209 -> 264).  Their
+// Lists that p decides about are taken at the K_top that they have at least, from p = 0.7 on at the p^2 of all blocks that they are expected
+// to have (98 x 12, p = 0.9, packed, 298 -> 261, 59 x 40 326 -> 303; lists of 0.28 of the blocks all the same 138 x 10 209 -> 264).  Their
 // heads are spread over all XCDs (plan_work), and with more than one generation six workgroups a CU then read more of a head's tiles
 // past the L2 than four do, except where a list holds most blocks of a head of up to 8 MB.  64 -> 32 keys: p = 0.3, k = 0.1, 220 x 40
 // 1319 -> 1456 us, 94 x 40 328 -> 366; p = 0.5 440 x 24 4.28 -> 4.58 ms; p = 0.7 444 x 24 6.78 -> 7.15, 220 x 24 1.96 -> 1.93; p = 0.9 96 x 40
@@ -304,8 +304,8 @@ bool attn_keys32(const jenga_plan* p, bool may_cut) {
   if (wgs <= resident) return false;
   const bool dense = c.cum_prob >= 0.7;
   if (f.M_c > 0 && !text_cut) {
-    const double blocks = wgs <= 1536 ? 2.2 * (dense ? usual : p->attn_len) : 1.5 * rows / 1536 * p->attn_len;
-    if (f.M > blocks) return false;
+    const double list = dense ? usual : p->attn_len;
+    if (f.M > (wgs <= 1536 ? 2.2 : 1.5 * rows / 1536) * list) return false;
   }
   if (may_cut && !uneven && p->attn_tail > 0) return true;
   if (wgs > 1536 && uneven && (!dense || 4ll * f.N_pad * c.head_dim > 8 << 20)) return false;
@@ -388,12 +388,13 @@ static void split_lists(jenga_plan* plan) {
       plan->attn_tail = 0;
       plan->attn_parts = 1;
     }
-    if (f.M >= 110 && text_rows > 0 && attn_keys32(plan, true)) {
+    if (f.M >= 110 && text_rows > 0 && (fine_even || attn_keys32(plan, true))) {
       const int parts = plan->attn_text_parts, more = parts > 1 ? parts + (parts + 1) / 3 : f.M >= 150 ? 2 : 1;
       plan->attn_text_parts = std::max(parts, std::min(most, more));
       while (plan->attn_text_parts > parts && (80 * text_rows * (plan->attn_text_parts - parts) > rows ||
                                                (gens <= 1.0 && 8ll * plan_deal(plan, work, false).positions() > places)))
         --plan->attn_text_parts;
+      if (!attn_keys32(plan, true)) plan->attn_text_parts = parts;
     }
     if (plan->attn_tail > 0 && plan->attn_first == 0) plan->attn_long = 28.f;
     return;

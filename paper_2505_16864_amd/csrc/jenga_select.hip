@@ -93,8 +93,9 @@ __global__ __launch_bounds__(256) void pool_kernel(const uint16_t* __restrict__ 
 // its launch.  A workgroup moves one block of one (batch, head); grid (heads, M, 3 * batch), so that neighbours read neighbouring heads
 // of the same tokens.  Sums in pool_kernel's order, so the means are the same bits.
 // Whole jenga_forward (this, and rows written to the thw side by the attention kernels), four calls -> one: 9 blocks of 32 x 2 heads,
-// D = 64, 22.9 -> 14.4 us (five launches -> three, of which each is 2.5 us however little it does), 17 of 128 x 8, D = 128, 56.8 ->
-// 52.2 us, 931 x 24 48.06 -> 47.82 ms.
+// D = 64, 22.6 -> 14.3 us (five launches -> three, of which each is 2.5 us however little it does), 17 of 128 x 8, D = 128, 55.6 ->
+// 51.4 us (inputs that no cache holds 61.6 -> 57.2), 931 x 24 48.34 -> 48.09 ms: 0.53 ms of pooling and un-permute go, and the
+// attention's second store takes half of that back.
 struct Moves {
   const uint4* src[3];
   uint4* dst[3];

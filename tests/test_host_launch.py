@@ -120,7 +120,7 @@ def test_parts_of_text_rows_are_bounded(driver, flags):
     (40, 40, 0, 0.25, 0.3, 0, 0), (62, 28, 0, 0.25, 0.3, 0, 0), (120, 14, 0, 0.25, 0.3, 1, 0), (62, 40, 0, 0.25, 0.3, 1, 1),
     (62, 24, 1, 0.1, 0.3, 0, 0), (62, 32, 1, 0.25, 0.3, 0, 0), (92, 24, 1, 0.25, 0.3, 0, 0), (222, 40, 2, 0.05, 0.3, 0, 0),
     (222, 8, 2, 0.25, 0.3, 1, 0), (222, 12, 2, 0.25, 0.3, 1, 0), (222, 24, 2, 0.25, 0.3, 1, 1), (492, 24, 4, 0.3, 0.3, 1, 1),
-    (40, 40, 1, 0.25, 0.9, 0, 0), (138, 10, 1, 0.25, 0.9, 1, 1), (150, 12, 1, 0.1, 0.5, 0, 0), (222, 12, 1, 0.25, 0.9, 0, 0),
+    (40, 40, 1, 0.25, 0.9, 0, 0), (138, 10, 1, 0.25, 0.9, 1, 1), (150, 12, 1, 0.1, 0.5, 0, 0), (222, 12, 1, 0.25, 0.9, 1, 1),
     (220, 40, 0, 0.1, 0.3, 0, 0), (94, 16, 0, 0.1, 0.3, 1, 1), (220, 24, 0, 0.2, 0.5, 0, 0), (222, 24, 2, 0.25, 0.9, 1, 1),
     (444, 24, 4, 0.25, 0.9, 0, 0), (700, 12, 4, 0.1, 0.9, 0, 0)])
 def test_steps_of_32_keys(driver, blocks, heads, text, topk, p, cuts, whole):
