@@ -236,7 +236,8 @@ int jenga_unpermute(const jenga_plan* plan, const void* src_curve, void* dst_thw
 
 /*
  * A whole layer on thw-side tensors: jenga_curve_permute_qkv, jenga_select_blocks, jenga_block_sparse_attn and jenga_unpermute
- * in one call and fewer launches, with the same results in the same places (all of those calls' arguments are outputs here too).
+ * in one call and fewer launches, with the same results in the same places (all of those calls' arguments are outputs here too; the
+ * same bits, but for the last ones of the attention under the paced walk, which differ from run to run).
  * Refuses what they refuse, before anything is launched.  An output that lies over an input is taken as those calls one after the
  * other take it.
  */
