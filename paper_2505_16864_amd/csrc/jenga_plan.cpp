@@ -250,9 +250,9 @@ int heads_per_launch(const jenga_plan* p, int threads) {
 // Text rows of less than 110 blocks: 92 x 24 204 -> 206; 62 x 32 137 -> 141.
 // The parts of text rows are what a call with short lists of its own waits for: alone on a CU a block takes 1.3 times as long in
 // these steps (1.6 us), so there are a third more parts than above, and two where text rows would stay whole, as far as one generation takes
-// them and they are no more than an eightieth of the rows (268 x 8, 64 text rows in 4 parts instead of 3, 456 -> 470 us).  Lists of 1 to 4 blocks, steps of 64 keys / of 32 without this / with it: 222 x 8 103 / 108 / 92 us, 120 x 9 49 / 61 / 52,
-// 300 x 5 105 / 136 / 114, 222 x 24 318 / 470 / 258, 492 x 24 778 / 1194 / 659; 160 x 9, whose generation
-// is full, 64 / 81 / 81.  Selected lists are the same to 1 % (120 x 9 102.7 -> 102.9, 222 x 24 716 -> 717, 300 x 16 846 -> 838, 110 x 15
+// them and they are no more than an eightieth of the rows (268 x 8, 64 text rows in 4 parts instead of 3, 456 -> 470 us).
+// Lists of 1 to 4 blocks, steps of 64 keys / of 32 without this / with it: 222 x 8 103 / 108 / 92 us, 120 x 9 49 / 61 / 52, 300 x 5
+// 105 / 136 / 114, 222 x 24 318 / 470 / 258, 492 x 24 778 / 1194 / 659; 160 x 9, whose generation is full, 64 / 81 / 81.  Selected lists are the same to 1 % (120 x 9 102.7 -> 102.9, 222 x 24 716 -> 717, 300 x 16 846 -> 838, 110 x 15
 // 122.7 -> 125.1); whole text rows of less than 150 blocks lose 2 % (62 x 60, 92 x 40) and stay whole.
 constexpr uint64_t RANGE_AREA_BYTES = 128ull << 20;
 
@@ -272,7 +272,8 @@ Deal plan_deal(const jenga_plan* p, const WorkMap& work, bool whole) {
 // whole ends after the others where it has more than 1.5 times the blocks that a place works off in the launch (in one generation 2.2
 // times the blocks of a list), and then it counts how fast one workgroup is.  Attention, 64 -> 32 keys a step, k = 0.25:
 //   up to 1024:  41 blocks x 8 heads 38.1 -> 41.5 us, 84 x 10 72 -> 78, 300 x 3 248 -> 285, no text 40 x 24 34.0 -> 35.4, 100 x 10 67 -> 70
-//   up to 1536:  lists cut into parts 120 x 6 106 -> 103, 305 x 2 218 -> 200, 369 x 2 326 -> 298, 71 x 3 42.3 -> 39.6; no text 62 x 20 68 -> 59, 120 x 12 137 -> 115; text rows cut 30 x 40 50.5 -> 44.8, 120 x 9 119 -> 104, 160 x 9 184 -> 153
+//   up to 1536:  lists cut into parts 120 x 6 106 -> 103, 305 x 2 218 -> 200, 369 x 2 326 -> 298, 71 x 3 42.3 -> 39.6; no text
+//                62 x 20 68 -> 59, 120 x 12 137 -> 115; text rows cut 30 x 40 50.5 -> 44.8, 120 x 9 119 -> 104, 160 x 9 184 -> 153
 //   up to 2048:  no text 62 x 28 84 -> 88, 92 x 18 113 -> 118, 40 x 40 60 -> 63; 90 x 20, k = 0.7, 283 -> 297
 //   above:       no text 62 x 40 115 -> 108, 120 x 20 196 -> 182, 222 x 16 478 -> 463; 62 x 60 178 -> 171, 222 x 24 776 -> 735, 492 x 24
 //                4.41 -> 4.05 ms, text rows cut 222 x 12 402 -> 387
